@@ -15,10 +15,11 @@ constexpr uint32_t HIGH_AGE = 0x80000000u;  // age of a slot created empty
 // never NaN, so no call's tag equals it).
 constexpr uint32_t MASK_NONE = 0x7FC00001u;
 constexpr int BLK_TILE = 4096;               // blocks per compaction tile
-constexpr int SLOT_TILE = 4096;              // slots per compaction tile (16 per thread)
-constexpr int RADIX_TILE = 1024;             // elements per radix tile (1 wave)
+constexpr int EVICT_TILE = 4096;             // slots per tile of the eviction's selection (1024 per wave)
+constexpr int EVICT_BITS = 11;               // key bits per pass of it
+constexpr int EVICT_BINS = 1 << EVICT_BITS;
+constexpr uint32_t EVICT_REFRESH = 1024;     // key span from which its base is looked for again
 constexpr int MC_MAX_GRID = 2048;           // workgroups of the count / emission grid at most
-constexpr int SCAN_TILE = 4096;              // u32 per look-back scan tile (16 per thread)
 constexpr int MC_WAVES = 4;                  // blocks (one per wave) per MC tile
 
 // look-back status words: 2 flag bits on top, value below
@@ -33,10 +34,8 @@ enum : uint32_t { ERR_CACHE_CAP = 1u, ERR_NONFINITE = 2u, ERR_INTERNAL = 4u, ERR
 struct Counters {
     unsigned long long n_act;        // active blocks
     unsigned long long n_new;        // active blocks not in the cache
-    unsigned long long n_avail;      // available slots (after growth)
-    unsigned long long n_slots;      // slots in use by the cache (after growth)
-    unsigned long long n_slots_old;  // slots before growth
-    unsigned long long n_avail_old;  // available slots before growth
+    unsigned long long n_slots;      // slots of the cache (after growth)
+    unsigned long long n_used;       // slots taken into use: [0, n_used) (after this call)
     unsigned long long n_grow;       // slots added this call
     unsigned long long n_evicted;    // blocks evicted this call
     unsigned long long n_occ;        // active blocks that emit triangles
@@ -44,17 +43,22 @@ struct Counters {
     unsigned long long total_verts;  // 3 * triangles
     unsigned long long n_live_rounds;  // 4096-block rounds holding an active block
     unsigned int err;                // ERR_* bits
-    unsigned int key_or, key_and;    // OR / AND of the sort keys of available slots
-    unsigned int pass_mask;          // radix digits that vary (bit p = digit p)
+    unsigned int oldest;             // no used slot was last used before this call (~0: not looked for)
+    unsigned int n_sort;             // available used slots (with n_evicted)
     unsigned int tile_ctr[16];       // dynamic work counters (tiles / batches)
 };
-enum { TC_ROUNDS = 0, TC_SLOT = 1, TC_MC = 2, TC_SCAN0 = 3 /* 3..6 per radix pass */,
-       TC_MCCOUNT = 7, TC_MCEMIT = 8, TC_RETRY = 9 /* blocks the low-rate decoder handed back */,
+enum { TC_ROUNDS = 0, TC_RETRY = 9 /* blocks the low-rate decoder handed back */,
        TC_CULL_LIVE = 10, TC_CULL_STALE = 11 /* the cull's queued tiles */ };
 // Double-precision streams up to this rate decode with the low-rate decoder
 // (and a general pass over the blocks it hands back).
 constexpr uint32_t LOW_RATE_MAX = 4;
 
+
+// The cache as a call finds it (host mirror).
+struct SlotState {
+    uint64_t n_slots, n_used, max_slots;
+    int identity;   // every block resident, no slots
+};
 
 // Geometry of a volume in blocks.
 struct Geom {
@@ -77,16 +81,14 @@ struct DevState {
     int32_t *I_slot = nullptr;      // per block: slot or -1
     // cache (max_slots entries)
     int32_t *S_block = nullptr;
-    uint32_t *S_age = nullptr;
+    uint32_t *S_stamp = nullptr;    // call that last used the slot (unused: that created it), 0: the reset
     float *slots = nullptr;         // [max_slots][64] decoded blocks
     uint64_t *masks = nullptr;      // [max_slots] per slot: bit i = sample i below iso
-    uint32_t *slot_or = nullptr;    // [slot tiles] OR / AND of each tile's sort keys
-    uint32_t *slot_and = nullptr;
     uint32_t *mask_iso = nullptr;   // [max_slots] bits of the isovalue masks[] was built for
                                     // (MASK_NONE: none)
-    uint32_t *sort_key[2] = {nullptr, nullptr};  // ~age of available slots
-    uint32_t *sort_val[2] = {nullptr, nullptr};  // slot ids
-    uint32_t *radix_hist = nullptr;              // 256 * radix tiles
+    uint32_t *evict[2] = {nullptr, nullptr};     // slots to evict, oldest first (two for passes)
+    uint32_t *evict_hist = nullptr;              // EVICT_BINS per EVICT_TILE slots
+    uint32_t *evict_tot = nullptr;               // EVICT_BINS
     // MC
     uint32_t *blk_cnt = nullptr;    // per active block vertex count
     uint64_t *blk_off = nullptr;    // per active block first vertex
@@ -104,17 +106,18 @@ struct DevState {
 
 // Offsets of each kernel's region inside DevState::status.
 struct StatusLayout {
-    uint64_t rnd, slot, mc, scan, total;
+    uint64_t rnd, total;
 };
 
 // ---- launchers (extract.hip) -------------------------------------------
 // prev_iso: the previous cull's isovalue (NaN after the flags were cleared).
 // gen: a number that differs from every earlier call's on these buffers
 // (rounds of blocks whose round_gen equals it hold this call's active blocks).
+// now: the call's number since the cache was reset (slots' stamps).
 void launch_cull(const Geom &g, const DevState &d, const StatusLayout &sl, float iso, float prev_iso,
-                 uint64_t n_slots_host, int identity_cache, uint32_t gen, hipStream_t s);
+                 int identity_cache, uint32_t now, uint32_t gen, hipStream_t s);
 void launch_compact_blocks(const Geom &g, const DevState &d, const StatusLayout &sl, uint32_t gen,
-                           hipStream_t s);
+                           const SlotState &ss, hipStream_t s);
 inline uint64_t block_rounds(uint64_t nb) { return (nb + BLK_TILE - 1) / BLK_TILE; }
 // Chunk entries of the count pass's and emission's chunk totals: a call
 // with n_act active blocks on W waves has ceil(n_act / cs) chunks of
@@ -124,13 +127,11 @@ inline uint64_t mc_chunk_slots(uint64_t nb) {
     const uint64_t a = (nb + 63) / 64, b = 4ull * MC_MAX_GRID;
     return a > b ? a : b;
 }
-// age_cap: exceeds the age of every slot used since the cache was reset.
-void launch_slot_pass(const DevState &d, const StatusLayout &sl, uint64_t n_slots_host,
-                      uint32_t age_cap, hipStream_t s);
-void launch_plan_grow(const DevState &d, uint64_t max_slots, uint64_t grow_bound, hipStream_t s);
-// Radix passes over the digits of keys up to age_cap (the others are zero).
-void launch_radix(const DevState &d, const StatusLayout &sl, uint64_t max_elems, uint32_t age_cap,
-                  hipStream_t s);
+// The slots to evict, oldest first (n_evicted entries of the returned list),
+// among [0, n_used); base: a call number no used slot's stamp is below.
+uint32_t *launch_evict(const DevState &d, uint32_t n_used, uint32_t base, uint32_t now, hipStream_t s);
+// Every block out of the cache; the slots from n_used on hold none.
+void launch_cache_empty(const DevState &d, uint64_t n_used, hipStream_t s);
 void launch_mc_count(const Geom &g, const DevState &d, const float *slots, const int32_t *I_slot,
                      int identity_cache, float iso, int fmt, hipStream_t s);
 
@@ -147,7 +148,6 @@ void launch_backward(const Geom &g, const DevState &d, const float *slots, float
                      const float *gV, uint64_t n_verts, float *dfield, float *diso, int fmt,
                      hipStream_t s);
 void launch_fill_u32(uint32_t *p, uint32_t v, uint64_t n, hipStream_t s);
-void launch_age_slots(uint32_t *S_age, uint64_t n, uint32_t k, hipStream_t s);
 void launch_copy_calibration(void *dst, const void *src, uint64_t n16, hipStream_t s);
 void launch_iota_i32(int32_t *p, uint64_t n, hipStream_t s);
 
@@ -167,8 +167,9 @@ uint64_t cull_tiles(const Geom &g);
 void launch_tile_ranges(const Geom &g, const float2 *ranges, float2 *tile_ranges, hipStream_t s);
 void launch_ranges_from_blocks(const Geom &g, const float *blocks, float2 *ranges,
                                unsigned int *err, hipStream_t s);
+// evict: launch_evict's list; ss, now: as the call began.
 void launch_assign_decode(const DevState &d, int is_f64, uint32_t rate, uint64_t max_new, float iso,
-                          hipStream_t s);
+                          const uint32_t *evict, const SlotState &ss, uint32_t now, hipStream_t s);
 void launch_encode(const Geom &g, const void *field, int is_f64, uint32_t rate,
                    uint64_t *stream, unsigned int *err, hipStream_t s);
 

@@ -75,15 +75,11 @@ __global__ __launch_bounds__(256) void k_tile_ranges(Geom g, const float2 *__res
 
 // The per-call counters and the look-back status words of the call's scans
 // start at zero: cleared first (the cull's tile queue counts in the counters).
-__global__ __launch_bounds__(256) void k_call_reset(Counters *ctr, uint64_t n_slots_host, uint64_t *status,
-                                                   uint64_t status_words) {
+__global__ __launch_bounds__(256) void k_call_reset(Counters *ctr, uint64_t *status, uint64_t status_words) {
     const uint64_t gid = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
     if (gid == 0) {
         Counters c{};
-        c.n_slots = n_slots_host;
-        c.n_slots_old = n_slots_host;
-        c.key_or = 0u;
-        c.key_and = ~0u;
+        c.oldest = ~0u;
         *ctr = c;
     }
     for (uint64_t w = gid; w < status_words; w += (uint64_t)gridDim.x * blockDim.x) status[w] = 0;
@@ -116,7 +112,9 @@ __global__ __launch_bounds__(256) void k_cull_scan(const float2 *__restrict__ ti
 }
 
 // Flags per block: bit 0 active, bit 1 may emit, bit 2 active without a
-// slot (new, Alg. 1 MarkNewBlocks; never set for an identity cache).
+// slot (new, Alg. 1 MarkNewBlocks; never set for an identity cache); the
+// slots of the active blocks that have one are stamped with the call's number
+// (Alg. 1 IncrementSlotAge: a slot's age is the calls since its stamp).
 // The flags are zero outside the tiles the previous call culled, so a tile
 // live then and dead now (stale) is cleared here, a live tile is rewritten
 // in full, and no other flag is touched.  Persistent: workgroup w takes
@@ -126,6 +124,7 @@ __global__ __launch_bounds__(256) void k_cull_scan(const float2 *__restrict__ ti
 __global__ __launch_bounds__(256) void k_cull(Geom g, const float2 *__restrict__ ranges, float iso,
                                              const uint32_t *__restrict__ list, uint64_t n_tiles,
                                              const int32_t *__restrict__ I_slot, int identity,
+                                             uint32_t *__restrict__ S_stamp, uint32_t now,
                                              uint8_t *__restrict__ active, Counters *ctr,
                                              uint32_t *__restrict__ round_gen, uint32_t gen) {
     constexpr int NL = CULL_TZ + 2, RX = CULL_TX + 2, RY = CULL_TY + 2, SLOTS = RX * RY;
@@ -236,6 +235,7 @@ __global__ __launch_bounds__(256) void k_cull(Geom g, const float2 *__restrict__
                 const bool a = (act >> z) & 1u;
                 const uint64_t b = ((uint64_t)(z0 + z) * g.nby + by) * g.nbx + bx;
                 active[b] = (a ? 1u : 0u) | (((can >> z) & 1u) ? 2u : 0u) | (a && sl[z] < 0 ? 4u : 0u);
+                if (!identity && a && sl[z] >= 0) S_stamp[sl[z]] = now;
             }
         }
         // mark the 4096-block rounds holding active blocks for the
@@ -348,9 +348,43 @@ __global__ __launch_bounds__(256) void k_round_counts(Geom g, const uint8_t *__r
     }
 }
 
+// Alg. 1's early exit (nothing new), growth and supply of slots, from the
+// call's counts.  Every active block that is not new holds one slot, so
+// n_slots - (n_act - n_new) slots are available, and growth (more new blocks
+// than that) needs no pass over the slots.  Slots are taken into use in
+// ascending order before any used one is evicted, so the unused ones are
+// always [n_used, n_slots): the new blocks take those first, then the oldest
+// n_evict of the used available ones.
+__device__ __forceinline__ void plan_slots(Counters *ctr, uint64_t n_act, uint64_t n_new, SlotState ss) {
+    ctr->n_act = n_act;
+    ctr->n_new = n_new;
+    ctr->n_slots = ss.n_slots;
+    ctr->n_used = ss.n_used;
+    if (ss.identity || n_new == 0) return;
+    const uint64_t avail = ss.n_slots - (n_act - n_new);
+    uint64_t grow = 0;
+    if (n_new > avail) {
+        grow = n_new - avail;
+        const uint64_t half = (ss.n_slots + 1) / 2;
+        if (half > grow) grow = half;
+        if (ss.n_slots + grow > ss.max_slots) grow = ss.max_slots - ss.n_slots;
+    }
+    if (avail + grow < n_new) {
+        ctr->err |= ERR_CACHE_CAP;
+        return;
+    }
+    const uint64_t unused = ss.n_slots + grow - ss.n_used;
+    ctr->n_grow = grow;
+    ctr->n_slots = ss.n_slots + grow;
+    ctr->n_evicted = n_new > unused ? n_new - unused : 0;
+    ctr->n_used = ss.n_used + (n_new < unused ? n_new : unused);
+}
+
 // Exclusive prefix of the live rounds' counts, in place; the totals are the
-// call's n_act and n_new.  One workgroup, 4096 rounds per step.
-__global__ __launch_bounds__(256) void k_round_scan(uint64_t *__restrict__ round_cnt, Counters *ctr) {
+// call's n_act and n_new, from which the slots are planned.  One workgroup,
+// 4096 rounds per step.
+__global__ __launch_bounds__(256) void k_round_scan(uint64_t *__restrict__ round_cnt, Counters *ctr,
+                                                   SlotState ss) {
     __shared__ uint64_t s_w[4];
     const uint64_t n = ctr->n_live_rounds;
     const int w = threadIdx.x >> 6;
@@ -380,10 +414,7 @@ __global__ __launch_bounds__(256) void k_round_scan(uint64_t *__restrict__ round
         carry += tot;
         __syncthreads();   // s_w is rewritten by the next step
     }
-    if (threadIdx.x == 0) {
-        ctr->n_act = carry >> 32;
-        ctr->n_new = carry & 0xFFFFFFFFull;
-    }
+    if (threadIdx.x == 0) plan_slots(ctr, carry >> 32, carry & 0xFFFFFFFFull, ss);
 }
 
 // Each live round's active and new block ids, from its offsets on.  A wave
@@ -433,306 +464,227 @@ __global__ __launch_bounds__(256) void k_compact_blocks(Geom g, const uint8_t *_
     }
 }
 
-// Alg. 1 IncrementSlotAge + the slot half of MarkNewBlocks, then
-// StreamCompactIDs of the available slots (I_avail) and StreamCompact of their
-// ages (K_age, stored as ~age so that ascending key = descending age).
-__global__ __launch_bounds__(256) void k_slot_pass(const uint8_t *__restrict__ active,
-                                                  const int32_t *__restrict__ S_block,
-                                                  uint32_t *__restrict__ S_age, uint64_t n_slots,
-                                                  uint32_t age_cap, uint32_t *__restrict__ keys,
-                                                  uint32_t *__restrict__ vals,
-                                                  uint32_t *__restrict__ part_or,
-                                                  uint32_t *__restrict__ part_and, Counters *ctr,
-                                                  uint64_t *status) {
-    const uint64_t n_tiles = (n_slots + SLOT_TILE - 1) / SLOT_TILE;
-    // the list of available slots (look-back order = ticket order) is needed
-    // only when the call has new blocks; otherwise the tiles just age, in any
-    // order, without a shared ticket counter
-    const bool need_list = ctr->n_new != 0;
-    const uint32_t t = need_list ? take_tile(&ctr->tile_ctr[TC_SLOT]) : blockIdx.x;
-    if (t >= n_tiles) return;
-    constexpr int PER = SLOT_TILE / 256;   // consecutive slots per thread (16-byte loads)
-    static_assert(PER % 4 == 0, "the vector path loads 4 slots at a time");
-    const uint64_t base = (uint64_t)t * SLOT_TILE + threadIdx.x * PER;
-    uint32_t availb = 0;
-    uint32_t age[PER];
-    int32_t blk[PER];
-    uint32_t kor = 0, kand = ~0u, key[PER];
-    const bool full = base + PER <= n_slots;
-    if (full) {
-#pragma unroll
-        for (int j = 0; j < PER; j += 4) {
-            const int4 bq = *reinterpret_cast<const int4 *>(S_block + base + j);
-            const uint4 aq = *reinterpret_cast<const uint4 *>(S_age + base + j);
-            blk[j] = bq.x; blk[j + 1] = bq.y; blk[j + 2] = bq.z; blk[j + 3] = bq.w;
-            age[j] = aq.x; age[j + 1] = aq.y; age[j + 2] = aq.z; age[j + 3] = aq.w;
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < PER; j++) {
-            blk[j] = base + j < n_slots ? S_block[base + j] : -1;
-            age[j] = base + j < n_slots ? S_age[base + j] : 0u;
-        }
+// ---------------------------------------------------------------------------
+// Alg. 1 SortByKey, as a selection: the n_evicted oldest used slots that hold
+// no active block, oldest first and by ascending slot among equals (the first
+// entries of the stable sort of all available slots by age; the unused slots,
+// older than every used one, precede them and need no list).  A slot's key is
+// the call that last used it less `base`, a call no used slot is older than.
+// One pass: k_evict_count counts the keys of each tile of slots, and
+// k_evict_list finds the key up to which slots are taken and ranks the tile's
+// slots below it.  The keys span the calls since the oldest slot's use (few,
+// since a cache that must evict drops the oldest), so one pass covers spans
+// of 2047 calls; longer spans take stable passes over 11-bit digits, the last
+// of which stops at n_evicted.  A full radix sort of the slots, with the pass
+// over all of them that ages them, took 31-42 us per call at 10^5 slots
+// in five launches; this takes 10-12 us in two, and nothing when every new
+// block finds an unused slot.
+// ---------------------------------------------------------------------------
+struct EvictPass {
+    uint32_t base, now;      // keys: stamps in [base, now)
+    int shift, bits;         // the pass's digit
+    int first, last;         // first: slots in slot order; else `in`
+    const uint32_t *in;      // the previous pass's list
+    uint32_t *out;           // this pass's list (last: n_evicted entries)
+    uint32_t n_used;         // used slots (first)
+    uint32_t tiles;          // stride of the histogram's rows
+    int scanned;             // the histogram rows hold prefixes (k_evict_scan ran)
+};
+
+// Elements of the pass, and element i's slot (~0u: none: not available).
+__device__ __forceinline__ uint32_t evict_count_in(const EvictPass &p, const Counters *ctr) {
+    return p.first ? p.n_used : ctr->n_sort;
+}
+__device__ __forceinline__ bool evict_elem(const EvictPass &p, const uint32_t *__restrict__ S_stamp, uint32_t i,
+                                           uint32_t n, uint32_t &slot, uint32_t &stamp) {
+    if (i >= n) return false;
+    slot = p.first ? i : p.in[i];
+    stamp = S_stamp[slot];
+    return !p.first || stamp < p.now;
+}
+__device__ __forceinline__ uint32_t evict_digit(const EvictPass &p, uint32_t stamp) {
+    return ((stamp - p.base) >> p.shift) & ((1u << p.bits) - 1u);
+}
+
+// Adds the wave's digits to h, one lane per distinct digit: neighbouring
+// slots were mostly last used by the same call.
+__device__ __forceinline__ void wave_digit_count(uint32_t *h, bool valid, uint32_t d) {
+    uint64_t left = __ballot(valid);
+    while (left) {
+        const int leader = (int)__builtin_ctzll(left);
+        const uint32_t ld = (uint32_t)__builtin_amdgcn_readlane((int)d, leader);
+        const uint64_t same = __ballot(valid && d == ld) & left;
+        if (lane() == leader) atomicAdd(&h[ld], (uint32_t)__popcll(same));
+        left &= ~same;
     }
+}
+
+// hist[digit][tile], tiles of EVICT_TILE elements.  refresh: the oldest
+// used slot's stamp, for the next calls' base.
+__global__ __launch_bounds__(256) void k_evict_count(EvictPass p, const uint32_t *__restrict__ S_stamp,
+                                                    uint32_t *__restrict__ hist, Counters *ctr, int refresh) {
+    __shared__ uint32_t h[EVICT_BINS];
+    if (ctr->err) return;
+    const bool need = ctr->n_evicted != 0;
+    if (!need && !refresh) return;
+    const uint32_t n = evict_count_in(p, ctr), tile = blockIdx.x;
+    for (int d = threadIdx.x; d < 1 << p.bits; d += 256) h[d] = 0;
+    __syncthreads();
+    uint32_t oldest = ~0u;
+    for (int r = 0; r < EVICT_TILE / 256; r++) {
+        uint32_t slot = 0, stamp = 0;
+        const uint32_t i = tile * EVICT_TILE + r * 256 + threadIdx.x;
+        const bool v = evict_elem(p, S_stamp, i, n, slot, stamp);
+        if (i < n) oldest = min(oldest, stamp);
+        if (need) wave_digit_count(h, v, evict_digit(p, stamp));
+    }
+    if (refresh) {
 #pragma unroll
-    for (int j = 0; j < PER; j++) {
-        key[j] = 0u;
-        if (base + j < n_slots) {
-            const bool act = blk[j] >= 0 && active[blk[j]];
-            uint32_t a = age[j];
-            a = act ? 0u : (a == 0xFFFFFFFFu ? a : a + 1u);
-            age[j] = a;
-            if (!act) {
-                availb |= 1u << j;
-                // sort key, ascending = oldest first: slots never used (age
-                // >= HIGH_AGE, created in slot order) before every used one,
-                // used ones by age descending.  age_cap exceeds every used
-                // slot's age, so the keys keep the exact order in few digits.
-                key[j] = a >= HIGH_AGE ? 0u : age_cap - a;
-                kor |= key[j];
-                kand &= key[j];
+        for (int d = 32; d >= 1; d >>= 1) oldest = min(oldest, (uint32_t)__shfl_xor((int)oldest, d, 64));
+        if (lane() == 0) atomicMin(&ctr->oldest, oldest);
+    }
+    if (!need) return;
+    __syncthreads();
+    for (int d = threadIdx.x; d < 1 << p.bits; d += 256) hist[(uint64_t)d * p.tiles + tile] = h[d];
+}
+
+// Many tiles: each digit's row of the histogram into its exclusive prefix,
+// the row's total to totals[digit]; one workgroup per digit.
+__global__ __launch_bounds__(256) void k_evict_scan(uint32_t tiles, uint32_t *__restrict__ hist,
+                                                   uint32_t *__restrict__ totals, const Counters *ctr) {
+    __shared__ uint32_t s_w[4];
+    if (ctr->err || !ctr->n_evicted) return;
+    uint32_t *row = hist + (uint64_t)blockIdx.x * tiles;
+    uint32_t carry = 0;
+    for (uint32_t t0 = 0; t0 < tiles; t0 += 256) {
+        const uint32_t t = t0 + threadIdx.x;
+        const uint32_t x = t < tiles ? row[t] : 0u;
+        const uint32_t incl = wave_incl_scan(x);
+        if (lane() == 63) s_w[threadIdx.x >> 6] = incl;
+        __syncthreads();
+        uint32_t o = carry + incl - x;
+        for (int i = 0; i < 4; i++) {
+            if (i < (int)(threadIdx.x >> 6)) o += s_w[i];
+            carry += s_w[i];
+        }
+        if (t < tiles) row[t] = o;
+        __syncthreads();   // s_w is rewritten next step
+    }
+    if (threadIdx.x == 0) totals[blockIdx.x] = carry;
+}
+
+// The pass's list.  Each workgroup forms the digits' offsets (totals over
+// all tiles, then the tile's own) and ranks its tile in order: each wave
+// owns 1024 consecutive elements and its own running counts.
+__global__ __launch_bounds__(256) void k_evict_list(EvictPass p, const uint32_t *__restrict__ S_stamp,
+                                                   const uint32_t *__restrict__ hist,
+                                                   const uint32_t *__restrict__ totals, Counters *ctr) {
+    __shared__ uint32_t off[EVICT_BINS];       // first position of the tile's elements, per digit
+    __shared__ uint32_t run[4][EVICT_BINS];    // per wave: elements of its share, then placed ones
+    __shared__ uint32_t s_w[4], s_thr;
+    if (ctr->err || !ctr->n_evicted) return;
+    const uint32_t bins = 1u << p.bits, n = evict_count_in(p, ctr), tile = blockIdx.x;
+    const uint32_t want = p.last ? (uint32_t)ctr->n_evicted : ~0u;   // positions past it are dropped
+    const int w = threadIdx.x >> 6, l = lane();
+    // per digit: elements in all tiles (run[0]) and in the tiles before this one (off)
+    for (uint32_t d = threadIdx.x; d < bins; d += 256) {
+        const uint32_t *row = hist + (uint64_t)d * p.tiles;
+        uint32_t all = 0, before = 0;
+        if (p.scanned) {
+            all = totals[d];
+            before = row[tile];
+        } else {
+#pragma unroll 8
+            for (uint32_t t = 0; t < p.tiles; t++) {
+                const uint32_t x = row[t];
+                all += x;
+                before += t < tile ? x : 0u;
             }
         }
+        run[0][d] = all;
+        off[d] = before;
     }
-    if (full) {
-#pragma unroll
-        for (int j = 0; j < PER; j += 4)
-            *reinterpret_cast<uint4 *>(S_age + base + j) = make_uint4(age[j], age[j + 1], age[j + 2], age[j + 3]);
-    } else {
-#pragma unroll
-        for (int j = 0; j < PER; j++)
-            if (base + j < n_slots) S_age[base + j] = age[j];
-    }
-    if (!need_list) return;
-    uint64_t incl_end;
-    uint64_t e = tile_scan_lookback((uint64_t)__popc(availb), status, t, &incl_end);
-#pragma unroll
-    for (int j = 0; j < PER; j++)
-        if ((availb >> j) & 1u) {
-            keys[e] = key[j];
-            vals[e] = (uint32_t)(base + j);
-            e++;
+    if (threadIdx.x == 0) s_thr = bins;
+    __syncthreads();
+    uint32_t carry = 0;
+    for (uint32_t d0 = 0; d0 < bins; d0 += 256) {   // exclusive prefix over the digits
+        const uint32_t d = d0 + threadIdx.x;
+        const uint32_t x = d < bins ? run[0][d] : 0u;
+        const uint32_t incl = wave_incl_scan(x);
+        if (l == 63) s_w[w] = incl;
+        __syncthreads();
+        uint32_t o = carry + incl - x;
+        for (int i = 0; i < 4; i++) {
+            if (i < w) o += s_w[i];
+            carry += s_w[i];
         }
-    // OR / AND of the keys (which radix digits vary), one entry per tile
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        kor |= __shfl_xor(kor, d, 64);
-        kand &= __shfl_xor(kand, d, 64);
+        if (d < bins) {
+            off[d] += o;
+            if (o < want && want - o <= x) s_thr = d;   // the digit the list ends in
+        }
+        __syncthreads();
     }
-    __shared__ uint32_t s_or[4], s_and[4];
-    if (lane() == 0) {
-        s_or[threadIdx.x >> 6] = kor;
-        s_and[threadIdx.x >> 6] = kand;
+    for (uint32_t d = threadIdx.x; d < bins; d += 256) run[0][d] = run[1][d] = run[2][d] = run[3][d] = 0;
+    const uint32_t thr = s_thr;
+    if (tile == 0 && threadIdx.x == 0) {
+        if (p.first) ctr->n_sort = carry;
+        if (p.last) {
+            if (carry < want) atomicOr(&ctr->err, ERR_INTERNAL);
+            ctr->oldest = p.base + (thr << p.shift);   // what stays is no older
+        }
+    }
+    if (carry < want && p.last) return;
+    __syncthreads();
+    const uint32_t e0 = tile * EVICT_TILE + w * (EVICT_TILE / 4);
+    for (int r = 0; r < EVICT_TILE / 256; r++) {
+        uint32_t slot = 0, stamp = 0;
+        const bool v = evict_elem(p, S_stamp, e0 + r * 64 + l, n, slot, stamp);
+        const uint32_t d = evict_digit(p, stamp);
+        wave_digit_count(run[w], v && d <= thr, d);
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        part_or[t] = s_or[0] | s_or[1] | s_or[2] | s_or[3];
-        part_and[t] = s_and[0] & s_and[1] & s_and[2] & s_and[3];
+    for (uint32_t d = threadIdx.x; d < bins; d += 256) {   // counts -> each wave's first position
+        uint32_t o = off[d];
+        for (int i = 0; i < 4; i++) {
+            const uint32_t x = run[i][d];
+            run[i][d] = o;
+            o += x;
+        }
     }
-    if (t == n_tiles - 1 && threadIdx.x == 0) ctr->n_avail_old = incl_end;
+    __syncthreads();
+    for (int r = 0; r < EVICT_TILE / 256; r++) {
+        uint32_t slot = 0, stamp = 0;
+        bool v = evict_elem(p, S_stamp, e0 + r * 64 + l, n, slot, stamp);
+        const uint32_t d = evict_digit(p, stamp);
+        v = v && d <= thr;
+        uint64_t left = __ballot(v);
+        while (left) {
+            const int leader = (int)__builtin_ctzll(left);
+            const uint32_t ld = (uint32_t)__builtin_amdgcn_readlane((int)d, leader);
+            const uint64_t same = __ballot(v && d == ld) & left;
+            const uint32_t o = run[w][ld];
+            wave_lds_sync();
+            if ((same >> l) & 1u) {
+                const uint32_t pos = o + mbcnt(same);
+                if (pos < (p.last ? want : n)) p.out[pos] = slot;
+            }
+            if (l == leader) run[w][ld] = o + (uint32_t)__popcll(same);
+            wave_lds_sync();
+            left &= ~same;
+        }
+    }
 }
 
-// Alg. 1's early exit (nothing new) and growth (more new blocks than available
-// slots): every workgroup
-// derives the same plan from values no kernel of this launch writes; block 0
-// publishes it and all threads initialise the appended slots (empty,
-// available, age HIGH_AGE) and append them to the available list.
-__global__ __launch_bounds__(256) void k_plan_grow(Counters *ctr, uint64_t max_slots,
-                                                  int32_t *__restrict__ S_block,
-                                                  uint32_t *__restrict__ S_age,
-                                                  uint32_t *__restrict__ keys,
-                                                  uint32_t *__restrict__ vals,
-                                                  const uint32_t *__restrict__ part_or,
-                                                  const uint32_t *__restrict__ part_and) {
-    const uint64_t n_new = ctr->n_new;
-    if (ctr->err || n_new == 0) return;
-    const uint64_t na = ctr->n_avail_old, ns = ctr->n_slots_old;
-    uint64_t grow = 0;
-    if (n_new > na) {
-        grow = n_new - na;
-        uint64_t half = (ns + 1) / 2;
-        if (half > grow) grow = half;
-        if (ns + grow > max_slots) grow = max_slots - ns;
-    }
-    const uint64_t gid = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
-    if (na + grow < n_new) {
-        if (gid == 0) ctr->err |= ERR_CACHE_CAP;
-        return;
-    }
-    if (blockIdx.x == 0) {   // the keys' OR / AND from the slot pass's tiles
-        const uint64_t n_tiles = (ns + SLOT_TILE - 1) / SLOT_TILE;
-        uint32_t o = 0u, a = ~0u;
-        for (uint64_t i = threadIdx.x; i < n_tiles; i += blockDim.x) {
-            o |= part_or[i];
-            a &= part_and[i];
-        }
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) {
-            o |= __shfl_xor(o, d, 64);
-            a &= __shfl_xor(a, d, 64);
-        }
-        __shared__ uint32_t s_or[4], s_and[4];
-        if (lane() == 0) {
-            s_or[threadIdx.x >> 6] = o;
-            s_and[threadIdx.x >> 6] = a;
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            ctr->key_or = s_or[0] | s_or[1] | s_or[2] | s_or[3];
-            ctr->key_and = s_and[0] & s_and[1] & s_and[2] & s_and[3];
-        }
-    }
-    if (gid == 0) {
-        uint32_t kor = ctr->key_or, kand = ctr->key_and;
-        if (grow) kand = 0u;   // appended slots: key 0
-        uint32_t vary = kor ^ kand;
-        uint32_t mask = 0;
-        for (int p = 0; p < 4; p++)
-            if ((vary >> (8 * p)) & 0xFFu) mask |= 1u << p;
-        ctr->pass_mask = mask;
-        ctr->n_grow = grow;
-        ctr->n_slots = ns + grow;
-        ctr->n_avail = na + grow;
-    }
-    for (uint64_t i = gid; i < grow; i += (uint64_t)gridDim.x * blockDim.x) {
-        uint64_t s = ns + i;
+// Empties the cache: the used slots lose their blocks (the others hold none).
+__global__ __launch_bounds__(256) void k_cache_empty(uint64_t n_used, int32_t *__restrict__ S_block,
+                                                    uint32_t *__restrict__ S_stamp,
+                                                    int32_t *__restrict__ I_slot) {
+    for (uint64_t s = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; s < n_used;
+         s += (uint64_t)gridDim.x * blockDim.x) {
+        const int32_t b = S_block[s];
+        if (b >= 0) I_slot[b] = -1;
         S_block[s] = -1;
-        S_age[s] = HIGH_AGE;
-        keys[na + i] = 0u;
-        vals[na + i] = (uint32_t)s;
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Alg. 1 SortByKey: stable LSD radix sort of the available slots by ~age
-// (8-bit digits).  Digits on which every key agrees are skipped: a pass over
-// such a digit is the identity.  Tiles of 1024 elements are owned by single
-// waves, striped as element = tile*1024 + round*64 + lane.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ bool radix_pass_live(const Counters *ctr, int p) {
-    return !ctr->err && ctr->n_new != 0 && ((ctr->pass_mask >> p) & 1u);
-}
-__device__ __forceinline__ int radix_in_buf(const Counters *ctr, int p) {
-    return __popc(ctr->pass_mask & ((1u << p) - 1u)) & 1;
-}
-
-__global__ __launch_bounds__(256) void k_radix_hist(Counters *ctr, int p,
-                                                   const uint32_t *__restrict__ keys0,
-                                                   const uint32_t *__restrict__ keys1,
-                                                   uint32_t *__restrict__ hist, uint64_t *status) {
-    if (!radix_pass_live(ctr, p)) return;
-    const uint32_t *keys = radix_in_buf(ctr, p) ? keys1 : keys0;
-    const uint64_t n = ctr->n_avail;
-    const uint64_t n_tiles = (n + RADIX_TILE - 1) / RADIX_TILE;
-    const uint64_t gid = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
-    const uint64_t gsz = (uint64_t)gridDim.x * blockDim.x;
-    // clear the scan's status words and tile counter for this pass
-    const uint64_t scan_tiles = (256 * n_tiles + SCAN_TILE - 1) / SCAN_TILE;
-    for (uint64_t w = gid; w < scan_tiles; w += gsz) status[w] = 0;
-    if (gid == 0) ctr->tile_ctr[TC_SCAN0 + p] = 0;
-    __shared__ uint32_t h[4][256];
-    const int w = threadIdx.x >> 6;
-    const int shift = 8 * p;
-    const uint64_t waves = (uint64_t)gridDim.x * 4;
-    for (uint64_t tb = blockIdx.x * 4ull; tb < n_tiles; tb += waves) {
-        uint64_t tile = tb + w;
-        for (int i = lane(); i < 256; i += 64) h[w][i] = 0;
-        __syncthreads();
-        if (tile < n_tiles) {
-            for (int r = 0; r < RADIX_TILE / 64; r++) {
-                uint64_t idx = tile * RADIX_TILE + r * 64 + lane();
-                if (idx < n) atomicAdd(&h[w][(keys[idx] >> shift) & 0xFFu], 1u);
-            }
-        }
-        __syncthreads();
-        if (tile < n_tiles)
-            for (int d = lane(); d < 256; d += 64) hist[(uint64_t)d * n_tiles + tile] = h[w][d];
-        __syncthreads();
-    }
-}
-
-// In-place exclusive scan of the digit-major histogram (256 * n_tiles u32).
-__global__ __launch_bounds__(256) void k_radix_scan(Counters *ctr, int p, uint32_t *hist,
-                                                   uint64_t *status) {
-    if (!radix_pass_live(ctr, p)) return;
-    const uint64_t n_tiles = (ctr->n_avail + RADIX_TILE - 1) / RADIX_TILE;
-    const uint64_t len = 256 * n_tiles;
-    const uint64_t scan_tiles = (len + SCAN_TILE - 1) / SCAN_TILE;
-    for (;;) {
-        const uint32_t t = take_tile(&ctr->tile_ctr[TC_SCAN0 + p]);
-        if (t >= scan_tiles) return;
-        constexpr int PER = SCAN_TILE / 256;   // consecutive entries per thread
-        const uint64_t base = (uint64_t)t * SCAN_TILE + threadIdx.x * PER;
-        uint32_t x[PER];
-        uint64_t sum = 0;
-#pragma unroll
-        for (int j = 0; j < PER; j++) {
-            x[j] = base + j < len ? hist[base + j] : 0u;
-            sum += x[j];
-        }
-        uint64_t incl_end;
-        uint64_t e = tile_scan_lookback(sum, status, t, &incl_end);
-#pragma unroll
-        for (int j = 0; j < PER; j++) {
-            if (base + j < len) hist[base + j] = (uint32_t)e;
-            e += x[j];
-        }
-    }
-}
-
-__global__ __launch_bounds__(256) void k_radix_scatter(Counters *ctr, int p,
-                                                      uint32_t *keys0, uint32_t *keys1,
-                                                      uint32_t *vals0, uint32_t *vals1,
-                                                      const uint32_t *__restrict__ hist) {
-    if (!radix_pass_live(ctr, p)) return;
-    const int in = radix_in_buf(ctr, p);
-    const uint32_t *__restrict__ kin = in ? keys1 : keys0;
-    const uint32_t *__restrict__ vin = in ? vals1 : vals0;
-    uint32_t *__restrict__ kout = in ? keys0 : keys1;
-    uint32_t *__restrict__ vout = in ? vals0 : vals1;
-    const uint64_t n = ctr->n_avail;
-    const uint64_t n_tiles = (n + RADIX_TILE - 1) / RADIX_TILE;
-    __shared__ uint32_t off[4][256];
-    const int w = threadIdx.x >> 6;
-    const int l = lane();
-    const int shift = 8 * p;
-    const uint64_t lt = (1ull << l) - 1ull;
-    const uint64_t waves = (uint64_t)gridDim.x * 4;
-    for (uint64_t tile = blockIdx.x * 4ull + w; tile < n_tiles; tile += waves) {
-        for (int d = l; d < 256; d += 64) off[w][d] = hist[(uint64_t)d * n_tiles + tile];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        for (int r = 0; r < RADIX_TILE / 64; r++) {
-            uint64_t idx = tile * RADIX_TILE + r * 64 + l;
-            bool valid = idx < n;
-            uint32_t key = valid ? kin[idx] : 0u;
-            uint32_t val = valid ? vin[idx] : 0u;
-            uint32_t d = (key >> shift) & 0xFFu;
-            uint64_t peers = __ballot(valid);
-#pragma unroll
-            for (int bit = 0; bit < 8; bit++) {
-                uint64_t m = __ballot((d >> bit) & 1u);
-                peers &= ((d >> bit) & 1u) ? m : ~m;
-            }
-            uint32_t base = off[w][d];
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            if (valid) {
-                uint32_t pos = base + (uint32_t)__popcll(peers & lt);
-                if (pos < n) {
-                    kout[pos] = key;
-                    vout[pos] = val;
-                } else {
-                    atomicOr(&ctr->err, ERR_INTERNAL);
-                }
-                if ((peers & lt) == 0) off[w][d] = base + (uint32_t)__popcll(peers);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        }
+        S_stamp[s] = 0;
     }
 }
 
@@ -1090,15 +1042,6 @@ __global__ __launch_bounds__(256) void k_copy_calibration(uint4 *__restrict__ ds
         dst[i] = src[i];
 }
 
-// Ages of the first n slots advanced by k, saturating at 2^32 - 1.
-__global__ void k_age_slots(uint32_t *S_age, uint64_t n, uint32_t k) {
-    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n;
-         i += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t a = S_age[i];
-        S_age[i] = a > 0xFFFFFFFFu - k ? 0xFFFFFFFFu : a + k;
-    }
-}
-
 __global__ void k_fill_u32(uint32_t *p, uint32_t v, uint64_t n) {
     for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n;
          i += (uint64_t)gridDim.x * blockDim.x)
@@ -1146,15 +1089,16 @@ static unsigned mc_grid(uint64_t max_blocks) {
 }
 
 void launch_cull(const Geom &g, const DevState &d, const StatusLayout &sl, float iso, float prev_iso,
-                 uint64_t n_slots_host, int identity_cache, uint32_t gen, hipStream_t s) {
+                 int identity_cache, uint32_t now, uint32_t gen, hipStream_t s) {
     static unsigned rgrid = 0;
     if (!rgrid) rgrid = resident_grid(k_cull, ~0ull >> 4);
     const uint64_t nt = cull_tiles(g);
-    k_call_reset<<<grid_cap(sl.total, 64), 256, 0, s>>>(d.ctr, n_slots_host, d.status, sl.total);
+    k_call_reset<<<grid_cap(sl.total, 64), 256, 0, s>>>(d.ctr, d.status, sl.total);
     k_cull_scan<<<(unsigned)((nt + 255) / 256), 256, 0, s>>>(d.tile_ranges, nt, iso, prev_iso, d.cull_list,
                                                              d.ctr);
     k_cull<<<(unsigned)std::min<uint64_t>(nt, rgrid), 256, 0, s>>>(
-        g, d.ranges, iso, d.cull_list, nt, d.I_slot, identity_cache, d.active, d.ctr, d.round_gen, gen);
+        g, d.ranges, iso, d.cull_list, nt, d.I_slot, identity_cache, d.S_stamp, now, d.active, d.ctr,
+        d.round_gen, gen);
 }
 
 uint64_t cull_tiles(const Geom &g) {
@@ -1167,7 +1111,7 @@ void launch_tile_ranges(const Geom &g, const float2 *ranges, float2 *tile_ranges
 }
 
 void launch_compact_blocks(const Geom &g, const DevState &d, const StatusLayout &sl, uint32_t gen,
-                           hipStream_t s) {
+                           const SlotState &ss, hipStream_t s) {
     static unsigned cgrid = 0, wgrid = 0;
     if (!cgrid) cgrid = resident_grid(k_round_counts, ~0ull >> 4);
     if (!wgrid) wgrid = resident_grid(k_compact_blocks, ~0ull >> 4);
@@ -1176,41 +1120,43 @@ void launch_compact_blocks(const Geom &g, const DevState &d, const StatusLayout 
                                                                       d.ctr, d.status + sl.rnd);
     k_round_counts<<<(unsigned)std::min<uint64_t>(n_rounds, cgrid), 256, 0, s>>>(
         g, d.active, d.round_list, d.round_cnt, d.part_cand, d.ctr);
-    k_round_scan<<<1, 256, 0, s>>>(d.round_cnt, d.ctr);
+    k_round_scan<<<1, 256, 0, s>>>(d.round_cnt, d.ctr, ss);
     k_compact_blocks<<<(unsigned)std::min<uint64_t>(n_rounds, wgrid), 256, 0, s>>>(
         g, d.active, d.round_list, d.round_cnt, d.I_active, d.I_new, d.ctr);
 }
 
-void launch_slot_pass(const DevState &d, const StatusLayout &sl, uint64_t n_slots_host,
-                      uint32_t age_cap, hipStream_t s) {
-    if (n_slots_host == 0) return;
-    unsigned tiles = (unsigned)((n_slots_host + SLOT_TILE - 1) / SLOT_TILE);
-    k_slot_pass<<<tiles, 256, 0, s>>>(d.active, d.S_block, d.S_age, n_slots_host, age_cap,
-                                      d.sort_key[0], d.sort_val[0], d.slot_or, d.slot_and, d.ctr,
-                                      d.status + sl.slot);
-}
-
-void launch_plan_grow(const DevState &d, uint64_t max_slots, uint64_t grow_bound, hipStream_t s) {
-    k_plan_grow<<<grid_cap(grow_bound, 2048), 256, 0, s>>>(d.ctr, max_slots, d.S_block, d.S_age,
-                                                          d.sort_key[0], d.sort_val[0], d.slot_or,
-                                                          d.slot_and);
-}
-
-void launch_radix(const DevState &d, const StatusLayout &sl, uint64_t max_elems, uint32_t age_cap,
-                  hipStream_t s) {
-    uint64_t tiles = (max_elems + RADIX_TILE - 1) / RADIX_TILE;
-    unsigned grid = (unsigned)((tiles + 3) / 4 < 2048 ? (tiles + 3) / 4 : 2048);
-    if (grid == 0) grid = 1;
-    uint64_t scan_tiles = (256 * tiles + SCAN_TILE - 1) / SCAN_TILE;
-    unsigned sgrid = (unsigned)(scan_tiles < 2048 ? scan_tiles : 2048);
-    if (sgrid == 0) sgrid = 1;
-    for (int p = 0; p < 4 && (p == 0 || (age_cap >> (8 * p)) != 0); p++) {
-        k_radix_hist<<<grid, 256, 0, s>>>(d.ctr, p, d.sort_key[0], d.sort_key[1], d.radix_hist,
-                                          d.status + sl.scan);
-        k_radix_scan<<<sgrid, 256, 0, s>>>(d.ctr, p, d.radix_hist, d.status + sl.scan);
-        k_radix_scatter<<<grid, 256, 0, s>>>(d.ctr, p, d.sort_key[0], d.sort_key[1], d.sort_val[0],
-                                             d.sort_val[1], d.radix_hist);
+uint32_t *launch_evict(const DevState &d, uint32_t n_used, uint32_t base, uint32_t now, hipStream_t s) {
+    if (n_used == 0 || now <= base) return d.evict[0];   // no slot was used before this call
+    const uint32_t tiles = (n_used + EVICT_TILE - 1) / EVICT_TILE;
+    const int key_bits = 32 - __builtin_clz((now - base) | 1u);
+    const int passes = (key_bits + EVICT_BITS - 1) / EVICT_BITS;
+    uint32_t *out = nullptr;
+    for (int k = 0; k < passes; k++) {
+        EvictPass p;
+        p.base = base;
+        p.now = now;
+        p.shift = k * EVICT_BITS;
+        p.bits = std::min(EVICT_BITS, key_bits - p.shift);
+        p.first = k == 0;
+        p.last = k == passes - 1;
+        p.in = out;
+        p.out = out = d.evict[k & 1];
+        p.n_used = n_used;
+        p.tiles = tiles;
+        // up to 64 tiles every workgroup of k_evict_list adds up the rows
+        // itself (at most 64 loads per digit); beyond, a launch scans them
+        p.scanned = tiles > 64;
+        const int refresh = k == 0 && now - base > EVICT_REFRESH;
+        k_evict_count<<<tiles, 256, 0, s>>>(p, d.S_stamp, d.evict_hist, d.ctr, refresh);
+        if (p.scanned) k_evict_scan<<<1u << p.bits, 256, 0, s>>>(tiles, d.evict_hist, d.evict_tot, d.ctr);
+        k_evict_list<<<tiles, 256, 0, s>>>(p, d.S_stamp, d.evict_hist, d.evict_tot, d.ctr);
     }
+    return out;
+}
+
+void launch_cache_empty(const DevState &d, uint64_t n_used, hipStream_t s) {
+    if (n_used)
+        k_cache_empty<<<grid_cap(n_used, 8192), 256, 0, s>>>(n_used, d.S_block, d.S_stamp, d.I_slot);
 }
 
 
@@ -1303,10 +1249,6 @@ void launch_backward(const Geom &g, const DevState &d, const float *slots, float
 void launch_copy_calibration(void *dst, const void *src, uint64_t n16, hipStream_t s) {
     if (n16) k_copy_calibration<<<grid_cap(n16, 16384), 256, 0, s>>>(
         reinterpret_cast<uint4 *>(dst), reinterpret_cast<const uint4 *>(src), n16);
-}
-
-void launch_age_slots(uint32_t *S_age, uint64_t n, uint32_t k, hipStream_t s) {
-    if (n && k) k_age_slots<<<grid_cap(n, 8192), 256, 0, s>>>(S_age, n, k);
 }
 
 void launch_fill_u32(uint32_t *p, uint32_t v, uint64_t n, hipStream_t s) {

@@ -156,9 +156,18 @@ __device__ __forceinline__ void store_slot(const float *v, uint64_t s, float iso
     mask_iso[s] = __float_as_uint(iso);
 }
 
-// Alg. 1 AssignSlots fused with DecompressBlocks: new block I_new[i] takes the
-// i-th slot of the age-sorted available list, evicting its previous owner,
-// and is decoded straight into that slot.
+// Alg. 1 AssignSlots: the slots of the call's new blocks, in their order:
+// the unused ones from n_used on, then the list of those to evict.
+struct SlotSource {
+    const uint32_t *evict;
+    uint64_t n_used, n_unused;   // before the call; unused ones after its growth
+    __device__ __forceinline__ uint64_t slot(uint64_t i) const {
+        return i < n_unused ? n_used + i : evict[i - n_unused];
+    }
+};
+
+// AssignSlots fused with DecompressBlocks: new block I_new[i] takes its
+// slot, evicting the previous owner, and is decoded straight into it.
 // LOW (double precision, staged, low rates): the decode is
 // decode_block_staged_low, which holds the kernel to the registers of the
 // low-rate decoder (4 waves per SIMD; 5 spills registers and is slower); the
@@ -166,10 +175,10 @@ __device__ __forceinline__ void store_slot(const float *v, uint64_t s, float iso
 // k_decode_retry.
 template <bool F64, bool STAGED, bool LOW = false>
 __global__ __launch_bounds__(256, LOW ? 4 : (F64 ? 1 : 4)) void k_assign_decode(Counters *ctr, const uint32_t *__restrict__ I_new,
-                                                      const uint32_t *__restrict__ sorted0,
-                                                      const uint32_t *__restrict__ sorted1,
+                                                      const uint32_t *__restrict__ evict,
+                                                      SlotState ss, uint32_t now,
                                                       int32_t *S_block, int32_t *I_slot,
-                                                      uint32_t *S_age, const uint64_t *__restrict__ stream,
+                                                      uint32_t *S_stamp, const uint64_t *__restrict__ stream,
                                                       int rate, float *__restrict__ slots,
                                                       uint64_t n_blocks, float iso,
                                                       uint64_t *__restrict__ masks,
@@ -179,32 +188,34 @@ __global__ __launch_bounds__(256, LOW ? 4 : (F64 ? 1 : 4)) void k_assign_decode(
     const uint64_t n_slots = ctr->n_slots;
     const uint64_t n_new = ctr->n_new;
     if (n_new == 0) return;
-    // the radix passes ping-pong; the result is in buffer (#passes run) & 1
-    const uint32_t *sorted = (__popc(ctr->pass_mask) & 1) ? sorted1 : sorted0;
+    const SlotSource src{evict, ss.n_used, n_slots - ss.n_used};
+    // slots this call created and leaves unused: their age counts from here
+    const uint64_t created = ctr->n_used > ss.n_slots ? ctr->n_used : ss.n_slots;
+    for (uint64_t i = created + blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n_slots;
+         i += (uint64_t)gridDim.x * blockDim.x)
+        S_stamp[i] = now;
     extern __shared__ uint64_t stage_lds[];
     constexpr bool staged = STAGED;
     uint64_t *st = stage_lds + (threadIdx.x >> 6) * (STAGED ? stage_wave_words(rate, F64) : 0u);
-    uint32_t evicted = 0;
     // whole waves iterate together (the staging is a wave-wide copy)
     for (uint64_t i0 = blockIdx.x * (uint64_t)blockDim.x + (threadIdx.x & ~63u); i0 < n_new;
          i0 += (uint64_t)gridDim.x * blockDim.x) {
         const uint64_t i = i0 + __lane_id();
         bool valid = i < n_new;
         const uint32_t b = valid ? I_new[i] : 0u;
-        const uint32_t s = valid ? sorted[i] : 0u;
+        const uint64_t s = valid ? src.slot(i) : 0u;
         if (valid && (b >= n_blocks || s >= n_slots)) {  // never expected: report, do not touch memory
             atomicOr(&ctr->err, ERR_INTERNAL);
             valid = false;
         }
         if (valid) {
-            int32_t old = S_block[s];
-            if (old >= 0) {
-                I_slot[old] = -1;
-                evicted++;
+            if (i >= src.n_unused) {
+                const int32_t old = S_block[s];
+                if (old >= 0) I_slot[old] = -1;
             }
             S_block[s] = (int32_t)b;
             I_slot[b] = (int32_t)s;
-            S_age[s] = 0;
+            S_stamp[s] = now;
         }
         float v[64];
         bool done = true;
@@ -232,9 +243,6 @@ __global__ __launch_bounds__(256, LOW ? 4 : (F64 ? 1 : 4)) void k_assign_decode(
             }
         }
     }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) evicted += __shfl_xor(evicted, d, 64);   // one atomic per wave
-    if (__lane_id() == 0 && evicted) atomicAdd(&ctr->n_evicted, (unsigned long long)evicted);
 }
 
 template <bool F64>
@@ -261,8 +269,7 @@ __global__ __launch_bounds__(256) void k_encode(Geom g, const void *__restrict__
 // The blocks the low-rate decoder handed back, decoded with the general
 // decoder from global memory into the slots the assignment gave them.
 __global__ __launch_bounds__(256) void k_decode_retry(const Counters *ctr, const uint32_t *__restrict__ I_new,
-                                                     const uint32_t *__restrict__ sorted0,
-                                                     const uint32_t *__restrict__ sorted1,
+                                                     const uint32_t *__restrict__ evict, SlotState ss,
                                                      const uint64_t *__restrict__ stream, int rate,
                                                      float *__restrict__ slots, float iso,
                                                      uint64_t *__restrict__ masks,
@@ -270,10 +277,11 @@ __global__ __launch_bounds__(256) void k_decode_retry(const Counters *ctr, const
                                                      const uint32_t *__restrict__ retry) {
     if (ctr->err) return;
     const uint32_t n = ctr->tile_ctr[TC_RETRY];
-    const uint32_t *sorted = (__popc(ctr->pass_mask) & 1) ? sorted1 : sorted0;
+    const SlotSource src{evict, ss.n_used, ctr->n_slots - ss.n_used};
     for (uint32_t j = blockIdx.x * blockDim.x + threadIdx.x; j < n; j += gridDim.x * blockDim.x) {
         const uint32_t i = retry[j];
-        const uint32_t b = I_new[i], s = sorted[i];
+        const uint32_t b = I_new[i];
+        const uint64_t s = src.slot(i);
         float v[64];
         decode_block<true>(stream + (uint64_t)b * rate, rate, v);
         store_slot(v, s, iso, slots, masks, mask_iso);
@@ -311,20 +319,19 @@ void launch_ranges_from_blocks(const Geom &g, const float *blocks, float2 *range
 }
 
 void launch_assign_decode(const DevState &d, int is_f64, uint32_t rate, uint64_t max_new, float iso,
-                          hipStream_t s) {
+                          const uint32_t *evict, const SlotState &ss, uint32_t now, hipStream_t s) {
     unsigned grid = grid_for(max_new, 2048);
     const unsigned lds = stage_lds_bytes((int)rate, is_f64 != 0);
     if (is_f64 && lds && rate <= LOW_RATE_MAX && d.retry) {
         k_assign_decode<true, true, true><<<grid, 256, lds, s>>>(
-            d.ctr, d.I_new, d.sort_val[0], d.sort_val[1], d.S_block, d.I_slot, d.S_age, d.stream,
-            (int)rate, d.slots, max_new, iso, d.masks, d.mask_iso, d.retry);
-        k_decode_retry<<<64, 256, 0, s>>>(d.ctr, d.I_new, d.sort_val[0], d.sort_val[1], d.stream,
-                                          (int)rate, d.slots, iso, d.masks, d.mask_iso, d.retry);
+            d.ctr, d.I_new, evict, ss, now, d.S_block, d.I_slot, d.S_stamp, d.stream, (int)rate, d.slots,
+            max_new, iso, d.masks, d.mask_iso, d.retry);
+        k_decode_retry<<<64, 256, 0, s>>>(d.ctr, d.I_new, evict, ss, d.stream, (int)rate, d.slots, iso,
+                                          d.masks, d.mask_iso, d.retry);
         return;
     }
-    BCMC_DECODE_LAUNCH(k_assign_decode, grid, rate, s, d.ctr, d.I_new, d.sort_val[0], d.sort_val[1],
-                       d.S_block, d.I_slot, d.S_age, d.stream, (int)rate, d.slots, max_new, iso,
-                       d.masks, d.mask_iso);
+    BCMC_DECODE_LAUNCH(k_assign_decode, grid, rate, s, d.ctr, d.I_new, evict, ss, now, d.S_block, d.I_slot,
+                       d.S_stamp, d.stream, (int)rate, d.slots, max_new, iso, d.masks, d.mask_iso);
 }
 
 void launch_encode(const Geom &g, const void *field, int is_f64, uint32_t rate, uint64_t *stream,
