@@ -27,7 +27,6 @@ struct bcmc_volume {
     int identity = 0;              // slots are the caller's decoded blocks
     const float *ext_blocks = nullptr;
     DevState d;
-    StatusLayout sl{};
     uint64_t init_slots = 0, max_slots = 0, n_slots = 0, n_used = 0;  // host mirror
     Counters *h_ctr = nullptr;     // pinned copy of the device counters
     bcmc_stats stats{};
@@ -40,8 +39,12 @@ struct bcmc_volume {
     int have_extract = 0;
     float last_iso = 0.0f;
     int last_format = BCMC_VERTEX_F32;   // the last extract's format (its grid set the chunks)
-    float cull_iso = NAN;          // isovalue of the last cull (NaN: the flags are all zero)
-    uint32_t gen = 0;              // extract calls, as the cull stamps rounds with active blocks
+    float cull_iso = NAN;          // isovalue of the last cull
+    int rewrite_flags = 1;         // the flags do not follow from the ranges and cull_iso
+    int counters_dirty = 1;        // the counts a call starts from are not known to be zero
+    Counters *ctr[2] = {nullptr, nullptr};       // a call counts in one and clears the other
+    uint64_t *round_cnt[2] = {nullptr, nullptr};
+    uint32_t turn = 0;             // which
 };
 
 namespace bcmc {
@@ -55,10 +58,18 @@ int volume_is_identity(const bcmc_volume *v) { return v->identity; }
 
 namespace {
 
-// After the ranges change: all flags zero, no tile culled before.
-void clear_flags(bcmc_volume *v, hipStream_t s) {
-    launch_fill_u32(reinterpret_cast<uint32_t *>(v->d.active), 0u, (v->g.nb + 3) / 4, s);
-    v->cull_iso = NAN;
+// Called before the kernels of a call: the copy of the counts it uses.
+void take_turn(bcmc_volume *v, hipStream_t s) {
+    if (v->counters_dirty)
+        for (int k = 0; k < 2; k++) {
+            launch_fill_u32(reinterpret_cast<uint32_t *>(v->ctr[k]), 0u, sizeof(Counters) / 4, s);
+            launch_fill_u32(reinterpret_cast<uint32_t *>(v->round_cnt[k]), 0u, 2 * block_rounds(v->g.nb), s);
+        }
+    v->turn ^= 1u;
+    v->d.ctr = v->ctr[v->turn];
+    v->d.ctr_next = v->ctr[v->turn ^ 1u];
+    v->d.round_cnt = v->round_cnt[v->turn];
+    v->d.round_next = v->round_cnt[v->turn ^ 1u];
 }
 
 int invalid(const std::string &msg) {
@@ -115,17 +126,7 @@ void free_cache(bcmc_volume *v) {
     for (int i = 0; i < 2; i++) dev_free(v->d.evict[i]);
     dev_free(v->d.evict_hist);
     dev_free(v->d.evict_tot);
-    dev_free(v->d.status);
 }
-
-StatusLayout status_layout(const Geom &g) {
-    StatusLayout s;
-    s.rnd = 0;
-    s.total = s.rnd + block_rounds(g.nb) / 4096 + 1;
-    return s;
-}
-
-void layout_status(bcmc_volume *v) { v->sl = status_layout(v->g); }
 
 int alloc_common(bcmc_volume *v) {
     int rc;
@@ -133,18 +134,20 @@ int alloc_common(bcmc_volume *v) {
     if ((rc = dev_alloc(&v->d.tile_ranges, cull_tiles(v->g)))) return rc;
     if ((rc = dev_alloc(&v->d.cull_list, 2 * cull_tiles(v->g)))) return rc;
     if ((rc = dev_alloc(&v->d.active, v->g.nb + 16))) return rc;
-    if ((rc = dev_alloc(&v->d.round_gen, block_rounds(v->g.nb)))) return rc;
-    BCMC_HIP_TRY(hipMemset(v->d.round_gen, 0, block_rounds(v->g.nb) * sizeof(uint32_t)));
     if ((rc = dev_alloc(&v->d.I_active, v->g.nb))) return rc;
     if ((rc = dev_alloc(&v->d.blk_cnt, v->g.nb))) return rc;
     if ((rc = dev_alloc(&v->d.blk_off, v->g.nb))) return rc;
-    if ((rc = dev_alloc(&v->d.part_cand, (v->g.nb + BLK_TILE - 1) / BLK_TILE))) return rc;
-    if ((rc = dev_alloc(&v->d.round_list, block_rounds(v->g.nb)))) return rc;
-    if ((rc = dev_alloc(&v->d.round_cnt, block_rounds(v->g.nb)))) return rc;
+    for (int k = 0; k < 2; k++) {
+        if ((rc = dev_alloc(&v->round_cnt[k], block_rounds(v->g.nb)))) return rc;
+        if ((rc = dev_alloc(&v->ctr[k], 1))) return rc;
+    }
+    v->d.ctr = v->ctr[0];
+    if (block_rounds(v->g.nb) > ROUNDS_DIRECT &&
+        (rc = dev_alloc(&v->d.round_sums, 2 * (block_rounds(v->g.nb) / 256 + 1))))
+        return rc;
     if ((rc = dev_alloc(&v->d.chunk_off, mc_chunk_slots(v->g.nb) + 8))) return rc;
     if ((rc = dev_alloc(&v->d.part_occw, 4 * MC_MAX_GRID))) return rc;
     if ((rc = dev_alloc(&v->d.part_giso, 4 * MC_MAX_GRID))) return rc;
-    if ((rc = dev_alloc(&v->d.ctr, 1))) return rc;
     if ((rc = dev_alloc(&v->d.mc_table, 256))) return rc;
     if (mc_table_status() != 0) return invalid("marching cubes table generation failed");
     BCMC_HIP_TRY(hipMemcpy(v->d.mc_table, mc_table_host(), 256 * sizeof(uint64_t),
@@ -163,20 +166,20 @@ void destroy(bcmc_volume *v) {
     dev_free(v->d.tile_ranges);
     dev_free(v->d.cull_list);
     dev_free(v->d.active);
-    dev_free(v->d.round_gen);
     dev_free(v->d.I_active);
     dev_free(v->d.I_new);
     dev_free(v->d.retry);
     dev_free(v->d.I_slot);
     dev_free(v->d.blk_cnt);
     dev_free(v->d.blk_off);
-    dev_free(v->d.part_cand);
-    dev_free(v->d.round_list);
-    dev_free(v->d.round_cnt);
+    for (int k = 0; k < 2; k++) {
+        dev_free(v->round_cnt[k]);
+        dev_free(v->ctr[k]);
+    }
+    dev_free(v->d.round_sums);
     dev_free(v->d.chunk_off);
     dev_free(v->d.part_occw);
     dev_free(v->d.part_giso);
-    dev_free(v->d.ctr);
     dev_free(v->d.mc_table);
     if (v->h_ctr) (void)hipHostFree(v->h_ctr);
     for (auto &e : v->ev)
@@ -214,7 +217,6 @@ int set_budget(bcmc_volume *v, uint64_t initial_bytes, uint64_t max_bytes, hipSt
     free_cache(v);
     v->init_slots = init;
     v->max_slots = maxs;
-    layout_status(v);
     int rc;
     if ((rc = dev_alloc(&v->d.S_block, maxs))) return rc;
     if ((rc = dev_alloc(&v->d.S_stamp, maxs))) return rc;
@@ -225,8 +227,6 @@ int set_budget(bcmc_volume *v, uint64_t initial_bytes, uint64_t max_bytes, hipSt
         if ((rc = dev_alloc(&v->d.evict[i], maxs))) return rc;
     if ((rc = dev_alloc(&v->d.evict_hist, (maxs + EVICT_TILE - 1) / EVICT_TILE * EVICT_BINS))) return rc;
     if ((rc = dev_alloc(&v->d.evict_tot, EVICT_BINS))) return rc;
-    if ((rc = dev_alloc(&v->d.status, v->sl.total))) return rc;
-    BCMC_HIP_TRY(hipMemsetAsync(v->d.status, 0, v->sl.total * sizeof(uint64_t), s));
     return reset_cache_state(v, s);
 }
 
@@ -297,7 +297,6 @@ int bcmc_load_compressed(const void *stream, uint64_t nbytes, int stream_is_devi
     }
     launch_decode_ranges(g, v->d.stream, v->is_f64, rate, v->d.ranges, nullptr, &v->d.ctr->err, s);
     launch_tile_ranges(g, v->d.ranges, v->d.tile_ranges, s);
-    clear_flags(v, s);
     if ((rc = sync_counters(v, s))) {
         destroy(v);
         return rc;
@@ -329,9 +328,7 @@ int bcmc_volume_from_blocks(const float *d_blocks, uint32_t nx, uint32_t ny, uin
     v->identity = 1;
     v->ext_blocks = d_blocks;
     v->max_slots = 0;
-    layout_status(v);
-    if ((rc = alloc_common(v)) || (rc = dev_alloc(&v->d.status, v->sl.total)) ||
-        (rc = dev_alloc(&v->d.masks, v->g.nb))) {
+    if ((rc = alloc_common(v)) || (rc = dev_alloc(&v->d.masks, v->g.nb))) {
         destroy(v);
         return rc;
     }
@@ -343,7 +340,6 @@ int bcmc_volume_from_blocks(const float *d_blocks, uint32_t nx, uint32_t ny, uin
     }
     launch_ranges_from_blocks(v->g, d_blocks, v->d.ranges, &v->d.ctr->err, s);
     launch_tile_ranges(v->g, v->d.ranges, v->d.tile_ranges, s);
-    clear_flags(v, s);
     if ((rc = sync_counters(v, s))) {
         destroy(v);
         return rc;
@@ -365,7 +361,7 @@ int bcmc_rebind_blocks(bcmc_volume *v, const float *d_blocks, void *hip_stream) 
     v->have_extract = 0;
     launch_ranges_from_blocks(v->g, d_blocks, v->d.ranges, &v->d.ctr->err, as_stream(hip_stream));
     launch_tile_ranges(v->g, v->d.ranges, v->d.tile_ranges, as_stream(hip_stream));
-    clear_flags(v, as_stream(hip_stream));
+    v->rewrite_flags = 1;
     BCMC_HIP_TRY(hipGetLastError());
     return BCMC_OK;
 }
@@ -438,10 +434,8 @@ int bcmc_extract(bcmc_volume *v, float iso, void *d_out, uint64_t capacity_verti
         return (marks >> i) & 1u ? hipEventRecord(v->ev[i], s) : hipSuccess;
     };
     BCMC_HIP_TRY(mark(0));
-    if (++v->gen == 0) {   // the stamps would repeat: start over from all-zero
-        launch_fill_u32(v->d.round_gen, 0u, block_rounds(v->g.nb), s);
-        v->gen = 1;
-    }
+    take_turn(v, s);
+    v->counters_dirty = 1;   // until every kernel of the call is enqueued
     if (!v->identity) {
         // a clock about to pass its end starts over with an empty cache
         if (v->calls_since_reset >= 0xFFFFFFF0u && (rc = reset_cache_state(v, s))) return rc;
@@ -449,9 +443,10 @@ int bcmc_extract(bcmc_volume *v, float iso, void *d_out, uint64_t capacity_verti
     }
     const uint32_t now = v->calls_since_reset;
     const SlotState ss{v->n_slots, v->n_used, v->max_slots, v->identity};
-    launch_cull(v->g, v->d, v->sl, iso, v->cull_iso, v->identity, now, v->gen, s);
+    launch_cull(v->g, v->d, iso, v->cull_iso, v->rewrite_flags, v->identity, now, s);
     v->cull_iso = iso;
-    launch_compact_blocks(v->g, v->d, v->sl, v->gen, ss, s);
+    v->rewrite_flags = 1;
+    launch_compact_blocks(v->g, v->d, ss, s);
     BCMC_HIP_TRY(mark(1));
     const uint32_t *evict = nullptr;
     if (!v->identity) evict = launch_evict(v->d, (uint32_t)v->n_used, v->evict_base, now, s);
@@ -465,11 +460,12 @@ int bcmc_extract(bcmc_volume *v, float iso, void *d_out, uint64_t capacity_verti
     launch_mc_emit(v->g, v->d, slots, v->d.I_slot, v->identity, iso, d_out, capacity_vertices,
                    v->vertex_format, s);
     BCMC_HIP_TRY(mark(6));
-    if (hipError_t le = hipGetLastError()) {   // a launch failed: the flags are unknown
-        clear_flags(v, s);
+    if (hipError_t le = hipGetLastError()) {   // a launch failed: counts and flags are unknown
         set_error(std::string("extract launch: ") + hipGetErrorString(le));
         return BCMC_E_HIP;
     }
+    v->counters_dirty = 0;
+    v->rewrite_flags = 0;
     if ((rc = sync_counters(v, s))) return rc;
     const Counters &c = *v->h_ctr;
     v->stats.calls++;
@@ -501,7 +497,7 @@ int bcmc_extract(bcmc_volume *v, float iso, void *d_out, uint64_t capacity_verti
     st.n_evicted = c.n_evicted;
     st.n_occupied = c.n_occ;
     st.n_candidates = c.n_cand;
-    st.n_general = v->identity ? 0 : c.tile_ctr[TC_RETRY];
+    st.n_general = v->identity ? 0 : c.n_retry;
     st.n_slots = v->n_slots;
     st.n_triangles = T;
     st.hit_rate = c.n_act ? 1.0 - (double)st.n_new / (double)c.n_act : 1.0;
@@ -602,7 +598,7 @@ int bcmc_decode_all(bcmc_volume *v, float *d_blocks, void *hip_stream) {
     launch_decode_ranges(v->g, v->d.stream, v->is_f64, v->rate, v->d.ranges, d_blocks,
                          &v->d.ctr->err, as_stream(hip_stream));
     launch_tile_ranges(v->g, v->d.ranges, v->d.tile_ranges, as_stream(hip_stream));
-    clear_flags(v, as_stream(hip_stream));
+    v->rewrite_flags = 1;
     BCMC_HIP_TRY(hipGetLastError());
     return BCMC_OK;
 }
@@ -825,32 +821,32 @@ int scratch_address(void **out) {
 
 // Carves the extraction's buffers out of the scratch array (256-byte
 // aligned pieces); returns the bytes needed.
-uint64_t carve_scratch(const Geom &g, const StatusLayout &sl, uintptr_t base, DevState &d,
-                       unsigned int **range_err) {
+uint64_t carve_scratch(const Geom &g, uintptr_t base, DevState &d, unsigned int **range_err,
+                       uint64_t *clear_words) {
     uint64_t off = 0;
     auto take = [&](uint64_t bytes) {
         unsigned char *p = reinterpret_cast<unsigned char *>(base + off);
         off += (bytes + 255) / 256 * 256;
         return p;
     };
+    // first what a call clears: counters, the ranges' error word, rounds
     d.ctr = reinterpret_cast<Counters *>(take(sizeof(Counters)));
     *range_err = reinterpret_cast<unsigned int *>(take(sizeof(unsigned int)));
+    d.round_cnt = reinterpret_cast<uint64_t *>(take(block_rounds(g.nb) * sizeof(uint64_t)));
+    *clear_words = off / 4;
+    d.ctr_next = reinterpret_cast<Counters *>(take(sizeof(Counters)));
+    d.round_next = reinterpret_cast<uint64_t *>(take(block_rounds(g.nb) * sizeof(uint64_t)));
     d.mc_table = reinterpret_cast<uint64_t *>(take(256 * sizeof(uint64_t)));
     d.ranges = reinterpret_cast<float2 *>(take(g.nb * sizeof(float2)));
     d.tile_ranges = reinterpret_cast<float2 *>(take(cull_tiles(g) * sizeof(float2)));
     d.cull_list = reinterpret_cast<uint32_t *>(take(2 * cull_tiles(g) * sizeof(uint32_t)));
     d.active = take((g.nb + 16 + 3) / 4 * 4);
-    d.round_gen = reinterpret_cast<uint32_t *>(take(block_rounds(g.nb) * sizeof(uint32_t)));
     d.I_active = reinterpret_cast<uint32_t *>(take(g.nb * sizeof(uint32_t)));
     d.blk_cnt = reinterpret_cast<uint32_t *>(take(g.nb * sizeof(uint32_t)));
     d.blk_off = reinterpret_cast<uint64_t *>(take(g.nb * sizeof(uint64_t)));
     d.masks = reinterpret_cast<uint64_t *>(take(g.nb * sizeof(uint64_t)));
-    d.part_cand = reinterpret_cast<uint32_t *>(take((g.nb + BLK_TILE - 1) / BLK_TILE * sizeof(uint32_t)));
-    d.round_list = reinterpret_cast<uint32_t *>(take(block_rounds(g.nb) * sizeof(uint32_t)));
-    d.round_cnt = reinterpret_cast<uint64_t *>(take(block_rounds(g.nb) * sizeof(uint64_t)));
     d.chunk_off = reinterpret_cast<uint64_t *>(take((mc_chunk_slots(g.nb) + 8) * sizeof(uint64_t)));
     d.part_occw = reinterpret_cast<uint32_t *>(take(4 * MC_MAX_GRID * sizeof(uint32_t)));
-    d.status = reinterpret_cast<uint64_t *>(take(sl.total * sizeof(uint64_t)));
     return off;
 }
 
@@ -868,30 +864,26 @@ extern "C" int bcmc_extract_blocks_noalloc(const float *d_blocks, uint32_t nx, u
     if (rc) return rc;
     if (mc_table_status() != 0) return invalid("marching cubes table generation failed");
     const Geom g = make_geom(nx, ny, nz);
-    const StatusLayout sl = status_layout(g);
     DevState d;
     unsigned int *range_err = nullptr;
-    const uint64_t need = carve_scratch(g, sl, 0, d, &range_err);   // sizes only
+    uint64_t clear_words = 0;
+    const uint64_t need = carve_scratch(g, 0, d, &range_err, &clear_words);   // sizes only
     if (need > kScratchBytes)
         return invalid("volume of " + std::to_string(g.nb) + " blocks needs " + std::to_string(need) +
                        " bytes of scratch; the static scratch holds " + std::to_string(kScratchBytes));
     void *base = nullptr;
     if ((rc = scratch_address(&base))) return rc;
-    carve_scratch(g, sl, reinterpret_cast<uintptr_t>(base), d, &range_err);
+    carve_scratch(g, reinterpret_cast<uintptr_t>(base), d, &range_err, &clear_words);
     hipStream_t s = as_stream(hip_stream);
-    const uint32_t gen = 1;   // the round stamps are cleared below, every call
     // the previous call on this device left its own contents: clear what
-    // must start at zero (counters, error word, flags), rewrite the table
-    launch_fill_u32(reinterpret_cast<uint32_t *>(d.ctr), 0u, sizeof(Counters) / 4, s);
-    launch_fill_u32(range_err, 0u, 1, s);
+    // must start at zero, rewrite the table (and the flags, in the cull)
+    launch_fill_u32(reinterpret_cast<uint32_t *>(d.ctr), 0u, clear_words, s);
     BCMC_HIP_TRY(hipMemcpyAsync(d.mc_table, mc_table_host(), 256 * sizeof(uint64_t),
                                 hipMemcpyHostToDevice, s));
     launch_ranges_from_blocks(g, d_blocks, d.ranges, range_err, s);
     launch_tile_ranges(g, d.ranges, d.tile_ranges, s);
-    launch_fill_u32(reinterpret_cast<uint32_t *>(d.active), 0u, (g.nb + 3) / 4, s);
-    launch_fill_u32(d.round_gen, 0u, block_rounds(g.nb), s);
-    launch_cull(g, d, sl, iso, NAN, 1, 0, gen, s);
-    launch_compact_blocks(g, d, sl, gen, SlotState{0, 0, 0, 1}, s);
+    launch_cull(g, d, iso, NAN, 1, 1, 0, s);
+    launch_compact_blocks(g, d, SlotState{0, 0, 0, 1}, s);
     launch_mc_count(g, d, d_blocks, nullptr, 1, iso, 0, s);
     launch_mc_emit(g, d, d_blocks, nullptr, 1, iso, d_out, capacity_vertices, 0, s);
     BCMC_HIP_TRY(hipGetLastError());

@@ -14,7 +14,16 @@ constexpr uint32_t HIGH_AGE = 0x80000000u;  // age of a slot created empty
 // Tag of a sign mask built for no isovalue: a NaN pattern (isovalues are
 // never NaN, so no call's tag equals it).
 constexpr uint32_t MASK_NONE = 0x7FC00001u;
-constexpr int BLK_TILE = 4096;               // blocks per compaction tile
+constexpr int BLK_TILE = 4096;               // blocks per round of the compaction
+// Volumes of more than 2048 rounds (8.4 M blocks) have the rounds' counts
+// summed in two levels, the first by a launch of its own (4.5 us, where every
+// workgroup would read up to 460 KB of counts at 236 M blocks); below, each
+// workgroup's own sum takes 1-2 us.
+constexpr uint64_t ROUNDS_DIRECT = 2048;
+// Tiles from which the cull takes the live ones from a queue: at 1800 (3.7 M
+// blocks) the cull alone takes less than the queue's launch more, while the
+// 115,200 of 236 M blocks, a tenth of them live, would mostly be dead workgroups.
+constexpr uint64_t CULL_DIRECT = 4096;
 constexpr int EVICT_TILE = 4096;             // slots per tile of the eviction's selection (1024 per wave)
 constexpr int EVICT_BITS = 11;               // key bits per pass of it
 constexpr int EVICT_BINS = 1 << EVICT_BITS;
@@ -22,33 +31,27 @@ constexpr uint32_t EVICT_REFRESH = 1024;     // key span from which its base is 
 constexpr int MC_MAX_GRID = 2048;           // workgroups of the count / emission grid at most
 constexpr int MC_WAVES = 4;                  // blocks (one per wave) per MC tile
 
-// look-back status words: 2 flag bits on top, value below
-constexpr uint64_t LB_AGG = 1ull << 62;
-constexpr uint64_t LB_PRE = 2ull << 62;
-constexpr uint64_t LB_VAL = (1ull << 62) - 1;
-
 enum : uint32_t { ERR_CACHE_CAP = 1u, ERR_NONFINITE = 2u, ERR_INTERNAL = 4u, ERR_TIMEOUT = 8u };
 
 // Device-resident scalars of one extract call.  Written only by kernels of
-// that call, read back once by the host at its end.
+// that call (zeroed by the call before), read back once by the host at its
+// end.
 struct Counters {
     unsigned long long n_act;        // active blocks
     unsigned long long n_new;        // active blocks not in the cache
     unsigned long long n_slots;      // slots of the cache (after growth)
     unsigned long long n_used;       // slots taken into use: [0, n_used) (after this call)
-    unsigned long long n_grow;       // slots added this call
     unsigned long long n_evicted;    // blocks evicted this call
     unsigned long long n_occ;        // active blocks that emit triangles
     unsigned long long n_cand;       // active blocks that may emit (staged by the count pass)
     unsigned long long total_verts;  // 3 * triangles
-    unsigned long long n_live_rounds;  // 4096-block rounds holding an active block
     unsigned int err;                // ERR_* bits
     unsigned int oldest;             // no used slot was last used before this call (~0: not looked for)
     unsigned int n_sort;             // available used slots (with n_evicted)
-    unsigned int tile_ctr[16];       // dynamic work counters (tiles / batches)
+    unsigned int n_retry;            // blocks the low-rate decoder handed back
+    unsigned int cull_live, cull_stale;  // the cull's queued tiles
+    unsigned int pad;
 };
-enum { TC_ROUNDS = 0, TC_RETRY = 9 /* blocks the low-rate decoder handed back */,
-       TC_CULL_LIVE = 10, TC_CULL_STALE = 11 /* the cull's queued tiles */ };
 // Double-precision streams up to this rate decode with the low-rate decoder
 // (and a general pass over the blocks it hands back).
 constexpr uint32_t LOW_RATE_MAX = 4;
@@ -74,7 +77,6 @@ struct DevState {
     float2 *tile_ranges = nullptr;  // per cull tile: hull of its blocks' and halo's ranges
     uint32_t *cull_list = nullptr;  // 2 x cull tiles: the call's live tiles, then its stale ones
     uint8_t *active = nullptr;      // M_active
-    uint32_t *round_gen = nullptr;  // per 4096-block round: the last call that found an active block in it
     uint32_t *I_active = nullptr;   // ascending active block ids
     uint32_t *I_new = nullptr;      // ascending new block ids
     uint32_t *retry = nullptr;      // low-rate f64 decode: indices into I_new handed back
@@ -92,32 +94,25 @@ struct DevState {
     // MC
     uint32_t *blk_cnt = nullptr;    // per active block vertex count
     uint64_t *blk_off = nullptr;    // per active block first vertex
-    uint32_t *part_cand = nullptr;  // per live round: blocks that may emit
-    uint32_t *round_list = nullptr; // ascending live rounds of the call
-    uint64_t *round_cnt = nullptr;  // per live round: (active << 32 | new) blocks, then their offsets
+    uint64_t *round_cnt = nullptr;  // per 4096-block round: counts of its blocks (round_pack)
+    uint64_t *round_next = nullptr; // the next call's, zeroed by this one
+    uint64_t *round_sums = nullptr; // more than ROUNDS_DIRECT rounds: sums of 256 of them
     uint64_t *chunk_off = nullptr;  // per 64-entry chunk of the active list: vertices, then first vertex
                                     // in its XCD eighth; then the 8 eighths' totals
     uint32_t *part_occw = nullptr;  // [4 * max MC grid] per-wave occupied blocks
     float *part_giso = nullptr;     // [4 * max MC grid] per-wave dL/diso of the backward
-    uint64_t *status = nullptr;     // look-back status words (all kernels)
     Counters *ctr = nullptr;
+    Counters *ctr_next = nullptr;   // the next call's, zeroed by this one
     uint64_t *mc_table = nullptr;   // 256 packed cases
 };
 
-// Offsets of each kernel's region inside DevState::status.
-struct StatusLayout {
-    uint64_t rnd, total;
-};
-
 // ---- launchers (extract.hip) -------------------------------------------
-// prev_iso: the previous cull's isovalue (NaN after the flags were cleared).
-// gen: a number that differs from every earlier call's on these buffers
-// (rounds of blocks whose round_gen equals it hold this call's active blocks).
-// now: the call's number since the cache was reset (slots' stamps).
-void launch_cull(const Geom &g, const DevState &d, const StatusLayout &sl, float iso, float prev_iso,
-                 int identity_cache, uint32_t now, uint32_t gen, hipStream_t s);
-void launch_compact_blocks(const Geom &g, const DevState &d, const StatusLayout &sl, uint32_t gen,
-                           const SlotState &ss, hipStream_t s);
+// prev_iso: the previous cull's isovalue; rewrite: the flags hold anything
+// (new ranges).  now: the call's number since the cache was reset (slots'
+// stamps).
+void launch_cull(const Geom &g, const DevState &d, float iso, float prev_iso, int rewrite, int identity_cache,
+                 uint32_t now, hipStream_t s);
+void launch_compact_blocks(const Geom &g, const DevState &d, const SlotState &ss, hipStream_t s);
 inline uint64_t block_rounds(uint64_t nb) { return (nb + BLK_TILE - 1) / BLK_TILE; }
 // Chunk entries of the count pass's and emission's chunk totals: a call
 // with n_act active blocks on W waves has ceil(n_act / cs) chunks of

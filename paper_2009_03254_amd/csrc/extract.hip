@@ -5,13 +5,14 @@
 //
 // Shared idioms:
 //   * wave64 primitives: ballot / mbcnt compaction, shuffle scans;
-//   * single-pass scans with decoupled look-back (Merrill & Garland 2016):
-//     each tile publishes its aggregate, then its inclusive prefix, in a
-//     64-bit status word (2 flag bits + value); tiles are taken from an atomic
-//     counter in order, so a tile only ever waits on tiles already running;
+//   * no launch for a prefix sum that is short: the counts of one kernel are
+//     added up by every workgroup of the next that needs a prefix of them
+//     (a launch costs 4-6 us of a small call, a few KB of counts 1-2 us);
+//   * what a call counts from zero is kept twice: a call counts in one copy
+//     and clears the other for the next call, so no launch resets them;
 //   * device-scope atomics on one address serialise (~14 ns each), so work
-//     without a look-back is spread statically (workgroup w takes items w,
-//     w + G, ...) and per-workgroup counts go to arrays, not one counter.
+//     is spread statically (workgroup w takes items w, w + G, ...) and counts
+//     go to arrays, not one counter.
 #include <stdint.h>
 
 #include <algorithm>
@@ -73,37 +74,28 @@ __global__ __launch_bounds__(256) void k_tile_ranges(Geom g, const float2 *__res
                                               fmaxf(fmaxf(s_h[0].y, s_h[1].y), fmaxf(s_h[2].y, s_h[3].y)));
 }
 
-// The per-call counters and the look-back status words of the call's scans
-// start at zero: cleared first (the cull's tile queue counts in the counters).
-__global__ __launch_bounds__(256) void k_call_reset(Counters *ctr, uint64_t *status, uint64_t status_words) {
-    const uint64_t gid = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
-    if (gid == 0) {
-        Counters c{};
-        c.oldest = ~0u;
-        *ctr = c;
-    }
-    for (uint64_t w = gid; w < status_words; w += (uint64_t)gridDim.x * blockDim.x) status[w] = 0;
+// A tile is live when its hull straddles iso (culled block by block), stale
+// when it is not and may hold flags (its hull straddled the previous call's
+// isovalue, or `rewrite`: nothing is known of them): they are cleared.
+__device__ __forceinline__ void tile_state(float2 hull, float iso, float prev_iso, int rewrite, bool &live,
+                                           bool &stale) {
+    live = hull.x < iso && iso <= hull.y;
+    stale = !live && (rewrite || (hull.x < prev_iso && prev_iso <= hull.y));
 }
 
-// Tile queue of the cull: the tiles whose hull straddles iso (live: culled
-// block by block) and those whose hull straddled the previous call's isovalue
-// only (stale: their flags are cleared), one tile per thread, appended with
+// Tile queue of a large volume's cull, one tile per thread, appended with
 // one atomic per wave.  live: n_tiles entries, stale: the n_tiles after.
 __global__ __launch_bounds__(256) void k_cull_scan(const float2 *__restrict__ tile_ranges, uint64_t n_tiles,
-                                                  float iso, float prev_iso, uint32_t *__restrict__ list,
-                                                  Counters *ctr) {
+                                                  float iso, float prev_iso, int rewrite,
+                                                  uint32_t *__restrict__ list, Counters *ctr) {
     const uint64_t t = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
     bool live = false, stale = false;
-    if (t < n_tiles) {
-        const float2 hull = tile_ranges[t];
-        live = hull.x < iso && iso <= hull.y;
-        stale = !live && hull.x < prev_iso && prev_iso <= hull.y;
-    }
+    if (t < n_tiles) tile_state(tile_ranges[t], iso, prev_iso, rewrite, live, stale);
     const uint64_t lm = __ballot(live), sm = __ballot(stale);
     uint32_t lb = 0, sb = 0;
     if (lane() == 0) {
-        if (lm) lb = atomicAdd(&ctr->tile_ctr[TC_CULL_LIVE], (uint32_t)__popcll(lm));
-        if (sm) sb = atomicAdd(&ctr->tile_ctr[TC_CULL_STALE], (uint32_t)__popcll(sm));
+        if (lm) lb = atomicAdd(&ctr->cull_live, (uint32_t)__popcll(lm));
+        if (sm) sb = atomicAdd(&ctr->cull_stale, (uint32_t)__popcll(sm));
     }
     lb = __shfl(lb, 0, 64);
     sb = __shfl(sb, 0, 64);
@@ -111,27 +103,55 @@ __global__ __launch_bounds__(256) void k_cull_scan(const float2 *__restrict__ ti
     if (stale) list[n_tiles + sb + mbcnt(sm)] = (uint32_t)t;
 }
 
+// A round's counts of active, new and may-emit blocks (at most 4096 each).
+__device__ __forceinline__ unsigned long long round_pack(uint32_t act, uint32_t fresh, uint32_t can) {
+    return (unsigned long long)__popc(act) | (unsigned long long)__popc(fresh) << 21 |
+           (unsigned long long)__popc(can) << 42;
+}
+constexpr unsigned long long ROUND_M = (1ull << 21) - 1;
+// ... as (active << 32 | new), for sums over rounds.
+__device__ __forceinline__ uint64_t round_lists(uint64_t c) { return (c & ROUND_M) << 32 | ((c >> 21) & ROUND_M); }
+
 // Flags per block: bit 0 active, bit 1 may emit, bit 2 active without a
 // slot (new, Alg. 1 MarkNewBlocks; never set for an identity cache); the
 // slots of the active blocks that have one are stamped with the call's number
 // (Alg. 1 IncrementSlotAge: a slot's age is the calls since its stamp).
 // The flags are zero outside the tiles the previous call culled, so a tile
 // live then and dead now (stale) is cleared here, a live tile is rewritten
-// in full, and no other flag is touched.  Persistent: workgroup w takes
-// queue entries w, w + G, ... (stale tiles first), so that a surface's live
-// tiles spread evenly over the workgroups whatever their layout, with no
-// shared counter (same-address atomics serialise, ~14 ns each).
-__global__ __launch_bounds__(256) void k_cull(Geom g, const float2 *__restrict__ ranges, float iso,
+// in full, and no other flag is touched.  The active, new and may-emit blocks
+// of each 4096-block round are counted in round_cnt (round_pack) for the
+// compaction: a tile adds up its rows that lie in one round first (an atomic
+// per row of 32 blocks, all on few cache lines: a 512^3 cull of 53 us instead
+// of 21).
+// QUEUE (many tiles): persistent, workgroup w takes entries w, w + G, ... of
+// k_cull_scan's queue (stale tiles first), so that a surface's live tiles
+// spread evenly over the workgroups whatever their layout.  Otherwise one
+// workgroup per tile, which looks at the tile's hull itself: no launch for the
+// queue (up to CULL_DIRECT tiles, where dead workgroups cost less than that).
+template <bool QUEUE>
+__global__ __launch_bounds__(256) void k_cull(Geom g, const float2 *__restrict__ ranges, float iso, float prev_iso,
+                                             int rewrite, const float2 *__restrict__ tile_ranges,
                                              const uint32_t *__restrict__ list, uint64_t n_tiles,
                                              const int32_t *__restrict__ I_slot, int identity,
                                              uint32_t *__restrict__ S_stamp, uint32_t now,
-                                             uint8_t *__restrict__ active, Counters *ctr,
-                                             uint32_t *__restrict__ round_gen, uint32_t gen) {
+                                             uint8_t *__restrict__ active, const Counters *ctr,
+                                             unsigned long long *__restrict__ round_cnt) {
     constexpr int NL = CULL_TZ + 2, RX = CULL_TX + 2, RY = CULL_TY + 2, SLOTS = RX * RY;
     __shared__ float2 sh[NL][RY][RX];
+    __shared__ unsigned long long s_cnt[CULL_TZ * CULL_TY];   // per row (z, y) of the tile: its counts
     const uint32_t ntx = (g.nbx + CULL_TX - 1) / CULL_TX, nty = (g.nby + CULL_TY - 1) / CULL_TY;
-    const uint32_t n_live = ctr->tile_ctr[TC_CULL_LIVE], n_stale = ctr->tile_ctr[TC_CULL_STALE];
-    const uint32_t n_q = n_stale + n_live;
+    uint32_t n_live, n_stale;
+    if constexpr (QUEUE) {
+        n_live = ctr->cull_live;
+        n_stale = ctr->cull_stale;
+    } else {   // a queue of this tile alone
+        bool live, stale;
+        tile_state(tile_ranges[blockIdx.x], iso, prev_iso, rewrite, live, stale);
+        n_live = live;
+        n_stale = stale;
+    }
+    const uint32_t n_q = n_stale + n_live, step = QUEUE ? gridDim.x : 1u;
+    auto live_tile = [&](uint32_t i) { return QUEUE ? list[i] : blockIdx.x; };
     const int lx = threadIdx.x % CULL_TX, ly = threadIdx.x / CULL_TX;
     auto tile_of = [&](uint32_t t, uint32_t &tx, uint32_t &ty, uint32_t &tz) {
         tx = t % ntx;
@@ -139,10 +159,10 @@ __global__ __launch_bounds__(256) void k_cull(Geom g, const float2 *__restrict__
         ty = t % nty;
         tz = t / nty;
     };
-    uint32_t q = blockIdx.x;
-    for (; q < n_stale; q += gridDim.x) {   // culled last time only: flags cleared
+    uint32_t q = QUEUE ? blockIdx.x : 0u;
+    for (; q < n_stale; q += step) {   // culled last time only: flags cleared
         uint32_t tx, ty, tz;
-        tile_of(list[n_tiles + q], tx, ty, tz);
+        tile_of(QUEUE ? list[n_tiles + q] : blockIdx.x, tx, ty, tz);
         const int z0 = (int)(tz * CULL_TZ), z1 = min(z0 + CULL_TZ, (int)g.nbz);
         const uint32_t bx = tx * CULL_TX + lx, by = ty * CULL_TY + ly;
         if (bx < g.nbx && by < g.nby)
@@ -153,7 +173,7 @@ __global__ __launch_bounds__(256) void k_cull(Geom g, const float2 *__restrict__
     constexpr int PER = (NL * SLOTS + 255) / 256;
     auto load_box = [&](uint32_t qq, float2 (&v)[PER]) {
         uint32_t tx, ty, tz;
-        tile_of(list[qq - n_stale], tx, ty, tz);
+        tile_of(live_tile(qq - n_stale), tx, ty, tz);
         const int z0 = (int)(tz * CULL_TZ), z1 = min(z0 + CULL_TZ, (int)g.nbz);
 #pragma unroll
         for (int k = 0; k < PER; k++) {
@@ -170,9 +190,9 @@ __global__ __launch_bounds__(256) void k_cull(Geom g, const float2 *__restrict__
     };
     float2 v[PER];
     if (q < n_q) load_box(q, v);
-    for (; q < n_q; q += gridDim.x) {
+    for (; q < n_q; q += step) {
         uint32_t tx, ty, tz;
-        tile_of(list[q - n_stale], tx, ty, tz);
+        tile_of(live_tile(q - n_stale), tx, ty, tz);
         const int z0 = (int)(tz * CULL_TZ), z1 = min(z0 + CULL_TZ, (int)g.nbz);
         const uint32_t bx = tx * CULL_TX + lx, by = ty * CULL_TY + ly;
 #pragma unroll
@@ -181,14 +201,13 @@ __global__ __launch_bounds__(256) void k_cull(Geom g, const float2 *__restrict__
             if (i < NL * SLOTS) (&sh[0][0][0])[i] = v[k];
         }
         __syncthreads();
-        if (q + gridDim.x < n_q) load_box(q + gridDim.x, v);
-        uint32_t act = 0;   // bit z - z0: block (bx, by, z) is active
+        if (QUEUE && q + step < n_q) load_box(q + step, v);
+        uint32_t act = 0, can = 0, fresh = 0;   // bit z - z0: block (bx, by, z) is active, may emit, is new
         if (bx < g.nbx && by < g.nby) {
             // per layer: 3x3 min / max, 2x2 positive min / max, own range
             float l3a = INFINITY, h3a = -INFINITY;                       // layer zl - 2
             float l3b = INFINITY, h3b = -INFINITY, p2lb = INFINITY, p2hb = -INFINITY;
             float2 ownb = make_float2(INFINITY, -INFINITY);             // layer zl - 1
-            uint32_t can = 0;
 #pragma unroll
             for (int li = 0; li < NL; li++) {
                 float l3 = INFINITY, h3 = -INFINITY, p2l = INFINITY, p2h = -INFINITY;
@@ -234,21 +253,43 @@ __global__ __launch_bounds__(256) void k_cull(Geom g, const float2 *__restrict__
                 if (z0 + z >= z1) break;
                 const bool a = (act >> z) & 1u;
                 const uint64_t b = ((uint64_t)(z0 + z) * g.nby + by) * g.nbx + bx;
-                active[b] = (a ? 1u : 0u) | (((can >> z) & 1u) ? 2u : 0u) | (a && sl[z] < 0 ? 4u : 0u);
+                const bool nw = a && sl[z] < 0;
+                fresh |= (nw ? 1u : 0u) << z;
+                active[b] = (a ? 1u : 0u) | (((can >> z) & 1u) ? 2u : 0u) | (nw ? 4u : 0u);
                 if (!identity && a && sl[z] >= 0) S_stamp[sl[z]] = now;
             }
         }
-        // mark the 4096-block rounds holding active blocks for the
-        // compaction: each half-wave is 32 consecutive blocks of one row, so
-        // its first and last active lanes name every round
+        // the rounds' counts: each half-wave is 32 consecutive blocks of one
+        // row, which lie in one round or in two
+        const int half = lane() & 32;
 #pragma unroll
         for (int z = 0; z < CULL_TZ; z++) {
-            const bool a = (act >> z) & 1u;
-            const uint64_t am = __ballot(a);
-            const uint32_t half = (uint32_t)(am >> (lane() & 32));
-            const int hl = lane() & 31;
-            if (a && (hl == __builtin_ctz(half) || hl == 31 - __builtin_clz(half)))
-                round_gen[(((uint64_t)(z0 + z) * g.nby + by) * g.nbx + bx) / BLK_TILE] = gen;
+            const uint32_t am = (uint32_t)(__ballot((act >> z) & 1u) >> half);
+            const uint32_t cm = (uint32_t)(__ballot((can >> z) & 1u) >> half);
+            const uint32_t nm = (uint32_t)(__ballot((fresh >> z) & 1u) >> half);
+            if (lane() == half) {
+                // the part of a row beyond its first block's round goes there directly
+                const uint64_t b0 = ((uint64_t)(z0 + z) * g.nby + by) * g.nbx + bx;
+                const uint32_t room = BLK_TILE - (uint32_t)(b0 % BLK_TILE);
+                const uint32_t m = room >= 32 ? ~0u : (1u << room) - 1u;
+                s_cnt[z * CULL_TY + ly] = round_pack(am & m, nm & m, cm & m);
+                if (am & ~m) atomicAdd(&round_cnt[b0 / BLK_TILE + 1], round_pack(am & ~m, nm & ~m, cm & ~m));
+            }
+        }
+        __syncthreads();
+        if (threadIdx.x < 64) {   // the rows' rounds ascend: one atomic per run of rows in one round
+            const int z = threadIdx.x / CULL_TY, y = threadIdx.x % CULL_TY;
+            const uint64_t b0 = ((uint64_t)(z0 + z) * g.nby + ty * CULL_TY + y) * g.nbx + tx * CULL_TX;
+            const uint32_t r = (uint32_t)(b0 / BLK_TILE);
+            const uint64_t sum = wave_incl_scan((uint64_t)s_cnt[threadIdx.x]);
+            const uint32_t after = (uint32_t)__shfl_down((int)r, 1, 64);
+            const uint64_t ends = __ballot(threadIdx.x == 63 || after != r);
+            const uint64_t mine = ends & ((1ull << threadIdx.x) - 1);
+            const int prev = mine ? 63 - __builtin_clzll(mine) : 0;
+            const uint64_t base = ((uint64_t)(uint32_t)__shfl((int)(sum >> 32), prev, 64) << 32) |
+                                  (uint32_t)__shfl((int)(uint32_t)sum, prev, 64);
+            const uint64_t c = sum - (mine ? base : 0ull);
+            if (((ends >> threadIdx.x) & 1u) && c) atomicAdd(&round_cnt[r], (unsigned long long)c);
         }
         __syncthreads();   // sh is restaged for the next live tile
     }
@@ -256,22 +297,19 @@ __global__ __launch_bounds__(256) void k_cull(Geom g, const float2 *__restrict__
 
 // I_active (StreamCompactIDs of M_active) and I_new (active blocks without a
 // slot, Alg. 1 MarkNewBlocks, flagged by the cull).  The blocks are cut into
-// rounds of 4096 consecutive blocks, and the cull stamped every round holding
-// an active block with the call's gen (the other rounds' flags are all zero).
-// k_round_list lists the live rounds in ascending order; k_round_counts
-// counts each one's active and new blocks, k_round_scan turns the counts into
-// offsets, and k_compact_blocks writes each round's ids there.  A surface
-// makes runs of live rounds: taking them one per workgroup (rounds w, w + G,
-// ...) spreads a run over the chip, with no waiting between workgroups and no
-// shared counter.  In a round each thread takes 16 consecutive flags (one
-// 16-byte load).
+// rounds of 4096 consecutive blocks, whose counts the cull has formed; the
+// flags of a round without active blocks are not looked at.  Each live round
+// is one workgroup's, with no waiting between workgroups: a round's place
+// in the lists is the sum of the counts before it, which its workgroup adds up
+// itself (up to ROUNDS_DIRECT rounds, 16 KB of counts; larger volumes: of
+// the sums that k_round_sums forms of 256 rounds each, then of rounds).
 // Bit 0 of each byte of w, gathered into bits 0..3: the four bits land on
 // bits 21..24 of the product with no carries between them.
 __device__ __forceinline__ uint32_t byte_bits(uint32_t w) {
     return (((w & 0x01010101u) * 0x00204081u) >> 21) & 0xFu;
 }
 
-__device__ __forceinline__ void flag_bits(uint4 q, uint32_t &actb, uint32_t &newb, uint32_t &cand) {
+__device__ __forceinline__ void flag_bits(uint4 q, uint32_t &actb, uint32_t &newb) {
     actb = newb = 0;
     if ((q.x | q.y | q.z | q.w) == 0) return;   // the common case of a sparse volume
     const uint32_t wds[4] = {q.x, q.y, q.z, q.w};
@@ -280,7 +318,6 @@ __device__ __forceinline__ void flag_bits(uint4 q, uint32_t &actb, uint32_t &new
         const uint32_t w = wds[i];
         actb |= byte_bits(w | (w >> 1) | (w >> 2)) << (4 * i);
         newb |= byte_bits(w >> 2) << (4 * i);
-        cand += (uint32_t)__popc(w & 0x02020202u);
     }
 }
 
@@ -294,60 +331,6 @@ __device__ __forceinline__ uint4 load_flags16(const uint8_t *__restrict__ active
 }
 
 
-// The live rounds (round_gen == gen) in ascending order: 16 stamps per thread
-// (4096 per workgroup), a look-back over the workgroups; the last one writes
-// their number.
-__global__ __launch_bounds__(256) void k_round_list(const uint32_t *__restrict__ round_gen, uint64_t n_rounds,
-                                                   uint32_t gen, uint32_t *__restrict__ list, Counters *ctr,
-                                                   uint64_t *status) {
-    const uint64_t t = take_tile(&ctr->tile_ctr[TC_ROUNDS]);   // look-back order = start order
-    const uint64_t n_tiles = (n_rounds + 4095) / 4096;
-    const uint64_t r0 = t * 4096 + 16u * threadIdx.x;
-    uint32_t live = 0;   // bit j: round r0 + j
-    if (r0 + 16 <= n_rounds) {
-        const uint4 *p = reinterpret_cast<const uint4 *>(round_gen + r0);
-#pragma unroll
-        for (int k = 0; k < 4; k++) {
-            const uint4 q = p[k];
-            live |= ((q.x == gen ? 1u : 0u) | (q.y == gen ? 2u : 0u) | (q.z == gen ? 4u : 0u) |
-                     (q.w == gen ? 8u : 0u)) << (4 * k);
-        }
-    } else {
-        for (int j = 0; j < 16; j++)
-            if (r0 + j < n_rounds && round_gen[r0 + j] == gen) live |= 1u << j;
-    }
-    uint64_t total;
-    uint64_t o = tile_scan_lookback((uint64_t)__popc(live), status, t, &total);
-    for (uint32_t m = live; m; m &= m - 1) list[o++] = (uint32_t)(r0 + __builtin_ctz(m));
-    if (t == n_tiles - 1 && threadIdx.x == 0) ctr->n_live_rounds = total;
-}
-
-// Per live round: (active << 32 | new) blocks, and the blocks that may emit.
-__global__ __launch_bounds__(256) void k_round_counts(Geom g, const uint8_t *__restrict__ active,
-                                                     const uint32_t *__restrict__ round_list,
-                                                     uint64_t *__restrict__ round_cnt,
-                                                     uint32_t *__restrict__ part_cand, const Counters *ctr) {
-    __shared__ uint64_t s_part[4];
-    const uint64_t n_live = ctr->n_live_rounds;
-    for (uint64_t k = blockIdx.x; k < n_live; k += gridDim.x) {
-        const uint64_t base = (uint64_t)round_list[k] * BLK_TILE + 16u * threadIdx.x;
-        uint32_t actb, newb, cand = 0;
-        flag_bits(load_flags16(active, base, g.nb), actb, newb, cand);
-        // three counts of at most 4096 in 21-bit fields
-        uint64_t v = (uint64_t)__popc(actb) | ((uint64_t)__popc(newb) << 21) | ((uint64_t)cand << 42);
-        v = wave_sum(v);
-        if (lane() == 0) s_part[threadIdx.x >> 6] = v;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            const uint64_t t = s_part[0] + s_part[1] + s_part[2] + s_part[3];
-            const uint64_t m21 = (1ull << 21) - 1;
-            round_cnt[k] = ((t & m21) << 32) | ((t >> 21) & m21);
-            part_cand[k] = (uint32_t)(t >> 42);
-        }
-        __syncthreads();   // s_part is rewritten by the next round
-    }
-}
-
 // Alg. 1's early exit (nothing new), growth and supply of slots, from the
 // call's counts.  Every active block that is not new holds one slot, so
 // n_slots - (n_act - n_new) slots are available, and growth (more new blocks
@@ -355,88 +338,152 @@ __global__ __launch_bounds__(256) void k_round_counts(Geom g, const uint8_t *__r
 // ascending order before any used one is evicted, so the unused ones are
 // always [n_used, n_slots): the new blocks take those first, then the oldest
 // n_evict of the used available ones.
-__device__ __forceinline__ void plan_slots(Counters *ctr, uint64_t n_act, uint64_t n_new, SlotState ss) {
+struct SlotPlan {
+    uint64_t grow, n_slots, n_used, n_evicted;
+    bool fits;
+};
+__device__ __forceinline__ SlotPlan plan_slots(uint64_t n_act, uint64_t n_new, const SlotState &ss) {
+    SlotPlan p{0, ss.n_slots, ss.n_used, 0, true};
+    if (ss.identity || n_new == 0) return p;
+    const uint64_t avail = ss.n_slots - (n_act - n_new);
+    if (n_new > avail) {
+        p.grow = n_new - avail;
+        const uint64_t half = (ss.n_slots + 1) / 2;
+        if (half > p.grow) p.grow = half;
+        if (ss.n_slots + p.grow > ss.max_slots) p.grow = ss.max_slots - ss.n_slots;
+    }
+    if (avail + p.grow < n_new) {
+        p.fits = false;
+        return p;
+    }
+    p.n_slots += p.grow;
+    const uint64_t unused = p.n_slots - ss.n_used;
+    p.n_evicted = n_new > unused ? n_new - unused : 0;
+    p.n_used += n_new < unused ? n_new : unused;
+    return p;
+}
+// ... published for the call's later kernels and the host, and the next
+// call's counters cleared (one thread).
+__device__ __forceinline__ void publish_plan(Counters *ctr, Counters *next, uint64_t n_act, uint64_t n_new,
+                                             uint64_t n_cand, const SlotState &ss) {
+    const SlotPlan p = plan_slots(n_act, n_new, ss);
     ctr->n_act = n_act;
     ctr->n_new = n_new;
-    ctr->n_slots = ss.n_slots;
-    ctr->n_used = ss.n_used;
-    if (ss.identity || n_new == 0) return;
-    const uint64_t avail = ss.n_slots - (n_act - n_new);
-    uint64_t grow = 0;
-    if (n_new > avail) {
-        grow = n_new - avail;
-        const uint64_t half = (ss.n_slots + 1) / 2;
-        if (half > grow) grow = half;
-        if (ss.n_slots + grow > ss.max_slots) grow = ss.max_slots - ss.n_slots;
-    }
-    if (avail + grow < n_new) {
-        ctr->err |= ERR_CACHE_CAP;
-        return;
-    }
-    const uint64_t unused = ss.n_slots + grow - ss.n_used;
-    ctr->n_grow = grow;
-    ctr->n_slots = ss.n_slots + grow;
-    ctr->n_evicted = n_new > unused ? n_new - unused : 0;
-    ctr->n_used = ss.n_used + (n_new < unused ? n_new : unused);
+    ctr->n_cand = n_cand;
+    ctr->n_slots = p.n_slots;
+    ctr->n_used = p.n_used;
+    ctr->n_evicted = p.n_evicted;
+    ctr->oldest = ~0u;
+    if (!p.fits) ctr->err |= ERR_CACHE_CAP;
+    *next = Counters{};
 }
 
-// Exclusive prefix of the live rounds' counts, in place; the totals are the
-// call's n_act and n_new, from which the slots are planned.  One workgroup,
-// 4096 rounds per step.
-__global__ __launch_bounds__(256) void k_round_scan(uint64_t *__restrict__ round_cnt, Counters *ctr,
-                                                   SlotState ss) {
-    __shared__ uint64_t s_w[4];
-    const uint64_t n = ctr->n_live_rounds;
-    const int w = threadIdx.x >> 6;
-    uint64_t carry = 0;
-    for (uint64_t c0 = 0; c0 < n; c0 += 4096) {
-        const uint64_t i0 = c0 + 16u * threadIdx.x;
-        uint64_t v[16], sum = 0;
-#pragma unroll
-        for (int j = 0; j < 16; j++) {
-            v[j] = i0 + j < n ? round_cnt[i0 + j] : 0ull;
-            sum += v[j];
-        }
-        const uint64_t incl = wave_incl_scan(sum);
-        if (lane() == 63) s_w[w] = incl;
-        __syncthreads();
-        uint64_t o = carry + incl - sum, tot = 0;
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            if (i < w) o += s_w[i];
-            tot += s_w[i];
-        }
-#pragma unroll
-        for (int j = 0; j < 16; j++) {
-            if (i0 + j < n) round_cnt[i0 + j] = o;
-            o += v[j];
-        }
-        carry += tot;
-        __syncthreads();   // s_w is rewritten by the next step
+// Large volumes: the sums of 256 rounds each as (active << 32 | new), their
+// may-emit blocks, and the next call's counts cleared.
+__global__ __launch_bounds__(256) void k_round_sums(const uint64_t *__restrict__ round_cnt, uint64_t n,
+                                                   uint64_t *__restrict__ sums, uint64_t *__restrict__ round_next) {
+    __shared__ uint64_t s_l[4], s_c[4];
+    const uint64_t i = blockIdx.x * 256ull + threadIdx.x;
+    const uint64_t c = i < n ? round_cnt[i] : 0ull;
+    if (i < n) round_next[i] = 0;
+    const uint64_t lists = wave_sum(round_lists(c)), cand = wave_sum(c >> 42);
+    if (lane() == 0) {
+        s_l[threadIdx.x >> 6] = lists;
+        s_c[threadIdx.x >> 6] = cand;
     }
-    if (threadIdx.x == 0) plan_slots(ctr, carry >> 32, carry & 0xFFFFFFFFull, ss);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        sums[2 * blockIdx.x] = s_l[0] + s_l[1] + s_l[2] + s_l[3];
+        sums[2 * blockIdx.x + 1] = s_c[0] + s_c[1] + s_c[2] + s_c[3];
+    }
+}
+
+// Sums over the workgroup (256 threads), returned to every thread; s has 12
+// entries and may be reused after a barrier.
+__device__ __forceinline__ void wg_sum3(uint64_t &a, uint64_t &b, uint64_t &c, uint64_t *s) {
+    a = wave_sum(a);
+    b = wave_sum(b);
+    c = wave_sum(c);
+    const int w = threadIdx.x >> 6;
+    if (lane() == 0) {
+        s[w] = a;
+        s[4 + w] = b;
+        s[8 + w] = c;
+    }
+    __syncthreads();
+    a = s[0] + s[1] + s[2] + s[3];
+    b = s[4] + s[5] + s[6] + s[7];
+    c = s[8] + s[9] + s[10] + s[11];
+}
+// One round's place in the lists (before), and the call's totals: both as
+// (active << 32 | new), cand the may-emit blocks of all rounds.
+__device__ __forceinline__ void round_sums_direct(const uint64_t *__restrict__ round_cnt, uint64_t n, uint64_t r,
+                                                  uint64_t &before, uint64_t &total, uint64_t &cand, uint64_t *s) {
+    before = total = cand = 0;
+    for (uint64_t i0 = threadIdx.x; i0 < n; i0 += 1024) {   // 4 loads in flight
+        uint64_t c[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) c[j] = i0 + 256 * j < n ? round_cnt[i0 + 256 * j] : 0ull;
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            const uint64_t v = round_lists(c[j]);
+            total += v;
+            before += i0 + 256 * j < r ? v : 0ull;
+            cand += c[j] >> 42;
+        }
+    }
+    wg_sum3(before, total, cand, s);
 }
 
 // Each live round's active and new block ids, from its offsets on.  A wave
 // takes 1024 consecutive flags of the round (16 per lane, one 16-byte load),
 // puts them in LDS and writes the ids 64 blocks at a time: lane l takes block
 // 64 j + l, a ballot orders the wave's ids, and each store covers one
-// contiguous run of the lists.
+// contiguous run of the lists.  LARGE: rounds blockIdx.x, + G, ... with
+// k_round_sums' sums; otherwise workgroup r has round r.  Workgroup 0
+// publishes the slots' plan.
+template <bool LARGE>
 __global__ __launch_bounds__(256) void k_compact_blocks(Geom g, const uint8_t *__restrict__ active,
-                                                       const uint32_t *__restrict__ round_list,
-                                                       const uint64_t *__restrict__ round_off,
+                                                       const uint64_t *__restrict__ round_cnt, uint64_t n_rounds,
+                                                       const uint64_t *__restrict__ sums,
+                                                       uint64_t *__restrict__ round_next,
                                                        uint32_t *__restrict__ I_active,
-                                                       uint32_t *__restrict__ I_new, const Counters *ctr) {
+                                                       uint32_t *__restrict__ I_new, Counters *ctr,
+                                                       Counters *next, SlotState ss) {
     __shared__ uint32_t s_w[4];
     __shared__ uint4 s_fl[4][64];   // per wave: its 1024 flags in block order
-    const uint64_t n_live = ctr->n_live_rounds;
+    __shared__ uint64_t s_sum[12];
     const int w = threadIdx.x >> 6, l = lane();
-    for (uint64_t k = blockIdx.x; k < n_live; k += gridDim.x) {
-        const uint64_t wbase = (uint64_t)round_list[k] * BLK_TILE + 1024u * w;
-        const uint64_t off = round_off[k];
+    uint64_t off = 0, total = 0, cand = 0;
+    if constexpr (LARGE) {
+        if (blockIdx.x == 0) {
+            for (uint64_t i = threadIdx.x; i < (n_rounds + 255) / 256; i += 256) {
+                total += sums[2 * i];
+                cand += sums[2 * i + 1];
+            }
+            wg_sum3(off, total, cand, s_sum);
+        }
+    } else {
+        if (threadIdx.x == 0) round_next[blockIdx.x] = 0;
+        if (blockIdx.x != 0 && round_cnt[blockIdx.x] == 0) return;
+        round_sums_direct(round_cnt, n_rounds, blockIdx.x, off, total, cand, s_sum);
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        publish_plan(ctr, next, total >> 32, total & 0xFFFFFFFFull, cand, ss);
+    for (uint64_t k = blockIdx.x; k < n_rounds; k += gridDim.x) {
+        if (round_cnt[k] == 0) continue;
+        const uint64_t wbase = k * BLK_TILE + 1024u * w;
         const uint4 q = load_flags16(active, wbase + 16u * l, g.nb);
-        uint32_t actb, newb, unused = 0;
-        flag_bits(q, actb, newb, unused);
+        if constexpr (LARGE) {
+            const uint64_t big = k / 256;
+            off = 256 * big + threadIdx.x < k ? round_lists(round_cnt[256 * big + threadIdx.x]) : 0ull;
+            for (uint64_t i = threadIdx.x; i < big; i += 256) off += sums[2 * i];
+            uint64_t none = 0, unused = 0;
+            __syncthreads();   // s_sum is rewritten
+            wg_sum3(off, none, unused, s_sum);
+        }
+        uint32_t actb, newb;
+        flag_bits(q, actb, newb);
         const uint32_t tot = wave_sum(((uint32_t)__popc(actb) << 16) | (uint32_t)__popc(newb));   // < 2^11 each
         if (l == 0) s_w[w] = tot;
         s_fl[w][l] = q;
@@ -781,18 +828,16 @@ __global__ __launch_bounds__(256) void k_mc_count(Geom g, const uint32_t *__rest
 // rounds of 16 K chunks (thread t holds chunks t + 1024 j, j < 16: coalesced loads; a
 // chunk holds at most 64 * 960 vertices, so a round's sums fit 32 bits), and
 // writes the eighth's total to xcd_tot[x] (the emission adds the totals of
-// the eighths before its own).  Workgroup 8 forms the call's occupied and
-// may-emit block counts.
+// the eighths before its own).  Workgroup 8 forms the call's occupied block
+// count.
 __global__ __launch_bounds__(1024) void k_chunk_scan(uint64_t *__restrict__ chunk_off,
                                                     uint64_t *__restrict__ xcd_tot,
                                                     const uint32_t *__restrict__ part_occw,
-                                                    uint32_t n_waves, uint32_t emit_waves,
-                                                    const uint32_t *__restrict__ part_cand,
-                                                    Counters *ctr) {
+                                                    uint32_t n_waves, uint32_t emit_waves, Counters *ctr) {
     constexpr int J = 16;
     __shared__ uint32_t s_w[J * 16];   // per (j, wave): the wave's total, then its exclusive prefix
     __shared__ uint32_t s_round;
-    __shared__ uint32_t s_occ[16], s_cand[16];
+    __shared__ uint32_t s_occ[16];
     if (ctr->err) return;
     const int t = threadIdx.x, w = t >> 6, l = lane();
     if (blockIdx.x < 8) {
@@ -842,7 +887,7 @@ __global__ __launch_bounds__(1024) void k_chunk_scan(uint64_t *__restrict__ chun
         return;
     }
     // 8 loads in flight per thread (a plain loop waits for each load)
-    uint32_t occ = 0, cand = 0;
+    uint32_t occ = 0;
     for (uint32_t i0 = t; i0 < n_waves; i0 += 8 * 1024) {
         uint32_t x[8];
 #pragma unroll
@@ -850,29 +895,13 @@ __global__ __launch_bounds__(1024) void k_chunk_scan(uint64_t *__restrict__ chun
 #pragma unroll
         for (int j = 0; j < 8; j++) occ += x[j];
     }
-    const uint64_t n_ct = ctr->n_live_rounds;
-    for (uint64_t i0 = t; i0 < n_ct; i0 += 8 * 1024) {
-        uint32_t x[8];
-#pragma unroll
-        for (int j = 0; j < 8; j++) x[j] = i0 + 1024u * j < n_ct ? part_cand[i0 + 1024u * j] : 0u;
-#pragma unroll
-        for (int j = 0; j < 8; j++) cand += x[j];
-    }
     occ = wave_sum(occ);
-    cand = wave_sum(cand);
-    if (l == 0) {
-        s_occ[w] = occ;
-        s_cand[w] = cand;
-    }
+    if (l == 0) s_occ[w] = occ;
     __syncthreads();
     if (t == 0) {
-        uint32_t o = 0, c = 0;
-        for (int k = 0; k < 16; k++) {
-            o += s_occ[k];
-            c += s_cand[k];
-        }
+        uint32_t o = 0;
+        for (int k = 0; k < 16; k++) o += s_occ[k];
         ctr->n_occ = o;
-        ctr->n_cand = c;
     }
 }
 
@@ -1088,17 +1117,22 @@ static unsigned mc_grid(uint64_t max_blocks) {
     return (unsigned)((g + 7) / 8 * 8);   // whole XCD rounds
 }
 
-void launch_cull(const Geom &g, const DevState &d, const StatusLayout &sl, float iso, float prev_iso,
-                 int identity_cache, uint32_t now, uint32_t gen, hipStream_t s) {
-    static unsigned rgrid = 0;
-    if (!rgrid) rgrid = resident_grid(k_cull, ~0ull >> 4);
+void launch_cull(const Geom &g, const DevState &d, float iso, float prev_iso, int rewrite, int identity_cache,
+                 uint32_t now, hipStream_t s) {
     const uint64_t nt = cull_tiles(g);
-    k_call_reset<<<grid_cap(sl.total, 64), 256, 0, s>>>(d.ctr, d.status, sl.total);
-    k_cull_scan<<<(unsigned)((nt + 255) / 256), 256, 0, s>>>(d.tile_ranges, nt, iso, prev_iso, d.cull_list,
-                                                             d.ctr);
-    k_cull<<<(unsigned)std::min<uint64_t>(nt, rgrid), 256, 0, s>>>(
-        g, d.ranges, iso, d.cull_list, nt, d.I_slot, identity_cache, d.S_stamp, now, d.active, d.ctr,
-        d.round_gen, gen);
+    unsigned long long *cnt = reinterpret_cast<unsigned long long *>(d.round_cnt);
+    if (nt <= CULL_DIRECT) {
+        k_cull<false><<<(unsigned)nt, 256, 0, s>>>(g, d.ranges, iso, prev_iso, rewrite, d.tile_ranges, nullptr, nt,
+                                                   d.I_slot, identity_cache, d.S_stamp, now, d.active, d.ctr, cnt);
+        return;
+    }
+    static unsigned rgrid = 0;
+    if (!rgrid) rgrid = resident_grid(k_cull<true>, ~0ull >> 4);
+    k_cull_scan<<<(unsigned)((nt + 255) / 256), 256, 0, s>>>(d.tile_ranges, nt, iso, prev_iso, rewrite,
+                                                             d.cull_list, d.ctr);
+    k_cull<true><<<(unsigned)std::min<uint64_t>(nt, rgrid), 256, 0, s>>>(
+        g, d.ranges, iso, prev_iso, rewrite, d.tile_ranges, d.cull_list, nt, d.I_slot, identity_cache, d.S_stamp,
+        now, d.active, d.ctr, cnt);
 }
 
 uint64_t cull_tiles(const Geom &g) {
@@ -1110,19 +1144,18 @@ void launch_tile_ranges(const Geom &g, const float2 *ranges, float2 *tile_ranges
     k_tile_ranges<<<(unsigned)cull_tiles(g), 256, 0, s>>>(g, ranges, tile_ranges);
 }
 
-void launch_compact_blocks(const Geom &g, const DevState &d, const StatusLayout &sl, uint32_t gen,
-                           const SlotState &ss, hipStream_t s) {
-    static unsigned cgrid = 0, wgrid = 0;
-    if (!cgrid) cgrid = resident_grid(k_round_counts, ~0ull >> 4);
-    if (!wgrid) wgrid = resident_grid(k_compact_blocks, ~0ull >> 4);
-    const uint64_t n_rounds = block_rounds(g.nb);
-    k_round_list<<<(unsigned)((n_rounds + 4095) / 4096), 256, 0, s>>>(d.round_gen, n_rounds, gen, d.round_list,
-                                                                      d.ctr, d.status + sl.rnd);
-    k_round_counts<<<(unsigned)std::min<uint64_t>(n_rounds, cgrid), 256, 0, s>>>(
-        g, d.active, d.round_list, d.round_cnt, d.part_cand, d.ctr);
-    k_round_scan<<<1, 256, 0, s>>>(d.round_cnt, d.ctr, ss);
-    k_compact_blocks<<<(unsigned)std::min<uint64_t>(n_rounds, wgrid), 256, 0, s>>>(
-        g, d.active, d.round_list, d.round_cnt, d.I_active, d.I_new, d.ctr);
+void launch_compact_blocks(const Geom &g, const DevState &d, const SlotState &ss, hipStream_t s) {
+    const uint64_t n = block_rounds(g.nb);
+    if (n <= ROUNDS_DIRECT) {
+        k_compact_blocks<false><<<(unsigned)n, 256, 0, s>>>(g, d.active, d.round_cnt, n, nullptr, d.round_next,
+                                                            d.I_active, d.I_new, d.ctr, d.ctr_next, ss);
+        return;
+    }
+    static unsigned wgrid = 0;
+    if (!wgrid) wgrid = resident_grid(k_compact_blocks<true>, ~0ull >> 4);
+    k_round_sums<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(d.round_cnt, n, d.round_sums, d.round_next);
+    k_compact_blocks<true><<<(unsigned)std::min<uint64_t>(n, wgrid), 256, 0, s>>>(
+        g, d.active, d.round_cnt, n, d.round_sums, d.round_next, d.I_active, d.I_new, d.ctr, d.ctr_next, ss);
 }
 
 uint32_t *launch_evict(const DevState &d, uint32_t n_used, uint32_t base, uint32_t now, hipStream_t s) {
@@ -1185,7 +1218,7 @@ void launch_mc_count(const Geom &g, const DevState &d, const float *slots, const
     k_mc_count<<<cgrid, 256, 0, s>>>(g, d.I_active, d.active, I_slot, identity_cache, d.masks,
                                      d.blk_cnt, d.chunk_off, d.part_occw, egrid * MC_WAVES, d.ctr);
     k_chunk_scan<<<9, 1024, 0, s>>>(d.chunk_off, d.chunk_off + mc_chunk_slots(g.nb), d.part_occw,
-                                    cgrid * MC_WAVES, egrid * MC_WAVES, d.part_cand, d.ctr);
+                                    cgrid * MC_WAVES, egrid * MC_WAVES, d.ctr);
 }
 
 void launch_mc_emit(const Geom &g, const DevState &d, const float *slots, const int32_t *I_slot,

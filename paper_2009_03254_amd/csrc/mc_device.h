@@ -1,5 +1,5 @@
 // Device-side building blocks shared by the extraction kernels: wave64
-// primitives, decoupled look-back, and the 5^3 LDS staging of a block with
+// primitives and the 5^3 LDS staging of a block with
 // its +x/+y/+z halo.  Internal linkage in every includer.
 #pragma once
 
@@ -49,116 +49,6 @@ __device__ __forceinline__ T wave_sum(T v) {
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
     return v;
-}
-
-__device__ __forceinline__ uint64_t lb_load(const uint64_t *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void lb_store(uint64_t *p, uint64_t v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Decoupled look-back, run by one whole wave: publishes `agg` for tile t and
-// returns the exclusive prefix of the tile.  256 predecessors are inspected
-// per step (4 status words per lane, all loads in flight together): the
-// window is summed up to (and including) the nearest tile that already holds
-// an inclusive prefix.  With ~1000 tiles running at once most windows hold
-// only aggregates, so the step width sets the latency of the walk.
-__device__ uint64_t lookback(uint64_t *status, uint64_t t, uint64_t agg) {
-    const int l = lane();
-    if (t == 0) {
-        if (l == 0) lb_store(&status[0], LB_PRE | agg);
-        return 0;
-    }
-    if (l == 0) lb_store(&status[t], LB_AGG | agg);
-    uint64_t excl = 0;
-    int64_t j = (int64_t)t - 1;
-    for (;;) {
-        uint64_t w[4];
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-            const int64_t idx = j - l - 64 * r;   // window position 64 r + l
-            w[r] = idx >= 0 ? lb_load(&status[idx]) : LB_PRE;
-        }
-        // first inclusive prefix in window order, and whether anything before it is missing
-        int first = 256;
-        bool missing = false;
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-            const uint64_t flag = w[r] & ~LB_VAL;
-            const uint64_t pre = __ballot(flag == LB_PRE);
-            const uint64_t notready = __ballot(flag == 0);
-            if (first == 256) {
-                const int f = pre ? (int)__builtin_ctzll(pre) : 64;
-                const uint64_t upto = f >= 63 ? ~0ull : ((2ull << f) - 1);
-                if (notready & upto) missing = true;
-                if (f < 64) first = 64 * r + f;
-            }
-        }
-        if (missing) {
-            __builtin_amdgcn_s_sleep(1);
-            continue;
-        }
-        uint64_t v = 0;
-#pragma unroll
-        for (int r = 0; r < 4; r++)
-            if (64 * r + l <= first) v += w[r] & LB_VAL;
-        excl += wave_sum(v);
-        if (first < 256) break;
-        j -= 256;
-    }
-    if (l == 0) lb_store(&status[t], LB_PRE | (excl + agg));
-    return excl;
-}
-
-// Workgroup (256 threads = 4 waves) exclusive scan of one value per thread
-// followed by the look-back; returns the thread's global exclusive prefix and
-// the tile total through *total (inclusive prefix of the tile in *incl_end).
-__device__ uint64_t tile_scan_lookback(uint64_t v, uint64_t *status, uint64_t t,
-                                       uint64_t *incl_end) {
-    __shared__ uint64_t s_w[4];
-    __shared__ uint64_t s_excl;
-    const int w = threadIdx.x >> 6;
-    uint64_t incl = wave_incl_scan(v);
-    if (lane() == 63) s_w[w] = incl;
-    __syncthreads();
-    uint64_t woff = 0, agg = 0;
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-        if (i < w) woff += s_w[i];
-        agg += s_w[i];
-    }
-    if (w == 0) {
-        uint64_t e = lookback(status, t, agg);
-        if (lane() == 0) s_excl = e;
-    }
-    __syncthreads();
-    uint64_t e = s_excl;
-    *incl_end = e + agg;
-    __syncthreads();  // s_w / s_excl are reused by the next tile
-    return e + woff + incl - v;
-}
-
-// Sum of one value per thread over a 256-thread workgroup, returned to every
-// thread (all threads must call it).  Device-wide counters are then bumped
-// once per workgroup: same-address atomics from every wave serialise.
-__device__ __forceinline__ uint32_t wg_sum_u32(uint32_t v) {
-    __shared__ uint32_t s_part[4];
-    v = wave_sum(v);
-    if (lane() == 0) s_part[threadIdx.x >> 6] = v;
-    __syncthreads();
-    const uint32_t t = s_part[0] + s_part[1] + s_part[2] + s_part[3];
-    __syncthreads();
-    return t;
-}
-
-__device__ __forceinline__ uint32_t take_tile(unsigned int *ctr) {
-    __shared__ uint32_t s_tile;
-    if (threadIdx.x == 0) s_tile = atomicAdd(ctr, 1u);
-    __syncthreads();
-    uint32_t t = s_tile;
-    __syncthreads();
-    return t;
 }
 
 // ---------------------------------------------------------------------------

@@ -237,7 +237,7 @@ __global__ __launch_bounds__(256, LOW ? 4 : (F64 ? 1 : 4)) void k_assign_decode(
                 const int first = (int)__builtin_ctzll(back);
                 uint32_t base = 0;
                 if (__lane_id() == (unsigned)first)
-                    base = atomicAdd(&ctr->tile_ctr[TC_RETRY], (uint32_t)__popcll(back));
+                    base = atomicAdd(&ctr->n_retry, (uint32_t)__popcll(back));
                 base = __shfl(base, first, 64);
                 if (valid && !done) retry[base + mbcnt_lo_hi(back)] = (uint32_t)i;
             }
@@ -276,7 +276,7 @@ __global__ __launch_bounds__(256) void k_decode_retry(const Counters *ctr, const
                                                      uint32_t *__restrict__ mask_iso,
                                                      const uint32_t *__restrict__ retry) {
     if (ctr->err) return;
-    const uint32_t n = ctr->tile_ctr[TC_RETRY];
+    const uint32_t n = ctr->n_retry;
     const SlotSource src{evict, ss.n_used, ctr->n_slots - ss.n_used};
     for (uint32_t j = blockIdx.x * blockDim.x + threadIdx.x; j < n; j += gridDim.x * blockDim.x) {
         const uint32_t i = retry[j];
