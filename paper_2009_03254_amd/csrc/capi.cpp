@@ -446,10 +446,10 @@ int bcmc_extract(bcmc_volume *v, float iso, void *d_out, uint64_t capacity_verti
     launch_cull(v->g, v->d, iso, v->cull_iso, v->rewrite_flags, v->identity, now, s);
     v->cull_iso = iso;
     v->rewrite_flags = 1;
-    launch_compact_blocks(v->g, v->d, ss, s);
+    launch_compact_blocks(v->g, v->d, ss, v->evict_base, now, s);
     BCMC_HIP_TRY(mark(1));
     const uint32_t *evict = nullptr;
-    if (!v->identity) evict = launch_evict(v->d, (uint32_t)v->n_used, v->evict_base, now, s);
+    if (!v->identity) evict = launch_evict(v->g, v->d, (uint32_t)v->n_used, v->evict_base, now, s);
     BCMC_HIP_TRY(mark(2));
     if (!v->identity) launch_assign_decode(v->d, v->is_f64, v->rate, v->g.nb, iso, evict, ss, now, s);
     BCMC_HIP_TRY(mark(3));
@@ -487,7 +487,7 @@ int bcmc_extract(bcmc_volume *v, float iso, void *d_out, uint64_t capacity_verti
     if (!v->identity) {
         v->n_slots = c.n_slots;
         v->n_used = c.n_used;
-        if (c.oldest != ~0u && c.oldest > v->evict_base) v->evict_base = std::min(c.oldest, now);
+        if (c.span) v->evict_base = std::max(v->evict_base, now + 1u - c.span);
     }
     const uint64_t T = c.total_verts / 3;
     *n_triangles = T;
@@ -883,7 +883,7 @@ extern "C" int bcmc_extract_blocks_noalloc(const float *d_blocks, uint32_t nx, u
     launch_ranges_from_blocks(g, d_blocks, d.ranges, range_err, s);
     launch_tile_ranges(g, d.ranges, d.tile_ranges, s);
     launch_cull(g, d, iso, NAN, 1, 1, 0, s);
-    launch_compact_blocks(g, d, SlotState{0, 0, 0, 1}, s);
+    launch_compact_blocks(g, d, SlotState{0, 0, 0, 1}, 0, 0, s);
     launch_mc_count(g, d, d_blocks, nullptr, 1, iso, 0, s);
     launch_mc_emit(g, d, d_blocks, nullptr, 1, iso, d_out, capacity_vertices, 0, s);
     BCMC_HIP_TRY(hipGetLastError());

@@ -24,10 +24,10 @@ constexpr uint64_t ROUNDS_DIRECT = 2048;
 // blocks) the cull alone takes less than the queue's launch more, while the
 // 115,200 of 236 M blocks, a tenth of them live, would mostly be dead workgroups.
 constexpr uint64_t CULL_DIRECT = 4096;
-constexpr int EVICT_TILE = 4096;             // slots per tile of the eviction's selection (1024 per wave)
-constexpr int EVICT_BITS = 11;               // key bits per pass of it
+constexpr int EVICT_TILE = 1024;             // slots per tile of the eviction's selection (256 per wave)
+constexpr int EVICT_BITS = 10;               // key bits per pass of it
 constexpr int EVICT_BINS = 1 << EVICT_BITS;
-constexpr uint32_t EVICT_REFRESH = 1024;     // key span from which its base is looked for again
+constexpr uint32_t EVICT_REFRESH = 512;      // key span from which its base is looked for again
 constexpr int MC_MAX_GRID = 2048;           // workgroups of the count / emission grid at most
 constexpr int MC_WAVES = 4;                  // blocks (one per wave) per MC tile
 
@@ -46,7 +46,7 @@ struct Counters {
     unsigned long long n_cand;       // active blocks that may emit (staged by the count pass)
     unsigned long long total_verts;  // 3 * triangles
     unsigned int err;                // ERR_* bits
-    unsigned int oldest;             // no used slot was last used before this call (~0: not looked for)
+    unsigned int span;               // 1 + calls since the oldest used slot's last use, at most (0: not looked for)
     unsigned int n_sort;             // available used slots (with n_evicted)
     unsigned int n_retry;            // blocks the low-rate decoder handed back
     unsigned int cull_live, cull_stale;  // the cull's queued tiles
@@ -112,7 +112,9 @@ struct DevState {
 // stamps).
 void launch_cull(const Geom &g, const DevState &d, float iso, float prev_iso, int rewrite, int identity_cache,
                  uint32_t now, hipStream_t s);
-void launch_compact_blocks(const Geom &g, const DevState &d, const SlotState &ss, hipStream_t s);
+// base, now: the stamps' range, as launch_evict.
+void launch_compact_blocks(const Geom &g, const DevState &d, const SlotState &ss, uint32_t base, uint32_t now,
+                           hipStream_t s);
 inline uint64_t block_rounds(uint64_t nb) { return (nb + BLK_TILE - 1) / BLK_TILE; }
 // Chunk entries of the count pass's and emission's chunk totals: a call
 // with n_act active blocks on W waves has ceil(n_act / cs) chunks of
@@ -124,7 +126,9 @@ inline uint64_t mc_chunk_slots(uint64_t nb) {
 }
 // The slots to evict, oldest first (n_evicted entries of the returned list),
 // among [0, n_used); base: a call number no used slot's stamp is below.
-uint32_t *launch_evict(const DevState &d, uint32_t n_used, uint32_t base, uint32_t now, hipStream_t s);
+// After launch_compact_blocks, which counts for the first pass.
+uint32_t *launch_evict(const Geom &g, const DevState &d, uint32_t n_used, uint32_t base, uint32_t now,
+                       hipStream_t s);
 // Every block out of the cache; the slots from n_used on hold none.
 void launch_cache_empty(const DevState &d, uint64_t n_used, hipStream_t s);
 void launch_mc_count(const Geom &g, const DevState &d, const float *slots, const int32_t *I_slot,

@@ -373,7 +373,6 @@ __device__ __forceinline__ void publish_plan(Counters *ctr, Counters *next, uint
     ctr->n_slots = p.n_slots;
     ctr->n_used = p.n_used;
     ctr->n_evicted = p.n_evicted;
-    ctr->oldest = ~0u;
     if (!p.fits) ctr->err |= ERR_CACHE_CAP;
     *next = Counters{};
 }
@@ -435,12 +434,103 @@ __device__ __forceinline__ void round_sums_direct(const uint64_t *__restrict__ r
     wg_sum3(before, total, cand, s);
 }
 
+// ---------------------------------------------------------------------------
+// Alg. 1 SortByKey, as a selection: the n_evicted oldest used slots that hold
+// no active block, oldest first and by ascending slot among equals (the first
+// entries of the stable sort of all available slots by age; the unused slots,
+// older than every used one, precede them and need no list).  A slot's key is
+// the call that last used it less `base`, a call no used slot is older than.
+// Per pass the keys' digits are counted per tile of slots (with the
+// compaction in the first pass, whose kernel waits on memory), and k_evict_list
+// finds the digit up to which slots are taken and ranks the tile's slots below
+// it.  The keys span the calls since the oldest slot's use (few, since a cache
+// that must evict drops the oldest), so one pass covers spans of 1023 calls;
+// longer spans take stable passes over 10-bit digits, the last of which stops
+// at n_evicted.  Latency bound: tiles of 1024 slots, every load of a tile in
+// flight at once.  At 1.5e5 slots the list takes 7 us and the counts under 1 of
+// the compaction (tiles of 4096, counted by a launch: 15 and 12 us; a radix sort
+// of all available slots after a pass that aged them: 31-42 us in five launches).
+// ---------------------------------------------------------------------------
+struct EvictPass {
+    uint32_t base, now;      // keys: stamps in [base, now)
+    int shift, bits;         // the pass's digit
+    int first, last;         // first: slots in slot order; else `in`
+    const uint32_t *in;      // the previous pass's list
+    uint32_t *out;           // this pass's list (last: n_evicted entries)
+    uint32_t n_used;         // used slots (first)
+    uint32_t tiles;          // stride of the histogram's rows
+    int scanned;             // the histogram rows hold prefixes (k_evict_scan ran)
+    int refresh;             // look for the oldest used slot's stamp, for the next calls' base
+};
+constexpr int EVICT_PER = EVICT_TILE / 256;   // elements per lane: wave w has [256 w, 256 w + 256) of the tile
+
+// The lane's elements of the tile: slots and stamps, all loads in flight;
+// bit r of the result: element r is there and available.
+__device__ __forceinline__ uint32_t evict_load(const EvictPass &p, const uint32_t *__restrict__ S_stamp, uint32_t n,
+                                               uint32_t tile, uint32_t (&slot)[EVICT_PER],
+                                               uint32_t (&stamp)[EVICT_PER]) {
+    const uint32_t i0 = tile * EVICT_TILE + (threadIdx.x >> 6) * (EVICT_TILE / 4) + lane();
+#pragma unroll
+    for (int r = 0; r < EVICT_PER; r++) {
+        const uint32_t i = i0 + 64 * r;
+        slot[r] = p.first ? i : (i < n ? p.in[i] : 0u);
+    }
+    uint32_t there = 0;
+#pragma unroll
+    for (int r = 0; r < EVICT_PER; r++) {
+        const bool in = i0 + 64 * r < n;
+        stamp[r] = in ? S_stamp[slot[r]] : ~0u;
+        there |= (in && (!p.first || stamp[r] < p.now) ? 1u : 0u) << r;
+    }
+    return there;
+}
+__device__ __forceinline__ uint32_t evict_digit(const EvictPass &p, uint32_t stamp) {
+    return ((stamp - p.base) >> p.shift) & ((1u << p.bits) - 1u);
+}
+
+// Adds the wave's digits to h, one lane per distinct digit: neighbouring
+// slots were mostly last used by the same call.
+__device__ __forceinline__ void wave_digit_count(uint32_t *h, bool valid, uint32_t d) {
+    uint64_t left = __ballot(valid);
+    while (left) {
+        const int leader = (int)__builtin_ctzll(left);
+        const uint32_t ld = (uint32_t)__builtin_amdgcn_readlane((int)d, leader);
+        const uint64_t same = __ballot(valid && d == ld) & left;
+        if (lane() == leader) atomicAdd(&h[ld], (uint32_t)__popcll(same));
+        left &= ~same;
+    }
+}
+
+// hist[digit][tile] of one tile (by a workgroup; h: EVICT_BINS words of LDS),
+// if slots have to be evicted.
+__device__ __forceinline__ void evict_count_tile(const EvictPass &p, const uint32_t *__restrict__ S_stamp,
+                                                 uint32_t n, uint32_t tile, const uint32_t (&stamp)[EVICT_PER],
+                                                 uint32_t there, bool need, uint32_t *h,
+                                                 uint32_t *__restrict__ hist, Counters *ctr) {
+    if (p.refresh) {
+        uint32_t oldest = ~0u;
+#pragma unroll
+        for (int r = 0; r < EVICT_PER; r++) oldest = min(oldest, stamp[r]);
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) oldest = min(oldest, (uint32_t)__shfl_xor((int)oldest, d, 64));
+        if (lane() == 0) atomicMax(&ctr->span, p.now - min(oldest, p.now) + 1u);
+    }
+    if (!need) return;
+    for (int d = threadIdx.x; d < 1 << p.bits; d += 256) h[d] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < EVICT_PER; r++) wave_digit_count(h, (there >> r) & 1u, evict_digit(p, stamp[r]));
+    __syncthreads();
+    for (int d = threadIdx.x; d < 1 << p.bits; d += 256) hist[(uint64_t)d * p.tiles + tile] = h[d];
+}
+
 // Each live round's active and new block ids, from its offsets on.  A wave
 // takes 1024 consecutive flags of the round (16 per lane, one 16-byte load),
 // puts them in LDS and writes the ids 64 blocks at a time: lane l takes block
 // 64 j + l, a ballot orders the wave's ids, and each store covers one
 // contiguous run of the lists.  LARGE: rounds blockIdx.x, + G, ... with
-// k_round_sums' sums; otherwise workgroup r has round r.  Workgroup 0
+// k_round_sums' sums; otherwise workgroup r has round r, and the workgroups
+// after the rounds' count tiles of slots for the eviction.  Workgroup 0
 // publishes the slots' plan.
 template <bool LARGE>
 __global__ __launch_bounds__(256) void k_compact_blocks(Geom g, const uint8_t *__restrict__ active,
@@ -449,9 +539,12 @@ __global__ __launch_bounds__(256) void k_compact_blocks(Geom g, const uint8_t *_
                                                        uint64_t *__restrict__ round_next,
                                                        uint32_t *__restrict__ I_active,
                                                        uint32_t *__restrict__ I_new, Counters *ctr,
-                                                       Counters *next, SlotState ss) {
+                                                       Counters *next, SlotState ss, EvictPass ev,
+                                                       const uint32_t *__restrict__ S_stamp,
+                                                       uint32_t *__restrict__ evict_hist) {
     __shared__ uint32_t s_w[4];
     __shared__ uint4 s_fl[4][64];   // per wave: its 1024 flags in block order
+    static_assert(sizeof(s_fl) >= EVICT_BINS * sizeof(uint32_t), "a tile's digit counts take the flags' place");
     __shared__ uint64_t s_sum[12];
     const int w = threadIdx.x >> 6, l = lane();
     uint64_t off = 0, total = 0, cand = 0;
@@ -464,6 +557,16 @@ __global__ __launch_bounds__(256) void k_compact_blocks(Geom g, const uint8_t *_
             wg_sum3(off, total, cand, s_sum);
         }
     } else {
+        if (blockIdx.x >= n_rounds) {
+            const uint32_t tile = blockIdx.x - (uint32_t)n_rounds;
+            uint32_t slot[EVICT_PER], stamp[EVICT_PER];
+            const uint32_t there = evict_load(ev, S_stamp, ev.n_used, tile, slot, stamp);
+            round_sums_direct(round_cnt, n_rounds, 0, off, total, cand, s_sum);
+            const SlotPlan p = plan_slots(total >> 32, total & 0xFFFFFFFFull, ss);
+            evict_count_tile(ev, S_stamp, ev.n_used, tile, stamp, there, p.fits && p.n_evicted,
+                             reinterpret_cast<uint32_t *>(s_fl), evict_hist, ctr);
+            return;
+        }
         if (threadIdx.x == 0) round_next[blockIdx.x] = 0;
         if (blockIdx.x != 0 && round_cnt[blockIdx.x] == 0) return;
         round_sums_direct(round_cnt, n_rounds, blockIdx.x, off, total, cand, s_sum);
@@ -511,88 +614,18 @@ __global__ __launch_bounds__(256) void k_compact_blocks(Geom g, const uint8_t *_
     }
 }
 
-// ---------------------------------------------------------------------------
-// Alg. 1 SortByKey, as a selection: the n_evicted oldest used slots that hold
-// no active block, oldest first and by ascending slot among equals (the first
-// entries of the stable sort of all available slots by age; the unused slots,
-// older than every used one, precede them and need no list).  A slot's key is
-// the call that last used it less `base`, a call no used slot is older than.
-// One pass: k_evict_count counts the keys of each tile of slots, and
-// k_evict_list finds the key up to which slots are taken and ranks the tile's
-// slots below it.  The keys span the calls since the oldest slot's use (few,
-// since a cache that must evict drops the oldest), so one pass covers spans
-// of 2047 calls; longer spans take stable passes over 11-bit digits, the last
-// of which stops at n_evicted.  A full radix sort of the slots, with the pass
-// over all of them that ages them, took 31-42 us per call at 10^5 slots
-// in five launches; this takes 10-12 us in two, and nothing when every new
-// block finds an unused slot.
-// ---------------------------------------------------------------------------
-struct EvictPass {
-    uint32_t base, now;      // keys: stamps in [base, now)
-    int shift, bits;         // the pass's digit
-    int first, last;         // first: slots in slot order; else `in`
-    const uint32_t *in;      // the previous pass's list
-    uint32_t *out;           // this pass's list (last: n_evicted entries)
-    uint32_t n_used;         // used slots (first)
-    uint32_t tiles;          // stride of the histogram's rows
-    int scanned;             // the histogram rows hold prefixes (k_evict_scan ran)
-};
-
-// Elements of the pass, and element i's slot (~0u: none: not available).
-__device__ __forceinline__ uint32_t evict_count_in(const EvictPass &p, const Counters *ctr) {
-    return p.first ? p.n_used : ctr->n_sort;
-}
-__device__ __forceinline__ bool evict_elem(const EvictPass &p, const uint32_t *__restrict__ S_stamp, uint32_t i,
-                                           uint32_t n, uint32_t &slot, uint32_t &stamp) {
-    if (i >= n) return false;
-    slot = p.first ? i : p.in[i];
-    stamp = S_stamp[slot];
-    return !p.first || stamp < p.now;
-}
-__device__ __forceinline__ uint32_t evict_digit(const EvictPass &p, uint32_t stamp) {
-    return ((stamp - p.base) >> p.shift) & ((1u << p.bits) - 1u);
-}
-
-// Adds the wave's digits to h, one lane per distinct digit: neighbouring
-// slots were mostly last used by the same call.
-__device__ __forceinline__ void wave_digit_count(uint32_t *h, bool valid, uint32_t d) {
-    uint64_t left = __ballot(valid);
-    while (left) {
-        const int leader = (int)__builtin_ctzll(left);
-        const uint32_t ld = (uint32_t)__builtin_amdgcn_readlane((int)d, leader);
-        const uint64_t same = __ballot(valid && d == ld) & left;
-        if (lane() == leader) atomicAdd(&h[ld], (uint32_t)__popcll(same));
-        left &= ~same;
-    }
-}
-
-// hist[digit][tile], tiles of EVICT_TILE elements.  refresh: the oldest
-// used slot's stamp, for the next calls' base.
+// The digits of a pass, a tile per workgroup (the first pass of a volume of
+// up to ROUNDS_DIRECT rounds is counted by the compaction).
 __global__ __launch_bounds__(256) void k_evict_count(EvictPass p, const uint32_t *__restrict__ S_stamp,
-                                                    uint32_t *__restrict__ hist, Counters *ctr, int refresh) {
+                                                    uint32_t *__restrict__ hist, Counters *ctr) {
     __shared__ uint32_t h[EVICT_BINS];
     if (ctr->err) return;
     const bool need = ctr->n_evicted != 0;
-    if (!need && !refresh) return;
-    const uint32_t n = evict_count_in(p, ctr), tile = blockIdx.x;
-    for (int d = threadIdx.x; d < 1 << p.bits; d += 256) h[d] = 0;
-    __syncthreads();
-    uint32_t oldest = ~0u;
-    for (int r = 0; r < EVICT_TILE / 256; r++) {
-        uint32_t slot = 0, stamp = 0;
-        const uint32_t i = tile * EVICT_TILE + r * 256 + threadIdx.x;
-        const bool v = evict_elem(p, S_stamp, i, n, slot, stamp);
-        if (i < n) oldest = min(oldest, stamp);
-        if (need) wave_digit_count(h, v, evict_digit(p, stamp));
-    }
-    if (refresh) {
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) oldest = min(oldest, (uint32_t)__shfl_xor((int)oldest, d, 64));
-        if (lane() == 0) atomicMin(&ctr->oldest, oldest);
-    }
-    if (!need) return;
-    __syncthreads();
-    for (int d = threadIdx.x; d < 1 << p.bits; d += 256) hist[(uint64_t)d * p.tiles + tile] = h[d];
+    if (!need && !p.refresh) return;
+    const uint32_t n = p.first ? p.n_used : ctr->n_sort;
+    uint32_t slot[EVICT_PER], stamp[EVICT_PER];
+    const uint32_t there = evict_load(p, S_stamp, n, blockIdx.x, slot, stamp);
+    evict_count_tile(p, S_stamp, n, blockIdx.x, stamp, there, need, h, hist, ctr);
 }
 
 // Many tiles: each digit's row of the histogram into its exclusive prefix,
@@ -622,36 +655,44 @@ __global__ __launch_bounds__(256) void k_evict_scan(uint32_t tiles, uint32_t *__
 
 // The pass's list.  Each workgroup forms the digits' offsets (totals over
 // all tiles, then the tile's own) and ranks its tile in order: each wave
-// owns 1024 consecutive elements and its own running counts.
+// owns 256 consecutive elements and its own running counts.
 __global__ __launch_bounds__(256) void k_evict_list(EvictPass p, const uint32_t *__restrict__ S_stamp,
                                                    const uint32_t *__restrict__ hist,
                                                    const uint32_t *__restrict__ totals, Counters *ctr) {
     __shared__ uint32_t off[EVICT_BINS];       // first position of the tile's elements, per digit
-    __shared__ uint32_t run[4][EVICT_BINS];    // per wave: elements of its share, then placed ones
+    __shared__ uint32_t run[4][EVICT_BINS];    // per wave: elements of its share, then its next position
     __shared__ uint32_t s_w[4], s_thr;
     if (ctr->err || !ctr->n_evicted) return;
-    const uint32_t bins = 1u << p.bits, n = evict_count_in(p, ctr), tile = blockIdx.x;
+    const uint32_t bins = 1u << p.bits, n = p.first ? p.n_used : ctr->n_sort, tile = blockIdx.x;
     const uint32_t want = p.last ? (uint32_t)ctr->n_evicted : ~0u;   // positions past it are dropped
     const int w = threadIdx.x >> 6, l = lane();
-    // per digit: elements in all tiles (run[0]) and in the tiles before this one (off)
-    for (uint32_t d = threadIdx.x; d < bins; d += 256) {
-        const uint32_t *row = hist + (uint64_t)d * p.tiles;
-        uint32_t all = 0, before = 0;
-        if (p.scanned) {
-            all = totals[d];
-            before = row[tile];
-        } else {
+    uint32_t slot[EVICT_PER], stamp[EVICT_PER], dig[EVICT_PER];
+    const uint32_t there = evict_load(p, S_stamp, n, tile, slot, stamp);
+    for (uint32_t d = threadIdx.x; d < bins; d += 256) run[0][d] = off[d] = 0;
+    if (threadIdx.x == 0) s_thr = bins;
+    __syncthreads();
+    // per digit: elements in all tiles (run[0]) and in the tiles before this
+    // one (off); few digits: several threads per row
+    if (p.scanned) {
+        for (uint32_t d = threadIdx.x; d < bins; d += 256) {
+            run[0][d] = totals[d];
+            off[d] = hist[(uint64_t)d * p.tiles + tile];
+        }
+    } else {
+        const uint32_t per = bins < 256 ? 256 / bins : 1u, part = threadIdx.x % per;
+        for (uint32_t d = threadIdx.x / per; d < bins; d += 256 / per) {
+            const uint32_t *row = hist + (uint64_t)d * p.tiles;
+            uint32_t all = 0, before = 0;
 #pragma unroll 8
-            for (uint32_t t = 0; t < p.tiles; t++) {
+            for (uint32_t t = part; t < p.tiles; t += per) {
                 const uint32_t x = row[t];
                 all += x;
                 before += t < tile ? x : 0u;
             }
+            if (all) atomicAdd(&run[0][d], all);
+            if (before) atomicAdd(&off[d], before);
         }
-        run[0][d] = all;
-        off[d] = before;
     }
-    if (threadIdx.x == 0) s_thr = bins;
     __syncthreads();
     uint32_t carry = 0;
     for (uint32_t d0 = 0; d0 < bins; d0 += 256) {   // exclusive prefix over the digits
@@ -667,27 +708,27 @@ __global__ __launch_bounds__(256) void k_evict_list(EvictPass p, const uint32_t 
         }
         if (d < bins) {
             off[d] += o;
+            run[0][d] = run[1][d] = run[2][d] = run[3][d] = 0;
             if (o < want && want - o <= x) s_thr = d;   // the digit the list ends in
         }
         __syncthreads();
     }
-    for (uint32_t d = threadIdx.x; d < bins; d += 256) run[0][d] = run[1][d] = run[2][d] = run[3][d] = 0;
     const uint32_t thr = s_thr;
     if (tile == 0 && threadIdx.x == 0) {
         if (p.first) ctr->n_sort = carry;
         if (p.last) {
             if (carry < want) atomicOr(&ctr->err, ERR_INTERNAL);
-            ctr->oldest = p.base + (thr << p.shift);   // what stays is no older
+            ctr->span = p.now - (p.base + (thr << p.shift)) + 1u;   // what stays is no older
         }
     }
     if (carry < want && p.last) return;
-    __syncthreads();
-    const uint32_t e0 = tile * EVICT_TILE + w * (EVICT_TILE / 4);
-    for (int r = 0; r < EVICT_TILE / 256; r++) {
-        uint32_t slot = 0, stamp = 0;
-        const bool v = evict_elem(p, S_stamp, e0 + r * 64 + l, n, slot, stamp);
-        const uint32_t d = evict_digit(p, stamp);
-        wave_digit_count(run[w], v && d <= thr, d);
+    uint32_t take = 0;
+#pragma unroll
+    for (int r = 0; r < EVICT_PER; r++) {
+        dig[r] = evict_digit(p, stamp[r]);
+        const bool v = ((there >> r) & 1u) && dig[r] <= thr;
+        take |= (v ? 1u : 0u) << r;
+        wave_digit_count(run[w], v, dig[r]);
     }
     __syncthreads();
     for (uint32_t d = threadIdx.x; d < bins; d += 256) {   // counts -> each wave's first position
@@ -699,21 +740,19 @@ __global__ __launch_bounds__(256) void k_evict_list(EvictPass p, const uint32_t 
         }
     }
     __syncthreads();
-    for (int r = 0; r < EVICT_TILE / 256; r++) {
-        uint32_t slot = 0, stamp = 0;
-        bool v = evict_elem(p, S_stamp, e0 + r * 64 + l, n, slot, stamp);
-        const uint32_t d = evict_digit(p, stamp);
-        v = v && d <= thr;
+#pragma unroll
+    for (int r = 0; r < EVICT_PER; r++) {
+        const bool v = (take >> r) & 1u;
         uint64_t left = __ballot(v);
         while (left) {
             const int leader = (int)__builtin_ctzll(left);
-            const uint32_t ld = (uint32_t)__builtin_amdgcn_readlane((int)d, leader);
-            const uint64_t same = __ballot(v && d == ld) & left;
+            const uint32_t ld = (uint32_t)__builtin_amdgcn_readlane((int)dig[r], leader);
+            const uint64_t same = __ballot(v && dig[r] == ld) & left;
             const uint32_t o = run[w][ld];
             wave_lds_sync();
             if ((same >> l) & 1u) {
                 const uint32_t pos = o + mbcnt(same);
-                if (pos < (p.last ? want : n)) p.out[pos] = slot;
+                if (pos < (p.last ? want : n)) p.out[pos] = slot[r];
             }
             if (l == leader) run[w][ld] = o + (uint32_t)__popcll(same);
             wave_lds_sync();
@@ -1144,47 +1183,56 @@ void launch_tile_ranges(const Geom &g, const float2 *ranges, float2 *tile_ranges
     k_tile_ranges<<<(unsigned)cull_tiles(g), 256, 0, s>>>(g, ranges, tile_ranges);
 }
 
-void launch_compact_blocks(const Geom &g, const DevState &d, const SlotState &ss, hipStream_t s) {
+// Pass k of the eviction's selection (k_evict_count, k_evict_list).
+static EvictPass evict_pass(const DevState &d, uint32_t n_used, uint32_t base, uint32_t now, int k) {
+    const int key_bits = 32 - __builtin_clz((now - base) | 1u);
+    EvictPass p;
+    p.base = base;
+    p.now = now;
+    p.shift = k * EVICT_BITS;
+    p.bits = std::min(EVICT_BITS, key_bits - p.shift);
+    p.first = k == 0;
+    p.last = p.shift + p.bits == key_bits;
+    p.in = d.evict[(k & 1) ^ 1];
+    p.out = d.evict[k & 1];
+    p.n_used = n_used;
+    p.tiles = (n_used + EVICT_TILE - 1) / EVICT_TILE;
+    // up to 32 K counts every workgroup of k_evict_list adds up the rows
+    // itself (128 loads a thread at most); beyond, a launch scans them
+    p.scanned = ((uint64_t)p.tiles << p.bits) > 32768;
+    p.refresh = k == 0 && now - base > EVICT_REFRESH;
+    return p;
+}
+
+void launch_compact_blocks(const Geom &g, const DevState &d, const SlotState &ss, uint32_t base, uint32_t now,
+                           hipStream_t s) {
     const uint64_t n = block_rounds(g.nb);
+    const EvictPass ev = evict_pass(d, (uint32_t)ss.n_used, base, now, 0);
     if (n <= ROUNDS_DIRECT) {
-        k_compact_blocks<false><<<(unsigned)n, 256, 0, s>>>(g, d.active, d.round_cnt, n, nullptr, d.round_next,
-                                                            d.I_active, d.I_new, d.ctr, d.ctr_next, ss);
+        k_compact_blocks<false><<<(unsigned)n + ev.tiles, 256, 0, s>>>(
+            g, d.active, d.round_cnt, n, nullptr, d.round_next, d.I_active, d.I_new, d.ctr, d.ctr_next, ss, ev,
+            d.S_stamp, d.evict_hist);
         return;
     }
     static unsigned wgrid = 0;
     if (!wgrid) wgrid = resident_grid(k_compact_blocks<true>, ~0ull >> 4);
     k_round_sums<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(d.round_cnt, n, d.round_sums, d.round_next);
     k_compact_blocks<true><<<(unsigned)std::min<uint64_t>(n, wgrid), 256, 0, s>>>(
-        g, d.active, d.round_cnt, n, d.round_sums, d.round_next, d.I_active, d.I_new, d.ctr, d.ctr_next, ss);
+        g, d.active, d.round_cnt, n, d.round_sums, d.round_next, d.I_active, d.I_new, d.ctr, d.ctr_next, ss, ev,
+        d.S_stamp, d.evict_hist);
 }
 
-uint32_t *launch_evict(const DevState &d, uint32_t n_used, uint32_t base, uint32_t now, hipStream_t s) {
-    if (n_used == 0 || now <= base) return d.evict[0];   // no slot was used before this call
-    const uint32_t tiles = (n_used + EVICT_TILE - 1) / EVICT_TILE;
-    const int key_bits = 32 - __builtin_clz((now - base) | 1u);
-    const int passes = (key_bits + EVICT_BITS - 1) / EVICT_BITS;
-    uint32_t *out = nullptr;
-    for (int k = 0; k < passes; k++) {
-        EvictPass p;
-        p.base = base;
-        p.now = now;
-        p.shift = k * EVICT_BITS;
-        p.bits = std::min(EVICT_BITS, key_bits - p.shift);
-        p.first = k == 0;
-        p.last = k == passes - 1;
-        p.in = out;
-        p.out = out = d.evict[k & 1];
-        p.n_used = n_used;
-        p.tiles = tiles;
-        // up to 64 tiles every workgroup of k_evict_list adds up the rows
-        // itself (at most 64 loads per digit); beyond, a launch scans them
-        p.scanned = tiles > 64;
-        const int refresh = k == 0 && now - base > EVICT_REFRESH;
-        k_evict_count<<<tiles, 256, 0, s>>>(p, d.S_stamp, d.evict_hist, d.ctr, refresh);
-        if (p.scanned) k_evict_scan<<<1u << p.bits, 256, 0, s>>>(tiles, d.evict_hist, d.evict_tot, d.ctr);
-        k_evict_list<<<tiles, 256, 0, s>>>(p, d.S_stamp, d.evict_hist, d.evict_tot, d.ctr);
+uint32_t *launch_evict(const Geom &g, const DevState &d, uint32_t n_used, uint32_t base, uint32_t now,
+                       hipStream_t s) {
+    if (n_used == 0) return d.evict[0];   // nothing to evict
+    for (int k = 0;; k++) {
+        const EvictPass p = evict_pass(d, n_used, base, now, k);
+        if (k > 0 || block_rounds(g.nb) > ROUNDS_DIRECT)
+            k_evict_count<<<p.tiles, 256, 0, s>>>(p, d.S_stamp, d.evict_hist, d.ctr);
+        if (p.scanned) k_evict_scan<<<1u << p.bits, 256, 0, s>>>(p.tiles, d.evict_hist, d.evict_tot, d.ctr);
+        k_evict_list<<<p.tiles, 256, 0, s>>>(p, d.S_stamp, d.evict_hist, d.evict_tot, d.ctr);
+        if (p.last) return p.out;
     }
-    return out;
 }
 
 void launch_cache_empty(const DevState &d, uint64_t n_used, hipStream_t s) {
