@@ -105,8 +105,8 @@ typedef struct {
                               stream; 0 for stages not profiled):
                               [0] cull + active/new compaction,
                               [1] cache update (slot pass, growth, age sort),
-                              [2] assign + decode of new blocks,
-                              [3] sign masks + marching cubes count pass,
+                              [2] assign + decode of new blocks, sign masks,
+                              [3] marching cubes count pass,
                               [4] empty (the block offsets are formed by the
                               emission pass from the count pass's per-wave
                               totals), [5] emission pass, [6] unused, [7] total

@@ -774,28 +774,20 @@ __global__ __launch_bounds__(256) void k_cache_empty(uint64_t n_used, int32_t *_
     }
 }
 
-// Sign masks (Sec. 4.4's per-cell classification, one bit per sample): for
-// every active block, bit i of masks[slot] is set when sample i of the
-// block (x fastest) is below iso.  One lane per block: its 16 float4 loads
-// are all in flight before the first compare.
+// Sign masks (Sec. 4.4's per-cell classification, one bit per sample) of the
+// active blocks of a volume whose blocks are all resident: bit i of masks[b]
+// is set when sample i of block b (x fastest) is below iso.  One lane per
+// block: its 16 float4 loads are all in flight before the first compare.
+// (Cached volumes build theirs with the decode.)
 __global__ __launch_bounds__(256) void k_masks(const uint32_t *__restrict__ I_active,
-                                              const int32_t *__restrict__ I_slot, int identity,
-                                              const float *__restrict__ slots, float iso,
-                                              uint64_t *__restrict__ masks,
-                                              uint32_t *__restrict__ mask_iso,
-                                              const Counters *ctr) {
+                                              const float *__restrict__ blocks, float iso,
+                                              uint64_t *__restrict__ masks, const Counters *ctr) {
     if (ctr->err) return;
     const uint64_t n_act = ctr->n_act;
-    // every active block was decoded by this call, its mask with it
-    if (!identity && ctr->n_new == n_act) return;
     for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n_act;
          i += (uint64_t)gridDim.x * blockDim.x) {
         const uint32_t b = I_active[i];
-        const int32_t s = identity ? (int32_t)b : I_slot[b];
-        if (s < 0) continue;
-        const uint32_t tag = __float_as_uint(iso);
-        if (!identity && mask_iso[s] == tag) continue;   // built for this isovalue already
-        const float4 *src = reinterpret_cast<const float4 *>(slots) + (uint64_t)s * 16;
+        const float4 *src = reinterpret_cast<const float4 *>(blocks) + (uint64_t)b * 16;
         float4 v[16];
 #pragma unroll
         for (int q = 0; q < 16; q++) v[q] = src[q];
@@ -806,8 +798,7 @@ __global__ __launch_bounds__(256) void k_masks(const uint32_t *__restrict__ I_ac
                                  (v[q].z < iso ? 4u : 0u) | (v[q].w < iso ? 8u : 0u);
             m |= nib << (4 * q);
         }
-        masks[s] = m;
-        if (!identity) mask_iso[s] = tag;
+        masks[b] = m;
     }
 }
 
@@ -1254,10 +1245,12 @@ static unsigned emit_grid(const Geom &g, int fmt) {
 
 void launch_mc_count(const Geom &g, const DevState &d, const float *slots, const int32_t *I_slot,
                      int identity_cache, float iso, int fmt, hipStream_t s) {
-    static unsigned mgrid = 0;
-    if (!mgrid) mgrid = resident_grid(k_masks, ~0ull >> 4);
-    k_masks<<<std::min<unsigned>(mgrid, mc_grid(g.nb / 16 + 1)), 256, 0, s>>>(
-        d.I_active, I_slot, identity_cache, slots, iso, d.masks, d.mask_iso, d.ctr);
+    if (identity_cache) {
+        static unsigned mgrid = 0;
+        if (!mgrid) mgrid = resident_grid(k_masks, ~0ull >> 4);
+        k_masks<<<std::min<unsigned>(mgrid, mc_grid(g.nb / 16 + 1)), 256, 0, s>>>(d.I_active, slots, iso, d.masks,
+                                                                                 d.ctr);
+    }
     // the count pass takes the emission's chunks on a grid of its own (all
     // of it resident)
     static unsigned cres = 0;

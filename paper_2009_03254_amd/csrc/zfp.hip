@@ -14,6 +14,8 @@
 //            64*rate bits; bits are LSB-first in little-endian u64 words.
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "common.h"
 #include "zfp_device.h"
 
@@ -139,21 +141,53 @@ __device__ __forceinline__ uint32_t mbcnt_lo_hi(uint64_t m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
+// Sign mask of a block: bit i = sample i below iso.
+__device__ __forceinline__ uint64_t sign_mask_of(const float4 (&f)[16], float iso) {
+    uint32_t mw[2] = {0u, 0u};
+#pragma unroll
+    for (int q = 0; q < 16; q++)
+        mw[q >> 3] |= ((f[q].x < iso ? 1u : 0u) | (f[q].y < iso ? 2u : 0u) | (f[q].z < iso ? 4u : 0u) |
+                       (f[q].w < iso ? 8u : 0u)) << (4 * (q & 7));
+    return (uint64_t)mw[1] << 32 | mw[0];
+}
+
 // Store a decoded block into its slot, with its sign mask for this call's
-// isovalue (so the mask pass need not read the freshly decoded slot back).
+// isovalue (so the freshly decoded slot need not be read back for it).
 __device__ __forceinline__ void store_slot(const float *v, uint64_t s, float iso, float *__restrict__ slots,
                                            uint64_t *__restrict__ masks, uint32_t *__restrict__ mask_iso) {
     float4 *o = reinterpret_cast<float4 *>(slots + s * 64);
-    uint32_t mw[2] = {0u, 0u};
+    float4 f[16];
 #pragma unroll
-    for (int q = 0; q < 16; q++) {
-        const float4 f = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
-        o[q] = f;
-        mw[q >> 3] |= ((f.x < iso ? 1u : 0u) | (f.y < iso ? 2u : 0u) | (f.z < iso ? 4u : 0u) |
-                       (f.w < iso ? 8u : 0u)) << (4 * (q & 7));
-    }
-    masks[s] = (uint64_t)mw[1] << 32 | mw[0];
+    for (int q = 0; q < 16; q++) o[q] = f[q] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+    masks[s] = sign_mask_of(f, iso);
     mask_iso[s] = __float_as_uint(iso);
+}
+
+// Sign masks for iso of the active blocks that were resident before the call
+// (not flagged new) and hold none for it, one lane per block, its 16 float4
+// loads all in flight before the first compare; the last waves first.
+__device__ __forceinline__ void resident_masks(const Counters *ctr, const uint32_t *__restrict__ I_active,
+                                               const uint8_t *__restrict__ active,
+                                               const int32_t *__restrict__ I_slot, const float *__restrict__ slots,
+                                               float iso, uint64_t *__restrict__ masks,
+                                               uint32_t *__restrict__ mask_iso) {
+    const uint64_t n_act = ctr->n_act;
+    if (ctr->n_new == n_act) return;
+    const uint32_t tag = __float_as_uint(iso);
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    const uint64_t wave0 = (blockIdx.x * (uint64_t)blockDim.x + threadIdx.x) & ~63ull;
+    for (uint64_t i = stride - 64 - wave0 + __lane_id(); i < n_act; i += stride) {
+        const uint32_t b = I_active[i];
+        if (active[b] & 4u) continue;
+        const int32_t s = I_slot[b];
+        if (s < 0 || mask_iso[s] == tag) continue;
+        const float4 *src = reinterpret_cast<const float4 *>(slots) + (uint64_t)s * 16;
+        float4 f[16];
+#pragma unroll
+        for (int q = 0; q < 16; q++) f[q] = src[q];
+        masks[s] = sign_mask_of(f, iso);
+        mask_iso[s] = tag;
+    }
 }
 
 // Alg. 1 AssignSlots: the slots of the call's new blocks, in their order:
@@ -168,11 +202,16 @@ struct SlotSource {
 
 // AssignSlots fused with DecompressBlocks: new block I_new[i] takes its
 // slot, evicting the previous owner, and is decoded straight into it.
+// The sign masks of the active blocks that were resident already, for calls
+// at an isovalue other than the one their masks were built for, go with the
+// decode: the waves that have no block to decode start on them (a launch of
+// their own took 4.5-5 us of every call, whether there was anything to build
+// or not).
 // LOW (double precision, staged, low rates): the decode is
 // decode_block_staged_low, which holds the kernel to the registers of the
 // low-rate decoder (4 waves per SIMD; 5 spills registers and is slower); the
 // blocks it hands back (their indices into I_new) are listed in `retry` for
-// k_decode_retry.
+// k_masks_retry, which builds the masks too.
 template <bool F64, bool STAGED, bool LOW = false>
 __global__ __launch_bounds__(256, LOW ? 4 : (F64 ? 1 : 4)) void k_assign_decode(Counters *ctr, const uint32_t *__restrict__ I_new,
                                                       const uint32_t *__restrict__ evict,
@@ -183,11 +222,12 @@ __global__ __launch_bounds__(256, LOW ? 4 : (F64 ? 1 : 4)) void k_assign_decode(
                                                       uint64_t n_blocks, float iso,
                                                       uint64_t *__restrict__ masks,
                                                       uint32_t *__restrict__ mask_iso,
+                                                      const uint32_t *__restrict__ I_active,
+                                                      const uint8_t *__restrict__ active,
                                                       uint32_t *__restrict__ retry = nullptr) {
     if (ctr->err) return;
     const uint64_t n_slots = ctr->n_slots;
     const uint64_t n_new = ctr->n_new;
-    if (n_new == 0) return;
     const SlotSource src{evict, ss.n_used, n_slots - ss.n_used};
     // slots this call created and leaves unused: their age counts from here
     const uint64_t created = ctr->n_used > ss.n_slots ? ctr->n_used : ss.n_slots;
@@ -243,6 +283,7 @@ __global__ __launch_bounds__(256, LOW ? 4 : (F64 ? 1 : 4)) void k_assign_decode(
             }
         }
     }
+    if constexpr (!LOW) resident_masks(ctr, I_active, active, I_slot, slots, iso, masks, mask_iso);
 }
 
 template <bool F64>
@@ -267,14 +308,18 @@ __global__ __launch_bounds__(256) void k_encode(Geom g, const void *__restrict__
 }
 
 // The blocks the low-rate decoder handed back, decoded with the general
-// decoder from global memory into the slots the assignment gave them.
-__global__ __launch_bounds__(256) void k_decode_retry(const Counters *ctr, const uint32_t *__restrict__ I_new,
+// decoder from global memory into the slots the assignment gave them, and the
+// resident blocks' masks.
+__global__ __launch_bounds__(256) void k_masks_retry(const Counters *ctr, const uint32_t *__restrict__ I_new,
                                                      const uint32_t *__restrict__ evict, SlotState ss,
                                                      const uint64_t *__restrict__ stream, int rate,
                                                      float *__restrict__ slots, float iso,
                                                      uint64_t *__restrict__ masks,
                                                      uint32_t *__restrict__ mask_iso,
-                                                     const uint32_t *__restrict__ retry) {
+                                                     const uint32_t *__restrict__ retry,
+                                                     const uint32_t *__restrict__ I_active,
+                                                     const uint8_t *__restrict__ active,
+                                                     const int32_t *__restrict__ I_slot) {
     if (ctr->err) return;
     const uint32_t n = ctr->n_retry;
     const SlotSource src{evict, ss.n_used, ctr->n_slots - ss.n_used};
@@ -286,6 +331,7 @@ __global__ __launch_bounds__(256) void k_decode_retry(const Counters *ctr, const
         decode_block<true>(stream + (uint64_t)b * rate, rate, v);
         store_slot(v, s, iso, slots, masks, mask_iso);
     }
+    resident_masks(ctr, I_active, active, I_slot, slots, iso, masks, mask_iso);
 }
 
 unsigned grid_for(uint64_t n, unsigned cap) {
@@ -325,13 +371,15 @@ void launch_assign_decode(const DevState &d, int is_f64, uint32_t rate, uint64_t
     if (is_f64 && lds && rate <= LOW_RATE_MAX && d.retry) {
         k_assign_decode<true, true, true><<<grid, 256, lds, s>>>(
             d.ctr, d.I_new, evict, ss, now, d.S_block, d.I_slot, d.S_stamp, d.stream, (int)rate, d.slots,
-            max_new, iso, d.masks, d.mask_iso, d.retry);
-        k_decode_retry<<<64, 256, 0, s>>>(d.ctr, d.I_new, evict, ss, d.stream, (int)rate, d.slots, iso,
-                                          d.masks, d.mask_iso, d.retry);
+            max_new, iso, d.masks, d.mask_iso, d.I_active, d.active, d.retry);
+        k_masks_retry<<<std::min(grid, 1024u), 256, 0, s>>>(d.ctr, d.I_new, evict, ss, d.stream, (int)rate, d.slots,
+                                                           iso, d.masks, d.mask_iso, d.retry, d.I_active, d.active,
+                                                           d.I_slot);
         return;
     }
     BCMC_DECODE_LAUNCH(k_assign_decode, grid, rate, s, d.ctr, d.I_new, evict, ss, now, d.S_block, d.I_slot,
-                       d.S_stamp, d.stream, (int)rate, d.slots, max_new, iso, d.masks, d.mask_iso);
+                       d.S_stamp, d.stream, (int)rate, d.slots, max_new, iso, d.masks, d.mask_iso, d.I_active,
+                       d.active);
 }
 
 void launch_encode(const Geom &g, const void *field, int is_f64, uint32_t rate, uint64_t *stream,
