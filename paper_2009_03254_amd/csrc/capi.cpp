@@ -145,8 +145,7 @@ int alloc_common(bcmc_volume *v) {
     if (block_rounds(v->g.nb) > ROUNDS_DIRECT &&
         (rc = dev_alloc(&v->d.round_sums, 2 * (block_rounds(v->g.nb) / 256 + 1))))
         return rc;
-    if ((rc = dev_alloc(&v->d.chunk_off, mc_chunk_slots(v->g.nb) + 8))) return rc;
-    if ((rc = dev_alloc(&v->d.part_occw, 4 * MC_MAX_GRID))) return rc;
+    if ((rc = dev_alloc(&v->d.chunk_tot, mc_chunk_slots(v->g.nb)))) return rc;
     if ((rc = dev_alloc(&v->d.part_giso, 4 * MC_MAX_GRID))) return rc;
     if ((rc = dev_alloc(&v->d.mc_table, 256))) return rc;
     if (mc_table_status() != 0) return invalid("marching cubes table generation failed");
@@ -177,8 +176,7 @@ void destroy(bcmc_volume *v) {
         dev_free(v->ctr[k]);
     }
     dev_free(v->d.round_sums);
-    dev_free(v->d.chunk_off);
-    dev_free(v->d.part_occw);
+    dev_free(v->d.chunk_tot);
     dev_free(v->d.part_giso);
     dev_free(v->d.mc_table);
     if (v->h_ctr) (void)hipHostFree(v->h_ctr);
@@ -236,7 +234,7 @@ hipStream_t as_stream(void *p) { return reinterpret_cast<hipStream_t>(p); }
 // polls an event instead of sleeping in the runtime (a sleeping wait adds
 // its wake-up latency to every call).
 int sync_counters(bcmc_volume *v, hipStream_t s) {
-    BCMC_HIP_TRY(hipMemcpyAsync(v->h_ctr, v->d.ctr, sizeof(Counters), hipMemcpyDeviceToHost, s));
+    BCMC_HIP_TRY(hipMemcpyAsync(v->h_ctr, v->d.ctr, CTR_READ, hipMemcpyDeviceToHost, s));
     if (!v->ev_done) BCMC_HIP_TRY(hipEventCreateWithFlags(&v->ev_done, hipEventDisableTiming));
     BCMC_HIP_TRY(hipEventRecord(v->ev_done, s));
     hipError_t e;
@@ -845,8 +843,7 @@ uint64_t carve_scratch(const Geom &g, uintptr_t base, DevState &d, unsigned int 
     d.blk_cnt = reinterpret_cast<uint32_t *>(take(g.nb * sizeof(uint32_t)));
     d.blk_off = reinterpret_cast<uint64_t *>(take(g.nb * sizeof(uint64_t)));
     d.masks = reinterpret_cast<uint64_t *>(take(g.nb * sizeof(uint64_t)));
-    d.chunk_off = reinterpret_cast<uint64_t *>(take((mc_chunk_slots(g.nb) + 8) * sizeof(uint64_t)));
-    d.part_occw = reinterpret_cast<uint32_t *>(take(4 * MC_MAX_GRID * sizeof(uint32_t)));
+    d.chunk_tot = reinterpret_cast<uint32_t *>(take(mc_chunk_slots(g.nb) * sizeof(uint32_t)));
     return off;
 }
 
@@ -889,7 +886,7 @@ extern "C" int bcmc_extract_blocks_noalloc(const float *d_blocks, uint32_t nx, u
     BCMC_HIP_TRY(hipGetLastError());
     Counters c;
     unsigned int rerr = 0;
-    BCMC_HIP_TRY(hipMemcpyAsync(&c, d.ctr, sizeof(Counters), hipMemcpyDeviceToHost, s));
+    BCMC_HIP_TRY(hipMemcpyAsync(&c, d.ctr, CTR_READ, hipMemcpyDeviceToHost, s));
     BCMC_HIP_TRY(hipMemcpyAsync(&rerr, range_err, sizeof(unsigned int), hipMemcpyDeviceToHost, s));
     BCMC_HIP_TRY(hipStreamSynchronize(s));
     if (rerr & ERR_NONFINITE) {

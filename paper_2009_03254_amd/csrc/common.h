@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include <string>
@@ -51,7 +52,13 @@ struct Counters {
     unsigned int n_retry;            // blocks the low-rate decoder handed back
     unsigned int cull_live, cull_stale;  // the cull's queued tiles
     unsigned int pad;
+    // per XCD eighth of the chunks (xcd_chunks), a cache line each: vertices
+    // and occupied blocks.  Not read back.
+    struct alignas(128) Xcd {
+        unsigned long long verts, occ;
+    } xcd[8];
 };
+constexpr size_t CTR_READ = offsetof(Counters, xcd);   // what the host reads
 // Double-precision streams up to this rate decode with the low-rate decoder
 // (and a general pass over the blocks it hands back).
 constexpr uint32_t LOW_RATE_MAX = 4;
@@ -97,9 +104,7 @@ struct DevState {
     uint64_t *round_cnt = nullptr;  // per 4096-block round: counts of its blocks (round_pack)
     uint64_t *round_next = nullptr; // the next call's, zeroed by this one
     uint64_t *round_sums = nullptr; // more than ROUNDS_DIRECT rounds: sums of 256 of them
-    uint64_t *chunk_off = nullptr;  // per 64-entry chunk of the active list: vertices, then first vertex
-                                    // in its XCD eighth; then the 8 eighths' totals
-    uint32_t *part_occw = nullptr;  // [4 * max MC grid] per-wave occupied blocks
+    uint32_t *chunk_tot = nullptr;  // vertices of each chunk of the active list (mc_chunk_slots entries)
     float *part_giso = nullptr;     // [4 * max MC grid] per-wave dL/diso of the backward
     Counters *ctr = nullptr;
     Counters *ctr_next = nullptr;   // the next call's, zeroed by this one
@@ -116,10 +121,10 @@ void launch_cull(const Geom &g, const DevState &d, float iso, float prev_iso, in
 void launch_compact_blocks(const Geom &g, const DevState &d, const SlotState &ss, uint32_t base, uint32_t now,
                            hipStream_t s);
 inline uint64_t block_rounds(uint64_t nb) { return (nb + BLK_TILE - 1) / BLK_TILE; }
-// Chunk entries of the count pass's and emission's chunk totals: a call
+// Entries of the count pass's chunk totals: a call
 // with n_act active blocks on W waves has ceil(n_act / cs) chunks of
 // cs = min(64, ceil(n_act / W)) blocks (mc_chunk_size), at most
-// max(ceil(nb / 64), W); the 8 XCD totals follow them.
+// max(ceil(nb / 64), W).
 inline uint64_t mc_chunk_slots(uint64_t nb) {
     const uint64_t a = (nb + 63) / 64, b = 4ull * MC_MAX_GRID;
     return a > b ? a : b;

@@ -363,9 +363,11 @@ __device__ __forceinline__ SlotPlan plan_slots(uint64_t n_act, uint64_t n_new, c
     return p;
 }
 // ... published for the call's later kernels and the host, and the next
-// call's counters cleared (one thread).
+// call's counters cleared (one workgroup).
 __device__ __forceinline__ void publish_plan(Counters *ctr, Counters *next, uint64_t n_act, uint64_t n_new,
                                              uint64_t n_cand, const SlotState &ss) {
+    for (unsigned i = threadIdx.x; i < sizeof(Counters) / 4; i += 256) reinterpret_cast<uint32_t *>(next)[i] = 0;
+    if (threadIdx.x != 0) return;
     const SlotPlan p = plan_slots(n_act, n_new, ss);
     ctr->n_act = n_act;
     ctr->n_new = n_new;
@@ -374,7 +376,6 @@ __device__ __forceinline__ void publish_plan(Counters *ctr, Counters *next, uint
     ctr->n_used = p.n_used;
     ctr->n_evicted = p.n_evicted;
     if (!p.fits) ctr->err |= ERR_CACHE_CAP;
-    *next = Counters{};
 }
 
 // Large volumes: the sums of 256 rounds each as (active << 32 | new), their
@@ -571,7 +572,7 @@ __global__ __launch_bounds__(256) void k_compact_blocks(Geom g, const uint8_t *_
         if (blockIdx.x != 0 && round_cnt[blockIdx.x] == 0) return;
         round_sums_direct(round_cnt, n_rounds, blockIdx.x, off, total, cand, s_sum);
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0)
+    if (blockIdx.x == 0)
         publish_plan(ctr, next, total >> 32, total & 0xFFFFFFFFull, cand, ss);
     for (uint64_t k = blockIdx.x; k < n_rounds; k += gridDim.x) {
         if (round_cnt[k] == 0) continue;
@@ -804,7 +805,9 @@ __global__ __launch_bounds__(256) void k_masks(const uint32_t *__restrict__ I_ac
 
 // Count pass (Sec. 4.4): vertex count of every active block (0 unless it can
 // emit), one lane per block, over the chunks of xcd_chunks (mc_chunk_size
-// blocks each); each chunk's total goes to chunk_off for k_chunk_scan.  The
+// blocks each); each chunk's total goes to chunk_tot, and the vertices and
+// occupied blocks of each XCD eighth (the split of xcd_chunks) are added up in
+// the counters, one atomic per workgroup on the eighth's own cache line.  The
 // cases of all 64 cells are evaluated at once on the corner masks, and the
 // triangle count per case by the bit-sliced diagram of the marching-cubes
 // table (mc_ntri_bits, generated at build time).
@@ -813,14 +816,16 @@ __global__ __launch_bounds__(256) void k_mc_count(Geom g, const uint32_t *__rest
                                                  const int32_t *__restrict__ I_slot, int identity,
                                                  const uint64_t *__restrict__ masks,
                                                  uint32_t *__restrict__ blk_cnt,
-                                                 uint64_t *__restrict__ chunk_off,
-                                                 uint32_t *__restrict__ part_occw, uint32_t emit_waves,
+                                                 uint32_t *__restrict__ chunk_tot, uint32_t emit_waves,
                                                  Counters *ctr) {
+    __shared__ uint64_t s_v[MC_WAVES];
+    __shared__ uint32_t s_o[MC_WAVES];
     if (ctr->err) return;
     const uint64_t n_act = ctr->n_act;
     const uint32_t cs = mc_chunk_size(n_act, emit_waves);   // the emission's chunks
     const ChunkRange cr = xcd_chunks((n_act + cs - 1) / cs);
     uint32_t wocc = 0;
+    uint64_t wverts = 0;
     for (uint64_t c = cr.first; c < cr.end; c += cr.stride) {
         const uint64_t i = c * cs + lane();
         const bool in = lane() < (int)cs && i < n_act;
@@ -844,101 +849,45 @@ __global__ __launch_bounds__(256) void k_mc_count(Geom g, const uint32_t *__rest
             }
         }
         if (in) blk_cnt[i] = cnt;
-        const uint32_t tot = wave_sum(cnt);   // the chunk's vertices (k_chunk_scan turns them into offsets)
-        if (lane() == 0) chunk_off[c] = tot;
+        const uint32_t tot = wave_sum(cnt);
+        if (lane() == 0) chunk_tot[c] = tot;
+        wverts += tot;
         wocc += cnt ? 1u : 0u;
     }
     wocc = wave_sum(wocc);
-    if (lane() == 0) part_occw[blockIdx.x * MC_WAVES + (threadIdx.x >> 6)] = wocc;
-}
-
-// Sec. 4.4's prefix sum over the block counts, at the granularity of the
-// count pass's chunks (up to 64 blocks).  Workgroup x < 8 scans the chunk
-// totals of XCD eighth x (the split of xcd_chunks) in place, exclusively, in
-// rounds of 16 K chunks (thread t holds chunks t + 1024 j, j < 16: coalesced loads; a
-// chunk holds at most 64 * 960 vertices, so a round's sums fit 32 bits), and
-// writes the eighth's total to xcd_tot[x] (the emission adds the totals of
-// the eighths before its own).  Workgroup 8 forms the call's occupied block
-// count.
-__global__ __launch_bounds__(1024) void k_chunk_scan(uint64_t *__restrict__ chunk_off,
-                                                    uint64_t *__restrict__ xcd_tot,
-                                                    const uint32_t *__restrict__ part_occw,
-                                                    uint32_t n_waves, uint32_t emit_waves, Counters *ctr) {
-    constexpr int J = 16;
-    __shared__ uint32_t s_w[J * 16];   // per (j, wave): the wave's total, then its exclusive prefix
-    __shared__ uint32_t s_round;
-    __shared__ uint32_t s_occ[16];
-    if (ctr->err) return;
-    const int t = threadIdx.x, w = t >> 6, l = lane();
-    if (blockIdx.x < 8) {
-        const uint32_t cs = mc_chunk_size(ctr->n_act, emit_waves);
-        const uint64_t n = (ctr->n_act + cs - 1) / cs, per = (n + 7) / 8;
-        uint64_t lo = blockIdx.x * per;
-        if (lo > n) lo = n;
-        const uint64_t hi = lo + per < n ? lo + per : n;
-        uint64_t carry = 0;
-        for (uint64_t base = lo; base < hi; base += J * 1024) {
-            uint32_t v[J], inc[J];
-#pragma unroll
-            for (int j = 0; j < J; j++) {
-                const uint64_t i = base + 1024 * (uint64_t)j + t;
-                v[j] = i < hi ? (uint32_t)chunk_off[i] : 0u;
-            }
-#pragma unroll
-            for (int j = 0; j < J; j++) inc[j] = wave_incl_scan(v[j]);
-            if (l == 63) {
-#pragma unroll
-                for (int j = 0; j < J; j++) s_w[16 * j + w] = inc[j];
-            }
-            __syncthreads();
-            if (w == 0) {   // exclusive scan of the 256 wave totals in chunk order (j, then wave)
-                uint32_t e[4], run = 0;
-#pragma unroll
-                for (int k = 0; k < 4; k++) {
-                    const uint32_t x = s_w[4 * l + k];
-                    e[k] = run;
-                    run += x;
-                }
-                const uint32_t incl = wave_incl_scan(run);
-#pragma unroll
-                for (int k = 0; k < 4; k++) s_w[4 * l + k] = incl - run + e[k];
-                if (l == 63) s_round = incl;
-            }
-            __syncthreads();
-#pragma unroll
-            for (int j = 0; j < J; j++) {
-                const uint64_t i = base + 1024 * (uint64_t)j + t;
-                if (i < hi) chunk_off[i] = carry + s_w[16 * j + w] + (inc[j] - v[j]);
-            }
-            carry += s_round;
-            __syncthreads();   // s_w and s_round are rewritten next round
-        }
-        if (t == 0) xcd_tot[blockIdx.x] = carry;
-        return;
+    if (lane() == 0) {
+        s_v[threadIdx.x >> 6] = wverts;
+        s_o[threadIdx.x >> 6] = wocc;
     }
-    // 8 loads in flight per thread (a plain loop waits for each load)
-    uint32_t occ = 0;
-    for (uint32_t i0 = t; i0 < n_waves; i0 += 8 * 1024) {
-        uint32_t x[8];
-#pragma unroll
-        for (int j = 0; j < 8; j++) x[j] = i0 + 1024u * j < n_waves ? part_occw[i0 + 1024u * j] : 0u;
-#pragma unroll
-        for (int j = 0; j < 8; j++) occ += x[j];
-    }
-    occ = wave_sum(occ);
-    if (l == 0) s_occ[w] = occ;
     __syncthreads();
-    if (t == 0) {
+    if (threadIdx.x == 0) {
+        uint64_t v = 0;
         uint32_t o = 0;
-        for (int k = 0; k < 16; k++) o += s_occ[k];
-        ctr->n_occ = o;
+        for (int k = 0; k < MC_WAVES; k++) {
+            v += s_v[k];
+            o += s_o[k];
+        }
+        if (o) {
+            atomicAdd(&ctr->xcd[blockIdx.x % 8u].verts, (unsigned long long)v);
+            atomicAdd(&ctr->xcd[blockIdx.x % 8u].occ, (unsigned long long)o);
+        }
     }
 }
 
+// The vertices of the chunks [a, b), summed by the calling wave.
+__device__ __forceinline__ uint32_t chunks_sum(const uint32_t *__restrict__ chunk_tot, uint64_t a, uint64_t b) {
+    uint32_t v = 0;
+#pragma unroll 4
+    for (uint64_t i = a + lane(); i < b; i += 64) v += chunk_tot[i];
+    return __builtin_amdgcn_readfirstlane(wave_sum(v));
+}
 
 // Emission pass (Sec. 4.5), over the chunks of xcd_chunks (the count pass's
-// schedule), each from its scanned offset: the chunk's block offsets by a
-// wave scan of the counts, then the occupied blocks restaged a few at a time;
+// schedule).  A wave's first chunk follows the eighths before its own and the
+// chunks of its eighth before it (fewer than the eighth's waves: 3.5 KB of
+// totals at most), each next one the chunks between: the wave adds them up
+// itself, which a launch scanning the totals (4.5-5 us of every call) does not
+// pay for.  Within a chunk: the block offsets by a wave scan of the counts, then the occupied blocks restaged a few at a time;
 // each block's in-block prefix of its per-cell triangle counts, the
 // triangles of the staged blocks listed together and written lane per vertex
 // from the first block's offset, in canonical order (block, cell, triangle,
@@ -951,8 +900,7 @@ __global__ __launch_bounds__(256, FMT == VFMT_GRAD ? 5 : 7) void k_mc_emit(Geom 
                                                 const uint32_t *__restrict__ blk_cnt,
                                                 uint64_t *__restrict__ blk_off,
                                                 void *__restrict__ out, uint64_t cap,
-                                                const uint64_t *__restrict__ chunk_off,
-                                                const uint64_t *__restrict__ xcd_tot,
+                                                const uint32_t *__restrict__ chunk_tot,
                                                 uint32_t chunk_waves, Counters *ctr,
                                                 const float *__restrict__ gV = nullptr,
                                                 float *__restrict__ dfield = nullptr,
@@ -965,8 +913,8 @@ __global__ __launch_bounds__(256, FMT == VFMT_GRAD ? 5 : 7) void k_mc_emit(Geom 
         for (int i = threadIdx.x; i < MC_WAVES * EMIT_SB * 128; i += blockDim.x) (&sh.acc[0][0][0])[i] = 0.0f;
     }
     __syncthreads();
-    const uint64_t n_act = ctr->n_act;
-    const int w = threadIdx.x >> 6, l = lane();
+    const uint64_t n_act = uniform64(ctr->n_act);
+    const int w = (int)wave_id(), l = lane();
     const uint32_t cs = mc_chunk_size(n_act, chunk_waves);   // the count pass's chunks
     const ChunkRange cr = xcd_chunks((n_act + cs - 1) / cs);
     GradCtx gc;
@@ -978,18 +926,23 @@ __global__ __launch_bounds__(256, FMT == VFMT_GRAD ? 5 : 7) void k_mc_emit(Geom 
         gc.nbxy = g.nbx * g.nby;
         gc.giso = 0.0f;
     }
-    // the vertices of the XCD eighths before this workgroup's (the chunk
-    // offsets are local to their eighth); workgroup 0 forms the call's total
-    uint64_t xbase = 0, all = 0;
+    // the vertices of the XCD eighths before this workgroup's; workgroup 0
+    // forms the call's totals
+    uint64_t base = 0, all = 0, occ = 0;
     for (uint32_t x = 0; x < 8; x++) {
-        const uint64_t tx = xcd_tot[x];
-        xbase += x < blockIdx.x % 8u ? tx : 0ull;
+        const uint64_t tx = ctr->xcd[x].verts;
+        base += x < blockIdx.x % 8u ? tx : 0ull;
         all += tx;
+        occ += ctr->xcd[x].occ;
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) ctr->total_verts = all;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        ctr->total_verts = all;
+        ctr->n_occ = occ;
+    }
+    base = uniform64(base);
+    if (cr.first < cr.end) base += chunks_sum(chunk_tot, cr.lo, cr.first);
     const LaneGeom q = lane_geom();
     for (uint64_t c = cr.first; c < cr.end; c += cr.stride) {
-        const uint64_t base = xbase + chunk_off[c];   // the chunk's first vertex (wave-uniform)
         const uint64_t idx = c * cs + l;
         const bool valid = l < (int)cs && idx < n_act;
         const uint32_t cnt = valid ? blk_cnt[idx] : 0u;
@@ -1038,6 +991,7 @@ __global__ __launch_bounds__(256, FMT == VFMT_GRAD ? 5 : 7) void k_mc_emit(Geom 
             }
             emit_batch<FMT>(nsb, info, sh.tiles[w], sh.tab, sh, w, ob, out, cap, &gc);
         }
+        if (c + cr.stride < cr.end) base += chunks_sum(chunk_tot, c, c + cr.stride);
     }
     if constexpr (FMT == VFMT_GRAD) {   // the wave's share of dL/diso (summed by k_sum_f32: no
                                         // same-address atomics, a fixed order)
@@ -1257,9 +1211,7 @@ void launch_mc_count(const Geom &g, const DevState &d, const float *slots, const
     if (!cres) cres = std::min<unsigned>(resident_grid(k_mc_count, ~0ull >> 4), MC_MAX_GRID);
     const unsigned egrid = emit_grid(g, fmt), cgrid = std::min<unsigned>(cres, mc_grid(g.nb));
     k_mc_count<<<cgrid, 256, 0, s>>>(g, d.I_active, d.active, I_slot, identity_cache, d.masks,
-                                     d.blk_cnt, d.chunk_off, d.part_occw, egrid * MC_WAVES, d.ctr);
-    k_chunk_scan<<<9, 1024, 0, s>>>(d.chunk_off, d.chunk_off + mc_chunk_slots(g.nb), d.part_occw,
-                                    cgrid * MC_WAVES, egrid * MC_WAVES, d.ctr);
+                                     d.blk_cnt, d.chunk_tot, egrid * MC_WAVES, d.ctr);
 }
 
 void launch_mc_emit(const Geom &g, const DevState &d, const float *slots, const int32_t *I_slot,
@@ -1268,8 +1220,7 @@ void launch_mc_emit(const Geom &g, const DevState &d, const float *slots, const 
     const unsigned n = emit_grid(g, fmt);
 #define BCMC_EMIT(F)                                                                          \
     k_mc_emit<F><<<n, 256, 0, s>>>(g, d.I_active, I_slot, identity_cache, slots, d.mc_table, iso, \
-                                   d.blk_cnt, d.blk_off, out, cap_verts, d.chunk_off,              \
-                                   d.chunk_off + mc_chunk_slots(g.nb), n * MC_WAVES, d.ctr)
+                                   d.blk_cnt, d.blk_off, out, cap_verts, d.chunk_tot, n * MC_WAVES, d.ctr)
     if (fmt == VFMT_EDGE8) BCMC_EMIT(VFMT_EDGE8);
     else if (fmt == VFMT_Q10) BCMC_EMIT(VFMT_Q10);
     else BCMC_EMIT(VFMT_F32);
@@ -1314,8 +1265,7 @@ void launch_backward(const Geom &g, const DevState &d, const float *slots, float
     if (!grid) grid = resident_grid(k_mc_emit<VFMT_GRAD>, ~0ull >> 4);
     const unsigned n = std::min<unsigned>(grid, mc_grid(g.nb));
     k_mc_emit<VFMT_GRAD><<<n, 256, 0, s>>>(g, d.I_active, nullptr, 1, slots, d.mc_table, iso, d.blk_cnt,
-                                          d.blk_off, nullptr, n_verts, d.chunk_off,
-                                          d.chunk_off + mc_chunk_slots(g.nb),
+                                          d.blk_off, nullptr, n_verts, d.chunk_tot,
                                           emit_grid(g, fmt) * MC_WAVES, d.ctr, gV, dfield, d.part_giso);
     k_sum_f32<<<1, 1024, 0, s>>>(d.part_giso, n * MC_WAVES, diso);
 }

@@ -11,6 +11,13 @@ namespace bcmc {
 namespace {
 
 __device__ __forceinline__ int lane() { return (int)__lane_id(); }
+// The wave's number in its workgroup, as a scalar.
+__device__ __forceinline__ uint32_t wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+// A wave-uniform value in scalar registers.
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+    return ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32) |
+           __builtin_amdgcn_readfirstlane((uint32_t)v);
+}
 
 __device__ __forceinline__ uint32_t mbcnt(uint64_t m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
@@ -290,18 +297,18 @@ __host__ __device__ __forceinline__ uint32_t mc_chunk_size(uint64_t n, uint32_t 
     return per >= 64 ? 64u : (per < 1 ? 1u : (uint32_t)per);
 }
 struct ChunkRange {
-    uint64_t first, end;
+    uint64_t lo, first, end;   // the eighth's chunks [lo, end); the wave's first one
     uint32_t stride;
 };
 __device__ __forceinline__ ChunkRange xcd_chunks(uint64_t n_chunks) {
     const uint32_t G = gridDim.x, g = blockIdx.x;
     const uint32_t per_xcd = (G / 8u) * MC_WAVES;                  // waves of one XCD
-    const uint32_t r = (g / 8u) * MC_WAVES + (threadIdx.x >> 6);  // this wave's rank there
+    const uint32_t r = (g / 8u) * MC_WAVES + wave_id();            // this wave's rank there
     const uint64_t per = (n_chunks + 7) / 8;
     uint64_t lo = (uint64_t)(g % 8u) * per;
     if (lo > n_chunks) lo = n_chunks;
     const uint64_t hi = lo + per < n_chunks ? lo + per : n_chunks;
-    return {lo + r, hi, per_xcd};
+    return {lo, lo + r, hi, per_xcd};
 }
 
 // Corner masks of the 64 cells of a block from the sign masks of the block
