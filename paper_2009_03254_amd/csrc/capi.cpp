@@ -28,14 +28,14 @@ struct bcmc_volume {
     const float *ext_blocks = nullptr;
     DevState d;
     uint64_t init_slots = 0, max_slots = 0, n_slots = 0, n_used = 0;  // host mirror
-    Counters *h_ctr = nullptr;     // pinned copy of the device counters
+    HostCounters *h_ctr = nullptr; // the last call's counters (pinned)
+    uint32_t h_seq = 0;            // number of the last readback
     bcmc_stats stats{};
     uint32_t profiling = 0;   // stage mask (bit i: events around stage i)
     int vertex_format = BCMC_VERTEX_F32;  // output records of bcmc_extract
     uint32_t calls_since_reset = 0;  // the clock of the slots' stamps
     uint32_t evict_base = 0;         // no used slot's stamp is below this
     hipEvent_t ev[8] = {};
-    hipEvent_t ev_done = nullptr;  // after the counters' readback (polled, not slept on)
     int have_extract = 0;
     float last_iso = 0.0f;
     int last_format = BCMC_VERTEX_F32;   // the last extract's format (its grid set the chunks)
@@ -151,8 +151,8 @@ int alloc_common(bcmc_volume *v) {
     if (mc_table_status() != 0) return invalid("marching cubes table generation failed");
     BCMC_HIP_TRY(hipMemcpy(v->d.mc_table, mc_table_host(), 256 * sizeof(uint64_t),
                            hipMemcpyHostToDevice));
-    BCMC_HIP_TRY(hipHostMalloc((void **)&v->h_ctr, sizeof(Counters), hipHostMallocDefault));
-    memset(v->h_ctr, 0, sizeof(Counters));
+    BCMC_HIP_TRY(hipHostMalloc((void **)&v->h_ctr, sizeof(HostCounters), hipHostMallocDefault));
+    memset(v->h_ctr, 0, sizeof(HostCounters));
     v->stats.n_blocks = v->g.nb;
     return BCMC_OK;
 }
@@ -182,7 +182,6 @@ void destroy(bcmc_volume *v) {
     if (v->h_ctr) (void)hipHostFree(v->h_ctr);
     for (auto &e : v->ev)
         if (e) (void)hipEventDestroy(e);
-    if (v->ev_done) (void)hipEventDestroy(v->ev_done);
     delete v;
 }
 
@@ -230,17 +229,33 @@ int set_budget(bcmc_volume *v, uint64_t initial_bytes, uint64_t max_bytes, hipSt
 
 hipStream_t as_stream(void *p) { return reinterpret_cast<hipStream_t>(p); }
 
-// Reads the counters back.  The caller waits for them anyway, so the wait
-// polls an event instead of sleeping in the runtime (a sleeping wait adds
-// its wake-up latency to every call).
+const Counters &counters(const bcmc_volume *v) { return *reinterpret_cast<const Counters *>(v->h_ctr->c); }
+
+// Reads the counters back.  The caller waits for them anyway, so a kernel at
+// the end of the call's work writes them to pinned memory and the host polls
+// the number behind them: a copy and an event took about 10 us more of every
+// call.  The stream's state is looked at now and then, so that an error ends
+// the wait.
 int sync_counters(bcmc_volume *v, hipStream_t s) {
-    BCMC_HIP_TRY(hipMemcpyAsync(v->h_ctr, v->d.ctr, CTR_READ, hipMemcpyDeviceToHost, s));
-    if (!v->ev_done) BCMC_HIP_TRY(hipEventCreateWithFlags(&v->ev_done, hipEventDisableTiming));
-    BCMC_HIP_TRY(hipEventRecord(v->ev_done, s));
-    hipError_t e;
-    while ((e = hipEventQuery(v->ev_done)) == hipErrorNotReady) {
+    const uint32_t want = ++v->h_seq;
+    launch_publish(v->d.ctr, v->h_ctr, want, s);
+    BCMC_HIP_TRY(hipGetLastError());
+    auto there = [&] { return __atomic_load_n(&v->h_ctr->seq, __ATOMIC_ACQUIRE) == want; };
+    for (uint32_t spins = 1; !there(); spins++) {
+        if (spins % 4096) {
+            __builtin_ia32_pause();
+            continue;
+        }
+        const hipError_t e = hipStreamQuery(s);
+        if (e == hipErrorNotReady) continue;
+        BCMC_HIP_TRY(e);
+        if (!there()) {   // the stream has ended: the write is there, or never comes
+            BCMC_HIP_TRY(hipStreamSynchronize(s));
+            if (there()) break;
+            set_error("the counters' readback did not arrive");
+            return BCMC_E_HIP;
+        }
     }
-    BCMC_HIP_TRY(e);
     return BCMC_OK;
 }
 
@@ -299,7 +314,7 @@ int bcmc_load_compressed(const void *stream, uint64_t nbytes, int stream_is_devi
         destroy(v);
         return rc;
     }
-    if (v->h_ctr->err & ERR_NONFINITE) {
+    if (counters(v).err & ERR_NONFINITE) {
         set_error("the stream decodes to non-finite values");
         destroy(v);
         return BCMC_E_NONFINITE;
@@ -342,7 +357,7 @@ int bcmc_volume_from_blocks(const float *d_blocks, uint32_t nx, uint32_t ny, uin
         destroy(v);
         return rc;
     }
-    if (v->h_ctr->err & ERR_NONFINITE) {
+    if (counters(v).err & ERR_NONFINITE) {
         set_error("the blocks hold non-finite values");
         destroy(v);
         return BCMC_E_NONFINITE;
@@ -465,7 +480,7 @@ int bcmc_extract(bcmc_volume *v, float iso, void *d_out, uint64_t capacity_verti
     v->counters_dirty = 0;
     v->rewrite_flags = 0;
     if ((rc = sync_counters(v, s))) return rc;
-    const Counters &c = *v->h_ctr;
+    const Counters &c = counters(v);
     v->stats.calls++;
     if (c.err & ERR_INTERNAL) {
         reset_cache_state(v, s);
@@ -528,7 +543,7 @@ int bcmc_backward(bcmc_volume *v, float iso, const float *d_gV, uint64_t n_verts
     if (!v || !d_dfield || !d_diso) return invalid("null argument");
     if (!v->identity) return invalid("backward needs a bcmc_volume_from_blocks handle");
     if (!v->have_extract || iso != v->last_iso) return invalid("no extract at this iso to differentiate");
-    if (n_verts != v->h_ctr->total_verts) return invalid("n_verts differs from the last extract");
+    if (n_verts != counters(v).total_verts) return invalid("n_verts differs from the last extract");
     if (n_verts && !d_gV) return invalid("null gradient");
     hipStream_t s = as_stream(hip_stream);
     BCMC_HIP_TRY(hipMemsetAsync(d_dfield, 0, v->g.nb * 64 * sizeof(float), s));
@@ -538,11 +553,8 @@ int bcmc_backward(bcmc_volume *v, float iso, const float *d_gV, uint64_t n_verts
     launch_backward(v->g, v->d, v->ext_blocks, iso, d_gV, n_verts, d_dfield, d_diso, v->last_format, s);
     BCMC_HIP_TRY(hipGetLastError());
     // the kernel compares each block's vertex count with the forward's
-    BCMC_HIP_TRY(hipMemcpyAsync(&v->h_ctr->err, &v->d.ctr->err, sizeof(unsigned int),
-                                hipMemcpyDeviceToHost, s));
-    BCMC_HIP_TRY(hipStreamSynchronize(s));
-    if (v->h_ctr->err) {
-        v->h_ctr->err = 0;
+    if (int rc = sync_counters(v, s)) return rc;
+    if (counters(v).err) {
         v->have_extract = 0;
         set_error("the field changed between the forward extract and the backward "
                   "(per-block vertex counts differ)");
@@ -620,7 +632,7 @@ int bcmc_debug_active(const bcmc_volume *v, uint8_t *h_active, uint32_t *h_I_act
     if (!v) return invalid("null handle");
     if (!v->have_extract) return invalid("no extract yet");
     BCMC_HIP_TRY(hipDeviceSynchronize());
-    uint64_t n = v->h_ctr->n_act;
+    uint64_t n = counters(v).n_act;
     if (h_n_active) *h_n_active = n;
     if (h_active) BCMC_HIP_TRY(hipMemcpy(h_active, v->d.active, v->g.nb, hipMemcpyDeviceToHost));
     if (h_I_active && n)
@@ -632,7 +644,7 @@ int bcmc_debug_new(const bcmc_volume *v, uint32_t *h_I_new, uint64_t *h_n_new) {
     if (!v) return invalid("null handle");
     if (!v->have_extract || v->identity) return invalid("no cached extract yet");
     BCMC_HIP_TRY(hipDeviceSynchronize());
-    uint64_t n = v->h_ctr->n_new;
+    uint64_t n = counters(v).n_new;
     if (h_n_new) *h_n_new = n;
     if (h_I_new && n) BCMC_HIP_TRY(hipMemcpy(h_I_new, v->d.I_new, n * 4, hipMemcpyDeviceToHost));
     return BCMC_OK;
@@ -670,7 +682,7 @@ int bcmc_debug_slot_data(const bcmc_volume *v, float *h_slots) {
 int bcmc_debug_block_counts(const bcmc_volume *v, uint32_t *h_cnt, uint64_t *h_off, uint64_t n) {
     if (!v) return invalid("null handle");
     if (!v->have_extract) return invalid("no extract yet");
-    if (n > v->h_ctr->n_act) return invalid("n exceeds the active block count");
+    if (n > counters(v).n_act) return invalid("n exceeds the active block count");
     BCMC_HIP_TRY(hipDeviceSynchronize());
     if (h_cnt && n) BCMC_HIP_TRY(hipMemcpy(h_cnt, v->d.blk_cnt, n * 4, hipMemcpyDeviceToHost));
     if (h_off && n) BCMC_HIP_TRY(hipMemcpy(h_off, v->d.blk_off, n * 8, hipMemcpyDeviceToHost));

@@ -59,6 +59,12 @@ struct Counters {
     } xcd[8];
 };
 constexpr size_t CTR_READ = offsetof(Counters, xcd);   // what the host reads
+// The host's copy of a call's counters (pinned memory the device writes):
+// valid for the call whose number seq holds.
+struct HostCounters {
+    unsigned char c[CTR_READ];
+    uint32_t seq;
+};
 // Double-precision streams up to this rate decode with the low-rate decoder
 // (and a general pass over the blocks it hands back).
 constexpr uint32_t LOW_RATE_MAX = 4;
@@ -151,6 +157,8 @@ void launch_debug_cases(const Geom &g, const DevState &d, const float *slots,
 void launch_backward(const Geom &g, const DevState &d, const float *slots, float iso,
                      const float *gV, uint64_t n_verts, float *dfield, float *diso, int fmt,
                      hipStream_t s);
+// Writes the counters, then value as host->seq, when s gets there.
+void launch_publish(const Counters *ctr, HostCounters *host, uint32_t value, hipStream_t s);
 void launch_fill_u32(uint32_t *p, uint32_t v, uint64_t n, hipStream_t s);
 void launch_copy_calibration(void *dst, const void *src, uint64_t n16, hipStream_t s);
 void launch_iota_i32(int32_t *p, uint64_t n, hipStream_t s);

@@ -1056,6 +1056,17 @@ __global__ __launch_bounds__(256) void k_debug_cases(Geom g, const uint32_t *__r
     }
 }
 
+// The call's counters to the host's copy (pinned memory), then the call's
+// number behind them: the host polls it.  As a kernel of its own it starts when
+// the emission has ended, so the number means that the soup is whole.
+__global__ __launch_bounds__(64) void k_publish(const Counters *ctr, uint32_t *__restrict__ host, uint32_t *seq,
+                                               uint32_t value) {
+    if (threadIdx.x < CTR_READ / 4) host[threadIdx.x] = reinterpret_cast<const uint32_t *>(ctr)[threadIdx.x];
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(seq, value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Plain streaming copy (16 B per lane per iteration): a known-size reference
 // for reading memory-traffic counters.
 __global__ __launch_bounds__(256) void k_copy_calibration(uint4 *__restrict__ dst,
@@ -1284,6 +1295,11 @@ void launch_backward(const Geom &g, const DevState &d, const float *slots, float
 void launch_copy_calibration(void *dst, const void *src, uint64_t n16, hipStream_t s) {
     if (n16) k_copy_calibration<<<grid_cap(n16, 16384), 256, 0, s>>>(
         reinterpret_cast<uint4 *>(dst), reinterpret_cast<const uint4 *>(src), n16);
+}
+
+void launch_publish(const Counters *ctr, HostCounters *host, uint32_t value, hipStream_t s) {
+    static_assert(CTR_READ / 4 <= 64, "one lane per word");
+    k_publish<<<1, 64, 0, s>>>(ctr, reinterpret_cast<uint32_t *>(host->c), &host->seq, value);
 }
 
 void launch_fill_u32(uint32_t *p, uint32_t v, uint64_t n, hipStream_t s) {
