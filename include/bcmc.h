@@ -312,15 +312,14 @@ BCMC_API void bcmc_batch_free(bcmc_batch *b);
 /* ---- dense baseline (Sec. 3.3.3) --------------------------------------- */
 /* The standard data-parallel marching cubes the paper measures as its
  * baseline (Sec. 3.3.3, tab:mc_naive_parallel_perf), over an uncompressed
- * float field resident in device memory: every cell classified, the cells
- * holding the surface compacted by a prefix sum, their vertex counts
- * summed by a second prefix sum, then a pass over the compacted cells
- * writes the soup.  No blocks, culling or cache.  Records are bcmc_vertex
+ * float field resident in device memory: every cell classified and counted,
+ * prefix sums over the counts, then a pass that lists the cells holding the
+ * surface and writes the soup.  No blocks, culling or cache.  Records are bcmc_vertex
  * (block-relative, computed as bcmc_extract computes them) with the cells in
  * global row-major order (x fastest): the same triangles as bcmc_extract of
  * the same field, in another order.
- * bcmc_dense_create reserves the scratch for an nx*ny*nz field (13 bytes per
- * cell; at most 2^32 - 1 samples).
+ * bcmc_dense_create reserves the scratch for an nx*ny*nz field (one bit per
+ * sample, rows padded to 64; at most 2^32 - 1 samples).
  * bcmc_dense_extract: d_field ([nz][ny][nx] float, device), output as
  * bcmc_extract (capacity in records, BCMC_E_CAPACITY with *n_triangles set);
  * synchronises hip_stream once.  bcmc_dense_active_cells: cells holding the

@@ -236,11 +236,10 @@ const Counters &counters(const bcmc_volume *v) { return *reinterpret_cast<const 
 // the number behind them: a copy and an event took about 10 us more of every
 // call.  The stream's state is looked at now and then, so that an error ends
 // the wait.
-int sync_counters(bcmc_volume *v, hipStream_t s) {
-    const uint32_t want = ++v->h_seq;
-    launch_publish(v->d.ctr, v->h_ctr, want, s);
+int await_counters(const void *ctr, HostCounters *host, uint32_t want, hipStream_t s) {
+    launch_publish(ctr, host, want, s);
     BCMC_HIP_TRY(hipGetLastError());
-    auto there = [&] { return __atomic_load_n(&v->h_ctr->seq, __ATOMIC_ACQUIRE) == want; };
+    auto there = [&] { return __atomic_load_n(&host->seq, __ATOMIC_ACQUIRE) == want; };
     for (uint32_t spins = 1; !there(); spins++) {
         if (spins % 4096) {
             __builtin_ia32_pause();
@@ -258,6 +257,7 @@ int sync_counters(bcmc_volume *v, hipStream_t s) {
     }
     return BCMC_OK;
 }
+int sync_counters(bcmc_volume *v, hipStream_t s) { return await_counters(v->d.ctr, v->h_ctr, ++v->h_seq, s); }
 
 }  // namespace
 
@@ -706,22 +706,21 @@ int bcmc_debug_cases(bcmc_volume *v, float iso, uint8_t *d_cases, void *hip_stre
 // ---------------------------------------------------------------------------
 struct bcmc_dense {
     uint32_t nx = 0, ny = 0, nz = 0;
-    uint32_t *ids = nullptr;
-    uint8_t *cases = nullptr;
-    uint64_t *first = nullptr, *work = nullptr, *mc_table = nullptr;
-    void *ctr = nullptr;
-    uint64_t *h_ctr = nullptr;   // pinned copy of the counters
+    uint64_t *bits = nullptr, *mc_table = nullptr;
+    uint32_t *chunk_tot = nullptr;
+    DenseCounters *ctr = nullptr;
+    HostCounters *h_ctr = nullptr;   // the last call's counters (pinned)
+    uint32_t h_seq = 0;
 };
 
 namespace {
+const DenseCounters &counters(const bcmc_dense *h) { return *reinterpret_cast<const DenseCounters *>(h->h_ctr->c); }
 void dense_destroy(bcmc_dense *h) {
     if (!h) return;
-    dev_free(h->ids);
-    dev_free(h->cases);
-    dev_free(h->first);
-    dev_free(h->work);
+    dev_free(h->bits);
+    dev_free(h->chunk_tot);
     dev_free(h->mc_table);
-    if (h->ctr) (void)hipFree(h->ctr);
+    dev_free(h->ctr);
     if (h->h_ctr) (void)hipHostFree(h->h_ctr);
     delete h;
 }
@@ -738,17 +737,14 @@ extern "C" int bcmc_dense_create(uint32_t nx, uint32_t ny, uint32_t nz, bcmc_den
     h->nx = nx;
     h->ny = ny;
     h->nz = nz;
-    const uint64_t cells = (uint64_t)(nx - 1) * (ny - 1) * (nz - 1);
     int rc;
-    if ((rc = dev_alloc(&h->ids, cells)) || (rc = dev_alloc(&h->cases, cells)) ||
-        (rc = dev_alloc(&h->first, cells)) ||
-        (rc = dev_alloc(&h->work, dense_work_words(nx, ny, nz))) ||
-        (rc = dev_alloc(&h->mc_table, 256))) {
+    if ((rc = dev_alloc(&h->bits, dense_sign_words(nx, ny, nz))) ||
+        (rc = dev_alloc(&h->chunk_tot, dense_chunk_words(nx, ny, nz))) ||
+        (rc = dev_alloc(&h->mc_table, 256)) || (rc = dev_alloc(&h->ctr, 1))) {
         dense_destroy(h);
         return rc;
     }
-    if (hipMalloc(&h->ctr, dense_counter_bytes()) != hipSuccess ||
-        hipHostMalloc((void **)&h->h_ctr, dense_counter_bytes(), hipHostMallocDefault) != hipSuccess ||
+    if (hipHostMalloc((void **)&h->h_ctr, sizeof(HostCounters), hipHostMallocDefault) != hipSuccess ||
         hipMemcpy(h->mc_table, mc_table_host(), 256 * sizeof(uint64_t), hipMemcpyHostToDevice) !=
             hipSuccess) {
         (void)hipGetLastError();
@@ -756,6 +752,7 @@ extern "C" int bcmc_dense_create(uint32_t nx, uint32_t ny, uint32_t nz, bcmc_den
         set_error("dense baseline set-up failed");
         return BCMC_E_NOMEM;
     }
+    memset(h->h_ctr, 0, sizeof(HostCounters));
     *out = h;
     return BCMC_OK;
 }
@@ -767,12 +764,11 @@ extern "C" int bcmc_dense_extract(bcmc_dense *h, const float *d_field, float iso
     if (!d_out && capacity_vertices) return invalid("null output buffer with nonzero capacity");
     if (iso != iso) return invalid("iso is NaN");
     hipStream_t s = as_stream(hip_stream);
-    launch_dense(h->nx, h->ny, h->nz, d_field, iso, h->ids, h->cases, h->first, h->work, h->ctr,
-                 h->mc_table, d_out, capacity_vertices, s);
+    launch_dense(h->nx, h->ny, h->nz, d_field, iso, h->bits, h->chunk_tot, h->ctr, h->mc_table, d_out,
+                 capacity_vertices, s);
     BCMC_HIP_TRY(hipGetLastError());
-    BCMC_HIP_TRY(hipMemcpyAsync(h->h_ctr, h->ctr, dense_counter_bytes(), hipMemcpyDeviceToHost, s));
-    BCMC_HIP_TRY(hipStreamSynchronize(s));
-    const uint64_t n_verts = h->h_ctr[3];   // counters: n_active at word 2, n_verts at word 3
+    if (int rc = await_counters(h->ctr, h->h_ctr, ++h->h_seq, s)) return rc;
+    const uint64_t n_verts = counters(h).n_verts;
     *n_triangles = n_verts / 3;
     if (n_verts > capacity_vertices) {
         set_error("vertex buffer too small: need " + std::to_string(n_verts) + " vertices");
@@ -783,7 +779,7 @@ extern "C" int bcmc_dense_extract(bcmc_dense *h, const float *d_field, float iso
 
 extern "C" int bcmc_dense_active_cells(const bcmc_dense *h, uint64_t *n_active) {
     if (!h || !n_active) return invalid("null argument");
-    *n_active = h->h_ctr[2];
+    *n_active = counters(h).n_active;
     return BCMC_OK;
 }
 

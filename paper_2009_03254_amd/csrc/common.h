@@ -158,17 +158,24 @@ void launch_backward(const Geom &g, const DevState &d, const float *slots, float
                      const float *gV, uint64_t n_verts, float *dfield, float *diso, int fmt,
                      hipStream_t s);
 // Writes the counters, then value as host->seq, when s gets there.
-void launch_publish(const Counters *ctr, HostCounters *host, uint32_t value, hipStream_t s);
+void launch_publish(const void *ctr, HostCounters *host, uint32_t value, hipStream_t s);
 void launch_fill_u32(uint32_t *p, uint32_t v, uint64_t n, hipStream_t s);
 void launch_copy_calibration(void *dst, const void *src, uint64_t n16, hipStream_t s);
 void launch_iota_i32(int32_t *p, uint64_t n, hipStream_t s);
 
 // ---- launchers (dense.hip): dense marching cubes baseline ---------------
-uint64_t dense_work_words(uint32_t nx, uint32_t ny, uint32_t nz);
-uint64_t dense_counter_bytes();
-void launch_dense(uint32_t nx, uint32_t ny, uint32_t nz, const float *field, float iso,
-                  uint32_t *ids, uint8_t *cases, uint64_t *first, uint64_t *work,
-                  void *ctr_mem, const uint64_t *mc_table, void *out, uint64_t cap, hipStream_t s);
+struct DenseCounters {
+    unsigned long long n_active, n_verts;
+    struct alignas(128) Xcd {   // per XCD eighth of the chunks, a cache line each
+        unsigned long long verts, cells;
+    } xcd[8];
+};
+static_assert(sizeof(DenseCounters) >= CTR_READ, "read back like an extract's counters");
+uint64_t dense_sign_words(uint32_t nx, uint32_t ny, uint32_t nz);
+uint64_t dense_chunk_words(uint32_t nx, uint32_t ny, uint32_t nz);
+void launch_dense(uint32_t nx, uint32_t ny, uint32_t nz, const float *field, float iso, uint64_t *bits,
+                  uint32_t *chunk_tot, DenseCounters *ctr, const uint64_t *mc_table, void *out, uint64_t cap,
+                  hipStream_t s);
 
 // ---- launchers (zfp.hip) -----------------------------------------------
 void launch_decode_ranges(const Geom &g, const uint64_t *stream, int is_f64, uint32_t rate,

@@ -1,290 +1,305 @@
 // Dense data-parallel marching cubes over an uncompressed field resident in
 // device memory: the standard GPU formulation the paper measures as its
-// baseline (Sec. 3.3.3, tab:mc_naive_parallel_perf).  Every cell of the
-// volume is classified, the cells that hold the surface are compacted by a
-// prefix sum, each of them gets its vertex count, a second prefix sum gives
-// the output offsets and the total, and a last pass over the compacted cells
-// writes the triangle soup.  No blocks, culling or cache: it measures what
-// the block-compressed path's culling buys.
+// baseline (Sec. 3.3.3, tab:mc_naive_parallel_perf): every cell of the volume
+// classified and counted, prefix sums over the counts, and a pass that writes
+// the soup of the cells that hold the surface.  No blocks, culling or cache:
+// it measures what the block-compressed path's culling buys.
 //
 // Records are the 16-byte vertices of the block path (block-relative float32
 // position + block id), computed with the same operations, so the soup is
 // the block path's soup with the cells in global row-major order (x fastest)
 // instead of block order.
 //
-// The two prefix sums run over tiles of 4096 cells: a pass classifies every
-// cell and counts each tile's cells with triangles and their vertices, one
-// workgroup scans the tile counts, and a pass over the stored cases writes
-// the compacted cells with their first vertex (the per-cell vertex counts
-// and the second prefix sum come with the first, so no pass of their own).
-// No same-address atomics: tiles are indexed by workgroup.
+// Cells are handled 64 at a time as bits of a word (a word: 64 cells of one
+// row, x fastest), in three launches.  k_dense_signs reads the field once and
+// keeps one bit per sample (below iso); k_dense_count gets the triangle counts
+// of 64 cells at once from the four rows' bits by the bit-sliced diagram of
+// the case table; k_dense_emit forms the words' bits again, lists their cells
+// and triangles in LDS and writes one vertex per lane.  Bound by memory: the
+// field read once for the signs and, where the surface lies, again for the
+// vertices, and the soup written.  512^3 turbulence at its median (14.5 M
+// triangles): 107 + 25 + 378 us, the signs at 5.0 TB/s (before, with each
+// cell's case and offset kept in memory: 985 for a classification whose lanes
+// read 64 bytes apart and 1433 for an emission whose lanes wrote 48 bytes
+// apart, 2.6 ms in all).  More waves (7 or 8 per SIMD, spilling) or two vertices
+// per lane in flight left the emission at 376-385 us.
 #include <stdint.h>
 
 #include <algorithm>
 
 #include "common.h"
 #include "mc_device.h"
+#include "mc_ntri.h"
 
 namespace bcmc {
 namespace {
 
-constexpr int DENSE_SEG = 16;   // cells per thread: a segment of one row of cells
-
-struct DenseCtr {
-    unsigned int unused[4];
-    unsigned long long n_active, n_verts;
-};
-
-// A row of cells is split into segments of DENSE_SEG cells; segment s covers
-// cells x in [16 k, min(16 k + 16, nx - 1)) of row r = s / segs_per_row
-// (r = y + (ny - 1) z), so the segments in order visit the cells in global
-// row-major order.  A tile is 256 segments.
 struct DenseGeom {
     uint32_t nx, ny, nz;
-    uint32_t segs_per_row;
-    uint64_t n_segs;      // segs_per_row * (ny - 1) * (nz - 1)
+    uint32_t swords;      // words per row of samples
+    uint32_t cwords;      // words per row of cells
+    uint32_t n_swords;    // swords * ny * nz (at most 2^32 - 1 samples)
+    uint32_t n_cwords;    // cwords * (ny - 1) * (nz - 1)
     uint32_t nbx, nby;    // blocks per row / per layer (for the block ids of the records)
 };
 
-// Segment s: first sample of its row, first cell x0, number of cells.
-__device__ __forceinline__ void dense_segment(const DenseGeom &g, uint64_t s, uint64_t &row_base, uint32_t &x0,
-                                              uint32_t &ncell) {
-    const uint32_t r = (uint32_t)(s / g.segs_per_row);
-    const uint32_t k = (uint32_t)(s - (uint64_t)r * g.segs_per_row);
-    const uint32_t y = r % (g.ny - 1), z = r / (g.ny - 1);
-    x0 = DENSE_SEG * k;
-    ncell = min((uint32_t)DENSE_SEG, g.nx - 1 - x0);
-    row_base = ((uint64_t)z * g.ny + y) * g.nx;
+// bits[row][w]: bit i = sample 64 w + i of the row is below iso (0 past its
+// end).  One lane per sample, 8 words in flight per wave.  Also clears the
+// counters of the passes that follow.
+__global__ __launch_bounds__(256) void k_dense_signs(DenseGeom g, const float *__restrict__ f, float iso,
+                                                    uint64_t *__restrict__ bits, DenseCounters *ctr) {
+    constexpr int J = 8;
+    if (blockIdx.x == 0)
+        for (unsigned i = threadIdx.x; i < sizeof(DenseCounters) / 4; i += 256) reinterpret_cast<uint32_t *>(ctr)[i] = 0;
+    const uint64_t waves = (uint64_t)gridDim.x * 4;
+    for (uint64_t w0 = ((uint64_t)blockIdx.x * 4 + wave_id()) * J; w0 < g.n_swords; w0 += waves * J) {
+        uint32_t row = (uint32_t)w0 / g.swords, wx = (uint32_t)w0 - row * g.swords;
+        float v[J];
+        bool in[J];
+#pragma unroll
+        for (int j = 0; j < J; j++) {
+            const uint32_t x = 64 * wx + (uint32_t)lane();
+            in[j] = w0 + j < g.n_swords && x < g.nx;
+            v[j] = in[j] ? f[(uint64_t)row * g.nx + x] : 0.0f;
+            if (++wx == g.swords) {
+                wx = 0;
+                row++;
+            }
+        }
+        uint64_t mine = 0;
+#pragma unroll
+        for (int j = 0; j < J; j++) {
+            const uint64_t b = __ballot(in[j] && v[j] < iso);
+            if (lane() == j) mine = b;
+        }
+        if (lane() < J && w0 + lane() < g.n_swords) bits[w0 + lane()] = mine;
+    }
 }
 
-// Pass 1: the cases of the segment's cells (stored as the segment's 16
-// bytes), and the tile's count of cells whose case is not 0 or 255 and of
-// their vertices (3 per triangle), as (vertices << 32 | cells).
-__global__ __launch_bounds__(256) void k_dense_classify(DenseGeom g, const float *__restrict__ f, float iso,
-                                                       const uint64_t *__restrict__ mc_table,
-                                                       uint4 *__restrict__ seg_cases,
-                                                       uint64_t *__restrict__ tile_cnt) {
-    __shared__ uint8_t s_ntri[256];
-    __shared__ uint64_t s_w[4];
-    s_ntri[threadIdx.x] = (uint8_t)(mc_table[threadIdx.x] >> 60);
-    __syncthreads();
-    const uint64_t s = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    uint32_t na = 0, nv = 0;
-    if (s < g.n_segs) {
-        uint64_t row_base;
-        uint32_t x0, ncell;
-        dense_segment(g, s, row_base, x0, ncell);
-        const uint64_t sy = g.nx, sz = (uint64_t)g.nx * g.ny;
-        // the four sample rows of the segment, DENSE_SEG + 1 samples each
-        float v[4][DENSE_SEG + 1];
+// Word i of the cells: the corner bits of its 64 cells (corner k at
+// +(k&1, k>>1&1, k>>2&1)), which of them are in the volume, and where it lies.
+struct CellWord {
+    uint64_t c[8], valid;
+    uint32_t x0, y, z;
+};
+__device__ __forceinline__ CellWord load_word(const DenseGeom &g, const uint64_t *__restrict__ bits, uint32_t i) {
+    CellWord q;
+    const uint32_t r = i / g.cwords, wx = i - r * g.cwords;
+    q.y = r % (g.ny - 1);
+    q.z = r / (g.ny - 1);
+    q.x0 = 64 * wx;
+    const bool more = wx + 1 < g.swords;
+    uint64_t a[4], b[4];
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            const float *p = f + row_base + x0 + (q & 1) * sy + (q >> 1) * sz;
-#pragma unroll
-            for (int j = 0; j <= DENSE_SEG; j++) v[q][j] = j <= (int)ncell ? p[j] : 0.0f;
-        }
-        uint32_t cw[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int j = 0; j < DENSE_SEG; j++) {
-            uint32_t c = 0;
-#pragma unroll
-            for (int kk = 0; kk < 8; kk++)
-                c |= (v[((kk >> 1) & 1) | ((kk >> 2) << 1)][j + (kk & 1)] < iso ? 1u : 0u) << kk;
-            cw[j >> 2] |= c << (8 * (j & 3));
-            if (j < (int)ncell && c != 0u && c != 255u) {
-                na++;
-                nv += 3u * s_ntri[c];
-            }
-        }
-        seg_cases[s] = make_uint4(cw[0], cw[1], cw[2], cw[3]);
+    for (int k = 0; k < 4; k++) {
+        const uint64_t at = ((uint64_t)(q.z + (k >> 1)) * g.ny + q.y + (k & 1)) * g.swords + wx;
+        a[k] = bits[at];
+        b[k] = more ? bits[at + 1] : 0ull;
     }
-    uint64_t x = wave_sum(((uint64_t)nv << 32) | na);
-    if (lane() == 0) s_w[threadIdx.x >> 6] = x;
-    __syncthreads();
-    if (threadIdx.x == 0) tile_cnt[blockIdx.x] = s_w[0] + s_w[1] + s_w[2] + s_w[3];
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        q.c[2 * k] = a[k];
+        q.c[2 * k + 1] = a[k] >> 1 | b[k] << 63;
+    }
+    const uint32_t n = min(64u, g.nx - 1 - q.x0);
+    q.valid = n == 64 ? ~0ull : (1ull << n) - 1;
+    return q;
 }
 
-// Pass 2 (one workgroup): exclusive prefix of the tiles' counts, tile_off[2t]
-// = cells before tile t, tile_off[2t + 1] = vertices before it; the totals.
-__global__ __launch_bounds__(256) void k_dense_scan(const uint64_t *__restrict__ tile_cnt, uint64_t n_tiles,
-                                                   uint64_t *__restrict__ tile_off, DenseCtr *ctr) {
-    __shared__ uint64_t s_a[4], s_v[4];
-    const int w = threadIdx.x >> 6;
-    uint64_t ca = 0, cv = 0;   // carries
-    for (uint64_t c0 = 0; c0 < n_tiles; c0 += 4096) {
-        const uint64_t i0 = c0 + 16u * threadIdx.x;
-        uint64_t t[16], sa = 0, sv = 0;
-#pragma unroll
-        for (int j = 0; j < 16; j++) {
-            t[j] = i0 + j < n_tiles ? tile_cnt[i0 + j] : 0ull;
-            sa += t[j] & 0xFFFFFFFFull;
-            sv += t[j] >> 32;
+// Vertices of the word's cells; act: the cells that have triangles.
+__device__ __forceinline__ uint32_t count_word(const CellWord &q, uint64_t &act) {
+    uint64_t n0, n1, n2;
+    mc_ntri_bits(q.c, n0, n1, n2);
+    n0 &= q.valid;
+    n1 &= q.valid;
+    n2 &= q.valid;
+    act = n0 | n1 | n2;
+    return 3u * ((uint32_t)__popcll(n0) + 2u * (uint32_t)__popcll(n1) + 4u * (uint32_t)__popcll(n2));
+}
+
+// Vertices per chunk of words (the emission's chunks: xcd_chunks), and the
+// vertices and active cells of each XCD eighth of them.
+__global__ __launch_bounds__(256) void k_dense_count(DenseGeom g, const uint64_t *__restrict__ bits,
+                                                    uint32_t cs, uint32_t *__restrict__ chunk_tot,
+                                                    DenseCounters *ctr) {
+    __shared__ uint64_t s_v[MC_WAVES], s_a[MC_WAVES];
+    const ChunkRange cr = xcd_chunks((g.n_cwords + (uint64_t)cs - 1) / cs);
+    uint64_t verts = 0, cells = 0;
+    for (uint64_t c = cr.first; c < cr.end; c += cr.stride) {
+        const uint64_t i = c * cs + lane();
+        uint32_t n = 0;
+        if (lane() < (int)cs && i < g.n_cwords) {
+            uint64_t act;
+            n = count_word(load_word(g, bits, (uint32_t)i), act);
+            cells += (uint64_t)__popcll(act);
         }
-        const uint64_t ia = wave_incl_scan(sa), iv = wave_incl_scan(sv);
-        if (lane() == 63) {
-            s_a[w] = ia;
-            s_v[w] = iv;
-        }
-        __syncthreads();
-        uint64_t oa = ca + ia - sa, ov = cv + iv - sv, ta = 0, tv = 0;
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            if (i < w) {
-                oa += s_a[i];
-                ov += s_v[i];
-            }
-            ta += s_a[i];
-            tv += s_v[i];
-        }
-#pragma unroll
-        for (int j = 0; j < 16; j++) {
-            if (i0 + j < n_tiles) {
-                tile_off[2 * (i0 + j)] = oa;
-                tile_off[2 * (i0 + j) + 1] = ov;
-            }
-            oa += t[j] & 0xFFFFFFFFull;
-            ov += t[j] >> 32;
-        }
-        ca += ta;
-        cv += tv;
-        __syncthreads();   // s_a / s_v are rewritten by the next step
+        n = wave_sum(n);
+        if (lane() == 0) chunk_tot[c] = n;
+        verts += n;
     }
+    cells = wave_sum(cells);
+    if (lane() == 0) {
+        s_v[wave_id()] = verts;
+        s_a[wave_id()] = cells;
+    }
+    __syncthreads();
     if (threadIdx.x == 0) {
-        ctr->n_active = ca;
-        ctr->n_verts = cv;
-    }
-}
-
-// Pass 3: the cells with triangles, in order: id (index of the cell's lowest
-// sample), case, first vertex (the tile's offsets plus a workgroup scan).
-__global__ __launch_bounds__(256) void k_dense_compact(DenseGeom g, const uint4 *__restrict__ seg_cases,
-                                                      const uint64_t *__restrict__ tile_off,
-                                                      const uint64_t *__restrict__ mc_table,
-                                                      uint32_t *__restrict__ ids, uint8_t *__restrict__ cases,
-                                                      uint64_t *__restrict__ first) {
-    __shared__ uint8_t s_ntri[256];
-    __shared__ uint32_t s_w[4];
-    s_ntri[threadIdx.x] = (uint8_t)(mc_table[threadIdx.x] >> 60);
-    __syncthreads();
-    const uint64_t s = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    uint32_t cw[4] = {0u, 0u, 0u, 0u}, act = 0, x0 = 0, ncell = 0;
-    uint64_t row_base = 0;
-    uint32_t na = 0, nv = 0;
-    if (s < g.n_segs) {
-        dense_segment(g, s, row_base, x0, ncell);
-        const uint4 q = seg_cases[s];
-        cw[0] = q.x; cw[1] = q.y; cw[2] = q.z; cw[3] = q.w;
-#pragma unroll
-        for (int j = 0; j < DENSE_SEG; j++) {
-            const uint32_t c = (cw[j >> 2] >> (8 * (j & 3))) & 0xFFu;
-            if (j < (int)ncell && c != 0u && c != 255u) {
-                act |= 1u << j;
-                na++;
-                nv += 3u * s_ntri[c];
-            }
+        for (int k = 1; k < MC_WAVES; k++) {
+            verts += s_v[k];
+            cells += s_a[k];
+        }
+        if (cells) {
+            atomicAdd(&ctr->xcd[blockIdx.x % 8u].verts, (unsigned long long)verts);
+            atomicAdd(&ctr->xcd[blockIdx.x % 8u].cells, (unsigned long long)cells);
         }
     }
-    // per thread na <= 16, nv <= 240; per workgroup na < 2^13, nv < 2^16
-    const uint32_t packed = na | (nv << 13);
-    const uint32_t incl = wave_incl_scan(packed);
-    if (lane() == 63) s_w[threadIdx.x >> 6] = incl;
-    __syncthreads();
-    uint32_t ex = incl - packed;
-#pragma unroll
-    for (int i = 0; i < 4; i++)
-        if (i < (int)(threadIdx.x >> 6)) ex += s_w[i];
-    uint64_t o = tile_off[2 * (uint64_t)blockIdx.x] + (ex & 0x1FFFu);
-    uint64_t ov = tile_off[2 * (uint64_t)blockIdx.x + 1] + (ex >> 13);
-    for (uint32_t m = act; m; m &= m - 1) {
-        const int j = __builtin_ctz(m);
-        const uint32_t c = (cw[j >> 2] >> (8 * (j & 3))) & 0xFFu;
-        ids[o] = (uint32_t)(row_base + x0 + (uint32_t)j);
-        cases[o] = (uint8_t)c;
-        first[o] = ov;
-        o++;
-        ov += 3u * s_ntri[c];
-    }
 }
 
-// Pass 4: one thread per compacted cell writes its triangles' vertices from
-// its first vertex on (records past cap dropped).
-__global__ __launch_bounds__(256) void k_dense_emit(DenseGeom g, const float *__restrict__ f, float iso,
-                                                   const uint32_t *__restrict__ ids,
-                                                   const uint8_t *__restrict__ cases,
-                                                   const uint64_t *__restrict__ first,
+// Per-wave LDS of the emission: up to 64 active cells and their triangles.
+struct DenseShared {
+    uint64_t tab[256];                // the case table
+    uint2 edge[12];                   // per edge: sample offsets of its two corners from the cell's lowest
+    uint32_t egeo[12];                // first corner as bytes x | y << 8 | z << 16, axis in byte 3
+    uint32_t at[MC_WAVES][64];        // per cell: index of its lowest sample
+    uint32_t geo[MC_WAVES][64];       // its place in its block as bytes x | y << 8 | z << 16, case in byte 3
+    uint32_t blk[MC_WAVES][64];       // its block
+    uint32_t tri[MC_WAVES][64 * 5];   // per triangle: cell | 3 edge ids << 20
+};
+
+__global__ __launch_bounds__(256, 6) void k_dense_emit(DenseGeom g, const float *__restrict__ f, float iso,
+                                                   const uint64_t *__restrict__ bits, uint32_t cs,
+                                                   const uint32_t *__restrict__ chunk_tot,
                                                    const uint64_t *__restrict__ mc_table,
-                                                   void *__restrict__ out, uint64_t cap,
-                                                   const DenseCtr *ctr) {
-    __shared__ uint64_t s_tab[256];
-    for (int i = threadIdx.x; i < 256; i += 256) s_tab[i] = mc_table[i];
+                                                   void *__restrict__ out, uint64_t cap, DenseCounters *ctr) {
+    __shared__ DenseShared sh;
+    sh.tab[threadIdx.x] = mc_table[threadIdx.x];
+    if (threadIdx.x < 12) {
+        const uint32_t d = (uint32_t)(kEdgeGeom >> (5 * threadIdx.x)) & 31u;   // ox | oy << 1 | oz << 2 | axis << 3
+        const uint32_t ox = d & 1u, oy = (d >> 1) & 1u, oz = (d >> 2) & 1u, axis = d >> 3;
+        const uint32_t d0 = ox + g.nx * (oy + g.ny * oz);
+        sh.edge[threadIdx.x] = make_uint2(d0, d0 + (axis == 0 ? 1u : (axis == 1 ? g.nx : g.nx * g.ny)));
+        sh.egeo[threadIdx.x] = ox | oy << 8 | oz << 16 | axis << 24;
+    }
     __syncthreads();
-    const uint64_t n = ctr->n_active;
-    const uint64_t sy = g.nx, sz = (uint64_t)g.nx * g.ny;
-    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n;
-         i += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t id = ids[i];
-        const uint32_t x = id % g.nx, r = id / g.nx, y = r % g.ny, z = r / g.ny;
-        float v[8];
-#pragma unroll
-        for (int k = 0; k < 8; k++)
-            v[k] = f[id + (k & 1) + ((k >> 1) & 1) * sy + (k >> 2) * sz];
-        const uint64_t tb = s_tab[cases[i]];
-        const int nv = 3 * (int)(tb >> 60);
-        const uint32_t b = (x >> 2) + g.nbx * ((y >> 2) + g.nby * (z >> 2));
-        const int cx = (int)(x & 3), cy = (int)(y & 3), cz = (int)(z & 3);
-        uint64_t o = first[i];
-        for (int j = 0; j < nv; j++, o++) {
-            const int e = (int)((tb >> (4 * j)) & 15u);
-            const uint32_t d = (uint32_t)(kEdgeGeom >> (5 * e)) & 31u;
-            const int axis = (int)(d >> 3);
-            const int k0 = (int)(d & 7u);            // first corner (ox | oy << 1 | oz << 2)
-            const int k1 = k0 | (1 << axis);
-            const float a = v[k0], bv = v[k1];
-            const float tt = (iso - a) / (bv - a);
-            const float px = (float)(cx + (int)(d & 1u)) + (axis == 0 ? tt : 0.0f);
-            const float py = (float)(cy + (int)((d >> 1) & 1u)) + (axis == 1 ? tt : 0.0f);
-            const float pz = (float)(cz + (int)((d >> 2) & 1u)) + (axis == 2 ? tt : 0.0f);
-            if (o < cap) store_record(out, o, px, py, pz, b);
+    const int w = (int)wave_id(), l = lane();
+    const ChunkRange cr = xcd_chunks((g.n_cwords + (uint64_t)cs - 1) / cs);
+    uint64_t base = 0, all = 0, cells = 0;
+    for (uint32_t x = 0; x < 8; x++) {
+        const uint64_t tx = ctr->xcd[x].verts;
+        base += x < blockIdx.x % 8u ? tx : 0ull;
+        all += tx;
+        cells += ctr->xcd[x].cells;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        ctr->n_verts = all;
+        ctr->n_active = cells;
+    }
+    base = uniform64(base);
+    if (cr.first < cr.end) base += chunks_sum(chunk_tot, cr.lo, cr.first);
+    for (uint64_t c = cr.first; c < cr.end; c += cr.stride) {
+        const uint64_t i = c * cs + l;
+        CellWord q;
+        uint64_t act = 0;
+        uint32_t n = 0;
+        if (l < (int)cs && i < g.n_cwords) {
+            q = load_word(g, bits, (uint32_t)i);
+            n = count_word(q, act);
         }
+        const uint32_t na = (uint32_t)__popcll(act);
+        const uint32_t incl = wave_incl_scan(na), vincl = wave_incl_scan(n);
+        const uint32_t total = bcast(incl, 63);
+        // the words in order, as many at a time as have 64 active cells
+        for (uint32_t done = 0; done < total;) {
+            const bool in = na && incl - na >= done && incl <= done + 64;
+            const uint64_t m = __ballot(in);
+            const int first = (int)__builtin_ctzll(m), last = 63 - (int)__builtin_clzll(m);
+            const uint32_t ncell = bcast(incl, last) - done;
+            const uint64_t o0 = base + bcast(vincl - n, first);
+            if (in) {
+                uint32_t slot = incl - na - done;
+                const uint32_t row = (q.z * g.ny + q.y) * g.nx + q.x0;
+                const uint32_t brow = (q.x0 >> 2) + g.nbx * ((q.y >> 2) + g.nby * (q.z >> 2));
+                const uint32_t geo = (q.y & 3u) << 8 | (q.z & 3u) << 16;
+                for (uint64_t a = act; a; a &= a - 1, slot++) {
+                    const uint32_t x = (uint32_t)__builtin_ctzll(a);
+                    uint32_t cse = 0;
+#pragma unroll
+                    for (int k = 0; k < 8; k++) cse |= (uint32_t)(q.c[k] >> x & 1u) << k;
+                    sh.at[w][slot] = row + x;
+                    sh.geo[w][slot] = geo | (x & 3u) | cse << 24;
+                    sh.blk[w][slot] = brow + (x >> 2);
+                }
+            }
+            wave_lds_sync();
+            const uint64_t tb = l < (int)ncell ? sh.tab[sh.geo[w][l] >> 24] : 0ull;
+            const uint32_t nt = (uint32_t)(tb >> 60);
+            const uint32_t tincl = wave_incl_scan(nt);
+            const int nv = 3 * (int)bcast(tincl, 63);
+            for (uint32_t t = 0; t < nt; t++)
+                sh.tri[w][tincl - nt + t] = (uint32_t)l | (uint32_t)(tb >> (12 * t)) << 20;
+            wave_lds_sync();
+            for (int j = l; j < nv; j += 64) {
+                const int t = (j * 43691) >> 17;   // j / 3 for j < 960
+                const uint32_t rec = sh.tri[w][t];
+                const uint32_t e = (rec >> (20 + 4 * (j - 3 * t))) & 15u, k = rec & 63u;
+                const uint2 d = sh.edge[e];
+                const uint32_t at = sh.at[w][k];
+                const float a = f[at + d.x], bv = f[at + d.y];
+                const uint32_t eg = sh.egeo[e], axis = eg >> 24;
+                const uint32_t p = (sh.geo[w][k] & 0x030303u) + (eg & 0x010101u);   // the edge's first corner
+                const float tt = (iso - a) / (bv - a);
+                const float px = (float)(p & 0xFFu) + (axis == 0 ? tt : 0.0f);
+                const float py = (float)((p >> 8) & 0xFFu) + (axis == 1 ? tt : 0.0f);
+                const float pz = (float)(p >> 16) + (axis == 2 ? tt : 0.0f);
+                const uint64_t o = o0 + (uint64_t)j;
+                if (o < cap) store_record(out, o, px, py, pz, sh.blk[w][k]);
+            }
+            wave_lds_sync();   // the lists are rewritten next
+            done += ncell;
+        }
+        if (c + cr.stride < cr.end) base += chunks_sum(chunk_tot, c, c + cr.stride);
     }
 }
 
-}  // namespace
-
-// 64-bit words of work memory: the segments' cases (2 words each), the
-// tiles' counts (1) and offsets (2).
-uint64_t dense_work_words(uint32_t nx, uint32_t ny, uint32_t nz) {
-    const uint64_t segs = (uint64_t)((nx - 2) / DENSE_SEG + 1) * (ny - 1) * (nz - 1);
-    const uint64_t tiles = (segs + 255) / 256;
-    return 2 * segs + 3 * tiles;
-}
-
-uint64_t dense_counter_bytes() { return sizeof(DenseCtr); }
-
-// ids, cases, first: per cell of the volume at most; work: see above;
-// ctr: dense_counter_bytes().  The counters' n_active and n_verts (u64 at
-// byte offsets 16 and 24) are valid when the stream reaches the end.
-void launch_dense(uint32_t nx, uint32_t ny, uint32_t nz, const float *field, float iso,
-                  uint32_t *ids, uint8_t *cases, uint64_t *first, uint64_t *work,
-                  void *ctr_mem, const uint64_t *mc_table, void *out, uint64_t cap, hipStream_t s) {
+DenseGeom dense_geom(uint32_t nx, uint32_t ny, uint32_t nz) {
     DenseGeom g;
     g.nx = nx;
     g.ny = ny;
     g.nz = nz;
-    g.segs_per_row = (nx - 2) / DENSE_SEG + 1;
-    g.n_segs = (uint64_t)g.segs_per_row * (ny - 1) * (nz - 1);
+    g.swords = (nx + 63) / 64;
+    g.cwords = (nx - 2) / 64 + 1;
+    g.n_swords = g.swords * ny * nz;
+    g.n_cwords = g.cwords * (ny - 1) * (nz - 1);
     g.nbx = (nx + 3) / 4;
     g.nby = (ny + 3) / 4;
-    DenseCtr *ctr = reinterpret_cast<DenseCtr *>(ctr_mem);
-    const uint64_t tiles = (g.n_segs + 255) / 256;
-    uint4 *seg_cases = reinterpret_cast<uint4 *>(work);
-    uint64_t *tile_cnt = work + 2 * g.n_segs, *tile_off = tile_cnt + tiles;
-    k_dense_classify<<<(unsigned)tiles, 256, 0, s>>>(g, field, iso, mc_table, seg_cases, tile_cnt);
-    k_dense_scan<<<1, 256, 0, s>>>(tile_cnt, tiles, tile_off, ctr);
-    k_dense_compact<<<(unsigned)tiles, 256, 0, s>>>(g, seg_cases, tile_off, mc_table, ids, cases, first);
-    const uint64_t cells = (uint64_t)(nx - 1) * (ny - 1) * (nz - 1);
-    k_dense_emit<<<(unsigned)std::min<uint64_t>((cells + 255) / 256, 8192), 256, 0, s>>>(
-        g, field, iso, ids, cases, first, mc_table, out, cap, ctr);
+    return g;
+}
+
+}  // namespace
+
+uint64_t dense_sign_words(uint32_t nx, uint32_t ny, uint32_t nz) { return dense_geom(nx, ny, nz).n_swords; }
+
+uint64_t dense_chunk_words(uint32_t nx, uint32_t ny, uint32_t nz) {
+    return mc_chunk_slots(dense_geom(nx, ny, nz).n_cwords);
+}
+
+// bits: dense_sign_words, chunk_tot: dense_chunk_words entries; ctr holds the
+// call's n_active and n_verts when the stream reaches the end.
+void launch_dense(uint32_t nx, uint32_t ny, uint32_t nz, const float *field, float iso, uint64_t *bits,
+                  uint32_t *chunk_tot, DenseCounters *ctr, const uint64_t *mc_table, void *out, uint64_t cap,
+                  hipStream_t s) {
+    const DenseGeom g = dense_geom(nx, ny, nz);
+    static unsigned sgrid = 0, cgrid = 0, egrid = 0;
+    if (!sgrid) sgrid = resident_grid(k_dense_signs);
+    if (!cgrid) cgrid = resident_grid(k_dense_count);
+    if (!egrid) egrid = std::min<unsigned>(resident_grid(k_dense_emit), MC_MAX_GRID);
+    const unsigned words = (unsigned)std::min<uint64_t>(((uint64_t)g.n_swords + 31) / 32, 1u << 20);
+    const unsigned need = ((unsigned)std::min<uint64_t>(g.n_cwords, 4u * MC_MAX_GRID) + 3) / 4;
+    const unsigned eg = std::min(egrid, (need + 7) / 8 * 8), cg = std::min(cgrid, (need + 7) / 8 * 8);
+    const uint32_t cs = mc_chunk_size(g.n_cwords, eg * MC_WAVES);
+    k_dense_signs<<<std::min(words, sgrid), 256, 0, s>>>(g, field, iso, bits, ctr);
+    k_dense_count<<<cg, 256, 0, s>>>(g, bits, cs, chunk_tot, ctr);
+    k_dense_emit<<<eg, 256, 0, s>>>(g, field, iso, bits, cs, chunk_tot, mc_table, out, cap, ctr);
 }
 
 }  // namespace bcmc

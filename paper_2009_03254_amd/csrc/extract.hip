@@ -884,14 +884,6 @@ __global__ __launch_bounds__(256) void k_mc_count(Geom g, const uint32_t *__rest
     }
 }
 
-// The vertices of the chunks [a, b), summed by the calling wave.
-__device__ __forceinline__ uint32_t chunks_sum(const uint32_t *__restrict__ chunk_tot, uint64_t a, uint64_t b) {
-    uint32_t v = 0;
-#pragma unroll 4
-    for (uint64_t i = a + lane(); i < b; i += 64) v += chunk_tot[i];
-    return __builtin_amdgcn_readfirstlane(wave_sum(v));
-}
-
 // Emission pass (Sec. 4.5), over the chunks of xcd_chunks (the count pass's
 // schedule).  A wave's first chunk follows the eighths before its own and the
 // chunks of its eighth before it (fewer than the eighth's waves: 3.5 KB of
@@ -1059,9 +1051,9 @@ __global__ __launch_bounds__(256) void k_debug_cases(Geom g, const uint32_t *__r
 // The call's counters to the host's copy (pinned memory), then the call's
 // number behind them: the host polls it.  As a kernel of its own it starts when
 // the emission has ended, so the number means that the soup is whole.
-__global__ __launch_bounds__(64) void k_publish(const Counters *ctr, uint32_t *__restrict__ host, uint32_t *seq,
-                                               uint32_t value) {
-    if (threadIdx.x < CTR_READ / 4) host[threadIdx.x] = reinterpret_cast<const uint32_t *>(ctr)[threadIdx.x];
+__global__ __launch_bounds__(64) void k_publish(const uint32_t *__restrict__ ctr, uint32_t *__restrict__ host,
+                                               uint32_t *seq, uint32_t value) {
+    if (threadIdx.x < CTR_READ / 4) host[threadIdx.x] = ctr[threadIdx.x];
     __threadfence_system();
     __syncthreads();
     if (threadIdx.x == 0) __hip_atomic_store(seq, value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -1096,26 +1088,6 @@ unsigned grid_cap(uint64_t n_threads, unsigned cap) {
 
 }  // namespace
 
-// Workgroups of a persistent kernel that are all resident at once (the
-// static per-wave shares assume no second round), in whole XCD rounds.
-template <typename K>
-static unsigned resident_grid(K kernel, uint64_t max_blocks) {
-    static int cus = 0;
-    if (!cus) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-            cus = 256;
-    }
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 256, 0) != hipSuccess || per_cu < 1)
-        per_cu = 1;
-    uint64_t g = (uint64_t)per_cu * cus;
-    uint64_t need = (max_blocks + MC_WAVES - 1) / MC_WAVES;
-    if (need < g) g = need;
-    g = g / 8 * 8;
-    return (unsigned)(g < 8 ? 8 : g);
-}
 static unsigned mc_grid(uint64_t max_blocks) {
     uint64_t g = (max_blocks + MC_WAVES - 1) / MC_WAVES;
     g = g < MC_MAX_GRID ? g : MC_MAX_GRID;
@@ -1133,7 +1105,7 @@ void launch_cull(const Geom &g, const DevState &d, float iso, float prev_iso, in
         return;
     }
     static unsigned rgrid = 0;
-    if (!rgrid) rgrid = resident_grid(k_cull<true, CULL_TZ>, ~0ull >> 4);
+    if (!rgrid) rgrid = resident_grid(k_cull<true, CULL_TZ>);
     k_cull_scan<<<(unsigned)((nt + 255) / 256), 256, 0, s>>>(d.tile_ranges, nt, iso, prev_iso, rewrite,
                                                              d.cull_list, d.ctr);
     k_cull<true, CULL_TZ><<<(unsigned)std::min<uint64_t>(nt, rgrid), 256, 0, s>>>(
@@ -1182,7 +1154,7 @@ void launch_compact_blocks(const Geom &g, const DevState &d, const SlotState &ss
         return;
     }
     static unsigned wgrid = 0;
-    if (!wgrid) wgrid = resident_grid(k_compact_blocks<true>, ~0ull >> 4);
+    if (!wgrid) wgrid = resident_grid(k_compact_blocks<true>);
     k_round_sums<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(d.round_cnt, n, d.round_sums, d.round_next);
     k_compact_blocks<true><<<(unsigned)std::min<uint64_t>(n, wgrid), 256, 0, s>>>(
         g, d.active, d.round_cnt, n, d.round_sums, d.round_next, d.I_active, d.I_new, d.ctr, d.ctr_next, ss, ev,
@@ -1213,9 +1185,9 @@ void launch_cache_empty(const DevState &d, uint64_t n_used, hipStream_t s) {
 // rounds.  Its wave count also sets the chunk size (mc_chunk_size).
 static unsigned emit_grid(const Geom &g, int fmt) {
     static unsigned grid[3] = {0, 0, 0};
-    if (!grid[0]) grid[0] = resident_grid(k_mc_emit<VFMT_F32>, ~0ull >> 4);
-    if (!grid[1]) grid[1] = resident_grid(k_mc_emit<VFMT_EDGE8>, ~0ull >> 4);
-    if (!grid[2]) grid[2] = resident_grid(k_mc_emit<VFMT_Q10>, ~0ull >> 4);
+    if (!grid[0]) grid[0] = resident_grid(k_mc_emit<VFMT_F32>);
+    if (!grid[1]) grid[1] = resident_grid(k_mc_emit<VFMT_EDGE8>);
+    if (!grid[2]) grid[2] = resident_grid(k_mc_emit<VFMT_Q10>);
     return std::min<unsigned>(grid[fmt >= 0 && fmt < 3 ? fmt : 0], mc_grid(g.nb));
 }
 
@@ -1223,14 +1195,14 @@ void launch_mc_count(const Geom &g, const DevState &d, const float *slots, const
                      int identity_cache, float iso, int fmt, hipStream_t s) {
     if (identity_cache) {
         static unsigned mgrid = 0;
-        if (!mgrid) mgrid = resident_grid(k_masks, ~0ull >> 4);
+        if (!mgrid) mgrid = resident_grid(k_masks);
         k_masks<<<std::min<unsigned>(mgrid, mc_grid(g.nb / 16 + 1)), 256, 0, s>>>(d.I_active, slots, iso, d.masks,
                                                                                  d.ctr);
     }
     // the count pass takes the emission's chunks on a grid of its own (all
     // of it resident)
     static unsigned cres = 0;
-    if (!cres) cres = std::min<unsigned>(resident_grid(k_mc_count, ~0ull >> 4), MC_MAX_GRID);
+    if (!cres) cres = std::min<unsigned>(resident_grid(k_mc_count), MC_MAX_GRID);
     const unsigned egrid = emit_grid(g, fmt), cgrid = std::min<unsigned>(cres, mc_grid(g.nb));
     k_mc_count<<<cgrid, 256, 0, s>>>(g, d.I_active, d.active, I_slot, identity_cache, d.masks,
                                      d.blk_cnt, d.chunk_tot, egrid * MC_WAVES, d.ctr);
@@ -1284,7 +1256,7 @@ void launch_backward(const Geom &g, const DevState &d, const float *slots, float
                      const float *gV, uint64_t n_verts, float *dfield, float *diso, int fmt,
                      hipStream_t s) {
     static unsigned grid = 0;
-    if (!grid) grid = resident_grid(k_mc_emit<VFMT_GRAD>, ~0ull >> 4);
+    if (!grid) grid = resident_grid(k_mc_emit<VFMT_GRAD>);
     const unsigned n = std::min<unsigned>(grid, mc_grid(g.nb));
     k_mc_emit<VFMT_GRAD><<<n, 256, 0, s>>>(g, d.I_active, nullptr, 1, slots, d.mc_table, iso, d.blk_cnt,
                                           d.blk_off, nullptr, n_verts, d.chunk_tot,
@@ -1297,9 +1269,10 @@ void launch_copy_calibration(void *dst, const void *src, uint64_t n16, hipStream
         reinterpret_cast<uint4 *>(dst), reinterpret_cast<const uint4 *>(src), n16);
 }
 
-void launch_publish(const Counters *ctr, HostCounters *host, uint32_t value, hipStream_t s) {
+void launch_publish(const void *ctr, HostCounters *host, uint32_t value, hipStream_t s) {
     static_assert(CTR_READ / 4 <= 64, "one lane per word");
-    k_publish<<<1, 64, 0, s>>>(ctr, reinterpret_cast<uint32_t *>(host->c), &host->seq, value);
+    k_publish<<<1, 64, 0, s>>>(reinterpret_cast<const uint32_t *>(ctr), reinterpret_cast<uint32_t *>(host->c),
+                               &host->seq, value);
 }
 
 void launch_fill_u32(uint32_t *p, uint32_t v, uint64_t n, hipStream_t s) {

@@ -311,6 +311,32 @@ __device__ __forceinline__ ChunkRange xcd_chunks(uint64_t n_chunks) {
     return {lo, lo + r, hi, per_xcd};
 }
 
+// The vertices of the chunks [a, b), summed by the calling wave.
+__device__ __forceinline__ uint32_t chunks_sum(const uint32_t *__restrict__ chunk_tot, uint64_t a, uint64_t b) {
+    uint32_t v = 0;
+#pragma unroll 4
+    for (uint64_t i = a + lane(); i < b; i += 64) v += chunk_tot[i];
+    return __builtin_amdgcn_readfirstlane(wave_sum(v));
+}
+
+// Workgroups of a persistent kernel of 256 threads that are all resident at
+// once (the static shares assume no second round), in whole XCD rounds.
+template <typename K>
+unsigned resident_grid(K kernel) {
+    static int cus = 0;
+    if (!cus) {
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+            cus = 256;
+    }
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 256, 0) != hipSuccess || per_cu < 1)
+        per_cu = 1;
+    const unsigned g = (unsigned)per_cu * cus / 8 * 8;
+    return g < 8 ? 8 : g;
+}
+
 // Corner masks of the 64 cells of a block from the sign masks of the block
 // and its 7 positive neighbours (M[dx | dy<<1 | dz<<2]): bit i of c[k] is the
 // sign bit of corner k = (k&1, k>>1&1, k>>2&1) of cell i.  sx / sy / sz give,
