@@ -517,6 +517,7 @@ int bcmc_extract(bcmc_volume *v, float iso, void *d_out, uint64_t capacity_verti
     st.alg_bytes = 8.0 * v->g.nb + (double)st.n_new * (8.0 * v->rate + 256.0) +
                    256.0 * (double)c.n_act + 24.0 * (double)T;
     for (int i = 0; i < 8; i++) st.stage_ms[i] = 0.0;
+    if (prof) BCMC_HIP_TRY(hipStreamSynchronize(s));   // the polled counters do not wait for the events
     for (int i = 0; i < 6; i++) {
         if (!((prof >> i) & 1u)) continue;
         float ms = 0;
