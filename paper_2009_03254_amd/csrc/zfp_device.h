@@ -672,92 +672,149 @@ __host__ __device__ inline unsigned stage_lds_bytes(int rate, bool f64) {
     return b <= STAGE_MAX_LDS ? b : 0u;
 }
 
-// ---- bit writer ------------------------------------------------------------
+// ---- encoder -----------------------------------------------------------------
+// Bits of one block, LSB first, into `rate` words at st[w * STRIDE]; what
+// comes after the last word is dropped: a block's code is the beginning of an
+// unbounded one, so the coder needs no budget.
+template <int STRIDE>
 struct BitWriter {
-    uint64_t *__restrict__ out;
+    uint64_t *__restrict__ st;
+    int rate, wi, na;      // words written, bits in acc
     uint64_t acc;
-    int na;
-    __device__ __forceinline__ void put(uint64_t v, int n) {  // v < 2^n, n <= 64
-        if (n == 0) return;
-        acc |= (na >= 64) ? 0 : (v << na);
-        if (na + n >= 64) {
-            *out++ = acc;
-            int used = 64 - na;
-            acc = (used >= 64) ? 0 : (v >> used);
-            na = na + n - 64;
-        } else {
-            na += n;
+    __device__ __forceinline__ bool open() const { return wi < rate; }
+    __device__ __forceinline__ void put(uint64_t v, int n) {   // v < 2^n, 1 <= n <= 64
+        acc |= v << na;
+        const int t = na + n;
+        if (t >= 64) {
+            if (wi < rate) st[wi * STRIDE] = acc;
+            wi++;
+            acc = (v >> 1) >> (63 - na);
         }
+        na = t & 63;
+    }
+    __device__ __forceinline__ void finish() {
+        if (wi < rate) st[wi * STRIDE] = acc;
+        for (int w = wi + 1; w < rate; w++) st[w * STRIDE] = 0;
     }
 };
 
-template <bool F64>
-__device__ __forceinline__ bool encode_block(const double *x, int rate, uint64_t *out) {
-    using T = Prec<F64>;
-    using UInt = typename T::UInt;
-    using Int = typename T::Int;
-    const int words = rate;
-    bool any = false, finite = true;
-    int emax = 0;
+// Embedded coding of 32 bit planes, from the highest: bit i of lo[k] / hi[k]
+// is bit k of coefficient i / 32 + i.  n: coefficients found significant.
+// Per plane the bits of the first n, then group tests: a 1 and the run up to
+// the next coefficient with a 1 (the last one, 63, implied by the test), or a
+// 0 that ends the plane.
+template <int STRIDE>
+__device__ __forceinline__ void encode_planes32(const uint32_t *lo, const uint32_t *hi, int &n,
+                                                BitWriter<STRIDE> &bw) {
 #pragma unroll
-    for (int i = 0; i < 64; i++) {
-        if (!isfinite(x[i])) finite = false;
-        if (x[i] != 0.0) {
-            int e;
-            frexp(x[i], &e);
-            emax = any ? (e > emax ? e : emax) : e;
-            any = true;
-        }
-    }
-    BitWriter bw{out, 0, 0};
-    if (!finite || !any) {
-        for (int w = 0; w < words; w++) out[w] = 0;
-        return finite;
-    }
-    if (emax < T::EMIN) emax = T::EMIN;
-    bw.put(1, 1);
-    bw.put((uint64_t)(emax + T::BIAS), T::EBITS);
-    Int v[64];
-#pragma unroll
-    for (int i = 0; i < 64; i++) {
-        if (F64) v[i] = (Int)ldexp(x[i], T::P - 2 - emax);
-        else v[i] = (Int)ldexpf((float)x[i], T::P - 2 - emax);
-    }
-    fwd_xyz(v);
-    UInt u[64];
-#pragma unroll
-    for (int r = 0; r < 64; r++) u[r] = ((UInt)v[kOrder.idx[r]] + T::NB) ^ T::NB;
-    int budget = 64 * rate - 1 - T::EBITS;
-    int n = 0;
-    for (int k = T::P - 1; k >= 0 && budget > 0; k--) {
-        uint64_t x64 = 0;
-#pragma unroll
-        for (int i = 0; i < 64; i++) x64 |= (uint64_t)((u[i] >> k) & 1u) << i;
-        int m = n < budget ? n : budget;
-        bw.put(m >= 64 ? x64 : (x64 & ((1ull << m) - 1)), m);
-        budget -= m;
-        while (n < 64 && budget > 0) {
-            uint64_t rest = x64 >> n;  // n < 64
-            budget--;
-            bw.put(rest ? 1 : 0, 1);
-            if (!rest) break;
-            int zeros = (int)__builtin_ctzll(rest);
-            int limit = 63 - n < budget ? 63 - n : budget;
-            if (zeros >= limit) {
-                bw.put(0, limit);
-                n += limit;
-                budget -= limit;
-            } else {
-                bw.put(1ull << zeros, zeros + 1);
-                budget -= zeros + 1;
-                n += zeros;
+    for (int k = 31; k >= 0; k--) {
+        if (bw.open()) {
+            const uint64_t x = (uint64_t)hi[k] << 32 | lo[k];
+            uint64_t rest = x;
+            if (n) {
+                bw.put(x & (~0ull >> (64 - n)), n);
+                rest = (x >> 1) >> (n - 1);
             }
-            n++;
+            while (n < 64 && bw.open()) {
+                if (!rest) {
+                    bw.put(0, 1);
+                    break;
+                }
+                const int z = ctz64(rest);
+                const bool implied = n + z == 63;
+                bw.put(1ull | (implied ? 0ull : 2ull << z), z + (implied ? 1 : 2));
+                n += z + 1;
+                rest = (rest >> 1) >> z;
+            }
         }
     }
-    if (bw.na > 0) *bw.out++ = bw.acc;
-    for (uint64_t *e = out + words; bw.out < e;) *bw.out++ = 0;
-    return true;
+}
+
+// Codes the block v (integers of emax's scale, block order); v is used up.
+template <int STRIDE>
+__device__ __forceinline__ void encode_coefficients(int32_t *v, BitWriter<STRIDE> &bw) {
+    constexpr uint32_t NB = Prec<false>::NB;
+    fwd_xyz(v);
+    uint32_t lo[32], hi[32];
+#pragma unroll
+    for (int r = 0; r < 32; r++) {
+        lo[r] = ((uint32_t)v[kOrder.idx[r]] + NB) ^ NB;
+        hi[r] = ((uint32_t)v[kOrder.idx[r + 32]] + NB) ^ NB;
+    }
+    transpose32(lo);
+    transpose32(hi);
+    int n = 0;
+    encode_planes32(lo, hi, n, bw);
+}
+// ... double precision: the upper 32 planes, then, for blocks that still have
+// room, the lower ones.
+template <int STRIDE>
+__device__ __forceinline__ void encode_coefficients(int64_t *v, BitWriter<STRIDE> &bw) {
+    constexpr uint64_t NB = Prec<true>::NB;
+    fwd_xyz(v);
+    uint32_t lo[32], hi[32], low[64];
+#pragma unroll
+    for (int r = 0; r < 32; r++) {
+        const uint64_t a = ((uint64_t)v[kOrder.idx[r]] + NB) ^ NB, b = ((uint64_t)v[kOrder.idx[r + 32]] + NB) ^ NB;
+        lo[r] = (uint32_t)(a >> 32);
+        hi[r] = (uint32_t)(b >> 32);
+        low[r] = (uint32_t)a;
+        low[r + 32] = (uint32_t)b;
+    }
+    transpose32(lo);
+    transpose32(hi);
+    int n = 0;
+    encode_planes32(lo, hi, n, bw);
+    if (__ballot(bw.open())) {
+        transpose32(low);
+        transpose32(low + 32);
+        encode_planes32(low, low + 32, n, bw);
+    }
+}
+
+// Largest magnitude of the block and whether all values are finite.
+__device__ __forceinline__ bool block_max(const float *x, float &m) {
+    uint32_t top = 0;   // magnitudes order as their bits; NaN and infinity on top
+#pragma unroll
+    for (int i = 0; i < 64; i++) top = max(top, __float_as_uint(x[i]) & 0x7FFFFFFFu);
+    m = __uint_as_float(top);
+    return top < 0x7F800000u;
+}
+__device__ __forceinline__ bool block_max(const double *x, double &m) {
+    uint32_t top = 0;
+    m = 0.0;
+#pragma unroll
+    for (int i = 0; i < 64; i++) {
+        top = max(top, (uint32_t)__double2hiint(x[i]) & 0x7FFFFFFFu);
+        m = fmax(m, fabs(x[i]));
+    }
+    return top < 0x7FF00000u;
+}
+__device__ __forceinline__ int32_t to_fixed(float x, int e) { return (int32_t)ldexpf(x, e); }
+__device__ __forceinline__ int64_t to_fixed(double x, int e) { return (int64_t)ldexp(x, e); }
+
+// Encodes block x (block order) into the `rate` words of bw; false (all
+// words zero) when a value is not finite.
+template <bool F64, int STRIDE>
+__device__ __forceinline__ bool encode_block(const std::conditional_t<F64, double, float> *x, int rate,
+                                             uint64_t *st) {
+    using T = Prec<F64>;
+    BitWriter<STRIDE> bw{st, rate, 0, 0, 0ull};
+    std::conditional_t<F64, double, float> m;
+    const bool finite = block_max(x, m);
+    if (finite && m > 0) {
+        int emax;
+        if constexpr (F64) frexp(m, &emax);
+        else frexpf(m, &emax);
+        if (emax < T::EMIN) emax = T::EMIN;
+        bw.put(1ull | (uint64_t)(emax + T::BIAS) << 1, 1 + T::EBITS);
+        typename T::Int v[64];
+#pragma unroll
+        for (int i = 0; i < 64; i++) v[i] = to_fixed(x[i], T::P - 2 - emax);
+        encode_coefficients(v, bw);
+    }
+    bw.finish();
+    return finite;
 }
 
 }  // namespace

@@ -1,0 +1,39 @@
+"""The encoder against the oracle's over its load forms (whole blocks by 16-byte
+rows; partial blocks and rows that are not aligned by samples), rates on both
+sides of the staged words' limit, and blocks whose last coefficient matters."""
+import numpy as np
+import pytest
+
+from tests.gpu_common import say, to_cuda, torch_cuda
+
+pytestmark = pytest.mark.gpu
+
+
+def _field(dims, dtype, seed):
+    nx, ny, nz = dims
+    r = np.random.default_rng(seed)
+    f = r.standard_normal((nz, ny, nx))
+    f[: nz // 2] *= 10.0 ** r.integers(-12, 12)
+    f[:, : ny // 2, : nx // 2] = 0.0                       # all-zero blocks among others
+    f[-1, -1, -1] = 1e30
+    z, y, x = np.indices(f.shape)
+    f[:, :, -nx // 3:] += np.where((x + y + z) % 2, 1.0, -1.0)[:, :, -nx // 3:]   # the highest coefficient
+    return f.astype(dtype)
+
+
+@pytest.mark.parametrize("dtype,rates", [(np.float32, (1, 3, 16, 17, 32)), (np.float64, (1, 2, 16, 17, 33, 64))])
+@pytest.mark.parametrize("dims,shift", [((64, 8, 8), 0), ((64, 8, 8), 1), ((260, 5, 4), 0), ((37, 9, 6), 0)])
+def test_encode_forms(orc, dtype, rates, dims, shift):
+    torch = torch_cuda()
+    import paper_2009_03254_amd as bc
+    f = _field(dims, dtype, 95)
+    say(f"[encode] {dims} {dtype.__name__} rates {rates} shift {shift}")
+    if shift:   # a field one sample past an aligned address
+        flat = torch.zeros(f.size + 1, dtype=torch.from_numpy(f).dtype, device="cuda")
+        g = flat[1:].view(f.shape)
+        g.copy_(torch.from_numpy(f))
+    else:
+        g = to_cuda(f)
+    for rate in rates:
+        got = bc.encode(g, rate).cpu().numpy()
+        assert np.array_equal(got, orc.zfp_encode(f, rate)), rate
