@@ -230,15 +230,13 @@ BCMC_API int bcmc_mc_table(uint64_t *packed256);
 BCMC_API int bcmc_copy_calibration(void *d_dst, const void *d_src, uint64_t nbytes,
                                    void *hip_stream);
 
-/* ---- batched extraction: many volumes x isovalues in one launch ------- */
+/* ---- batched extraction: many volumes x isovalues in one call --------- */
 /* A batch of jobs j = (volume job_vol[j], isovalue job_iso[j]) over
  * compressed volumes that share one scalar type (the volumes must outlive
  * the batch; their own caches are not used).  bcmc_batch_run extracts every
- * job in four launches: a persistent front kernel that culls and lists (its
- * phases separated by grid barriers), a decode kernel that decodes the new
- * blocks and builds sign masks, a count kernel, and an emission kernel in
- * which each workgroup sums the count kernel's per-wave totals before it;
- * replayed from a hipGraph when the runtime allows it.  Job j's
+ * job in six launches (flags, lists, decode with sign masks, count, emission,
+ * results to the host), each adding up what it needs of the counts before its
+ * share; replayed from a hipGraph when the runtime allows it.  Job j's
  * soup equals, byte for byte, bcmc_extract of its volume at its isovalue,
  * and the jobs' soups are concatenated in job order.  The batch keeps one
  * decoded-block store: a block needed by any job of its volume is decoded
@@ -255,23 +253,20 @@ typedef struct {
     uint32_t stage_blocks;    /* schedule: blocks staged per memory round trip (4 or 8) */
     uint32_t grid;            /* schedule: workgroups of the back kernel */
     uint32_t workgroups_per_cu;  /* of the back kernel */
-    uint32_t front_grid;      /* schedule: workgroups of the front kernel */
-    uint32_t scan_schedule;   /* schedule: 0 = workgroup 0 scans the front kernel's
-                                 counts, then a grid barrier; 1 = every workgroup
-                                 sums the counts before its own */
+    uint32_t front_grid;      /* schedule: workgroups of the flags and lists kernels */
+    uint32_t scan_schedule;   /* schedule: 0 or 1 as set; both run the same kernels
+                                 (every wave sums the counts before its own) */
     uint32_t decode_grid;     /* workgroups of the decode kernel */
     uint32_t ran_front_grid;  /* grids the last run's kernels were launched with, */
     uint32_t ran_decode_grid; /* as each kernel recorded them (0: that kernel */
     uint32_t ran_grid;        /* did not run, e.g. nothing to decode) */
     int32_t graph;            /* 1: the last run replayed a hipGraph */
-    int32_t graph_unsupported;/* 1: capturing the cooperative launch failed */
+    int32_t graph_unsupported;/* 1: capturing the launches failed */
     float last_ms;            /* GPU time of the last run (HIP events) */
-    float phase_ms[8];        /* the last run's phases (device clock at the grid
-                                 barriers and kernel ends): reset, flags, scan of
-                                 the counts of new blocks and pairs, list scatter,
-                                 decode and masks, count, the emission kernel's
-                                 prefix of the per-wave totals (each of the last
-                                 three with the gap before its kernel), emission */
+    float phase_ms[8];        /* the last run's phases (device clock at their starts,
+                                 each with the gap to the next one's kernel): reset
+                                 (empty), flags, totals, lists, decode and masks,
+                                 count, the emission's offsets, emission */
 } bcmc_batch_info;
 
 BCMC_API int bcmc_batch_create(bcmc_volume *const *vols, uint32_t n_vols, const uint32_t *job_vol,
@@ -292,15 +287,15 @@ BCMC_API int bcmc_batch_run(bcmc_batch *b, void *d_out, uint64_t capacity_vertic
                             uint64_t *h_job_off, void *hip_stream);
 /* Set the schedule by hand: stage_blocks (4 or 8) blocks staged per round
  * trip, per_cu workgroups per CU of the back kernel and front_per_cu of the
- * front kernel, each clamped to what stays resident (bcmc_batch_get_info
- * reports the grids), and scan_schedule (0 or 1, see bcmc_batch_info) for the
- * offsets of the front kernel's lists.  The next run captures its graph again.
+ * flags and lists kernels, each clamped to what stays resident
+ * (bcmc_batch_get_info reports the grids), and scan_schedule (0 or 1, see
+ * bcmc_batch_info).  The next run captures its graph again if a grid or
+ * stage_blocks changed.
  * Errors: BCMC_E_INVALID. */
 BCMC_API int bcmc_batch_set_schedule(bcmc_batch *b, int stage_blocks, int per_cu,
                                      int front_per_cu, int scan_schedule);
 /* Autotune the schedule (blocks staged per round trip, workgroups per CU
- * of the back and the front kernel, the front kernel's scan schedule) by
- * timing cold + warm runs of this batch; the best is kept and appended
+ * of the back kernel and of the flags and lists kernels) by timing cold + warm runs of this batch; the best is kept and appended
  * to cache_path (one JSON object per line, keyed by arch, scalar type and
  * batch shape; NULL: $BCMC_AUTOTUNE_CACHE, or nothing).  Batches created
  * later with a matching key start from the stored schedule.  Empties the

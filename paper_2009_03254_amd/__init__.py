@@ -399,7 +399,7 @@ class FieldVolume(_Handle):
 
 
 class Batch:
-    """Many volumes x isovalues extracted in one persistent launch (hipGraph
+    """Many volumes x isovalues extracted in one call (hipGraph
     replay).  jobs: list of (volume_index, isovalue)."""
 
     def __init__(self, volumes, jobs, stream=None):

@@ -20,6 +20,7 @@ struct BatchVol {
 struct BatchCounters {
     unsigned long long n_slots;      // decoded blocks resident (persists across runs)
     unsigned long long n_new;        // blocks decoded by this run
+    unsigned long long n_res;        // used blocks that were resident
     unsigned long long n_list;       // (job, block) pairs that may emit
     unsigned long long total_verts;
     unsigned long long slot_base;    // first slot of this run's new blocks
@@ -28,17 +29,8 @@ struct BatchCounters {
     unsigned int pad[2];
 };
 
-// Grid barrier words (u32 units): the generation, the top-level arrival
-// count, the arrival counts of BAR_GROUPS workgroup groups and the finish
-// count.  Each word sits on its own 256-byte line so that arrivals on one
-// word do not queue behind polls of another.
-constexpr int BAR_PAD = 64;
-constexpr int BAR_GROUPS = 16;
-constexpr int BAR_GEN = 0;
-constexpr int BAR_TOP = BAR_PAD;
-constexpr int BAR_DONE = 2 * BAR_PAD;
-constexpr int BAR_SUB = 3 * BAR_PAD;
-constexpr int BAR_WORDS = BAR_SUB + BAR_GROUPS * BAR_PAD;
+// Blocks of one volume that a workgroup of the flags kernel takes at a time.
+constexpr int BATCH_UNIT = 1024;
 
 struct BatchParams {
     const BatchVol *vols;
@@ -51,42 +43,44 @@ struct BatchParams {
     uint64_t n_gblocks, n_jblocks, max_slots;
     uint32_t uniform_rate;       // the rate of every volume when they share one <= 16, else 0
     uint32_t max_vol_jobs;       // most jobs of one volume
-    uint32_t scan_sched;         // offsets of the front kernel's lists: 0 = workgroup 0 scans the
-                                 // counts, then a grid barrier; 1 = every workgroup sums the
-                                 // counts before its own (no barrier)
+    uint64_t n_units, n_junits;  // units of all volumes, of all jobs' volumes
+    const uint64_t *vol_unit;    // [n_vols] first unit of each volume
+    const uint64_t *job_unit;    // [n_jobs] first unit of each job among the jobs' units
     int32_t *I_slot;             // [n_gblocks] slot of each global block or -1
     float *slots;                // [max_slots][64]
-    uint8_t *need;               // [n_gblocks] 0 unused, 1 used and new, 2 used and resident
-    uint8_t *emit_flag;          // [n_jblocks rounded up to 4] (padding zero)
+    uint64_t *new_bits;          // [n_units][BATCH_UNIT / 64] used and new
+    uint64_t *res_bits;          // [n_units][BATCH_UNIT / 64] used and resident
+    uint64_t *pair_bits;         // [n_junits][BATCH_UNIT / 64] may emit
+    uint32_t *unit_cnt;          // [n_units] new | resident << 16
+    uint32_t *pair_cnt;          // [n_junits] may emit
+    unsigned long long *vol_tot; // [n_vols] new << 32 | resident (zero between runs)
+    unsigned long long *job_tot; // [n_jobs] may emit (zero between runs)
     uint64_t *jmask;             // [n_jblocks] sign masks of the used blocks per job
     uint32_t *new_list;          // [n_gblocks]
+    uint32_t *res_list;          // [n_gblocks]
     uint32_t *list;              // [n_jblocks] (job-major, block-ascending)
     uint32_t *list_job;          // [n_jblocks] job of each list entry
     uint32_t *cnt;               // [n_jblocks] vertex count of each list entry
-    uint64_t *part_new;          // [front grid] per-workgroup new blocks, then offsets
-    uint64_t *part_list;         // [front grid * 4] per-wave pairs, then offsets
-    uint64_t *part_wave;         // [back grid * 4] per-wave vertex counts, then offsets
+    uint64_t *part_wave;         // [back grid * 4] per-wave vertex counts
     uint64_t *job_off;           // [n_jobs + 1] vertex offsets of the jobs' soups
     const uint64_t *mc_table;
     void *out;
     uint64_t cap;
     BatchCounters *ctr;
-    unsigned int *bar;           // [BAR_WORDS] grid barrier
-    unsigned long long *phase_ts;  // [9] real-time clock at the phase boundaries
+    unsigned long long *phase_ts;  // [8] real-time clock at the phases' starts
+    // the host's copies (pinned)
+    BatchCounters *h_ctr;
+    uint64_t *h_job_off;
+    unsigned long long *h_ts;      // [9]
 };
 
-// Resident workgroups per CU of the front kernel (flags and lists), the
-// decode kernel (decode and sign masks) and the back kernel (count, scan,
-// emission; `sb` blocks staged per wave round trip).
+// Resident workgroups per CU of the lists kernel, the decode kernel (decode
+// and sign masks) and the back kernel (`sb` blocks staged per wave round trip).
 int batch_front_per_cu(int *per_cu);
 int batch_decode_per_cu(const BatchParams &p, int is_f64, int *per_cu);
 int batch_back_per_cu(int sb, int *per_cu);
-// Launches the three kernels with grids[0..2] workgroups.  cooperative = 1:
-// the persistent front and back kernels by hipLaunchCooperativeKernel
-// (residency guaranteed by the runtime); 0: plain launches (for graph
-// capture; each grid never exceeds the resident capacity and the barriers
-// are bounded).
-hipError_t launch_batch(const BatchParams &p, int is_f64, int sb, const unsigned grids[3],
-                        hipStream_t s, int cooperative);
+// Launches the run's kernels: flags and lists on grids[0] workgroups, decode
+// on grids[1], count and back on grids[2].
+hipError_t launch_batch(const BatchParams &p, int is_f64, int sb, const unsigned grids[3], hipStream_t s);
 
 }  // namespace bcmc

@@ -1,6 +1,5 @@
 // Batched extraction: many volumes of uneven size, several isovalues each,
-// in four launches (the first persistent, its phases separated by grid
-// barriers), replayable from a hipGraph.
+// in six launches, replayable from a hipGraph.
 //
 // Each job j = (volume v_j, isovalue iso_j) produces exactly the triangle soup
 // a single-volume extract of v_j at iso_j produces (same arithmetic, same
@@ -12,25 +11,22 @@
 // unbounded cache: nothing is evicted, so later runs decode only blocks no
 // earlier run needed).
 //
-// Front kernel (persistent):
-//   0  reset the run's counters
-//   1  per global block: used by some job of its volume (new or resident)
-//      and, per job of its volume, whether it may emit for that job (2x2x2
-//      hull rule); per-workgroup counts of new blocks, per-wave counts of
-//      the pairs that may emit
-//   2  workgroup 0 scans the counts and reserves the new blocks' slots
-//   3  scatter: list of new blocks; list L of (job, block) pairs in job-major,
-//      block-ascending order (= the concatenated canonical orders)
-// Decode kernel (grid-stride; its grid sized by the decoder's registers):
-//   4  decode the new blocks into slots slot_base + rank; sign masks of every
-//      used block for every job of its volume
-// Count kernel (grid autotuned; every wave owns one contiguous share of L):
-//   5  count pass over L from the sign masks (Sec. 4.4), per-wave totals
-// Back kernel (same grid and shares as the count kernel, no barriers):
-//   6  each workgroup sums the per-wave totals before its waves
-//   7  emission over L (Sec. 4.5), offsets by a running wave scan of the
-//      counts; per-job output offsets
-// Every thread of a persistent grid reaches every barrier of its kernel.
+//   flags   per block, in units of BATCH_UNIT consecutive blocks of one volume:
+//           used by some job of its volume (new or resident) and, per job,
+//           whether it may emit (2x2x2 hull rule), as bits, with counts per
+//           unit and totals per volume and per job
+//   lists   the new blocks, the resident used ones, and the list L of
+//           (job, block) pairs in job-major, block-ascending order (= the
+//           concatenated canonical orders): a wave per unit and list, whose
+//           place is the sum of the totals and counts before it
+//   decode  the new blocks into slots slot_base + rank; sign masks of every
+//           used block for every job of its volume
+//   count   count pass over L from the sign masks (Sec. 4.4); every wave owns
+//           one contiguous share of L
+//   back    each workgroup sums the per-wave totals before its waves, then
+//           the emission over L (Sec. 4.5), offsets by a running wave scan of
+//           the counts; per-job output offsets
+//   done    the run's results to the host's copies
 #include <stdint.h>
 
 #include "batch.h"
@@ -55,167 +51,6 @@ __device__ __forceinline__ uint32_t find_base(const uint64_t *base, uint32_t n, 
     return lo;
 }
 
-// Index -> segment lookup for increasing indices: caches [lo, hi) of the
-// current segment and searches again only when the index leaves it.
-struct SegCursor {
-    uint32_t seg;
-    uint64_t lo, hi;
-    __device__ __forceinline__ void reset() { lo = 1; hi = 0; seg = 0; }
-    __device__ __forceinline__ uint32_t find(const uint64_t *base, uint32_t n, uint64_t end, uint64_t x) {
-        if (x < lo || x >= hi) {
-            seg = find_base(base, n, x);
-            lo = base[seg];
-            hi = seg + 1 < n ? base[seg + 1] : end;
-        }
-        return seg;
-    }
-};
-
-// Grid-wide barrier for a grid whose workgroups are all resident.  Arrivals
-// are counted in two levels: workgroup g in group g % BAR_GROUPS, the last of
-// a group in the top-level count, whose last arrival advances the generation.
-// Waiters poll the generation with plain device-scope loads and acquire once
-// when it moves.  The spin is bounded: on timeout it raises ERR_TIMEOUT and
-// returns false, and the caller leaves the kernel, so a barrier can never
-// hang the device.
-constexpr unsigned BARRIER_SPIN_LIMIT = 1u << 21;
-
-__device__ __forceinline__ unsigned ld_relaxed(const unsigned *a) {
-    return __hip_atomic_load(a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ bool grid_barrier(unsigned int *bar, unsigned int *err) {
-    __shared__ int ok;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        ok = 1;
-        const unsigned G = gridDim.x, k = blockIdx.x % BAR_GROUPS;
-        const unsigned groups = G < (unsigned)BAR_GROUPS ? G : (unsigned)BAR_GROUPS;
-        const unsigned members = G / BAR_GROUPS + (k < G % BAR_GROUPS ? 1u : 0u);
-        const unsigned gen = ld_relaxed(&bar[BAR_GEN]);
-        __threadfence();   // release this workgroup's writes; gen read before arriving
-        bool last = false;
-        if (atomicAdd(&bar[BAR_SUB + k * BAR_PAD], 1u) + 1u == members) {
-            __hip_atomic_store(&bar[BAR_SUB + k * BAR_PAD], 0u, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-            __threadfence();
-            if (atomicAdd(&bar[BAR_TOP], 1u) + 1u == groups) {
-                __hip_atomic_store(&bar[BAR_TOP], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __threadfence();
-                atomicAdd(&bar[BAR_GEN], 1u);
-                last = true;
-            }
-        }
-        if (!last) {
-            unsigned spins = 0;
-            while (ld_relaxed(&bar[BAR_GEN]) == gen) {
-                if (ld_relaxed(err) & ERR_TIMEOUT || ++spins > BARRIER_SPIN_LIMIT) {
-                    atomicOr(err, ERR_TIMEOUT);
-                    ok = 0;
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(4);
-            }
-        }
-        __threadfence();   // acquire the other workgroups' writes
-    }
-    __syncthreads();
-    return ok;
-}
-
-// Workgroup-wide exclusive scan of one u32 per thread; returns the total.
-__device__ uint32_t wg_excl_scan(uint32_t v, uint32_t &excl, uint32_t *sh_w) {
-    const int w = threadIdx.x >> 6;
-    uint32_t incl = wave_incl_scan(v);
-    if (lane() == 63) sh_w[w] = incl;
-    __syncthreads();
-    uint32_t off = 0, tot = 0;
-#pragma unroll
-    for (int i = 0; i < BT / 64; i++) {
-        if (i < w) off += sh_w[i];
-        tot += sh_w[i];
-    }
-    __syncthreads();
-    excl = off + incl - v;
-    return tot;
-}
-
-// Contiguous share of [0, n) for workgroup g of G.
-__device__ __forceinline__ void wg_range(uint64_t n, uint64_t &lo, uint64_t &hi) {
-    const uint64_t chunk = (n + gridDim.x - 1) / gridDim.x;
-    lo = (uint64_t)blockIdx.x * chunk;
-    hi = lo + chunk < n ? lo + chunk : n;
-    if (lo > n) lo = n;
-}
-
-// Exclusive scan, by workgroup 0, of partial[0..n) in place; returns total.
-// Each thread takes a contiguous run (its loads all in flight together),
-// the runs' sums are scanned across the workgroup.
-__device__ uint64_t scan_partials(uint64_t *partial, uint32_t n, uint64_t *sh_w) {
-    const int w = threadIdx.x >> 6;
-    const uint32_t per = (n + BT - 1) / BT;
-    const uint32_t a = threadIdx.x * per, z = a + per < n ? a + per : n;
-    uint64_t s = 0;
-#pragma unroll 8
-    for (uint32_t i = a; i < z; i++) s += partial[i];
-    const uint64_t incl = wave_incl_scan(s);
-    if (lane() == 63) sh_w[w] = incl;
-    __syncthreads();
-    uint64_t off = incl - s, tot = 0;
-#pragma unroll
-    for (int k = 0; k < BT / 64; k++) {
-        if (k < w) off += sh_w[k];
-        tot += sh_w[k];
-    }
-    __syncthreads();
-#pragma unroll 8
-    for (uint32_t i = a; i < z; i++) {
-        const uint64_t v = partial[i];
-        partial[i] = off;
-        off += v;
-    }
-    return tot;
-}
-
-// Sum of part[0..n) over the workgroup (its loads spread over the threads,
-// 8 in flight each); with m > 0 also the sum of part[0..m) into *all.  Every
-// thread of the workgroup calls it and gets the sums.
-__device__ uint64_t sum_before(const uint64_t *part, uint32_t n, uint32_t m, uint64_t *sh_w, uint64_t *all) {
-    const uint32_t lim = n > m ? n : m;
-    uint64_t s = 0, t = 0;
-    for (uint32_t i0 = threadIdx.x; i0 < lim; i0 += 8u * BT) {
-        uint64_t v[8];
-#pragma unroll
-        for (int j = 0; j < 8; j++) {
-            const uint32_t i = i0 + (uint32_t)j * BT;
-            v[j] = i < lim ? part[i] : 0ull;
-        }
-#pragma unroll
-        for (int j = 0; j < 8; j++) {
-            const uint32_t i = i0 + (uint32_t)j * BT;
-            if (i < n) s += v[j];
-            if (i < m) t += v[j];
-        }
-    }
-    s = wave_sum(s);
-    t = wave_sum(t);
-    const int w = threadIdx.x >> 6;
-    if (lane() == 0) sh_w[w] = s;
-    __syncthreads();
-    uint64_t S = 0;
-#pragma unroll
-    for (int k = 0; k < BT / 64; k++) S += sh_w[k];
-    __syncthreads();
-    if (lane() == 0) sh_w[w] = t;
-    __syncthreads();
-    uint64_t T = 0;
-#pragma unroll
-    for (int k = 0; k < BT / 64; k++) T += sh_w[k];
-    __syncthreads();
-    *all = T;
-    return S;
-}
-
 // Sign mask of a decoded block for one isovalue: bit i = (sample i < iso),
 // the inside test of the per-cell classification (Sec. 4.4).
 __device__ __forceinline__ uint64_t sign_mask(const float *v, float iso) {
@@ -238,22 +73,9 @@ __device__ __forceinline__ void store_masks(const BatchParams &p, const BatchVol
     }
 }
 
-// Clock stamp k by workgroup 0 (after a grid barrier every workgroup has
-// passed the previous phase).
+// Clock stamp k, at the start of a phase (by workgroup 0).
 __device__ __forceinline__ void stamp(const BatchParams &p, int k) {
     if (blockIdx.x == 0 && threadIdx.x == 0) p.phase_ts[k] = wall_clock64();
-}
-
-// Clock stamp k by the last workgroup to finish the kernel.
-__device__ __forceinline__ void stamp_last(const BatchParams &p, int k) {
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        __threadfence();
-        if (atomicAdd(&p.bar[BAR_DONE], 1u) + 1u == gridDim.x) {
-            p.phase_ts[k] = wall_clock64();
-            __hip_atomic_store(&p.bar[BAR_DONE], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
 }
 
 // Contiguous share [lo, hi) of n items for the calling wave: the workgroups
@@ -272,178 +94,164 @@ __device__ __forceinline__ uint32_t wave_share(uint64_t n, uint64_t &lo, uint64_
     return wv;
 }
 
-// ---- front kernel: phases 0-3 ---------------------------------------------
-__global__ __launch_bounds__(BT) void k_batch_front(BatchParams p) {
-    __shared__ uint32_t sh_w[BT / 64];
-    __shared__ uint64_t sh_w64[BT / 64];
-    const uint64_t gtid = blockIdx.x * (uint64_t)BT + threadIdx.x;
+// ---- flags -------------------------------------------------------------------
+// Per block, with its volume uniform over the workgroup's unit: the ranges of
+// its 3x3x3 neighbourhood (indices clamped into the volume: a clamped
+// neighbour is one already in the neighbourhood, so no load is conditional),
+// whether some job of the volume uses it (Sec. 4.1 rule) and, per job, whether
+// it may emit (2x2x2 hull of its octet).  A bit per block and per pair (word w
+// of a unit from wave w), and the number of bits per unit.  Latency bound: a
+// block per thread, 27 loads in flight each, and no workgroup waits for another
+// (as phases of one persistent kernel between grid barriers, with a byte per
+// pair, flags and lists took 300 us of the batch of 48 volumes x 4 isovalues,
+// 2.7 M blocks; as two launches 98 + 18; units of 512 or 256 blocks: 101 + 29,
+// 126 + 48).
+constexpr int UNIT_WAVES = BATCH_UNIT / 64;
+__global__ __launch_bounds__(BATCH_UNIT) void k_batch_flags(BatchParams p) {
+    constexpr int JOBS = 32;   // jobs between two barriers
+    __shared__ uint32_t s_n[JOBS][UNIT_WAVES], s_u[UNIT_WAVES];
     stamp(p, 0);
-    // phase 0: reset the run's counters
-    if (gtid == 0) {
-        p.ctr->n_new = 0;
-        p.ctr->n_list = 0;
-        p.ctr->total_verts = 0;
-        p.ctr->err = 0;
-        p.ctr->grid_front = gridDim.x;
-    }
-    if (!grid_barrier(p.bar, &p.ctr->err)) return;
     stamp(p, 1);
-
-    // ---- phase 1: flags ----------------------------------------------------------
-    // Per global block, with its volume uniform over the workgroup's loop: the
-    // ranges of its 3x3x3 neighbourhood (indices clamped into the volume: a
-    // clamped neighbour is one already in the neighbourhood, so no load is
-    // conditional), whether some job of the volume uses it (Sec. 4.1 rule) and,
-    // per job, whether it may emit (2x2x2 hull of its octet).
-    {
-        uint64_t lo, hi;
-        wg_range(p.n_gblocks, lo, hi);
-        uint32_t cnt = 0;
-        for (uint32_t v = lo < hi ? find_base(p.vol_gbase, p.n_vols, lo) : p.n_vols; v < p.n_vols; v++) {
-            const BatchVol &vol = p.vols[v];
-            if (vol.gbase >= hi) break;
-            const Geom g = vol.g;
-            const uint64_t s0 = vol.gbase > lo ? vol.gbase : lo;
-            const uint64_t s1 = vol.gbase + g.nb < hi ? vol.gbase + g.nb : hi;
-            for (uint64_t gb = s0 + threadIdx.x; gb < s1; gb += BT) {
-                const uint32_t b = (uint32_t)(gb - vol.gbase);
-                const uint32_t r = b / g.nbx, bx = b - r * g.nbx, by = r % g.nby, bz = r / g.nby;
-                uint32_t xs[3], ys[3], zs[3];
-                xs[0] = bx ? bx - 1 : 0; xs[1] = bx; xs[2] = bx + 1 < g.nbx ? bx + 1 : bx;
-                ys[0] = by ? by - 1 : 0; ys[1] = by; ys[2] = by + 1 < g.nby ? by + 1 : by;
-                zs[0] = bz ? bz - 1 : 0; zs[1] = bz; zs[2] = bz + 1 < g.nbz ? bz + 1 : bz;
-                float2 q[27];
+    if (blockIdx.x == 0 && threadIdx.x == 0) p.ctr->grid_front = gridDim.x;
+    const int w = (int)wave_id(), l = lane();
+    for (uint32_t u = blockIdx.x; u < p.n_units; u += gridDim.x) {
+        const uint32_t vi = find_base(p.vol_unit, p.n_vols, u);
+        const BatchVol &vol = p.vols[vi];
+        const Geom g = vol.g;
+        const uint32_t k = u - (uint32_t)p.vol_unit[vi];   // the volume's k-th unit
+        const uint32_t b0 = k * BATCH_UNIT + threadIdx.x, b = b0 < g.nb ? b0 : (uint32_t)g.nb - 1;
+        const uint32_t r = b / g.nbx, bx = b - r * g.nbx, by = r % g.nby, bz = r / g.nby;
+        uint32_t xs[3], ys[3], zs[3];
+        xs[0] = bx ? bx - 1 : 0; xs[1] = bx; xs[2] = bx + 1 < g.nbx ? bx + 1 : bx;
+        ys[0] = by ? by - 1 : 0; ys[1] = by; ys[2] = by + 1 < g.nby ? by + 1 : by;
+        zs[0] = bz ? bz - 1 : 0; zs[1] = bz; zs[2] = bz + 1 < g.nbz ? bz + 1 : bz;
+        float2 q[27];
 #pragma unroll
-                for (int k = 0; k < 27; k++)
-                    q[k] = vol.ranges[xs[k % 3] + g.nbx * ((uint64_t)ys[(k / 3) % 3] + (uint64_t)g.nby * zs[k / 9])];
-                float LO = q[0].x, HI = q[0].y, PLO = q[13].x, PHI = q[13].y;
+        for (int t = 0; t < 27; t++)
+            q[t] = vol.ranges[xs[t % 3] + g.nbx * ((uint64_t)ys[(t / 3) % 3] + (uint64_t)g.nby * zs[t / 9])];
+        float LO = q[0].x, HI = q[0].y, PLO = q[13].x, PHI = q[13].y;
 #pragma unroll
-                for (int k = 1; k < 27; k++) {
-                    LO = fminf(LO, q[k].x);
-                    HI = fmaxf(HI, q[k].y);
-                }
-#pragma unroll
-                for (int k = 14; k < 27; k++)
-                    if (k % 3 != 0 && (k / 3) % 3 != 0) {   // offsets in {0, 1}^3
-                        PLO = fminf(PLO, q[k].x);
-                        PHI = fmaxf(PHI, q[k].y);
-                    }
-                const float2 own = q[13];
-                bool used = false;
-                for (uint32_t k = vol.job_lo; k < vol.job_hi; k++) {
-                    const uint32_t j = p.vol_jobs[k];
-                    const float iso = p.job_iso[j];
-                    if ((own.x < iso && iso <= HI) || (LO < iso && iso <= own.y)) used = true;
-                    p.emit_flag[p.job_jbase[j] + b] = (PLO < iso && iso <= PHI) ? 1 : 0;
-                }
-                const uint8_t need = used ? (p.I_slot[gb] < 0 ? 1 : 2) : 0;
-                p.need[gb] = need;
-                cnt += need == 1;
-            }
+        for (int t = 1; t < 27; t++) {
+            LO = fminf(LO, q[t].x);
+            HI = fmaxf(HI, q[t].y);
         }
-        uint32_t excl;
-        const uint32_t tot = wg_excl_scan(cnt, excl, sh_w);
-        if (threadIdx.x == 0) p.part_new[blockIdx.x] = tot;
+#pragma unroll
+        for (int t = 14; t < 27; t++)
+            if (t % 3 != 0 && (t / 3) % 3 != 0) {   // offsets in {0, 1}^3
+                PLO = fminf(PLO, q[t].x);
+                PHI = fmaxf(PHI, q[t].y);
+            }
+        float2 own = q[13];
+        if (b0 >= g.nb) {   // past the volume: no isovalue lies in an empty range
+            own = make_float2(INFINITY, -INFINITY);
+            PLO = LO = INFINITY;
+        }
+        bool used = false;
+        for (uint32_t t0 = vol.job_lo; t0 < vol.job_hi; t0 += JOBS) {
+            const uint32_t nt = min((uint32_t)JOBS, vol.job_hi - t0);
+            for (uint32_t t = 0; t < nt; t++) {
+                const uint32_t j = p.vol_jobs[t0 + t];
+                const float iso = p.job_iso[j];
+                used = used || (own.x < iso && iso <= HI) || (LO < iso && iso <= own.y);
+                const uint64_t m = __ballot(PLO < iso && iso <= PHI);
+                if (l == 0) {
+                    p.pair_bits[(p.job_unit[j] + k) * UNIT_WAVES + w] = m;
+                    s_n[t][w] = (uint32_t)__popcll(m);
+                }
+            }
+            __syncthreads();
+            if (threadIdx.x < nt) {   // one atomic per unit and job
+                const uint32_t j = p.vol_jobs[t0 + threadIdx.x];
+                uint32_t n = 0;
+                for (int i = 0; i < UNIT_WAVES; i++) n += s_n[threadIdx.x][i];
+                p.pair_cnt[p.job_unit[j] + k] = n;
+                if (n) atomicAdd(&p.job_tot[j], (unsigned long long)n);
+            }
+            __syncthreads();   // s_n is rewritten
+        }
+        const int32_t sl = used ? p.I_slot[vol.gbase + b] : 0;
+        const uint64_t nm = __ballot(used && sl < 0), rm = __ballot(used && sl >= 0);
+        if (l == 0) {
+            p.new_bits[(uint64_t)u * UNIT_WAVES + w] = nm;
+            p.res_bits[(uint64_t)u * UNIT_WAVES + w] = rm;
+            s_u[w] = (uint32_t)__popcll(nm) | (uint32_t)__popcll(rm) << 16;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            uint32_t n = 0;
+            for (int i = 0; i < UNIT_WAVES; i++) n += s_u[i];
+            p.unit_cnt[u] = n;
+            if (n) atomicAdd(&p.vol_tot[vi], (unsigned long long)(n & 0xFFFFu) << 32 | (n >> 16));
+        }
+        __syncthreads();   // s_u is rewritten
     }
-    if (!grid_barrier(p.bar, &p.ctr->err)) return;
-    // Pairs that may emit, per wave share of the flags (4 flags per word; the
-    // flag array is zero-padded to a multiple of 4).
-    const uint64_t n_words = (p.n_jblocks + 3) / 4;
-    const uint32_t *flag_words = reinterpret_cast<const uint32_t *>(p.emit_flag);
-    {
-        uint64_t lo, hi;
-        const uint32_t wv = wave_share(n_words, lo, hi);
-        uint64_t c = 0;
-        for (uint64_t i = lo + lane(); i < hi; i += 64) c += __popc(flag_words[i]);
-        c = wave_sum(c);
-        if (lane() == 0) p.part_list[wv] = c;
+}
+
+// ---- lists -------------------------------------------------------------------
+// The bits of one unit as list entries first + bit, from list[o] on.
+template <class Put>
+__device__ __forceinline__ void list_unit(const uint64_t *__restrict__ words, uint64_t o, const Put &put) {
+    constexpr int W = UNIT_WAVES;
+    const uint64_t mine = lane() < W ? words[lane()] : 0ull;
+#pragma unroll
+    for (int i = 0; i < W; i++) {
+        const uint64_t m = ((uint64_t)bcast((uint32_t)(mine >> 32), i) << 32) | bcast((uint32_t)mine, i);
+        if ((m >> lane()) & 1u) put(o + mbcnt(m), 64u * i + (uint32_t)lane());
+        o += (uint64_t)__popcll(m);
     }
-    if (!grid_barrier(p.bar, &p.ctr->err)) return;
+}
+// Sum of a[lo..hi) over the wave.
+template <typename T, class Get>
+__device__ __forceinline__ uint64_t wave_range_sum(const T *__restrict__ a, uint64_t lo, uint64_t hi, const Get &get) {
+    uint64_t v = 0;
+#pragma unroll 4
+    for (uint64_t i = lo + lane(); i < hi; i += 64) v += get(a[i]);
+    return wave_sum(v);
+}
+
+__global__ __launch_bounds__(BT) void k_batch_lists(BatchParams p) {
     stamp(p, 2);
-
-    // ---- phase 2: offsets of the workgroups' new blocks and the waves' pairs ----
-    // scan_sched 0: workgroup 0 scans both count arrays in place, then a grid
-    // barrier; 1: every workgroup sums the counts before its own (and
-    // workgroup 0 all of them for the totals), no barrier.  The autotuner
-    // picks one.
-    uint64_t new_off, list_off;
-    uint32_t wv_list;   // the wave's share of the flag words (index into part_list)
-    {
-        uint64_t slo, shi;
-        wv_list = wave_share(n_words, slo, shi);
-    }
-    if (p.scan_sched == 0) {
-        if (blockIdx.x == 0) {
-            uint64_t tn = scan_partials(p.part_new, gridDim.x, sh_w64);
-            uint64_t tl = scan_partials(p.part_list, gridDim.x * (BT / 64), sh_w64);
-            if (threadIdx.x == 0) {
-                const uint64_t n_slots0 = p.ctr->n_slots;
-                p.ctr->slot_base = n_slots0;
-                p.ctr->n_slots = n_slots0 + tn;
-                p.ctr->n_new = tn;
-                p.ctr->n_list = tl;
-            }
-        }
-        if (!grid_barrier(p.bar, &p.ctr->err)) return;
-        new_off = p.part_new[blockIdx.x];
-        list_off = p.part_list[wv_list];
-    } else {
-        const uint32_t nw = gridDim.x * (BT / 64);
-        const bool all = blockIdx.x == 0;
-        new_off = sum_before(p.part_new, blockIdx.x, all ? gridDim.x : 0u, sh_w64, &list_off);
-        const uint64_t tn = list_off;
-        // the waves before this workgroup's first wave, then its own earlier waves
-        const uint32_t wv0 = wv_list - (threadIdx.x >> 6);
-        uint64_t tl;
-        list_off = sum_before(p.part_list, wv0, all ? nw : 0u, sh_w64, &tl);
-        for (uint32_t k = wv0; k < wv_list; k++) list_off += p.part_list[k];
-        if (all && threadIdx.x == 0) {
-            const uint64_t n_slots0 = p.ctr->n_slots;
-            p.ctr->slot_base = n_slots0;
-            p.ctr->n_slots = n_slots0 + tn;
+    constexpr int W = UNIT_WAVES;
+    auto all = [](uint64_t x) { return x; };
+    if (blockIdx.x == 0 && wave_id() == 0) {   // the run's totals; the new blocks' slots
+        const uint64_t tv = wave_range_sum(p.vol_tot, 0, p.n_vols, all), tl = wave_range_sum(p.job_tot, 0, p.n_jobs, all);
+        if (lane() == 0) {
+            const uint64_t n0 = p.ctr->n_slots, tn = tv >> 32;
+            p.ctr->slot_base = n0;
+            p.ctr->n_slots = n0 + tn;
             p.ctr->n_new = tn;
+            p.ctr->n_res = tv & 0xFFFFFFFFull;
             p.ctr->n_list = tl;
         }
     }
     stamp(p, 3);
-
-    // ---- phase 3: ordered scatter of both lists --------------------------------
-    {
-        uint64_t lo, hi;
-        wg_range(p.n_gblocks, lo, hi);
-        const uint64_t per = (hi - lo + BT - 1) / BT;    // contiguous items per thread
-        uint64_t a = lo + threadIdx.x * per, z = a + per < hi ? a + per : hi;
-        uint32_t c = 0;
-        for (uint64_t i = a; i < z; i++) c += p.need[i] == 1;
-        uint32_t excl;
-        wg_excl_scan(c, excl, sh_w);
-        uint64_t o = new_off + excl;
-        for (uint64_t i = a; i < z; i++)
-            if (p.need[i] == 1) p.new_list[o++] = (uint32_t)i;
-
-        // L: each wave walks its share of the flag words again, 64 words per
-        // step, placing the pairs by a wave scan of the per-word counts.
-        wave_share(n_words, lo, hi);
-        uint64_t base = list_off;
-        SegCursor cur;
-        cur.reset();
-        for (uint64_t i0 = lo; i0 < hi; i0 += 64) {
-            const uint64_t i = i0 + lane();
-            const uint32_t fw = i < hi ? flag_words[i] : 0u;
-            const uint32_t cw = __popc(fw);
-            const uint32_t incl = wave_incl_scan(cw);
-            uint64_t o2 = base + incl - cw;
-            base += __shfl(incl, 63, 64);
-#pragma unroll
-            for (int t = 0; t < 4; t++)
-                if ((fw >> (8 * t)) & 0xFFu) {
-                    const uint64_t e = 4 * i + t;
-                    p.list[o2] = (uint32_t)e;
-                    p.list_job[o2++] = cur.find(p.job_jbase, p.n_jobs, p.n_jblocks, e);
-                }
+    const uint64_t waves = (uint64_t)gridDim.x * (BT / 64);
+    for (uint64_t t = (uint64_t)blockIdx.x * (BT / 64) + wave_id(); t < p.n_units + p.n_junits; t += waves) {
+        if (t < p.n_units) {
+            const uint32_t n = p.unit_cnt[t];
+            if (!n) continue;
+            const uint32_t vi = find_base(p.vol_unit, p.n_vols, t);
+            auto parts = [](uint32_t x) { return (uint64_t)(x & 0xFFFFu) << 32 | (x >> 16); };
+            const uint64_t o = wave_range_sum(p.vol_tot, 0, vi, all) +
+                               wave_range_sum(p.unit_cnt, p.vol_unit[vi], t, parts);
+            const uint32_t gb0 = (uint32_t)(p.vols[vi].gbase + (t - p.vol_unit[vi]) * BATCH_UNIT);
+            if (n & 0xFFFFu)
+                list_unit(p.new_bits + t * W, o >> 32, [&](uint64_t at, uint32_t i) { p.new_list[at] = gb0 + i; });
+            if (n >> 16)
+                list_unit(p.res_bits + t * W, o & 0xFFFFFFFFull, [&](uint64_t at, uint32_t i) { p.res_list[at] = gb0 + i; });
+        } else {
+            const uint64_t ju = t - p.n_units;
+            if (!p.pair_cnt[ju]) continue;
+            const uint32_t j = find_base(p.job_unit, p.n_jobs, ju);
+            const uint64_t o = wave_range_sum(p.job_tot, 0, j, all) +
+                               wave_range_sum(p.pair_cnt, p.job_unit[j], ju, all);
+            const uint32_t e0 = (uint32_t)(p.job_jbase[j] + (ju - p.job_unit[j]) * BATCH_UNIT);
+            list_unit(p.pair_bits + ju * W, o, [&](uint64_t at, uint32_t i) {
+                p.list[at] = e0 + i;
+                p.list_job[at] = j;
+            });
         }
     }
-    stamp_last(p, 4);
 }
 
 // ---- decode kernel: phase 4 ---------------------------------------------------
@@ -452,7 +260,8 @@ __global__ __launch_bounds__(BT) void k_batch_front(BatchParams p) {
 // together: the staging is a wave-wide copy).
 template <bool F64, bool STAGED>
 __global__ __launch_bounds__(BT) void k_batch_decode(BatchParams p) {
-    if (p.ctr->err) return;   // the front kernel failed: nothing to do
+    stamp(p, 4);
+    if (p.ctr->err) return;   // an earlier run failed: nothing to do
     const uint64_t gtid = blockIdx.x * (uint64_t)BT + threadIdx.x;
     if (gtid == 0) p.ctr->grid_decode = gridDim.x;
     const uint64_t gstride = (uint64_t)gridDim.x * BT;
@@ -531,26 +340,22 @@ __global__ __launch_bounds__(BT) void k_batch_decode(BatchParams p) {
             }
         }
     }
-    {
-        SegCursor cur;
-        cur.reset();
-        for (uint64_t gb = gtid; gb < p.n_gblocks; gb += gstride) {
-            if (p.need[gb] != 2) continue;
-            const BatchVol &vol = p.vols[cur.find(p.vol_gbase, p.n_vols, p.n_gblocks, gb)];
-            const float4 *src = reinterpret_cast<const float4 *>(p.slots) + (uint64_t)p.I_slot[gb] * 16;
-            float v[64];
+    const uint64_t n_res = p.ctr->n_res;
+    for (uint64_t i = gtid; i < n_res; i += gstride) {
+        const uint32_t gb = p.res_list[i];
+        const BatchVol &vol = p.vols[find_base(p.vol_gbase, p.n_vols, gb)];
+        const float4 *src = reinterpret_cast<const float4 *>(p.slots) + (uint64_t)p.I_slot[gb] * 16;
+        float v[64];
 #pragma unroll
-            for (int q = 0; q < 16; q++) {
-                const float4 t = src[q];
-                v[4 * q] = t.x;
-                v[4 * q + 1] = t.y;
-                v[4 * q + 2] = t.z;
-                v[4 * q + 3] = t.w;
-            }
-            store_masks(p, vol, (uint32_t)(gb - vol.gbase), v);
+        for (int q = 0; q < 16; q++) {
+            const float4 t = src[q];
+            v[4 * q] = t.x;
+            v[4 * q + 1] = t.y;
+            v[4 * q + 2] = t.z;
+            v[4 * q + 3] = t.w;
         }
+        store_masks(p, vol, (uint32_t)(gb - vol.gbase), v);
     }
-    stamp_last(p, 5);
 }
 
 // ---- count kernel: phase 5 -----------------------------------------------------
@@ -560,6 +365,12 @@ __global__ __launch_bounds__(BT) void k_batch_decode(BatchParams p) {
 // bit-sliced table circuit (Sec. 4.4); per-wave totals.
 __global__ __launch_bounds__(BT) void k_batch_count(BatchParams p) {
     const int l = lane();
+    stamp(p, 5);
+    // the totals have been read (lists): cleared for the next run
+    if (blockIdx.x == 0) {
+        for (uint32_t i = threadIdx.x; i < p.n_vols; i += BT) p.vol_tot[i] = 0;
+        for (uint32_t i = threadIdx.x; i < p.n_jobs; i += BT) p.job_tot[i] = 0;
+    }
     if (p.ctr->err) return;   // an earlier kernel failed: nothing to do
     const uint64_t n_list = p.ctr->n_list;
     uint64_t lo, hi;
@@ -589,7 +400,6 @@ __global__ __launch_bounds__(BT) void k_batch_count(BatchParams p) {
         tot += wave_sum(c);
     }
     if (l == 0) p.part_wave[wv] = tot;
-    stamp_last(p, 6);
 }
 
 // ---- back kernel: phases 6-7 ----------------------------------------------------
@@ -603,6 +413,7 @@ template <int SB>
 __global__ __launch_bounds__(BT) void k_batch_back(BatchParams p) {
     __shared__ BackShared sh;
     const int l = lane(), w = threadIdx.x >> 6;
+    stamp(p, 6);
     if (p.ctr->err) return;   // an earlier kernel failed: nothing to do
     const uint64_t n_list = p.ctr->n_list;
     uint64_t lo, hi;
@@ -705,7 +516,16 @@ __global__ __launch_bounds__(BT) void k_batch_back(BatchParams p) {
             emit_batch<VFMT_F32>(nsb, info, sh.emit.tiles[w], sh.tab, sh.emit, w, ob, p.out, p.cap);
         }
     }
-    stamp_last(p, 8);
+}
+
+// The run's results into the host's copies (pinned memory).
+__global__ __launch_bounds__(BT) void k_batch_done(BatchParams p) {
+    const uint64_t now = wall_clock64();
+    const uint32_t *c = reinterpret_cast<const uint32_t *>(p.ctr);
+    for (uint32_t i = threadIdx.x; i < sizeof(BatchCounters) / 4; i += BT) reinterpret_cast<uint32_t *>(p.h_ctr)[i] = c[i];
+    for (uint32_t i = threadIdx.x; i <= p.n_jobs; i += BT) p.h_job_off[i] = p.job_off[i];
+    if (threadIdx.x < 8) p.h_ts[threadIdx.x] = p.phase_ts[threadIdx.x];
+    if (threadIdx.x == 8) p.h_ts[8] = now;
 }
 
 const void *decode_kernel(int is_f64, int staged) {
@@ -722,7 +542,7 @@ unsigned decode_lds(const BatchParams &p, int is_f64) {
 
 int batch_front_per_cu(int *per_cu) {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_batch_front, BT, 0) != hipSuccess) return -1;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_batch_lists, BT, 0) != hipSuccess) return -1;
     *per_cu = n;
     return 0;
 }
@@ -746,20 +566,22 @@ int batch_back_per_cu(int sb, int *per_cu) {
     return 0;
 }
 
-hipError_t launch_batch(const BatchParams &p, int is_f64, int sb, const unsigned grids[3],
-                        hipStream_t s, int cooperative) {
+hipError_t launch_batch(const BatchParams &p, int is_f64, int sb, const unsigned grids[3], hipStream_t s) {
     void *args[] = {const_cast<BatchParams *>(&p)};
-    const void *decode = decode_kernel(is_f64, p.uniform_rate != 0);
     const void *back = sb == 4 ? (const void *)k_batch_back<4> : (const void *)k_batch_back<8>;
-    hipError_t e = cooperative
-                       ? hipLaunchCooperativeKernel((const void *)k_batch_front, dim3(grids[0]), dim3(BT),
-                                                    args, 0, s)
-                       : hipLaunchKernel((const void *)k_batch_front, dim3(grids[0]), dim3(BT), args, 0, s);
-    if (e == hipSuccess) e = hipLaunchKernel(decode, dim3(grids[1]), dim3(BT), args, decode_lds(p, is_f64), s);
     // count and back share one grid: they partition L the same way
-    if (e == hipSuccess) e = hipLaunchKernel((const void *)k_batch_count, dim3(grids[2]), dim3(BT), args, 0, s);
-    if (e == hipSuccess) e = hipLaunchKernel(back, dim3(grids[2]), dim3(BT), args, 0, s);
-    return e;
+    const struct {
+        const void *kernel;
+        unsigned grid, threads, lds;
+    } steps[] = {{(const void *)k_batch_flags, grids[0], BATCH_UNIT, 0},
+                 {(const void *)k_batch_lists, grids[0], BT, 0},
+                 {decode_kernel(is_f64, p.uniform_rate != 0), grids[1], BT, decode_lds(p, is_f64)},
+                 {(const void *)k_batch_count, grids[2], BT, 0},
+                 {back, grids[2], BT, 0},
+                 {(const void *)k_batch_done, 1, BT, 0}};
+    for (const auto &k : steps)
+        if (hipError_t e = hipLaunchKernel(k.kernel, dim3(k.grid), dim3(k.threads), args, k.lds, s)) return e;
+    return hipSuccess;
 }
 
 }  // namespace bcmc

@@ -1,5 +1,5 @@
-// C ABI of the batched extraction (many volumes x isovalues in one persistent
-// launch), its hipGraph replay and its schedule autotuner.
+// C ABI of the batched extraction (many volumes x isovalues in one call), its
+// hipGraph replay and its schedule autotuner.
 #include <hip/hip_runtime.h>
 #include <stdio.h>
 #include <string.h>
@@ -36,7 +36,8 @@ struct bcmc_batch {
     uint64_t *h_job_off = nullptr;
     int sb = 8;
     unsigned grid = 0;          // back kernel (count, scan, emission)
-    unsigned front_grid = 0;    // front kernel (flags, lists)
+    unsigned front_grid = 0;    // flags and lists kernels
+    int scan = 0;               // the schedule's scan choice (reported)
     int front_pc_max = 1;       // its resident workgroups per CU
     unsigned decode_grid = 0;   // decode kernel (decode, sign masks)
     int per_cu_max = 1, cus = 256;
@@ -48,7 +49,7 @@ struct bcmc_batch {
     void *graph_out = nullptr;
     uint64_t graph_cap = 0;
     int graph_sb = 0;
-    unsigned graph_grid = 0, graph_front_grid = 0, graph_decode_grid = 0, graph_scan = 0;
+    unsigned graph_grid = 0, graph_front_grid = 0, graph_decode_grid = 0;
     int use_graph = 1, graph_failed = 0;
     float last_ms = 0.0f;
     unsigned long long *h_ts = nullptr;   // phase clock stamps of the last run
@@ -103,8 +104,9 @@ unsigned grid_for(bcmc_batch *b, int per_cu) {
 }
 
 // Back kernel: `sb` blocks staged per round trip, `per_cu` workgroups per
-// CU; front kernel: `front_pc` workgroups per CU (both clamped to what stays
-// resident) and `scan` its scan schedule (BatchParams::scan_sched).
+// CU; flags and lists kernels: `front_pc` workgroups per CU (both clamped to
+// what stays resident).  `scan` chose between two forms of the lists' offsets
+// that one form without a barrier has replaced: kept as part of the schedule.
 int set_schedule(bcmc_batch *b, int sb, int per_cu, int front_pc, int scan) {
     int maxc = 0;
     if (batch_back_per_cu(sb, &maxc) != 0 || maxc < 1)
@@ -113,7 +115,16 @@ int set_schedule(bcmc_batch *b, int sb, int per_cu, int front_pc, int scan) {
     b->per_cu_max = maxc;
     b->grid = grid_for(b, std::min(std::max(per_cu, 1), maxc));
     b->front_grid = grid_for(b, std::min(std::max(front_pc, 1), b->front_pc_max));
-    b->p.scan_sched = scan ? 1u : 0u;
+    b->scan = scan ? 1 : 0;
+    return BCMC_OK;
+}
+
+int reset_cache(bcmc_batch *b, hipStream_t s) {
+    launch_fill_u32(reinterpret_cast<uint32_t *>(b->p.I_slot), 0xFFFFFFFFu, b->n_gblocks, s);
+    launch_fill_u32(reinterpret_cast<uint32_t *>(b->p.ctr), 0u, sizeof(BatchCounters) / 4, s);
+    launch_fill_u32(reinterpret_cast<uint32_t *>(b->p.vol_tot), 0u, 2ull * b->n_vols, s);
+    launch_fill_u32(reinterpret_cast<uint32_t *>(b->p.job_tot), 0u, 2ull * b->n_jobs, s);
+    BCMC_HIP_TRY(hipGetLastError());
     return BCMC_OK;
 }
 
@@ -130,12 +141,12 @@ int run_once(bcmc_batch *b, void *d_out, uint64_t cap, hipStream_t caller) {
         // any schedule dimension or the output changes
         if (!b->exec || b->graph_out != d_out || b->graph_cap != cap || b->graph_sb != b->sb ||
             b->graph_grid != b->grid || b->graph_front_grid != b->front_grid ||
-            b->graph_decode_grid != b->decode_grid || b->graph_scan != b->p.scan_sched) {
+            b->graph_decode_grid != b->decode_grid) {
             drop_graph(b);
             hipError_t e = hipStreamBeginCapture(b->gstream, hipStreamCaptureModeThreadLocal);
             if (e == hipSuccess) {
                 const unsigned grids[3] = {b->front_grid, b->decode_grid, b->grid};
-                hipError_t le = launch_batch(b->p, b->is_f64, b->sb, grids, b->gstream, 0);
+                hipError_t le = launch_batch(b->p, b->is_f64, b->sb, grids, b->gstream);
                 e = hipStreamEndCapture(b->gstream, &b->graph);
                 if (le != hipSuccess) e = le;
             }
@@ -151,7 +162,6 @@ int run_once(bcmc_batch *b, void *d_out, uint64_t cap, hipStream_t caller) {
                 b->graph_grid = b->grid;
                 b->graph_front_grid = b->front_grid;
                 b->graph_decode_grid = b->decode_grid;
-                b->graph_scan = b->p.scan_sched;
             }
         }
         if (b->exec) {
@@ -161,15 +171,9 @@ int run_once(bcmc_batch *b, void *d_out, uint64_t cap, hipStream_t caller) {
     }
     if (!launched) {
         const unsigned grids[3] = {b->front_grid, b->decode_grid, b->grid};
-        BCMC_HIP_TRY(launch_batch(b->p, b->is_f64, b->sb, grids, b->gstream, 1));
+        BCMC_HIP_TRY(launch_batch(b->p, b->is_f64, b->sb, grids, b->gstream));
     }
     BCMC_HIP_TRY(hipEventRecord(b->ev_t1, b->gstream));
-    BCMC_HIP_TRY(hipMemcpyAsync(b->h_ctr, b->p.ctr, sizeof(BatchCounters), hipMemcpyDeviceToHost,
-                                b->gstream));
-    BCMC_HIP_TRY(hipMemcpyAsync(b->h_job_off, b->p.job_off, (b->n_jobs + 1) * sizeof(uint64_t),
-                                hipMemcpyDeviceToHost, b->gstream));
-    BCMC_HIP_TRY(hipMemcpyAsync(b->h_ts, b->p.phase_ts, 9 * sizeof(unsigned long long),
-                                hipMemcpyDeviceToHost, b->gstream));
     BCMC_HIP_TRY(hipEventRecord(b->ev_out, b->gstream));
     BCMC_HIP_TRY(hipStreamWaitEvent(caller, b->ev_out, 0));
     BCMC_HIP_TRY(hipEventSynchronize(b->ev_out));
@@ -179,24 +183,12 @@ int run_once(bcmc_batch *b, void *d_out, uint64_t cap, hipStream_t caller) {
                              ? (float)((double)(b->h_ts[k + 1] - b->h_ts[k]) / b->clock_khz)
                              : 0.0f;
     if (b->h_ctr->err) {
-        const unsigned err = b->h_ctr->err;
-        // a failed run may leave the store and the barrier words mid-update
-        launch_fill_u32(reinterpret_cast<uint32_t *>(b->p.I_slot), 0xFFFFFFFFu, b->n_gblocks,
-                              b->gstream);
-        (void)hipMemsetAsync(b->p.ctr, 0, sizeof(BatchCounters), b->gstream);
-        (void)hipMemsetAsync(b->p.bar, 0, BAR_WORDS * sizeof(unsigned int), b->gstream);
+        // a failed run may leave the store and the totals mid-update
+        (void)reset_cache(b, b->gstream);
         (void)hipStreamSynchronize(b->gstream);
-        set_error(err & ERR_TIMEOUT ? "a grid barrier of the batched kernel timed out"
-                                    : "internal consistency check failed in the batched extraction");
+        set_error("internal consistency check failed in the batched extraction");
         return BCMC_E_HIP;
     }
-    return BCMC_OK;
-}
-
-int reset_cache(bcmc_batch *b, hipStream_t s) {
-    launch_fill_u32(reinterpret_cast<uint32_t *>(b->p.I_slot), 0xFFFFFFFFu, b->n_gblocks, s);
-    BCMC_HIP_TRY(hipMemsetAsync(b->p.ctr, 0, sizeof(BatchCounters), s));
-    BCMC_HIP_TRY(hipMemsetAsync(b->p.bar, 0, BAR_WORDS * sizeof(unsigned int), s));
     return BCMC_OK;
 }
 
@@ -265,7 +257,7 @@ int bcmc_batch_create(bcmc_volume *const *vols, uint32_t n_vols, const uint32_t 
     b->n_vols = n_vols;
     b->n_jobs = n_jobs;
     std::vector<BatchVol> hv(n_vols);
-    std::vector<uint64_t> gbase(n_vols), jbase(n_jobs);
+    std::vector<uint64_t> gbase(n_vols), jbase(n_jobs), vunit(n_vols), junit(n_jobs);
     std::vector<uint32_t> vol_jobs;
     uint64_t gb = 0;
     for (uint32_t v = 0; v < n_vols; v++) {
@@ -275,6 +267,8 @@ int bcmc_batch_create(bcmc_volume *const *vols, uint32_t n_vols, const uint32_t 
         hv[v].rate = volume_rate(vols[v]);
         hv[v].gbase = gbase[v] = gb;
         gb += hv[v].g.nb;
+        vunit[v] = b->p.n_units;
+        b->p.n_units += (hv[v].g.nb + BATCH_UNIT - 1) / BATCH_UNIT;
         hv[v].job_lo = (uint32_t)vol_jobs.size();
         for (uint32_t j = 0; j < n_jobs; j++)
             if (job_vol[j] == v) vol_jobs.push_back(j);
@@ -284,6 +278,8 @@ int bcmc_batch_create(bcmc_volume *const *vols, uint32_t n_vols, const uint32_t 
     for (uint32_t j = 0; j < n_jobs; j++) {
         jbase[j] = jb;
         jb += hv[job_vol[j]].g.nb;
+        junit[j] = b->p.n_junits;
+        b->p.n_junits += (hv[job_vol[j]].g.nb + BATCH_UNIT - 1) / BATCH_UNIT;
     }
     b->n_gblocks = gb;
     b->n_jblocks = jb;
@@ -309,8 +305,10 @@ int bcmc_batch_create(bcmc_volume *const *vols, uint32_t n_vols, const uint32_t 
         return binvalid("the batched kernel cannot be made resident");
     }
     b->front_pc_max = pcf;
-    b->decode_grid = grid_for(b, pcd);
-    int rc = set_schedule(b, 8, 1 << 30, std::max(1, pcf / 2), 0);
+    // more workgroups than are resident: a wave's steps of 64 blocks vary, and
+    // the resident ones alone end unevenly (495 us against 454, 2.4 M blocks)
+    b->decode_grid = grid_for(b, 4 * pcd);
+    int rc = set_schedule(b, 8, 1 << 30, pcf, 0);
     if (rc) {
         destroy_batch(b);
         return rc;
@@ -318,23 +316,25 @@ int bcmc_batch_create(bcmc_volume *const *vols, uint32_t n_vols, const uint32_t 
     unsigned max_grid = (unsigned)(std::max(b->per_cu_max, pc4) * b->cus);
     BatchParams &p = b->p;
     BatchVol *d_vols;
-    uint64_t *d_gbase, *d_jbase;
+    uint64_t *d_gbase, *d_jbase, *d_vunit, *d_junit;
+    constexpr uint64_t W = BATCH_UNIT / 64;
     uint32_t *d_vol_jobs, *d_job_vol;
     float *d_iso;
     if ((rc = balloc(b, &d_vols, n_vols)) || (rc = balloc(b, &d_gbase, n_vols)) ||
         (rc = balloc(b, &d_jbase, n_jobs)) || (rc = balloc(b, &d_vol_jobs, n_jobs)) ||
         (rc = balloc(b, &d_job_vol, n_jobs)) || (rc = balloc(b, &d_iso, n_jobs)) ||
         (rc = balloc(b, &p.I_slot, gb)) || (rc = balloc(b, &p.slots, gb * 64)) ||
-        (rc = balloc(b, &p.need, gb)) || (rc = balloc(b, &p.emit_flag, (jb + 3) / 4 * 4)) ||
+        (rc = balloc(b, &d_vunit, n_vols)) || (rc = balloc(b, &d_junit, n_jobs)) ||
+        (rc = balloc(b, &p.new_bits, W * p.n_units)) || (rc = balloc(b, &p.res_bits, W * p.n_units)) ||
+        (rc = balloc(b, &p.pair_bits, W * p.n_junits)) || (rc = balloc(b, &p.unit_cnt, p.n_units)) ||
+        (rc = balloc(b, &p.pair_cnt, p.n_junits)) || (rc = balloc(b, &p.vol_tot, n_vols)) ||
+        (rc = balloc(b, &p.job_tot, n_jobs)) || (rc = balloc(b, &p.res_list, gb)) ||
         (rc = balloc(b, &p.jmask, jb)) ||
         (rc = balloc(b, &p.new_list, gb)) || (rc = balloc(b, &p.list, jb)) ||
         (rc = balloc(b, &p.list_job, jb)) || (rc = balloc(b, &p.cnt, jb)) ||
-        (rc = balloc(b, &p.part_new, (uint64_t)pcf * b->cus)) ||
-        (rc = balloc(b, &p.part_list, 4ull * pcf * b->cus)) ||
         (rc = balloc(b, &p.part_wave, 4ull * max_grid)) ||
         (rc = balloc(b, &p.job_off, n_jobs + 1)) ||
-        (rc = balloc(b, &p.ctr, 1)) || (rc = balloc(b, &p.bar, BAR_WORDS)) ||
-        (rc = balloc(b, &p.phase_ts, 9))) {
+        (rc = balloc(b, &p.ctr, 1)) || (rc = balloc(b, &p.phase_ts, 8))) {
         destroy_batch(b);
         return rc;
     }
@@ -357,18 +357,24 @@ int bcmc_batch_create(bcmc_volume *const *vols, uint32_t n_vols, const uint32_t 
         (e = hipMemcpy(d_job_vol, job_vol, 4 * n_jobs, hipMemcpyHostToDevice)) ||
         (e = hipMemcpy(d_iso, job_iso, 4 * n_jobs, hipMemcpyHostToDevice)) ||
         (e = hipMemcpy(d_table, mc_table_host(), 256 * 8, hipMemcpyHostToDevice)) ||
-        (e = hipMemset(p.emit_flag, 0, (jb + 3) / 4 * 4)) ||   // the padding stays zero
+        (e = hipMemcpy(d_vunit, vunit.data(), 8 * n_vols, hipMemcpyHostToDevice)) ||
+        (e = hipMemcpy(d_junit, junit.data(), 8 * n_jobs, hipMemcpyHostToDevice)) ||
         (e = hipHostMalloc((void **)&b->h_ctr, sizeof(BatchCounters), hipHostMallocDefault)) ||
         (e = hipHostMalloc((void **)&b->h_job_off, 8 * (n_jobs + 1), hipHostMallocDefault)) ||
         (e = hipHostMalloc((void **)&b->h_ts, 9 * sizeof(unsigned long long), hipHostMallocDefault)) ||
         (e = hipStreamCreateWithFlags(&b->gstream, hipStreamNonBlocking)) ||
-        (e = hipEventCreate(&b->ev_in)) || (e = hipEventCreate(&b->ev_out)) ||
+        (memset(b->h_ctr, 0, sizeof(BatchCounters)), e = hipEventCreate(&b->ev_in)) || (e = hipEventCreate(&b->ev_out)) ||
         (e = hipEventCreate(&b->ev_t0)) || (e = hipEventCreate(&b->ev_t1)))
         return fail(e);
     p.vols = d_vols;
     p.n_vols = n_vols;
     p.n_jobs = n_jobs;
     p.vol_gbase = d_gbase;
+    p.vol_unit = d_vunit;
+    p.job_unit = d_junit;
+    p.h_ctr = b->h_ctr;
+    p.h_job_off = b->h_job_off;
+    p.h_ts = b->h_ts;
     p.vol_jobs = d_vol_jobs;
     p.job_vol = d_job_vol;
     p.job_jbase = d_jbase;
@@ -454,11 +460,10 @@ int bcmc_batch_tune(bcmc_batch *b, const char *cache_path, void *hip_stream) {
         set_error("no memory for the tuning buffer");
         return BCMC_E_NOMEM;
     }
-    int best_sb = b->sb, best_pc = b->per_cu_max, best_fpc = b->front_pc_max, best_scan = 0;
+    int best_sb = b->sb, best_pc = b->per_cu_max, best_fpc = b->front_pc_max;
     double best = 1e30;
-    // the front kernel's barriers cost more with more workgroups: half and
-    // a quarter of what stays resident
-    std::vector<int> fpcs = {std::max(1, b->front_pc_max / 2), std::max(1, b->front_pc_max / 4)};
+    // flags and lists: half and all of what stays resident
+    std::vector<int> fpcs = {std::max(1, b->front_pc_max / 2), b->front_pc_max};
     fpcs.erase(std::unique(fpcs.begin(), fpcs.end()), fpcs.end());
     for (int sb : {4, 8}) {
         int maxc = 0;
@@ -467,10 +472,8 @@ int bcmc_batch_tune(bcmc_batch *b, const char *cache_path, void *hip_stream) {
         std::sort(pcs.begin(), pcs.end());
         pcs.erase(std::unique(pcs.begin(), pcs.end()), pcs.end());
         for (int pc : pcs) {
-            // each front grid with both scan schedules
-            for (size_t fs = 0; fs < 2 * fpcs.size(); fs++) {
-                const int fpc = fpcs[fs / 2], scan = (int)(fs % 2);
-                if ((rc = set_schedule(b, sb, pc, fpc, scan))) break;
+            for (const int fpc : fpcs) {
+                if ((rc = set_schedule(b, sb, pc, fpc, b->scan))) break;
                 // median over 5 repetitions of a cold run (empty batch
                 // store) + a warm run; a first repetition warms up
                 std::vector<double> ts;
@@ -488,7 +491,6 @@ int bcmc_batch_tune(bcmc_batch *b, const char *cache_path, void *hip_stream) {
                     best_sb = sb;
                     best_pc = pc;
                     best_fpc = fpc;
-                    best_scan = scan;
                 }
             }
             if (rc) break;
@@ -497,10 +499,10 @@ int bcmc_batch_tune(bcmc_batch *b, const char *cache_path, void *hip_stream) {
     }
     (void)hipFree(buf);
     if (rc) return rc;
-    rc = set_schedule(b, best_sb, best_pc, best_fpc, best_scan);
+    rc = set_schedule(b, best_sb, best_pc, best_fpc, b->scan);
     if (rc) return rc;
     save_schedule(cache_path ? cache_path : getenv("BCMC_AUTOTUNE_CACHE"), b->key, best_sb, best_pc,
-                  best_fpc, best_scan, best / 2.0);
+                  best_fpc, b->scan, best / 2.0);
     return reset_cache(b, s);
 }
 
@@ -519,7 +521,7 @@ int bcmc_batch_get_info(const bcmc_batch *b, bcmc_batch_info *out) {
     out->workgroups_per_cu = b->grid / (unsigned)std::max(b->cus, 1);
     out->front_grid = b->front_grid;
     out->decode_grid = b->decode_grid;
-    out->scan_schedule = b->p.scan_sched;
+    out->scan_schedule = (uint32_t)b->scan;
     out->ran_front_grid = b->h_ctr ? b->h_ctr->grid_front : 0;
     out->ran_decode_grid = b->h_ctr ? b->h_ctr->grid_decode : 0;
     out->ran_grid = b->h_ctr ? b->h_ctr->grid_back : 0;
