@@ -27,6 +27,9 @@ struct BatchCounters {
     unsigned int err;
     unsigned int grid_front, grid_decode, grid_back;   // grids the kernels ran with
     unsigned int pad[2];
+    struct alignas(128) Xcd {        // vertices per XCD eighth of the chunks, a cache line each
+        unsigned long long verts;
+    } xcd[8];
 };
 
 // Blocks of one volume that a workgroup of the flags kernel takes at a time.
@@ -61,7 +64,7 @@ struct BatchParams {
     uint32_t *list;              // [n_jblocks] (job-major, block-ascending)
     uint32_t *list_job;          // [n_jblocks] job of each list entry
     uint32_t *cnt;               // [n_jblocks] vertex count of each list entry
-    uint64_t *part_wave;         // [back grid * 4] per-wave vertex counts
+    uint32_t *chunk_tot;         // [mc_chunk_slots(n_jblocks)] vertices of each chunk of the list
     uint64_t *job_off;           // [n_jobs + 1] vertex offsets of the jobs' soups
     const uint64_t *mc_table;
     void *out;

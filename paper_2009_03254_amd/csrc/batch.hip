@@ -21,11 +21,11 @@
 //           place is the sum of the totals and counts before it
 //   decode  the new blocks into slots slot_base + rank; sign masks of every
 //           used block for every job of its volume
-//   count   count pass over L from the sign masks (Sec. 4.4); every wave owns
-//           one contiguous share of L
-//   back    each workgroup sums the per-wave totals before its waves, then
-//           the emission over L (Sec. 4.5), offsets by a running wave scan of
-//           the counts; per-job output offsets
+//   count   count pass over L from the sign masks (Sec. 4.4), in the chunks of
+//           xcd_chunks; totals per chunk and per XCD eighth
+//   back    the emission over L (Sec. 4.5), chunk by chunk: a wave adds up the
+//           totals before each of its chunks, a wave scan of the chunk's counts
+//           gives its entries' offsets; per-job output offsets
 //   done    the run's results to the host's copies
 #include <stdint.h>
 
@@ -78,22 +78,6 @@ __device__ __forceinline__ void stamp(const BatchParams &p, int k) {
     if (blockIdx.x == 0 && threadIdx.x == 0) p.phase_ts[k] = wall_clock64();
 }
 
-// Contiguous share [lo, hi) of n items for the calling wave: the workgroups
-// of one XCD (blockIdx % 8) take one contiguous eighth of the range, so that
-// blocks whose halos overlap are staged through the same L2; returns the
-// share's rank in item order.
-__device__ __forceinline__ uint32_t wave_share(uint64_t n, uint64_t &lo, uint64_t &hi) {
-    const uint32_t G = gridDim.x, g = blockIdx.x;
-    const uint32_t logical = (g % 8u) * (G / 8u) + g / 8u;
-    const uint64_t waves = (uint64_t)G * (BT / 64);
-    const uint32_t wv = logical * (BT / 64) + (threadIdx.x >> 6);
-    const uint64_t chunk = (n + waves - 1) / waves;
-    lo = wv * chunk;
-    if (lo > n) lo = n;
-    hi = lo + chunk < n ? lo + chunk : n;
-    return wv;
-}
-
 // ---- flags -------------------------------------------------------------------
 // Per block, with its volume uniform over the workgroup's unit: the ranges of
 // its 3x3x3 neighbourhood (indices clamped into the volume: a clamped
@@ -113,6 +97,7 @@ __global__ __launch_bounds__(BATCH_UNIT) void k_batch_flags(BatchParams p) {
     stamp(p, 0);
     stamp(p, 1);
     if (blockIdx.x == 0 && threadIdx.x == 0) p.ctr->grid_front = gridDim.x;
+    if (blockIdx.x == 0 && threadIdx.x < 8) p.ctr->xcd[threadIdx.x].verts = 0;   // for the count pass
     const int w = (int)wave_id(), l = lane();
     for (uint32_t u = blockIdx.x; u < p.n_units; u += gridDim.x) {
         const uint32_t vi = find_base(p.vol_unit, p.n_vols, u);
@@ -358,12 +343,12 @@ __global__ __launch_bounds__(BT) void k_batch_decode(BatchParams p) {
     }
 }
 
-// ---- count kernel: phase 5 -----------------------------------------------------
-// One lane per (job, block) pair of L, each wave over its share of L (the
-// partition the emission uses: same grid): the cases of the block's 64 cells
-// from the sign masks of its octet, the triangle count per case by the
-// bit-sliced table circuit (Sec. 4.4); per-wave totals.
+// ---- count kernel ---------------------------------------------------------------
+// One lane per (job, block) pair of L, over the chunks that the emission uses:
+// the cases of the block's 64 cells from the sign masks of its octet, the
+// triangle count per case by the bit-sliced table circuit (Sec. 4.4).
 __global__ __launch_bounds__(BT) void k_batch_count(BatchParams p) {
+    __shared__ uint64_t s_v[MC_WAVES];
     const int l = lane();
     stamp(p, 5);
     // the totals have been read (lists): cleared for the next run
@@ -372,14 +357,14 @@ __global__ __launch_bounds__(BT) void k_batch_count(BatchParams p) {
         for (uint32_t i = threadIdx.x; i < p.n_jobs; i += BT) p.job_tot[i] = 0;
     }
     if (p.ctr->err) return;   // an earlier kernel failed: nothing to do
-    const uint64_t n_list = p.ctr->n_list;
-    uint64_t lo, hi;
-    const uint32_t wv = wave_share(n_list, lo, hi);
-    uint64_t tot = 0;
-    for (uint64_t i0 = lo; i0 < hi; i0 += 64) {
-        const uint64_t idx = i0 + l;
+    const uint64_t n_list = uniform64(p.ctr->n_list);
+    const uint32_t cs = mc_chunk_size(n_list, gridDim.x * MC_WAVES);
+    const ChunkRange cr = xcd_chunks((n_list + cs - 1) / cs);
+    uint64_t verts = 0;
+    for (uint64_t k = cr.first; k < cr.end; k += cr.stride) {
+        const uint64_t idx = k * cs + l;
         uint32_t c = 0;
-        if (idx < hi) {
+        if (l < (int)cs && idx < n_list) {
             const uint32_t j = p.list_job[idx];
             const uint64_t jb = p.job_jbase[j];
             const BatchVol &vol = p.vols[p.job_vol[j]];
@@ -397,75 +382,62 @@ __global__ __launch_bounds__(BT) void k_batch_count(BatchParams p) {
                       4u * (uint32_t)__popcll(n2 & V));
             p.cnt[idx] = c;
         }
-        tot += wave_sum(c);
+        c = wave_sum(c);
+        if (l == 0) p.chunk_tot[k] = c;
+        verts += c;
     }
-    if (l == 0) p.part_wave[wv] = tot;
+    if (l == 0) s_v[wave_id()] = verts;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        verts = 0;
+        for (int k = 0; k < MC_WAVES; k++) verts += s_v[k];
+        if (verts) atomicAdd(&p.ctr->xcd[blockIdx.x % 8u].verts, (unsigned long long)verts);
+    }
 }
 
-// ---- back kernel: phases 6-7 ----------------------------------------------------
+// ---- back kernel ----------------------------------------------------
 struct BackShared {
     EmitShared emit;
     uint64_t tab[256];   // the triangle table (per-lane lookups at LDS latency)
-    uint64_t w64[2][BT / 64];
 };
 
 template <int SB>
 __global__ __launch_bounds__(BT) void k_batch_back(BatchParams p) {
     __shared__ BackShared sh;
-    const int l = lane(), w = threadIdx.x >> 6;
+    const int l = lane(), w = (int)wave_id();
     stamp(p, 6);
     if (p.ctr->err) return;   // an earlier kernel failed: nothing to do
-    const uint64_t n_list = p.ctr->n_list;
-    uint64_t lo, hi;
-    const uint32_t wv = wave_share(n_list, lo, hi);
-
-    // ---- phase 6: each workgroup sums the per-wave totals before its first
-    // wave and all of them (no grid barrier: the counts are a kernel earlier)
-    for (int i = threadIdx.x; i < 256; i += BT) sh.tab[i] = p.mc_table[i];   // published by the barrier below
+    const uint64_t n_list = uniform64(p.ctr->n_list);
+    const uint32_t cs = mc_chunk_size(n_list, gridDim.x * MC_WAVES);   // the count pass's chunks
+    const ChunkRange cr = xcd_chunks((n_list + cs - 1) / cs);
+    for (int i = threadIdx.x; i < 256; i += BT) sh.tab[i] = p.mc_table[i];
     if (threadIdx.x < 16) sh.emit.edge[threadIdx.x] = edge_entry((int)threadIdx.x);
-    const uint32_t W = gridDim.x * (BT / 64), wv0 = wv - (uint32_t)w;
-    uint64_t before = 0, all = 0;
-    for (uint32_t i0 = threadIdx.x; i0 < W; i0 += 8u * BT) {   // 8 loads in flight at a time
-        uint64_t v[8];
-#pragma unroll
-        for (int j = 0; j < 8; j++) v[j] = i0 + (uint32_t)j * BT < W ? p.part_wave[i0 + (uint32_t)j * BT] : 0ull;
-#pragma unroll
-        for (int j = 0; j < 8; j++) {
-            all += v[j];
-            if (i0 + (uint32_t)j * BT < wv0) before += v[j];
-        }
-    }
-    before = wave_sum(before);
-    all = wave_sum(all);
-    if (l == 0) {
-        sh.w64[0][w] = before;
-        sh.w64[1][w] = all;
-    }
     __syncthreads();
     uint64_t base = 0, total = 0;
-#pragma unroll
-    for (int k = 0; k < BT / 64; k++) {
-        base += sh.w64[0][k];
-        total += sh.w64[1][k];
+    for (uint32_t x = 0; x < 8; x++) {
+        const uint64_t tx = p.ctr->xcd[x].verts;
+        base += x < blockIdx.x % 8u ? tx : 0ull;
+        total += tx;
     }
-    for (uint32_t k = 0; k < (uint32_t)w; k++) base += p.part_wave[wv0 + k];
+    base = uniform64(base);
+    total = uniform64(total);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         p.ctr->total_verts = total;
         p.ctr->grid_back = gridDim.x;
     }
+    if (cr.first < cr.end) base += chunks_sum(p.chunk_tot, cr.lo, cr.first);
     stamp(p, 7);
 
-    // ---- phase 7: emission (Sec. 4.5) and the jobs' output offsets --------------
+    // emission (Sec. 4.5) and the jobs' output offsets
     if (n_list == 0 && blockIdx.x == 0)
         for (uint32_t j = threadIdx.x; j <= p.n_jobs; j += BT) p.job_off[j] = 0;
     const LaneGeom q = lane_geom();
-    for (uint64_t i0 = lo; i0 < hi; i0 += 64) {
-        const uint64_t idx = i0 + l;
-        const bool valid = idx < hi;
+    for (uint64_t k = cr.first; k < cr.end; k += cr.stride) {
+        const uint64_t idx = k * cs + l;
+        const bool valid = l < (int)cs && idx < n_list;
         const uint32_t c = valid ? p.cnt[idx] : 0u;
         const uint32_t incl = wave_incl_scan(c);
         const uint64_t off = base + incl - c;
-        base += __shfl(incl, 63, 64);
         uint32_t j = 0;
         if (valid) {
             j = p.list_job[idx];
@@ -515,6 +487,7 @@ __global__ __launch_bounds__(BT) void k_batch_back(BatchParams p) {
             };
             emit_batch<VFMT_F32>(nsb, info, sh.emit.tiles[w], sh.tab, sh.emit, w, ob, p.out, p.cap);
         }
+        if (k + cr.stride < cr.end) base += chunks_sum(p.chunk_tot, k, k + cr.stride);
     }
 }
 

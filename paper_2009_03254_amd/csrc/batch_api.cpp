@@ -332,7 +332,7 @@ int bcmc_batch_create(bcmc_volume *const *vols, uint32_t n_vols, const uint32_t 
         (rc = balloc(b, &p.jmask, jb)) ||
         (rc = balloc(b, &p.new_list, gb)) || (rc = balloc(b, &p.list, jb)) ||
         (rc = balloc(b, &p.list_job, jb)) || (rc = balloc(b, &p.cnt, jb)) ||
-        (rc = balloc(b, &p.part_wave, 4ull * max_grid)) ||
+        (rc = balloc(b, &p.chunk_tot, std::max<uint64_t>(mc_chunk_slots(jb), 4ull * max_grid))) ||
         (rc = balloc(b, &p.job_off, n_jobs + 1)) ||
         (rc = balloc(b, &p.ctr, 1)) || (rc = balloc(b, &p.phase_ts, 8))) {
         destroy_batch(b);
