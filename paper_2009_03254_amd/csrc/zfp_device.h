@@ -306,111 +306,152 @@ __host__ __device__ __forceinline__ void decode_block_from(BR br, int rate, floa
 // precision deposits each plane word into the coefficients below n_{k+1}.
 //
 // Word w of the lane's block is st[w * STAGE_STRIDE]; rec holds the lane's
-// P/2 record words (plane k's record is the low half of word k/2 for even
-// k, the high half for odd k: group-test bits in the low byte, the advance
-// of n in the high byte; whole words are written, an odd plane's record
-// waits for its even neighbour).
+// P/2 record words (plane k's record is their k-th half-word: group-test bits
+// in the low byte, the advance of n in the high byte).
 template <bool F64>
 struct RecLayout {
     static constexpr int STRIDE = Prec<F64>::P / 2 + 1;   // 32-bit words per lane (odd: no bank conflicts)
     static constexpr int WORDS = 64 * STRIDE / 2;          // 64-bit words of record area per wave
 };
 
+// The word of the lane's block that holds bit off (the mask tells the compiler
+// that a 24-bit multiply does).
+template <class SP>
+__host__ __device__ __forceinline__ SP staged_word(SP st, uint32_t off) {
+    return st + (((off >> 6) & 0xFFFFu) * (uint32_t)STAGE_STRIDE);
+}
+
 // The 64 stream bits from bit offset off (< 64 * rate) on.  Reads words
 // off/64 and off/64 + 1: the word past the block's last one lies in the
 // wave's record area (which follows the staged words), in bounds of the
 // wave's LDS; its bits are masked out by every caller.
-__host__ __device__ __forceinline__ uint64_t peek_staged(const uint64_t *st, int off) {
-    const uint32_t wi = (uint32_t)off >> 6, sh = (uint32_t)off & 63u;
-    const uint64_t *p = st + wi * (uint32_t)STAGE_STRIDE;
+template <class SP>
+__host__ __device__ __forceinline__ uint64_t peek_staged(SP st, uint32_t off) {
+    const SP p = staged_word(st, off);
     const uint64_t w0 = p[0], w1 = p[STAGE_STRIDE];
-    return (w0 >> sh) | ((w1 << 1) << (63u - sh));
+    return (w0 >> (off & 63u)) | ((w1 << 1) << (~off & 63u));
+}
+
+// Pass 2 of one visited plane, in stream order: its word (the bits of its
+// first nn coefficients, read at offset o, and ones at the found coefficients
+// that its group tests passed over), given its record.
+struct PlaneState {
+    uint32_t o, nn;          // where the plane's bits begin (o < end), significant coefficients before it
+    uint64_t above, rest;    // bits nn .. 63; the found coefficients from nn on
+};
+template <class SP>
+__host__ __device__ __forceinline__ uint64_t plane_word(SP st, uint32_t end, uint32_t rec, PlaneState &s) {
+    const int past = (int)(s.o + 64u - end);   // bits of the window past the end
+    uint64_t x = peek_staged(st, s.o) & ~s.above & (~0ull >> (past > 0 ? past : 0));
+    s.o += s.nn + (rec & 0xFFu);
+    s.nn += rec >> 8;
+    s.above = (~0ull << (s.nn >> 1)) << (s.nn - (s.nn >> 1));   // nn may be 64
+    x |= s.rest & ~s.above;
+    s.rest &= s.above;
+    return x;
 }
 
 __host__ __device__ __forceinline__ int ctz64(uint64_t x) {   // x != 0
     return (int)__builtin_ctzll(x);
 }
 
+// Index of the lowest set bit of x, at least 32 bits' worth more than any index
+// when there is none (v_ffbl_b32 gives ~0).
+__host__ __device__ __forceinline__ uint32_t ffbl(uint32_t x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    uint32_t r;
+    asm("v_ffbl_b32 %0, %1" : "=v"(r) : "v"(x));
+    return r;
+#else
+    return x ? (uint32_t)__builtin_ctz(x) : ~0u;
+#endif
+}
+
 // Pass 1 (after a nonzero block header): returns the found set; kend is the
 // lowest plane visited, and the records of planes kend..P-1 are written.
 // The group tests form one serial chain (each starts where the previous one
-// ended), so the words under the read position are held in registers (words
-// wb and wb + 1) and fetched again only when the position moves to another
-// word: most steps then wait on no memory read.
-template <bool F64>
-__host__ __device__ __forceinline__ uint64_t staged_pass1(const uint64_t *st, uint32_t *rec, int rate,
-                                                          int &kend) {
+// ended), one per step.  The words under the read position are held in
+// registers and fetched again only when it moves to another word.  A step is
+// free of branches but for the end of a plane: a test bit of 0 ends it; a 1 is
+// followed by zeros up to the next significant coefficient, which the run may
+// not pass: coefficient 63 (implied) and the end of the bits (the run stops
+// there) bound it at lim; after a find, a 0 as the next test (mostly still in
+// the window) ends the plane in the same step.  The planes left when
+// every coefficient is significant have no group tests: their loop only counts.
+typedef uint16_t __attribute__((may_alias)) rec_half;
+__host__ __device__ __forceinline__ rec_half *rec_halves(uint32_t *rec) { return reinterpret_cast<rec_half *>(rec); }
+// The staging area as LDS addresses: 32-bit address arithmetic (through
+// generic pointers every word's address took a 64-bit multiply-add).
+typedef const uint64_t __attribute__((address_space(3))) *lds_words;
+typedef uint32_t __attribute__((address_space(3))) *lds_rec;
+__host__ __device__ __forceinline__ uint16_t __attribute__((address_space(3))) *rec_halves(lds_rec rec) {
+    return (uint16_t __attribute__((address_space(3))) *)rec;
+}
+template <bool F64, class SP, class RP>
+__host__ __device__ __forceinline__ uint64_t staged_pass1(SP st, RP rec, int rate, int &kend) {
     using T = Prec<F64>;
-    const int end_bits = 64 * rate;
-    int off = 1 + T::EBITS, budget = end_bits - off, n = 0, k = T::P - 1;
-    int gstart = 0, nstart = 0;
-    bool at_start = true;
+    const auto r16 = rec_halves(rec);
+    const uint32_t end = 64u * (uint32_t)rate;
+    uint32_t off = 1 + T::EBITS, n = 0;
+    uint32_t gs = off, ns = 0;   // where the plane's group tests began, and n there
+    int k = T::P - 1;
     uint64_t found = 0;
-    uint32_t pend = 0;   // record of the odd plane above, written with its even neighbour
-    int wb = 0;
-    uint64_t w0 = st[0], w1 = rate > 1 ? st[STAGE_STRIDE] : 0ull;
-    while (k >= 0 && budget > 0) {
-        if (at_start) {   // skip the bits of the n significant coefficients
-            const int m = n < budget ? n : budget;
-            off += m;
-            budget -= m;
-            gstart = off;
-            nstart = n;
-            at_start = false;
+    uint32_t wb = 0;
+    uint64_t w0 = st[0], w1 = st[STAGE_STRIDE] << 1;   // (past the last word: bits that lim keeps out)
+    for (;;) {   // n < 64 and off < end
+        const uint32_t wi = off >> 6;
+        if (wi != wb) {
+            wb = wi;
+            const SP p = staged_word(st, off);
+            w0 = p[0];
+            w1 = p[STAGE_STRIDE] << 1;
         }
-        bool end = true;
-        if (n < 64 && budget > 0) {
-            // one group test: a 0 ends the plane; a 1 is followed by zeros up
-            // to the next significant coefficient, which the run may not
-            // pass: coefficient 63 (implied) and the budget (the run stops
-            // where the bits end) bound it at lim
-            const int wi = off >> 6;   // < rate: budget > 0
-            if (wi != wb) {
-                wb = wi;
-                w0 = st[wi * STAGE_STRIDE];
-                w1 = wi + 1 < rate ? st[(wi + 1) * STAGE_STRIDE] : 0ull;
+        const uint64_t w = (w0 >> (off & 63u)) | (w1 << (~off & 63u));
+        const uint32_t lo = (uint32_t)w, hi = (uint32_t)(w >> 32);
+        // 1 + zeros of the run, at most lim
+        const uint32_t lim = 64u - n < end - off ? 64u - n : end - off;
+        const uint32_t a = ffbl(lo & ~1u), b = ffbl(hi) | 32u;
+        uint32_t z1 = a < b ? a : b;
+        z1 = z1 < lim ? z1 : lim;
+        const uint32_t g = lo & 1u;
+        const uint32_t adv = g ? z1 + (z1 == lim ? 0u : 1u) : 1u;
+        found |= (uint64_t)g << ((n + z1 - 1u) & 63u);
+        n += g ? z1 : 0u;
+        off += adv;
+        bool stop = !g || n == 64u || off >= end;
+        // (adv = 64 looks at bit 0 of the window, which is g = 1: no end seen)
+        const bool next0 = !((w >> (adv & 63u)) & 1u);
+        off += !stop && next0 ? 1u : 0u;
+        stop = stop || next0;
+        if (stop) {
+            r16[k--] = (uint16_t)((off - gs) | (n - ns) << 8);
+            if (k < 0 || off >= end) break;
+            off += n;   // the significant coefficients' bits of the next plane
+            gs = off;
+            ns = n;
+            if (n == 64u || off >= end) {   // planes without group tests
+                for (;;) {
+                    r16[k--] = 0;
+                    if (k < 0 || off >= end) break;
+                    off += n;
+                }
+                break;
             }
-            const uint32_t sh = (uint32_t)off & 63u;
-            const uint64_t w = (w0 >> sh) | ((w1 << 1) << (63u - sh));
-            const int lim = (63 - n < budget - 1) ? 63 - n : budget - 1;
-            const int z = ctz64((w >> 1) | (1ull << lim));
-            const bool g = (w & 1u) != 0;
-            const int adv = g ? 2 + z - (z == lim ? 1 : 0) : 1;
-            off += adv;
-            budget -= adv;
-            found |= (uint64_t)g << (n + z);
-            n += g ? z + 1 : 0;
-            end = !g || n == 64 || budget == 0;
-            // after a find, a 0 as the next group test (mostly still inside
-            // w) ends the plane in this step
-            if (!end && adv < 64 && !((w >> adv) & 1u)) {
-                off++;
-                budget--;
-                end = true;
-            }
-        }
-        if (end) {
-            const uint32_t r = (uint32_t)(off - gstart) | ((uint32_t)(n - nstart) << 8);
-            if (k & 1) pend = r;
-            else rec[k >> 1] = r | (pend << 16);
-            k--;
-            at_start = true;
         }
     }
     kend = k + 1;
-    if (kend & 1) rec[kend >> 1] = pend << 16;
     return found;
 }
 
-__host__ __device__ __forceinline__ void decode_block_staged_f32(const uint64_t *st, uint32_t *rec,
-                                                                 int rate, float *out) {
+template <class SP, class RP>
+__host__ __device__ __forceinline__ void decode_block_staged_f32(SP st, RP rec, int rate, float *out) {
     using T = Prec<false>;
     const uint64_t head = st[0];
     // an all-zero block takes the same path with no plane visited (see
     // decode_block_staged_f64_low)
     const bool zero = !(head & 1u);
     const int emax = zero ? 0 : (int)((head >> 1) & 0xFFu) - T::BIAS;
-    const int end_bits = 64 * rate;
+    const uint32_t end_bits = 64u * (uint32_t)rate;
     int kend = T::P;
     uint64_t found = 0;
     if (!zero) found = staged_pass1<false>(st, rec, rate, kend);
@@ -419,22 +460,12 @@ __host__ __device__ __forceinline__ void decode_block_staged_f32(const uint64_t 
 #pragma unroll
     for (int j = 0; j < 16; j++) R[j] = rec[j];
     uint32_t lo[32], hi[32];
-    int o = 1 + T::EBITS, nn = 0;
-    uint64_t below = 0;   // coefficients below nn
+    PlaneState ps{1 + T::EBITS, 0u, ~0ull, found};
 #pragma unroll
     for (int kk = T::P - 1; kk >= 0; kk--) {
         uint64_t x = 0;
-        if (kk >= kend) {
-            const uint32_t rk = (kk & 1) ? (R[kk >> 1] >> 16) : (R[kk >> 1] & 0xFFFFu);
-            const int m = nn < end_bits - o ? nn : end_bits - o;
-            if (m > 0) x = peek_staged(st, o) & (~0ull >> (64 - m));
-            const int nn2 = nn + (int)(rk >> 8);
-            const uint64_t below2 = nn2 >= 64 ? ~0ull : ((1ull << nn2) - 1);
-            x |= found & below2 & ~below;
-            below = below2;
-            nn = nn2;
-            o += m + (int)(rk & 0xFFu);
-        }
+        if (kk >= kend)
+            x = plane_word(st, end_bits, (kk & 1) ? (R[kk >> 1] >> 16) : (R[kk >> 1] & 0xFFFFu), ps);
         lo[kk] = (uint32_t)x;
         hi[kk] = (uint32_t)(x >> 32);
     }
@@ -464,31 +495,22 @@ __host__ __device__ __forceinline__ void decode_block_staged_f32(const uint64_t 
 // and never subnormal, else it is formed in double as the plain decoder does.
 // SINGLE_ONLY: the caller guarantees -96 <= emax <= 96 (no double-precision
 // branch, whose results the compiler would merge with register copies).
-template <bool SINGLE_ONLY = false>
-__host__ __device__ __forceinline__ void staged_f64_top_planes(const uint64_t *st, const uint32_t *rec,
-                                                               int rate, uint64_t found, int kend, int emax,
-                                                               float *out) {
+template <bool SINGLE_ONLY = false, class SP, class RP>
+__host__ __device__ __forceinline__ void staged_f64_top_planes(SP st, RP rec, int rate, uint64_t found, int kend,
+                                                               int emax, float *out) {
     using T = Prec<true>;
-    const int end_bits = 64 * rate;
+    const uint32_t end_bits = 64u * (uint32_t)rate;
     uint32_t lo[32], hi[32];
 #pragma unroll
     for (int r = 0; r < WRAP32_KMIN - 32; r++) lo[r] = hi[r] = 0u;
-    int o = 1 + T::EBITS, nn = 0;
-    uint64_t below = 0;
+    PlaneState ps{1 + T::EBITS, 0u, ~0ull, found};
 #pragma unroll
     for (int r = 31; r >= WRAP32_KMIN - 32; r--) {
         const int kk = 32 + r;
         uint64_t x = 0;
         if (kk >= kend) {
-            const uint32_t rw = rec[kk >> 1], rk = (kk & 1) ? (rw >> 16) : (rw & 0xFFFFu);
-            const int m = nn < end_bits - o ? nn : end_bits - o;
-            if (m > 0) x = peek_staged(st, o) & (~0ull >> (64 - m));
-            const int nn2 = nn + (int)(rk >> 8);
-            const uint64_t below2 = nn2 >= 64 ? ~0ull : ((1ull << nn2) - 1);
-            x |= found & below2 & ~below;
-            below = below2;
-            nn = nn2;
-            o += m + (int)(rk & 0xFFu);
+            const uint32_t rw = rec[kk >> 1];
+            x = plane_word(st, end_bits, (kk & 1) ? (rw >> 16) : (rw & 0xFFFFu), ps);
         }
         lo[r] = (uint32_t)x;
         hi[r] = (uint32_t)(x >> 32);
@@ -514,8 +536,8 @@ __host__ __device__ __forceinline__ void staged_f64_top_planes(const uint64_t *s
     }
 }
 
-__host__ __device__ __forceinline__ void decode_block_staged_f64(const uint64_t *st, uint32_t *rec,
-                                                                 int rate, float *out) {
+template <class SP, class RP>
+__host__ __device__ __forceinline__ void decode_block_staged_f64(SP st, RP rec, int rate, float *out) {
     using T = Prec<true>;
     const uint64_t head = st[0];
     if (!(head & 1u)) {
@@ -524,7 +546,7 @@ __host__ __device__ __forceinline__ void decode_block_staged_f64(const uint64_t 
         return;
     }
     const int emax = (int)((head >> 1) & 0x7FFu) - T::BIAS;
-    const int end_bits = 64 * rate;
+    const uint32_t end_bits = 64u * (uint32_t)rate;
     int kend;
     const uint64_t found = staged_pass1<true>(st, rec, rate, kend);
     const double s = ldexp(1.0, emax - 62);
@@ -537,22 +559,14 @@ __host__ __device__ __forceinline__ void decode_block_staged_f64(const uint64_t 
     uint64_t c[64];
 #pragma unroll
     for (int i = 0; i < 64; i++) c[i] = 0;
-    int o = 1 + T::EBITS, nn = 0;
-    uint64_t below = 0;
+    PlaneState ps{1 + T::EBITS, 0u, ~0ull, found};
     for (int kk = T::P - 1; kk >= kend; kk--) {
-        const uint32_t rw = rec[kk >> 1], rk = (kk & 1) ? (rw >> 16) : (rw & 0xFFFFu);
-        const int m = nn < end_bits - o ? nn : end_bits - o;
-        uint64_t x = m > 0 ? peek_staged(st, o) & (~0ull >> (64 - m)) : 0ull;
-        const int nn2 = nn + (int)(rk >> 8);
-        const uint64_t below2 = nn2 >= 64 ? ~0ull : ((1ull << nn2) - 1);
-        x |= found & below2 & ~below;
-        below = below2;
-        nn = nn2;
-        o += m + (int)(rk & 0xFFu);
+        const uint32_t rw = rec[kk >> 1];
+        const uint64_t x = plane_word(st, end_bits, (kk & 1) ? (rw >> 16) : (rw & 0xFFFFu), ps);
         const uint32_t xl = (uint32_t)x, xh = (uint32_t)(x >> 32);
 #pragma unroll
         for (int g = 0; g < 8; g++) {
-            if (nn > 8 * g) {
+            if (ps.nn > 8u * g) {
                 const uint32_t wv = g < 4 ? xl : xh;
 #pragma unroll
                 for (int i = 8 * g; i < 8 * g + 8; i++) c[i] |= (uint64_t)((wv >> (i & 31)) & 1u) << kk;
@@ -572,8 +586,8 @@ __host__ __device__ __forceinline__ void decode_block_staged_f64(const uint64_t 
 // values as decode_block_staged_f64) and true; false, with out untouched, for
 // a block whose stream goes on below that plane or whose exponent is outside
 // that range (the caller decodes it with the general decoder).
-__host__ __device__ __forceinline__ bool decode_block_staged_f64_low(const uint64_t *st, uint32_t *rec,
-                                                                    int rate, float *out) {
+template <class SP, class RP>
+__host__ __device__ __forceinline__ bool decode_block_staged_f64_low(SP st, RP rec, int rate, float *out) {
     using T = Prec<true>;
     const uint64_t head = st[0];
     // An all-zero block takes the same path with no plane visited (every
@@ -648,17 +662,17 @@ __host__ __device__ inline unsigned stage_wave_words(int rate, bool f64) {
 
 // Lane l's block from the staging area by decode_block_staged_f64_low.
 __device__ __forceinline__ bool decode_block_staged_low(uint64_t *st, int rate, float *out) {
-    uint32_t *rec = reinterpret_cast<uint32_t *>(st + STAGE_STRIDE * rate) + __lane_id() * RecLayout<true>::STRIDE;
-    return decode_block_staged_f64_low(st + __lane_id(), rec, rate, out);
+    const lds_rec rec = (lds_rec)(st + STAGE_STRIDE * rate) + __lane_id() * RecLayout<true>::STRIDE;
+    return decode_block_staged_f64_low((lds_words)st + __lane_id(), rec, rate, out);
 }
 
 // Decode lane l's block from the staging area (stage_wave_words(rate, F64)
 // words per wave) written by stage_words.
 template <bool F64>
 __device__ __forceinline__ void decode_block_staged(uint64_t *st, int rate, float *out) {
-    uint32_t *rec = reinterpret_cast<uint32_t *>(st + STAGE_STRIDE * rate) + __lane_id() * RecLayout<F64>::STRIDE;
-    if constexpr (F64) decode_block_staged_f64(st + __lane_id(), rec, rate, out);
-    else decode_block_staged_f32(st + __lane_id(), rec, rate, out);
+    const lds_rec rec = (lds_rec)(st + STAGE_STRIDE * rate) + __lane_id() * RecLayout<F64>::STRIDE;
+    if constexpr (F64) decode_block_staged_f64((lds_words)st + __lane_id(), rec, rate, out);
+    else decode_block_staged_f32((lds_words)st + __lane_id(), rec, rate, out);
 }
 
 // Bytes of dynamic LDS a 256-thread workgroup needs for staging at `rate`
