@@ -275,12 +275,27 @@ DenseGeom dense_geom(uint32_t nx, uint32_t ny, uint32_t nz) {
     return g;
 }
 
+// Words per chunk: mc_chunk_size's, but not whole rows a multiple of 4 KB
+// apart.  The waves would then start every chunk at the same x of such rows
+// and gather through the same few L2 channels: 512^3 turbulence 565 us with
+// chunks of 64 words (8 rows of 2 KB), 514 with 61 (509..514 with 60..62, 534
+// with 63, 542 with 56); 256 x 256 x 256 121 with 64, 103 with 61.  Where the
+// rows differ, 61 measured from 4 % faster (384^3, 300^3) to 4 % slower
+// (640 x 512 x 512): those keep 64.
+constexpr uint32_t DENSE_ODD_CHUNK = 61;
+uint32_t dense_chunk_size(const DenseGeom &g, uint32_t waves) {
+    const uint32_t cs = mc_chunk_size(g.n_cwords, waves);
+    if (cs % g.cwords || (uint64_t)(cs / g.cwords) * g.nx % 1024) return cs;
+    return cs > DENSE_ODD_CHUNK ? DENSE_ODD_CHUNK : cs + 1;
+}
+
 }  // namespace
 
 uint64_t dense_sign_words(uint32_t nx, uint32_t ny, uint32_t nz) { return dense_geom(nx, ny, nz).n_swords; }
 
 uint64_t dense_chunk_words(uint32_t nx, uint32_t ny, uint32_t nz) {
-    return mc_chunk_slots(dense_geom(nx, ny, nz).n_cwords);
+    return std::max<uint64_t>(mc_chunk_slots(dense_geom(nx, ny, nz).n_cwords),
+                              dense_geom(nx, ny, nz).n_cwords / DENSE_ODD_CHUNK + 1);
 }
 
 // bits: dense_sign_words, chunk_tot: dense_chunk_words entries; ctr holds the
@@ -296,7 +311,7 @@ void launch_dense(uint32_t nx, uint32_t ny, uint32_t nz, const float *field, flo
     const unsigned words = (unsigned)std::min<uint64_t>(((uint64_t)g.n_swords + 31) / 32, 1u << 20);
     const unsigned need = ((unsigned)std::min<uint64_t>(g.n_cwords, 4u * MC_MAX_GRID) + 3) / 4;
     const unsigned eg = std::min(egrid, (need + 7) / 8 * 8), cg = std::min(cgrid, (need + 7) / 8 * 8);
-    const uint32_t cs = mc_chunk_size(g.n_cwords, eg * MC_WAVES);
+    const uint32_t cs = dense_chunk_size(g, eg * MC_WAVES);
     k_dense_signs<<<std::min(words, sgrid), 256, 0, s>>>(g, field, iso, bits, ctr);
     k_dense_count<<<cg, 256, 0, s>>>(g, bits, cs, chunk_tot, ctr);
     k_dense_emit<<<eg, 256, 0, s>>>(g, field, iso, bits, cs, chunk_tot, mc_table, out, cap, ctr);

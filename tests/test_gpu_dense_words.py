@@ -39,3 +39,24 @@ def test_dense_words(orc, kind, dims):
         assert np.array_equal(got[: 3 * T, 3].view(np.uint32), vb)
         assert (got[3 * T:] == -7).all()
     dm.close()
+
+
+@pytest.mark.parametrize("dims", [(512, 120, 120), (512, 512, 128)])
+def test_dense_chunks_across_rows(orc, dims):
+    """Rows whole chunks of which lie a multiple of 4 KB apart: the chunks are
+    one word longer (the first) or 61 words (the second)."""
+    torch = torch_cuda()
+    import paper_2009_03254_amd as bc
+    f = _field("plane", dims, 0)
+    iso = np.float32(100.0)
+    say(f"[dense chunks] {dims}")
+    dm = bc.DenseMC(dims)
+    v, vb = orc.mc_extract_dense(f, iso)
+    out = torch.full((len(vb) + 8, 4), -7, dtype=torch.int32, device="cuda")
+    rc, T = dm.extract_into(to_cuda(f), float(iso), out)
+    assert rc == 0 and 3 * T == len(vb)
+    got = out.cpu().numpy()
+    assert np.array_equal(got[: 3 * T, :3].view(np.uint32), v.view(np.uint32))
+    assert np.array_equal(got[: 3 * T, 3].view(np.uint32), vb)
+    assert (got[3 * T:] == -7).all()
+    dm.close()
