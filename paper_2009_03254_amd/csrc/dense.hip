@@ -18,11 +18,12 @@
 // and triangles in LDS and writes one vertex per lane.  Bound by memory: the
 // field read once for the signs and, where the surface lies, again for the
 // vertices, and the soup written.  512^3 turbulence at its median (14.5 M
-// triangles): 107 + 25 + 378 us, the signs at 5.0 TB/s (before, with each
+// triangles): 107 + 25 + 330 us, the signs at 5.0 TB/s (before, with each
 // cell's case and offset kept in memory: 985 for a classification whose lanes
 // read 64 bytes apart and 1433 for an emission whose lanes wrote 48 bytes
 // apart, 2.6 ms in all).  More waves (7 or 8 per SIMD, spilling) or two vertices
-// per lane in flight left the emission at 376-385 us.
+// per lane in flight gained nothing (376-385 us against 378, before
+// dense_chunk_size).
 #include <stdint.h>
 
 #include <algorithm>

@@ -336,11 +336,11 @@ __device__ __forceinline__ void load_block(const Geom &g, const T *__restrict__ 
 // through the wave's LDS (word w of lane l at st[w * STAGE_STRIDE + l]) and out
 // in one contiguous run.  VALU bound: the planes are formed by bit transposes of
 // the coefficients (a bit extract per plane and coefficient took 6,000
-// instructions of a wave's single-precision blocks), and the coder emits a
-// group test with its run at once: 6,200 VALU instructions of a wave at rate 8,
-// three quarters of them the coder's, whose loop takes a wave's slowest lane
-// in every plane.  512^3 float32 at rate 8: 436 us (964 before), at 3 waves per
-// SIMD (4 spill: 497).
+// instructions of a wave's single-precision blocks), and the coder, whose loop
+// takes a wave's slowest lane in every plane, emits a group test with its run,
+// and with the 0 that ends the plane, at once.  512^3 float32 at rate 8: 367 us
+// (964 with the planes extracted bit by bit, 436 with the planes' ending 0 a
+// step of its own), at 3 waves per SIMD (4 spill).
 template <bool F64, bool STAGED>
 __global__ __launch_bounds__(256, F64 ? 2 : 3) void k_encode(Geom g, const void *__restrict__ field, int aligned,
                                                             int rate, uint64_t *__restrict__ stream,

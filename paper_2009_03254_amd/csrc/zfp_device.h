@@ -716,7 +716,8 @@ struct BitWriter {
 // is bit k of coefficient i / 32 + i.  n: coefficients found significant.
 // Per plane the bits of the first n, then group tests: a 1 and the run up to
 // the next coefficient with a 1 (the last one, 63, implied by the test), or a
-// 0 that ends the plane.
+// 0 that ends the plane, which goes out with what precedes it: a wave then
+// takes a step per run of its slowest lane, and none in planes that have no run.
 template <int STRIDE>
 __device__ __forceinline__ void encode_planes32(const uint32_t *lo, const uint32_t *hi, int &n,
                                                 BitWriter<STRIDE> &bw) {
@@ -724,21 +725,21 @@ __device__ __forceinline__ void encode_planes32(const uint32_t *lo, const uint32
     for (int k = 31; k >= 0; k--) {
         if (bw.open()) {
             const uint64_t x = (uint64_t)hi[k] << 32 | lo[k];
-            uint64_t rest = x;
-            if (n) {
-                bw.put(x & (~0ull >> (64 - n)), n);
-                rest = (x >> 1) >> (n - 1);
-            }
-            while (n < 64 && bw.open()) {
-                if (!rest) {
-                    bw.put(0, 1);
-                    break;
-                }
+            uint64_t rest = n ? (x >> 1) >> (n - 1) : x;
+            const int head = n + (!rest && n < 64 ? 1 : 0);
+            if (head) bw.put(n ? x & (~0ull >> (64 - n)) : 0ull, head);
+            while (rest && bw.open()) {
                 const int z = ctz64(rest);
-                const bool implied = n + z == 63;
-                bw.put(1ull | (implied ? 0ull : 2ull << z), z + (implied ? 1 : 2));
                 n += z + 1;
                 rest = (rest >> 1) >> z;
+                const int tail = n == 64 ? 0 : (rest ? 1 : 2);   // the run's 1 (implied: none) and the plane's 0
+                const uint64_t run = 1ull | (tail ? 2ull << z : 0ull);
+                if (__builtin_expect(z == 62 && tail == 2, 0)) {   // 65 bits
+                    bw.put(run, 64);
+                    bw.put(0, 1);
+                } else {
+                    bw.put(run, z + 1 + tail);
+                }
             }
         }
     }

@@ -37,3 +37,28 @@ def test_encode_forms(orc, dtype, rates, dims, shift):
     for rate in rates:
         got = bc.encode(g, rate).cpu().numpy()
         assert np.array_equal(got, orc.zfp_encode(f, rate)), rate
+
+
+def _bits(words):
+    return "".join(str((int(w) >> i) & 1) for w in words for i in range(64))
+
+
+@pytest.mark.parametrize("dtype,ebits,bias", [(np.float32, 8, 127), (np.float64, 11, 1023)])
+@pytest.mark.parametrize("coef", [61, 62, 63])
+def test_first_run_to_the_last_coefficients(orc, dtype, ebits, bias, coef):
+    """Blocks whose first group test runs to one of the last coefficients and
+    finds nothing after it: with the 0 that ends the plane 64 and 65 bits
+    (61, 62), the one implied (63)."""
+    torch_cuda()
+    import paper_2009_03254_amd as bc
+    say(f"[encode runs] {dtype.__name__} coefficient {coef}")
+    code = "1" + "".join(str(((3 + bias) >> i) & 1) for i in range(ebits)) + "001" + "0" * coef + "10"
+    code += "0" * (512 - len(code))
+    w = np.array([int(code[64 * i: 64 * i + 64][::-1], 2) for i in range(8)], dtype=np.uint64)
+    f = orc.zfp_decode_f64(w, (4, 4, 4), 8) if dtype == np.float64 else orc.zfp_decode(w, (4, 4, 4), 8)
+    f = np.ascontiguousarray(np.tile(f.reshape(4, 4, 4).astype(dtype), (1, 1, 80)))
+    want = orc.zfp_encode(f, 8)
+    assert _bits(want[:8])[1 + ebits:].startswith("001" + "0" * coef + ("10" if coef < 63 else ""))
+    assert np.array_equal(bc.encode(to_cuda(f), 8).cpu().numpy(), want)
+    for rate in (1, 2, 20):
+        assert np.array_equal(bc.encode(to_cuda(f), rate).cpu().numpy(), orc.zfp_encode(f, rate)), rate
