@@ -336,17 +336,20 @@ __device__ __forceinline__ void load_block(const Geom &g, const T *__restrict__ 
 // through the wave's LDS (word w of lane l at st[w * STAGE_STRIDE + l]) and out
 // in one contiguous run.  VALU bound: the planes are formed by bit transposes of
 // the coefficients (a bit extract per plane and coefficient took 6,000
-// instructions of a wave's single-precision blocks), and the coder, whose loop
-// takes a wave's slowest lane in every plane, emits a group test with its run,
-// and with the 0 that ends the plane, at once.  512^3 float32 at rate 8: 367 us
-// (964 with the planes extracted bit by bit, 436 with the planes' ending 0 a
-// step of its own), at 3 waves per SIMD (4 spill).
+// instructions of a wave's single-precision blocks), and the coder forms the
+// group tests of 16 coefficients at a time from a table of 256 bytes'
+// (encode_planes32).  512^3 float32 at rate 8: 255 us (964 with the planes
+// extracted bit by bit; 362 with a step per run, 328 with the runs placed by
+// one shift), at 3 waves per SIMD (4 spill).
 template <bool F64, bool STAGED>
 __global__ __launch_bounds__(256, F64 ? 2 : 3) void k_encode(Geom g, const void *__restrict__ field, int aligned,
                                                             int rate, uint64_t *__restrict__ stream,
                                                             unsigned int *err) {
     using T = std::conditional_t<F64, double, float>;
     extern __shared__ uint64_t stage_lds[];
+    __shared__ uint16_t group[256];
+    group[threadIdx.x] = (uint16_t)group_bits(threadIdx.x);
+    __syncthreads();
     uint64_t *st = stage_lds + (threadIdx.x >> 6) * (STAGED ? STAGE_STRIDE * rate : 0);
     const T *f = static_cast<const T *>(field);
     const uint32_t l = __lane_id();
@@ -362,7 +365,7 @@ __global__ __launch_bounds__(256, F64 ? 2 : 3) void k_encode(Geom g, const void 
         T x[64];
         load_block(g, f, bx, by, bz, aligned && !__ballot(!whole), x);
         if constexpr (STAGED) {
-            finite &= encode_block<F64, STAGE_STRIDE>(x, rate, st + l) || !valid;
+            finite &= encode_block<F64, STAGE_STRIDE>(x, rate, (lds_group)group, (lds_out)st + l) || !valid;
             wave_sync();
             const uint32_t total = (uint32_t)(g.nb - b0 < 64 ? g.nb - b0 : 64) * (uint32_t)rate;
             const uint64_t magic = ((1ull << 32) + (uint64_t)rate - 1) / (uint64_t)rate;   // i / rate, i < 2^32 / rate
@@ -373,7 +376,7 @@ __global__ __launch_bounds__(256, F64 ? 2 : 3) void k_encode(Geom g, const void 
             }
             wave_sync();   // st is rewritten by the next round
         } else if (valid) {
-            finite &= encode_block<F64, 1>(x, rate, stream + b * rate);
+            finite &= encode_block<F64, 1>(x, rate, (lds_group)group, stream + b * rate);
         }
     }
     if (__ballot(!finite) && l == 0) atomicOr(err, ERR_NONFINITE);

@@ -384,6 +384,7 @@ __host__ __device__ __forceinline__ rec_half *rec_halves(uint32_t *rec) { return
 // generic pointers every word's address took a 64-bit multiply-add).
 typedef const uint64_t __attribute__((address_space(3))) *lds_words;
 typedef uint32_t __attribute__((address_space(3))) *lds_rec;
+typedef uint64_t __attribute__((address_space(3))) *lds_out;
 __host__ __device__ __forceinline__ uint16_t __attribute__((address_space(3))) *rec_halves(lds_rec rec) {
     return (uint16_t __attribute__((address_space(3))) *)rec;
 }
@@ -687,67 +688,93 @@ __host__ __device__ inline unsigned stage_lds_bytes(int rate, bool f64) {
 }
 
 // ---- encoder -----------------------------------------------------------------
-// Bits of one block, LSB first, into `rate` words at st[w * STRIDE]; what
-// comes after the last word is dropped: a block's code is the beginning of an
-// unbounded one, so the coder needs no budget.
-template <int STRIDE>
+// Bits of one block, LSB first, into the words at p, p + STRIDE, ... before
+// `end`; what comes after the last word is dropped: a block's code is the
+// beginning of an unbounded one, so the coder needs no budget.  Written to only
+// while open().
+template <int STRIDE, class SP>
 struct BitWriter {
-    uint64_t *__restrict__ st;
-    int rate, wi, na;      // words written, bits in acc
+    SP p, end;
     uint64_t acc;
-    __device__ __forceinline__ bool open() const { return wi < rate; }
-    __device__ __forceinline__ void put(uint64_t v, int n) {   // v < 2^n, 1 <= n <= 64
+    uint32_t na;   // bits in acc
+    __device__ __forceinline__ bool open() const { return p != end; }
+    __device__ __forceinline__ void next(uint64_t rest) {
+        *p = acc;
+        p += STRIDE;
+        acc = rest;
+    }
+    __device__ __forceinline__ void put(uint64_t v, uint32_t n) {   // v < 2^n, 1 <= n <= 64
         acc |= v << na;
-        const int t = na + n;
-        if (t >= 64) {
-            if (wi < rate) st[wi * STRIDE] = acc;
-            wi++;
-            acc = (v >> 1) >> (63 - na);
-        }
+        const uint32_t t = na + n;
+        if (t >= 64) next((v >> 1) >> (63 - na));
         na = t & 63;
     }
     __device__ __forceinline__ void finish() {
-        if (wi < rate) st[wi * STRIDE] = acc;
-        for (int w = wi + 1; w < rate; w++) st[w * STRIDE] = 0;
+        while (open()) next(0);
     }
 };
+
+// The group tests of 8 coefficients' bits of a plane: the bits with a 1 put in
+// after each 1 (the test that finds the next), 8 + popcount bits.
+constexpr uint32_t group_bits(uint32_t byte) {
+    uint32_t c = 0, at = 0;
+    for (int i = 0; i < 8; i++) {
+        if ((byte >> i) & 1u) {
+            c |= 3u << at;
+            at++;
+        }
+        at++;
+    }
+    return c;
+}
+typedef uint16_t __attribute__((address_space(3))) *lds_group;   // group_bits of every byte
 
 // Embedded coding of 32 bit planes, from the highest: bit i of lo[k] / hi[k]
 // is bit k of coefficient i / 32 + i.  n: coefficients found significant.
 // Per plane the bits of the first n, then group tests: a 1 and the run up to
 // the next coefficient with a 1 (the last one, 63, implied by the test), or a
-// 0 that ends the plane, which goes out with what precedes it: a wave then
-// takes a step per run of its slowest lane, and none in planes that have no run.
-template <int STRIDE>
-__device__ __forceinline__ void encode_planes32(const uint32_t *lo, const uint32_t *hi, int &n,
-                                                BitWriter<STRIDE> &bw) {
+// 0 that ends the plane.  With the first test taken to the first n bits, what
+// follows is the plane's other bits up to the last 1, a test put in after each
+// 1: formed for 16 bits at a time from group_bits, whatever runs they hold (a
+// step per run takes a wave's slowest lane, about 8 steps a plane against 3).
+template <class BW>
+__device__ __forceinline__ void encode_planes32(const uint32_t *lo, const uint32_t *hi, lds_group tab, uint32_t &n,
+                                                BW &bw) {
 #pragma unroll
     for (int k = 31; k >= 0; k--) {
         if (bw.open()) {
             const uint64_t x = (uint64_t)hi[k] << 32 | lo[k];
-            uint64_t rest = n ? (x >> 1) >> (n - 1) : x;
-            const int head = n + (!rest && n < 64 ? 1 : 0);
-            if (head) bw.put(n ? x & (~0ull >> (64 - n)) : 0ull, head);
-            while (rest && bw.open()) {
-                const int z = ctz64(rest);
-                n += z + 1;
-                rest = (rest >> 1) >> z;
-                const int tail = n == 64 ? 0 : (rest ? 1 : 2);   // the run's 1 (implied: none) and the plane's 0
-                const uint64_t run = 1ull | (tail ? 2ull << z : 0ull);
-                if (__builtin_expect(z == 62 && tail == 2, 0)) {   // 65 bits
-                    bw.put(run, 64);
-                    bw.put(0, 1);
-                } else {
-                    bw.put(run, z + 1 + tail);
+            const uint64_t above = n < 64 ? ~0ull << n : 0ull;
+            const bool found = (x & above) != 0;
+            bw.put((x & ~above) | (uint64_t)(found ? 1u : 0u) << (n & 63), n < 64 ? n + 1 : 64);
+            uint64_t rest = found && bw.open() ? x >> (n & 63) : 0ull;
+            n = found ? 64u - (uint32_t)__clzll((long long)x) : n;
+            const uint32_t implied = n == 64 ? 1u : 0u;
+            while (rest) {
+                const uint32_t b = (uint32_t)rest & 0xFFFFu, b0 = b & 0xFFu;
+                rest >>= 16;
+                uint32_t c = (uint32_t)tab[b0] | (uint32_t)tab[b >> 8] << (8u + (uint32_t)__popc(b0));
+                uint32_t len = 16u + (uint32_t)__popc(b);
+                if (!rest) {   // the last test is a 0; coefficient 63 and its test are not written
+                    const uint32_t top = 31u - (uint32_t)__clz((int)c);
+                    c &= ~(~0u << (top - implied));
+                    len = top + 1u - 2u * implied;
                 }
+                bw.acc |= (uint64_t)c << bw.na;
+                const uint32_t t = bw.na + len;
+                if (t >= 64) {   // na >= 32
+                    bw.next((uint64_t)c >> (64u - bw.na));
+                    if (!bw.open()) rest = 0;
+                }
+                bw.na = t & 63;
             }
         }
     }
 }
 
 // Codes the block v (integers of emax's scale, block order); v is used up.
-template <int STRIDE>
-__device__ __forceinline__ void encode_coefficients(int32_t *v, BitWriter<STRIDE> &bw) {
+template <class BW>
+__device__ __forceinline__ void encode_coefficients(int32_t *v, lds_group tab, BW &bw) {
     constexpr uint32_t NB = Prec<false>::NB;
     fwd_xyz(v);
     uint32_t lo[32], hi[32];
@@ -758,13 +785,13 @@ __device__ __forceinline__ void encode_coefficients(int32_t *v, BitWriter<STRIDE
     }
     transpose32(lo);
     transpose32(hi);
-    int n = 0;
-    encode_planes32(lo, hi, n, bw);
+    uint32_t n = 0;
+    encode_planes32(lo, hi, tab, n, bw);
 }
 // ... double precision: the upper 32 planes, then, for blocks that still have
 // room, the lower ones.
-template <int STRIDE>
-__device__ __forceinline__ void encode_coefficients(int64_t *v, BitWriter<STRIDE> &bw) {
+template <class BW>
+__device__ __forceinline__ void encode_coefficients(int64_t *v, lds_group tab, BW &bw) {
     constexpr uint64_t NB = Prec<true>::NB;
     fwd_xyz(v);
     uint32_t lo[32], hi[32], low[64];
@@ -778,12 +805,12 @@ __device__ __forceinline__ void encode_coefficients(int64_t *v, BitWriter<STRIDE
     }
     transpose32(lo);
     transpose32(hi);
-    int n = 0;
-    encode_planes32(lo, hi, n, bw);
+    uint32_t n = 0;
+    encode_planes32(lo, hi, tab, n, bw);
     if (__ballot(bw.open())) {
         transpose32(low);
         transpose32(low + 32);
-        encode_planes32(low, low + 32, n, bw);
+        encode_planes32(low, low + 32, tab, n, bw);
     }
 }
 
@@ -808,13 +835,13 @@ __device__ __forceinline__ bool block_max(const double *x, double &m) {
 __device__ __forceinline__ int32_t to_fixed(float x, int e) { return (int32_t)ldexpf(x, e); }
 __device__ __forceinline__ int64_t to_fixed(double x, int e) { return (int64_t)ldexp(x, e); }
 
-// Encodes block x (block order) into the `rate` words of bw; false (all
+// Encodes block x (block order) into `rate` words at st, STRIDE apart; false (all
 // words zero) when a value is not finite.
-template <bool F64, int STRIDE>
+template <bool F64, int STRIDE, class SP>
 __device__ __forceinline__ bool encode_block(const std::conditional_t<F64, double, float> *x, int rate,
-                                             uint64_t *st) {
+                                             lds_group tab, SP st) {
     using T = Prec<F64>;
-    BitWriter<STRIDE> bw{st, rate, 0, 0, 0ull};
+    BitWriter<STRIDE, SP> bw{st, st + STRIDE * rate, 0ull, 0u};
     std::conditional_t<F64, double, float> m;
     const bool finite = block_max(x, m);
     if (finite && m > 0) {
@@ -826,7 +853,7 @@ __device__ __forceinline__ bool encode_block(const std::conditional_t<F64, doubl
         typename T::Int v[64];
 #pragma unroll
         for (int i = 0; i < 64; i++) v[i] = to_fixed(x[i], T::P - 2 - emax);
-        encode_coefficients(v, bw);
+        encode_coefficients(v, tab, bw);
     }
     bw.finish();
     return finite;

@@ -44,11 +44,11 @@ def _bits(words):
 
 
 @pytest.mark.parametrize("dtype,ebits,bias", [(np.float32, 8, 127), (np.float64, 11, 1023)])
-@pytest.mark.parametrize("coef", [61, 62, 63])
-def test_first_run_to_the_last_coefficients(orc, dtype, ebits, bias, coef):
-    """Blocks whose first group test runs to one of the last coefficients and
-    finds nothing after it: with the 0 that ends the plane 64 and 65 bits
-    (61, 62), the one implied (63)."""
+@pytest.mark.parametrize("coef", [0, 7, 8, 15, 16, 31, 32, 47, 48, 61, 62, 63])
+def test_first_run_alone(orc, dtype, ebits, bias, coef):
+    """Blocks whose first group test runs to the one coefficient of the plane:
+    on both sides of the steps of 8 and 16 coefficients that the tests are
+    formed in, and the last, whose 1 is implied."""
     torch_cuda()
     import paper_2009_03254_amd as bc
     say(f"[encode runs] {dtype.__name__} coefficient {coef}")
