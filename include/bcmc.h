@@ -104,11 +104,11 @@ typedef struct {
     double stage_ms[8];    /* for the profiled stages (HIP events on the
                               stream; 0 for stages not profiled):
                               [0] cull + active/new compaction,
-                              [1] cache update (slot pass, growth, age sort),
+                              [1] cache update (the slots to evict),
                               [2] assign + decode of new blocks, sign masks,
                               [3] marching cubes count pass,
                               [4] empty (the block offsets are formed by the
-                              emission pass from the count pass's per-wave
+                              emission pass from the count pass's chunk
                               totals), [5] emission pass, [6] unused, [7] total
                               (when stages 0 and 5 are both profiled) */
 } bcmc_stats;
@@ -367,7 +367,7 @@ BCMC_API int bcmc_debug_slot_data(const bcmc_volume *v, float *h_slots /* [n_slo
  * bcmc_extract calls at an isovalue outside the data would (Alg. 1's age
  * update: every slot's age += k, saturating at 2^32 - 1; every cached block
  * becomes available), without running them.  The cache's age clock counts
- * at most 2^31 - 1 calls since its reset.  A test hook for the age sort's
+ * at most 2^31 - 1 calls since its reset.  A test hook for the eviction's
  * wide keys.  Errors: BCMC_E_INVALID (identity volume, clock overflow). */
 BCMC_API int bcmc_debug_age_cache(bcmc_volume *v, uint32_t k, void *hip_stream);
 BCMC_API int bcmc_debug_block_counts(const bcmc_volume *v, uint32_t *h_cnt, uint64_t *h_off,
