@@ -547,10 +547,11 @@ int bcmc_backward(bcmc_volume *v, float iso, const float *d_gV, uint64_t n_verts
     if (n_verts != counters(v).total_verts) return invalid("n_verts differs from the last extract");
     if (n_verts && !d_gV) return invalid("null gradient");
     hipStream_t s = as_stream(hip_stream);
-    BCMC_HIP_TRY(hipMemsetAsync(d_dfield, 0, v->g.nb * 64 * sizeof(float), s));
-    BCMC_HIP_TRY(hipMemsetAsync(d_diso, 0, sizeof(float), s));
-    if (!n_verts) return BCMC_OK;
-    BCMC_HIP_TRY(hipMemsetAsync(&v->d.ctr->err, 0, sizeof(unsigned int), s));
+    if (!n_verts) {
+        BCMC_HIP_TRY(hipMemsetAsync(d_dfield, 0, v->g.nb * 64 * sizeof(float), s));
+        BCMC_HIP_TRY(hipMemsetAsync(d_diso, 0, sizeof(float), s));
+        return BCMC_OK;
+    }
     launch_backward(v->g, v->d, v->ext_blocks, iso, d_gV, n_verts, d_dfield, d_diso, v->last_format, s);
     BCMC_HIP_TRY(hipGetLastError());
     // the kernel compares each block's vertex count with the forward's

@@ -1074,6 +1074,20 @@ __global__ void k_fill_u32(uint32_t *p, uint32_t v, uint64_t n) {
         p[i] = v;
 }
 
+// The backward's outputs before it adds to them: the field's gradient zero
+// (16 bytes per lane where it is so aligned) and the call's error bits clear.
+// One launch for what were three memory commands, 6 us each of a 256^3 pass.
+__global__ __launch_bounds__(256) void k_clear_gradient(float *__restrict__ dfield, uint64_t n, int wide, Counters *ctr) {
+    const uint64_t i0 = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x, step = (uint64_t)gridDim.x * blockDim.x;
+    if (i0 == 0) ctr->err = 0;
+    if (wide) {
+        for (uint64_t i = i0; i < n / 4; i += step)
+            reinterpret_cast<float4 *>(dfield)[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    } else {
+        for (uint64_t i = i0; i < n; i += step) dfield[i] = 0.0f;
+    }
+}
+
 __global__ void k_iota_i32(int32_t *p, uint64_t n) {
     for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n;
          i += (uint64_t)gridDim.x * blockDim.x)
@@ -1250,7 +1264,8 @@ void launch_debug_cases(const Geom &g, const DevState &d, const float *slots,
 // offsets) in VFMT_GRAD mode, which for a vertex on an edge along axis e
 // with g = dL/dv[e] adds g (t - 1)/(b - a) to dL/da, -g t/(b - a) to dL/db
 // and g/(b - a) to dL/diso (float atomics into the field through per-block
-// LDS sums; dL/diso by per-wave partial sums).  fmt: the extract's vertex
+// LDS sums; dL/diso by per-wave partial sums).  Both outputs are written in
+// full.  fmt: the extract's vertex
 // format (its grid set the chunks).
 void launch_backward(const Geom &g, const DevState &d, const float *slots, float iso,
                      const float *gV, uint64_t n_verts, float *dfield, float *diso, int fmt,
@@ -1258,6 +1273,9 @@ void launch_backward(const Geom &g, const DevState &d, const float *slots, float
     static unsigned grid = 0;
     if (!grid) grid = resident_grid(k_mc_emit<VFMT_GRAD>);
     const unsigned n = std::min<unsigned>(grid, mc_grid(g.nb));
+    const uint64_t nf = g.nb * 64;
+    k_clear_gradient<<<grid_cap(nf / 4, 4096), 256, 0, s>>>(dfield, nf, reinterpret_cast<uintptr_t>(dfield) % 16 == 0,
+                                                            d.ctr);
     k_mc_emit<VFMT_GRAD><<<n, 256, 0, s>>>(g, d.I_active, nullptr, 1, slots, d.mc_table, iso, d.blk_cnt,
                                           d.blk_off, nullptr, n_verts, d.chunk_tot,
                                           emit_grid(g, fmt) * MC_WAVES, d.ctr, gV, dfield, d.part_giso);
