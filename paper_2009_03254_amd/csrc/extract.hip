@@ -893,7 +893,11 @@ __global__ __launch_bounds__(256) void k_mc_count(Geom g, const uint32_t *__rest
 // each block's in-block prefix of its per-cell triangle counts, the
 // triangles of the staged blocks listed together and written lane per vertex
 // from the first block's offset, in canonical order (block, cell, triangle,
-// vertex).
+// vertex).  Bound by memory and VALU issue together (70 % busy at 512^3): with
+// the place of a block's cells looked at only at the volume's far faces, one LDS
+// address for a cell's corners and the list's length a scalar, a wave's blocks
+// take 153 VALU instructions each instead of 170 (edge records 166 -> 158 us,
+// 16 calls of a 1280 x 960 sheet 410 -> 391).
 template <int FMT>
 __global__ __launch_bounds__(256, FMT == VFMT_GRAD ? 5 : 7) void k_mc_emit(Geom g, const uint32_t *__restrict__ I_active,
                                                 const int32_t *__restrict__ I_slot, int identity,
@@ -1196,12 +1200,16 @@ void launch_cache_empty(const DevState &d, uint64_t n_used, hipStream_t s) {
 
 // Grid of the emission: as many workgroups as are resident at once (their
 // waves sweep the chunks of the active list as one window), in whole XCD
-// rounds.  Its wave count also sets the chunk size (mc_chunk_size).
+// rounds.  Its wave count also sets the chunk size (mc_chunk_size).  One
+// workgroup per CU fewer than fit (8: 64 VGPRs, 19.8 KB of LDS): the eighth
+// measured slower, its waves being more than the memory serves (a call on 512^3
+// turbulence 553 against 530 us, with edge records 284 against 267).
+constexpr int EMIT_PER_CU = 7;
 static unsigned emit_grid(const Geom &g, int fmt) {
     static unsigned grid[3] = {0, 0, 0};
-    if (!grid[0]) grid[0] = resident_grid(k_mc_emit<VFMT_F32>);
-    if (!grid[1]) grid[1] = resident_grid(k_mc_emit<VFMT_EDGE8>);
-    if (!grid[2]) grid[2] = resident_grid(k_mc_emit<VFMT_Q10>);
+    if (!grid[0]) grid[0] = resident_grid(k_mc_emit<VFMT_F32>, EMIT_PER_CU);
+    if (!grid[1]) grid[1] = resident_grid(k_mc_emit<VFMT_EDGE8>, EMIT_PER_CU);
+    if (!grid[2]) grid[2] = resident_grid(k_mc_emit<VFMT_Q10>, EMIT_PER_CU);
     return std::min<unsigned>(grid[fmt >= 0 && fmt < 3 ? fmt : 0], mc_grid(g.nb));
 }
 

@@ -5,6 +5,8 @@
 
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "common.h"
 
 namespace bcmc {
@@ -267,16 +269,23 @@ __device__ __forceinline__ void stage_batch_tab(const LaneGeom &q, const float *
     }
 }
 
-// Case of the lane's cell in block (bx,by,bz) staged in `tile`, -1 outside.
-__device__ __forceinline__ int tile_case(const Geom &g, uint32_t bx, uint32_t by, uint32_t bz,
-                                         const float *tile, float iso) {
+// Case of the lane's cell in block (bx,by,bz) staged in `tile`, 0 (no
+// triangles) outside the volume.  The block is the wave's: only one at the
+// volume's far faces looks at its cells' places.
+__device__ __forceinline__ uint32_t tile_case(const Geom &g, uint32_t bx, uint32_t by, uint32_t bz,
+                                              const float *tile, float iso) {
     const int l = lane();
     const int lx = l & 3, ly = (l >> 2) & 3, lz = l >> 4;
-    if (4 * bx + lx + 1 >= g.nx || 4 * by + ly + 1 >= g.ny || 4 * bz + lz + 1 >= g.nz) return -1;
-    int cs = 0;
+    typedef const float __attribute__((address_space(3))) *lds_floats;
+    lds_floats t = (lds_floats)tile + tix(lx, ly, lz);
+    // one address for the eight samples (the compiler would add the tiles'
+    // place in LDS to each)
+    asm("" : "+v"(t));
+    uint32_t cs = 0;
 #pragma unroll
-    for (int k = 0; k < 8; k++)
-        if (tile[tix(lx + (k & 1), ly + ((k >> 1) & 1), lz + (k >> 2))] < iso) cs |= 1 << k;
+    for (int k = 7; k >= 0; k--) cs = cs + cs + (t[tix(k & 1, (k >> 1) & 1, k >> 2)] < iso ? 1u : 0u);
+    if (4 * bx + 4 >= g.nx || 4 * by + 4 >= g.ny || 4 * bz + 4 >= g.nz)
+        if (4 * bx + lx + 1 >= g.nx || 4 * by + ly + 1 >= g.ny || 4 * bz + lz + 1 >= g.nz) cs = 0;
     return cs;
 }
 
@@ -320,9 +329,10 @@ __device__ __forceinline__ uint32_t chunks_sum(const uint32_t *__restrict__ chun
 }
 
 // Workgroups of a persistent kernel of 256 threads that are all resident at
-// once (the static shares assume no second round), in whole XCD rounds.
+// once (the static shares assume no second round), at most max_per_cu per CU,
+// in whole XCD rounds.
 template <typename K>
-unsigned resident_grid(K kernel) {
+unsigned resident_grid(K kernel, int max_per_cu = 64) {
     static int cus = 0;
     if (!cus) {
         int dev = 0;
@@ -333,7 +343,7 @@ unsigned resident_grid(K kernel) {
     int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 256, 0) != hipSuccess || per_cu < 1)
         per_cu = 1;
-    const unsigned g = (unsigned)per_cu * cus / 8 * 8;
+    const unsigned g = (unsigned)std::min(per_cu, max_per_cu) * cus / 8 * 8;
     return g < 8 ? 8 : g;
 }
 
@@ -630,11 +640,10 @@ __device__ __forceinline__ void emit_batch(int nsb, const Info &info, float (*ti
         uint32_t b, bx, by, bz;
         float iso;
         info(k, g, b, bx, by, bz, iso);
-        const int cs = tile_case(g, bx, by, bz, tiles[k], iso);
-        const uint64_t tb = cs < 0 ? 0ull : mc_table[cs];   // 2 KB table (LDS-resident for the callers)
+        const uint64_t tb = mc_table[tile_case(g, bx, by, bz, tiles[k], iso)];   // 2 KB table (LDS-resident for the callers)
         const uint32_t nt = (uint32_t)(tb >> 60);
         const uint32_t incl = wave_incl_scan(nt);
-        const uint32_t tot = __shfl(incl, 63, 64);
+        const uint32_t tot = bcast(incl, 63);   // and with it the list's length: scalar
         if (FMT == VFMT_GRAD && 3 * tot != gc->expect[k] && l == 0) atomicOr(gc->err, ERR_INTERNAL);
         if (run + tot > (uint32_t)EMIT_TRIS) flush();
         if (l == 0) {
