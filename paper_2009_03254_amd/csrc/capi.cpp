@@ -448,7 +448,10 @@ int bcmc_extract(bcmc_volume *v, float iso, void *d_out, uint64_t capacity_verti
     };
     BCMC_HIP_TRY(mark(0));
     take_turn(v, s);
-    v->counters_dirty = 1;   // until every kernel of the call is enqueued
+    // until the call's counters have arrived nothing is known of what its kernels
+    // did: they may have been enqueued and never run (a capturing stream)
+    v->counters_dirty = 1;
+    v->have_extract = 0;
     if (!v->identity) {
         // a clock about to pass its end starts over with an empty cache
         if (v->calls_since_reset >= 0xFFFFFFF0u && (rc = reset_cache_state(v, s))) return rc;
@@ -473,13 +476,13 @@ int bcmc_extract(bcmc_volume *v, float iso, void *d_out, uint64_t capacity_verti
     launch_mc_emit(v->g, v->d, slots, v->d.I_slot, v->identity, iso, d_out, capacity_vertices,
                    v->vertex_format, s);
     BCMC_HIP_TRY(mark(6));
-    if (hipError_t le = hipGetLastError()) {   // a launch failed: counts and flags are unknown
+    if (hipError_t le = hipGetLastError()) {
         set_error(std::string("extract launch: ") + hipGetErrorString(le));
         return BCMC_E_HIP;
     }
+    if ((rc = sync_counters(v, s))) return rc;
     v->counters_dirty = 0;
     v->rewrite_flags = 0;
-    if ((rc = sync_counters(v, s))) return rc;
     const Counters &c = counters(v);
     v->stats.calls++;
     if (c.err & ERR_INTERNAL) {

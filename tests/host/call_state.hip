@@ -1,0 +1,230 @@
+// The host side of the calls (capi.cpp, batch_api.cpp) on a pretended device:
+// device memory is host memory, the launchers below do with it what the kernels
+// do (one slot per new block, counts from zero), and the HIP calls can be made
+// to fail.  Checks what the next calls find after one that failed.  Prints a
+// line and exits 1 at the first thing that does not hold.
+#include <hip/hip_runtime.h>
+#include <math.h>
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include <string>
+#include <vector>
+
+#include "../../include/bcmc.h"
+#include "../../paper_2009_03254_amd/csrc/batch.h"
+#include "../../paper_2009_03254_amd/csrc/common.h"
+
+#define CHECK(x)                                                        \
+    do {                                                                \
+        if (!(x)) {                                                     \
+            printf("line %d: %s does not hold\n", __LINE__, #x);        \
+            exit(1);                                                    \
+        }                                                               \
+    } while (0)
+
+// ---- what is made to fail -------------------------------------------------
+static bool lost = false;            // kernels are enqueued but never run, waits fail
+static bool readback_fails = false;  // kernels run, the wait for the counters fails
+static bool launch_fails = false;    // hipGetLastError after the launches
+static size_t malloc_limit = ~(size_t)0;
+static int launches = 0;             // kernels enqueued
+static std::vector<uint32_t> active_now;   // the blocks the next call finds active
+
+// ---- HIP --------------------------------------------------------------------
+extern "C" {
+hipError_t hipMalloc(void **p, size_t n) {
+    *p = n > malloc_limit ? nullptr : calloc(1, n);
+    return *p ? hipSuccess : hipErrorOutOfMemory;
+}
+hipError_t hipFree(void *p) { free(p); return hipSuccess; }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = aligned_alloc(128, (n + 127) / 128 * 128); return hipSuccess; }
+hipError_t hipHostFree(void *p) { free(p); return hipSuccess; }
+hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) { memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemset(void *d, int v, size_t n) { memset(d, v, n); return hipSuccess; }
+hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t) { memset(d, v, n); return hipSuccess; }
+hipError_t hipStreamQuery(hipStream_t) { return lost || readback_fails ? hipErrorLaunchFailure : hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return lost || readback_fails ? hipErrorLaunchFailure : hipSuccess; }
+hipError_t hipDeviceSynchronize() { return hipSuccess; }
+hipError_t hipGetLastError() { return launch_fails ? hipErrorLaunchFailure : hipSuccess; }
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { *v = 8; return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t *) { return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 0; return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = nullptr; return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+}
+
+// ---- the kernels --------------------------------------------------------------
+namespace bcmc {
+template <typename T>
+static bool all_zero(const T *p, uint64_t n) {
+    for (uint64_t i = 0; i < n * sizeof(T); i++)
+        if (reinterpret_cast<const unsigned char *>(p)[i]) return false;
+    return true;
+}
+static bool enqueue() { launches++; return !lost; }   // does the kernel run?
+
+uint64_t cull_tiles(const Geom &) { return 1; }
+static int last_rewrite = -1;
+static float last_prev = 0;
+void launch_cull(const Geom &g, const DevState &d, float, float prev_iso, int rewrite, int identity, uint32_t now,
+                 hipStream_t) {
+    last_rewrite = rewrite;
+    last_prev = prev_iso;
+    if (!enqueue()) return;
+    CHECK(all_zero(d.ctr, 1));                              // a call counts from zero
+    CHECK(all_zero(d.round_cnt, block_rounds(g.nb)));
+    for (uint32_t b : active_now) {
+        d.round_cnt[b / BLK_TILE]++;
+        if (!identity && d.I_slot[b] >= 0) d.S_stamp[d.I_slot[b]] = now;
+    }
+}
+void launch_compact_blocks(const Geom &g, const DevState &d, const SlotState &ss, uint32_t, uint32_t, hipStream_t) {
+    if (!enqueue()) return;
+    memset(d.ctr_next, 0, sizeof(Counters));
+    memset(d.round_next, 0, 8 * block_rounds(g.nb));
+    uint64_t n_new = 0;
+    for (uint32_t b : active_now)
+        if (!ss.identity && d.I_slot[b] < 0) d.I_new[n_new++] = b;
+    d.ctr->n_act = active_now.size();
+    d.ctr->n_new = n_new;
+    d.ctr->n_used = ss.n_used + n_new;
+    d.ctr->n_slots = std::max(ss.n_slots, ss.n_used + n_new);
+    if (!ss.identity && d.ctr->n_slots > ss.max_slots) d.ctr->err |= ERR_CACHE_CAP;
+}
+uint32_t *launch_evict(const Geom &, const DevState &d, uint32_t, uint32_t, uint32_t, hipStream_t) {
+    enqueue();
+    return d.evict[0];
+}
+void launch_assign_decode(const DevState &d, int, uint32_t, uint64_t, float, const uint32_t *, const SlotState &ss,
+                          uint32_t now, hipStream_t) {
+    if (!enqueue() || d.ctr->err) return;
+    for (uint64_t i = 0; i < d.ctr->n_new; i++) {
+        const uint64_t s = ss.n_used + i;
+        CHECK(d.S_block[s] < 0);   // the slots past the used ones hold no block
+        d.S_block[s] = (int32_t)d.I_new[i];
+        d.I_slot[d.I_new[i]] = (int32_t)s;
+        d.S_stamp[s] = now;
+    }
+}
+void launch_mc_count(const Geom &, const DevState &d, const float *, const int32_t *, int, float, int, hipStream_t) {
+    if (enqueue() && !d.ctr->err) d.ctr->xcd[0].verts += 3 * d.ctr->n_act;
+}
+void launch_mc_emit(const Geom &, const DevState &d, const float *, const int32_t *, int, float, void *, uint64_t, int,
+                    hipStream_t) {
+    if (enqueue() && !d.ctr->err) d.ctr->total_verts = d.ctr->xcd[0].verts;
+}
+void launch_publish(const void *ctr, HostCounters *host, uint32_t value, hipStream_t) {
+    if (!enqueue() || readback_fails) return;
+    memcpy(host->c, ctr, CTR_READ);
+    host->seq = value;
+}
+void launch_cache_empty(const DevState &d, uint64_t n_used, hipStream_t) {
+    if (!enqueue()) return;
+    for (uint64_t s = 0; s < n_used; s++) {
+        CHECK(d.S_block);
+        if (d.S_block[s] >= 0) d.I_slot[d.S_block[s]] = -1;
+        d.S_block[s] = -1;
+        d.S_stamp[s] = 0;
+    }
+}
+void launch_fill_u32(uint32_t *p, uint32_t v, uint64_t n, hipStream_t) {
+    if (!enqueue()) return;
+    CHECK(p || !n);
+    for (uint64_t i = 0; i < n; i++) p[i] = v;
+}
+void launch_backward(const Geom &, const DevState &d, const float *, float, const float *, uint64_t, float *, float *,
+                     int, hipStream_t) {
+    if (enqueue()) d.ctr->err = 0;
+}
+void launch_decode_ranges(const Geom &, const uint64_t *, int, uint32_t, float2 *, float *, unsigned int *, hipStream_t) { enqueue(); }
+void launch_tile_ranges(const Geom &, const float2 *, float2 *, hipStream_t) { enqueue(); }
+void launch_ranges_from_blocks(const Geom &, const float *, float2 *, unsigned int *, hipStream_t) { enqueue(); }
+void launch_encode(const Geom &, const void *, int, uint32_t, uint64_t *, unsigned int *, hipStream_t) { enqueue(); }
+void launch_vertices_q10(const void *, uint64_t, void *, hipStream_t) { enqueue(); }
+void launch_debug_cases(const Geom &, const DevState &, const float *, const int32_t *, int, float, uint8_t *, uint64_t,
+                        hipStream_t) { enqueue(); }
+void launch_copy_calibration(void *, const void *, uint64_t, hipStream_t) { enqueue(); }
+uint64_t dense_sign_words(uint32_t, uint32_t, uint32_t) { return 1; }
+uint64_t dense_chunk_words(uint32_t, uint32_t, uint32_t) { return 1; }
+void launch_dense(uint32_t, uint32_t, uint32_t, const float *, float, uint64_t *, uint32_t *, DenseCounters *,
+                  const uint64_t *, void *, uint64_t, hipStream_t) { enqueue(); }
+int batch_front_per_cu(int *n) { return *n = 1, 0; }
+int batch_decode_per_cu(const BatchParams &, int, int *n) { return *n = 1, 0; }
+int batch_back_per_cu(int, int *n) { return *n = 1, 0; }
+hipError_t launch_batch(const BatchParams &, int, int, const unsigned *, hipStream_t) { return hipSuccess; }
+}  // namespace bcmc
+using namespace bcmc;
+
+// ---- the scenarios --------------------------------------------------------------
+static const uint32_t NX = 40, NB = 1000;
+
+static bcmc_volume *load() {
+    static std::vector<uint64_t> words(NB);
+    bcmc_volume *v = nullptr;
+    CHECK(bcmc_load_compressed(words.data(), 8 * NB, 0, NX, NX, NX, BCMC_F32, 1, nullptr, &v) == BCMC_OK);
+    return v;
+}
+static int extract(bcmc_volume *v, float iso, std::vector<uint32_t> blocks, uint64_t *T = nullptr) {
+    uint64_t t = 0;
+    active_now = blocks;
+    const int rc = bcmc_extract(v, iso, nullptr, 0, &t, nullptr);
+    if (T) *T = t;
+    return rc;
+}
+// The call's triangles, and a cache in which every block's slot holds it.
+static void good_call(bcmc_volume *v, float iso, std::vector<uint32_t> blocks) {
+    uint64_t T = 0;
+    CHECK(extract(v, iso, blocks, &T) == BCMC_E_CAPACITY && T == blocks.size());
+    std::vector<int32_t> I_slot(NB), S_block(NB);
+    uint64_t n = 0;
+    CHECK(bcmc_debug_cache_state(v, I_slot.data(), S_block.data(), nullptr, &n) == BCMC_OK);
+    for (uint32_t b : blocks) CHECK(I_slot[b] >= 0);
+    for (uint32_t b = 0; b < NB; b++)
+        if (I_slot[b] >= 0) CHECK((uint64_t)I_slot[b] < n && S_block[I_slot[b]] == (int32_t)b);
+}
+
+// A call whose kernels never run, then one whose counters do not arrive: the
+// next ones count from zero and rewrite the flags.
+static void counts() {
+    bcmc_volume *v = load();
+    good_call(v, 0.5f, {1, 2, 3});
+    good_call(v, 0.25f, {2, 3, 4});
+    CHECK(last_rewrite == 0 && last_prev == 0.5f);
+    lost = true;
+    CHECK(extract(v, 0.75f, {9}) == BCMC_E_HIP);
+    lost = false;
+    good_call(v, 0.5f, {1, 2, 7});
+    CHECK(last_rewrite == 1);
+    good_call(v, 0.25f, {2, 3, 4});
+    CHECK(last_rewrite == 0);
+    // caller-owned blocks: the failed call's volume holds no extract to look at
+    std::vector<float> blocks(64 * NB);
+    float g = 0;
+    uint64_t T = 0;
+    std::vector<float> field(64 * NB);
+    CHECK(bcmc_volume_from_blocks(blocks.data(), NX, NX, NX, nullptr, &v) == BCMC_OK);
+    CHECK(extract(v, 0.5f, {1, 2, 3}, &T) == BCMC_E_CAPACITY && T == 3);
+    std::vector<float> gV(9 * 3);
+    CHECK(bcmc_backward(v, 0.5f, gV.data(), 9, field.data(), &g, nullptr) == BCMC_OK);
+    lost = true;
+    CHECK(extract(v, 0.75f, {9}) == BCMC_E_HIP);
+    lost = false;
+    CHECK(bcmc_backward(v, 0.5f, gV.data(), 9, field.data(), &g, nullptr) == BCMC_E_INVALID);
+    CHECK(extract(v, 0.5f, {1, 2, 3, 4}, &T) == BCMC_E_CAPACITY && T == 4);
+}
+
+int main(int argc, char **argv) {
+    const std::string what = argc > 1 ? argv[1] : "";
+    if (what == "counts") counts();
+    else return 2;
+    printf("%s ok\n", what.c_str());
+    return 0;
+}
