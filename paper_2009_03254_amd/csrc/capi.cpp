@@ -42,6 +42,7 @@ struct bcmc_volume {
     float cull_iso = NAN;          // isovalue of the last cull
     int rewrite_flags = 1;         // the flags do not follow from the ranges and cull_iso
     int counters_dirty = 1;        // the counts a call starts from are not known to be zero
+    int cache_dirty = 0;           // the host mirror may not follow the device's cache
     Counters *ctr[2] = {nullptr, nullptr};       // a call counts in one and clears the other
     uint64_t *round_cnt[2] = {nullptr, nullptr};
     uint32_t turn = 0;             // which
@@ -191,6 +192,7 @@ void cache_emptied(bcmc_volume *v) {
     v->evict_base = 0;
     v->n_slots = v->init_slots;
     v->n_used = 0;
+    v->cache_dirty = 0;
     v->have_extract = 0;
 }
 
@@ -388,6 +390,7 @@ int bcmc_set_cache_budget(bcmc_volume *v, uint64_t initial_bytes, uint64_t max_b
 int bcmc_reset_cache(bcmc_volume *v, void *hip_stream) {
     if (!v) return invalid("null handle");
     if (v->identity) return BCMC_OK;
+    if (v->cache_dirty) return reset_cache_state(v, as_stream(hip_stream));
     // the used slots alone: an explored part of a large volume is emptied
     // without a pass over one entry per block (5120x3840x768: 180 -> 12 us)
     launch_cache_empty(v->d, v->n_used, as_stream(hip_stream));
@@ -453,9 +456,12 @@ int bcmc_extract(bcmc_volume *v, float iso, void *d_out, uint64_t capacity_verti
     v->counters_dirty = 1;
     v->have_extract = 0;
     if (!v->identity) {
-        // a clock about to pass its end starts over with an empty cache
-        if (v->calls_since_reset >= 0xFFFFFFF0u && (rc = reset_cache_state(v, s))) return rc;
+        // a clock about to pass its end starts over with an empty cache, and so
+        // does one whose used slots are not known (a call that failed may have
+        // put blocks into slots past the mirror's)
+        if ((v->cache_dirty || v->calls_since_reset >= 0xFFFFFFF0u) && (rc = reset_cache_state(v, s))) return rc;
         v->calls_since_reset++;
+        v->cache_dirty = 1;   // until the mirror follows this call
     }
     const uint32_t now = v->calls_since_reset;
     const SlotState ss{v->n_slots, v->n_used, v->max_slots, v->identity};
@@ -504,6 +510,7 @@ int bcmc_extract(bcmc_volume *v, float iso, void *d_out, uint64_t capacity_verti
         v->n_slots = c.n_slots;
         v->n_used = c.n_used;
         if (c.span) v->evict_base = std::max(v->evict_base, now + 1u - c.span);
+        v->cache_dirty = 0;
     }
     const uint64_t T = c.total_verts / 3;
     *n_triangles = T;

@@ -221,9 +221,32 @@ static void counts() {
     CHECK(extract(v, 0.5f, {1, 2, 3, 4}, &T) == BCMC_E_CAPACITY && T == 4);
 }
 
+// A call that assigns slots and whose counters do not arrive: the next call
+// takes no slot that a block holds, and an emptied cache is empty.
+static void cache() {
+    for (int how = 0; how < 2; how++) {
+        bcmc_volume *v = load();
+        good_call(v, 0.5f, {1, 2, 3});
+        (how ? launch_fails : readback_fails) = true;
+        CHECK(extract(v, 0.75f, {3, 4, 5, 6}) == BCMC_E_HIP);
+        readback_fails = launch_fails = false;
+        good_call(v, 0.25f, {3, 6, 7});
+        good_call(v, 0.5f, {1, 2, 3, 4, 5, 6});
+        (how ? launch_fails : readback_fails) = true;
+        CHECK(extract(v, 0.75f, {11, 12}) == BCMC_E_HIP);
+        readback_fails = launch_fails = false;
+        CHECK(bcmc_reset_cache(v, nullptr) == BCMC_OK);
+        std::vector<int32_t> I_slot(NB);
+        CHECK(bcmc_debug_cache_state(v, I_slot.data(), nullptr, nullptr, nullptr) == BCMC_OK);
+        for (uint32_t b = 0; b < NB; b++) CHECK(I_slot[b] == -1);
+        good_call(v, 0.5f, {1, 2, 3});
+    }
+}
+
 int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "counts") counts();
+    else if (what == "cache") cache();
     else return 2;
     printf("%s ok\n", what.c_str());
     return 0;
