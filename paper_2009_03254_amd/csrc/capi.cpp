@@ -233,6 +233,20 @@ hipStream_t as_stream(void *p) { return reinterpret_cast<hipStream_t>(p); }
 
 const Counters &counters(const bcmc_volume *v) { return *reinterpret_cast<const Counters *>(v->h_ctr->c); }
 
+// For a call that waits for its counters, before anything is enqueued: a
+// capturing stream would record the kernels, the wait would fail, and a replay
+// would count into copies that no call has cleared.
+int refuse_capture(hipStream_t s) {
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &c) != hipSuccess) {
+        (void)hipGetLastError();   // the launches report it
+        return BCMC_OK;
+    }
+    if (c == hipStreamCaptureStatusNone) return BCMC_OK;
+    set_error("the call waits for its results: it cannot run on a capturing stream");
+    return BCMC_E_HIP;
+}
+
 // Reads the counters back.  The caller waits for them anyway, so a kernel at
 // the end of the call's work writes them to pinned memory and the host polls
 // the number behind them: a copy and an event took about 10 us more of every
@@ -443,7 +457,8 @@ int bcmc_extract(bcmc_volume *v, float iso, void *d_out, uint64_t capacity_verti
     if (!d_out && capacity_vertices) return invalid("null output buffer with nonzero capacity");
     if (iso != iso) return invalid("iso is NaN");
     hipStream_t s = as_stream(hip_stream);
-    int rc = BCMC_OK;
+    int rc = refuse_capture(s);
+    if (rc) return rc;
     // event i opens stage i and closes stage i - 1: record it when either is profiled
     const uint32_t prof = v->profiling, marks = prof | (prof << 1);
     auto mark = [&](int i) -> hipError_t {
@@ -562,6 +577,7 @@ int bcmc_backward(bcmc_volume *v, float iso, const float *d_gV, uint64_t n_verts
         BCMC_HIP_TRY(hipMemsetAsync(d_diso, 0, sizeof(float), s));
         return BCMC_OK;
     }
+    if (int rc = refuse_capture(s)) return rc;
     launch_backward(v->g, v->d, v->ext_blocks, iso, d_gV, n_verts, d_dfield, d_diso, v->last_format, s);
     BCMC_HIP_TRY(hipGetLastError());
     // the kernel compares each block's vertex count with the forward's
@@ -776,6 +792,7 @@ extern "C" int bcmc_dense_extract(bcmc_dense *h, const float *d_field, float iso
     if (!d_out && capacity_vertices) return invalid("null output buffer with nonzero capacity");
     if (iso != iso) return invalid("iso is NaN");
     hipStream_t s = as_stream(hip_stream);
+    if (int rc = refuse_capture(s)) return rc;
     launch_dense(h->nx, h->ny, h->nz, d_field, iso, h->bits, h->chunk_tot, h->ctr, h->mc_table, d_out,
                  capacity_vertices, s);
     BCMC_HIP_TRY(hipGetLastError());

@@ -28,6 +28,7 @@
 static bool lost = false;            // kernels are enqueued but never run, waits fail
 static bool readback_fails = false;  // kernels run, the wait for the counters fails
 static bool launch_fails = false;    // hipGetLastError after the launches
+static bool capturing = false;       // the stream records: kernels do not run, waits fail
 static size_t malloc_limit = ~(size_t)0;
 static int launches = 0;             // kernels enqueued
 static std::vector<uint32_t> active_now;   // the blocks the next call finds active
@@ -45,8 +46,12 @@ hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { memcpy(d
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) { memcpy(d, s, n); return hipSuccess; }
 hipError_t hipMemset(void *d, int v, size_t n) { memset(d, v, n); return hipSuccess; }
 hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t) { memset(d, v, n); return hipSuccess; }
-hipError_t hipStreamQuery(hipStream_t) { return lost || readback_fails ? hipErrorLaunchFailure : hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { return lost || readback_fails ? hipErrorLaunchFailure : hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *c) {
+    *c = capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+hipError_t hipStreamQuery(hipStream_t) { return lost || readback_fails || capturing ? hipErrorLaunchFailure : hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return lost || readback_fails || capturing ? hipErrorLaunchFailure : hipSuccess; }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
 hipError_t hipGetLastError() { return launch_fails ? hipErrorLaunchFailure : hipSuccess; }
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
@@ -69,7 +74,7 @@ static bool all_zero(const T *p, uint64_t n) {
         if (reinterpret_cast<const unsigned char *>(p)[i]) return false;
     return true;
 }
-static bool enqueue() { launches++; return !lost; }   // does the kernel run?
+static bool enqueue() { launches++; return !lost && !capturing; }   // does the kernel run?
 
 uint64_t cull_tiles(const Geom &) { return 1; }
 static int last_rewrite = -1;
@@ -243,10 +248,39 @@ static void cache() {
     }
 }
 
+// On a capturing stream the calls that wait for their counters fail without a
+// launch (what a replay would run), and leave the handle as it was.
+static void capture() {
+    bcmc_volume *v = load();
+    good_call(v, 0.5f, {1, 2, 3});
+    capturing = true;
+    int before = launches;
+    CHECK(extract(v, 0.75f, {9}) == BCMC_E_HIP && launches == before);
+    capturing = false;
+    good_call(v, 0.25f, {2, 3, 4});
+    CHECK(last_rewrite == 0 && last_prev == 0.5f);
+    std::vector<float> blocks(64 * NB), field(64 * NB), gV(27);
+    float g = 0;
+    uint64_t T = 0;
+    CHECK(bcmc_volume_from_blocks(blocks.data(), NX, NX, NX, nullptr, &v) == BCMC_OK);
+    CHECK(extract(v, 0.5f, {1, 2, 3}, &T) == BCMC_E_CAPACITY && T == 3);
+    bcmc_dense *h = nullptr;
+    CHECK(bcmc_dense_create(NX, NX, NX, &h) == BCMC_OK);
+    capturing = true;
+    before = launches;
+    CHECK(extract(v, 0.75f, {9}) == BCMC_E_HIP);
+    CHECK(bcmc_backward(v, 0.5f, gV.data(), 9, field.data(), &g, nullptr) == BCMC_E_HIP);
+    CHECK(bcmc_dense_extract(h, blocks.data(), 0.5f, nullptr, 0, &T, nullptr) == BCMC_E_HIP);
+    CHECK(launches == before);
+    capturing = false;
+    CHECK(bcmc_backward(v, 0.5f, gV.data(), 9, field.data(), &g, nullptr) == BCMC_OK);
+}
+
 int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "counts") counts();
     else if (what == "cache") cache();
+    else if (what == "capture") capture();
     else return 2;
     printf("%s ok\n", what.c_str());
     return 0;
