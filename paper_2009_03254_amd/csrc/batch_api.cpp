@@ -51,6 +51,7 @@ struct bcmc_batch {
     int graph_sb = 0;
     unsigned graph_grid = 0, graph_front_grid = 0, graph_decode_grid = 0;
     int use_graph = 1, graph_failed = 0;
+    int dirty = 0;              // a run failed: the store and the totals may be mid-update
     float last_ms = 0.0f;
     unsigned long long *h_ts = nullptr;   // phase clock stamps of the last run
     float phase_ms[8] = {};
@@ -134,6 +135,11 @@ int run_once(bcmc_batch *b, void *d_out, uint64_t cap, hipStream_t caller) {
     b->p.cap = cap;
     BCMC_HIP_TRY(hipEventRecord(b->ev_in, caller));
     BCMC_HIP_TRY(hipStreamWaitEvent(b->gstream, b->ev_in, 0));
+    // after a failed run the totals, which the flags add to, need not be zero
+    // (on the private stream: behind whatever that run enqueued)
+    if (b->dirty)
+        if (int rc = reset_cache(b, b->gstream)) return rc;
+    b->dirty = 1;   // until this run's results are there
     BCMC_HIP_TRY(hipEventRecord(b->ev_t0, b->gstream));
     bool launched = false;
     if (b->use_graph && !b->graph_failed) {
@@ -183,12 +189,10 @@ int run_once(bcmc_batch *b, void *d_out, uint64_t cap, hipStream_t caller) {
                              ? (float)((double)(b->h_ts[k + 1] - b->h_ts[k]) / b->clock_khz)
                              : 0.0f;
     if (b->h_ctr->err) {
-        // a failed run may leave the store and the totals mid-update
-        (void)reset_cache(b, b->gstream);
-        (void)hipStreamSynchronize(b->gstream);
         set_error("internal consistency check failed in the batched extraction");
         return BCMC_E_HIP;
     }
+    b->dirty = 0;
     return BCMC_OK;
 }
 

@@ -164,7 +164,21 @@ void launch_dense(uint32_t, uint32_t, uint32_t, const float *, float, uint64_t *
 int batch_front_per_cu(int *n) { return *n = 1, 0; }
 int batch_decode_per_cu(const BatchParams &, int, int *n) { return *n = 1, 0; }
 int batch_back_per_cu(int, int *n) { return *n = 1, 0; }
-hipError_t launch_batch(const BatchParams &, int, int, const unsigned *, hipStream_t) { return hipSuccess; }
+// A run whose launches end after the flags (batch_fails), or one in full.
+static bool batch_fails = false;
+hipError_t launch_batch(const BatchParams &p, int, int, const unsigned *, hipStream_t) {
+    if (!enqueue()) return hipSuccess;
+    CHECK(all_zero(p.vol_tot, p.n_vols));   // the flags add to them
+    CHECK(all_zero(p.job_tot, p.n_jobs));
+    for (uint32_t v = 0; v < p.n_vols; v++) p.vol_tot[v] = 7ull << 32;
+    for (uint32_t j = 0; j < p.n_jobs; j++) p.job_tot[j] = 5;
+    if (batch_fails) return hipErrorLaunchFailure;
+    memset(p.vol_tot, 0, 8 * p.n_vols);
+    memset(p.job_tot, 0, 8 * p.n_jobs);
+    p.ctr->n_slots += 7;
+    *p.h_ctr = *p.ctr;
+    return hipSuccess;
+}
 }  // namespace bcmc
 using namespace bcmc;
 
@@ -276,11 +290,39 @@ static void capture() {
     CHECK(bcmc_backward(v, 0.5f, gV.data(), 9, field.data(), &g, nullptr) == BCMC_OK);
 }
 
+// A batch whose launches end half-way: the next run starts from zero totals.
+static void batch() {
+    bcmc_volume *v = load();
+    const uint32_t job_vol[2] = {0, 0};
+    const float iso[2] = {0.5f, 0.25f};
+    bcmc_batch *b = nullptr;
+    uint64_t off[3];
+    CHECK(bcmc_batch_create(&v, 1, job_vol, iso, 2, nullptr, &b) == BCMC_OK);
+    CHECK(bcmc_batch_set_graph(b, 0) == BCMC_OK);
+    auto resident = [&] {
+        bcmc_batch_info i;
+        CHECK(bcmc_batch_get_info(b, &i) == BCMC_OK);
+        return i.n_resident;
+    };
+    for (uint64_t k = 1; k <= 2; k++) {
+        CHECK(bcmc_batch_run(b, nullptr, 0, off, nullptr) == BCMC_OK);
+        CHECK(resident() == 7 * k);   // the store carries over
+    }
+    batch_fails = true;
+    CHECK(bcmc_batch_run(b, nullptr, 0, off, nullptr) == BCMC_E_HIP);
+    batch_fails = false;
+    for (uint64_t k = 1; k <= 2; k++) {
+        CHECK(bcmc_batch_run(b, nullptr, 0, off, nullptr) == BCMC_OK);
+        CHECK(resident() == 7 * k);   // started over
+    }
+}
+
 int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "counts") counts();
     else if (what == "cache") cache();
     else if (what == "capture") capture();
+    else if (what == "batch") batch();
     else return 2;
     printf("%s ok\n", what.c_str());
     return 0;
