@@ -216,16 +216,20 @@ int set_budget(bcmc_volume *v, uint64_t initial_bytes, uint64_t max_bytes, hipSt
     free_cache(v);
     v->init_slots = init;
     v->max_slots = maxs;
+    v->cache_dirty = 1;
     int rc;
-    if ((rc = dev_alloc(&v->d.S_block, maxs))) return rc;
-    if ((rc = dev_alloc(&v->d.S_stamp, maxs))) return rc;
-    if ((rc = dev_alloc(&v->d.slots, maxs * 64))) return rc;
-    if ((rc = dev_alloc(&v->d.masks, maxs))) return rc;
-    if ((rc = dev_alloc(&v->d.mask_iso, maxs))) return rc;
-    for (int i = 0; i < 2; i++)
-        if ((rc = dev_alloc(&v->d.evict[i], maxs))) return rc;
-    if ((rc = dev_alloc(&v->d.evict_hist, (maxs + EVICT_TILE - 1) / EVICT_TILE * EVICT_BINS))) return rc;
-    if ((rc = dev_alloc(&v->d.evict_tot, EVICT_BINS))) return rc;
+    if ((rc = dev_alloc(&v->d.S_block, maxs)) || (rc = dev_alloc(&v->d.S_stamp, maxs)) ||
+        (rc = dev_alloc(&v->d.slots, maxs * 64)) || (rc = dev_alloc(&v->d.masks, maxs)) ||
+        (rc = dev_alloc(&v->d.mask_iso, maxs)) || (rc = dev_alloc(&v->d.evict[0], maxs)) ||
+        (rc = dev_alloc(&v->d.evict[1], maxs)) ||
+        (rc = dev_alloc(&v->d.evict_hist, (maxs + EVICT_TILE - 1) / EVICT_TILE * EVICT_BINS)) ||
+        (rc = dev_alloc(&v->d.evict_tot, EVICT_BINS))) {
+        // no slots until a budget fits: nothing of the cache is there to touch
+        free_cache(v);
+        v->init_slots = v->max_slots = 0;
+        (void)reset_cache_state(v, s);
+        return rc;
+    }
     return reset_cache_state(v, s);
 }
 

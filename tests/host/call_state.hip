@@ -317,12 +317,32 @@ static void batch() {
     }
 }
 
+// A budget that does not fit the memory: no slots, and no array that is not
+// there is touched; the next budget that fits works.
+static void budget() {
+    bcmc_volume *v = load();
+    good_call(v, 0.5f, {1, 2, 3});
+    for (size_t limit : {(size_t)2000, (size_t)1 << 17}) {   // the first array fails, the slots fail
+        malloc_limit = limit;
+        CHECK(bcmc_set_cache_budget(v, 256 * 100, 256 * 1000) == BCMC_E_NOMEM);
+        malloc_limit = ~(size_t)0;
+        CHECK(extract(v, 0.5f, {1, 2, 3}) == BCMC_E_CACHE_CAP);
+        CHECK(bcmc_reset_cache(v, nullptr) == BCMC_OK);
+        CHECK(extract(v, 0.5f, {2, 3, 4}) == BCMC_E_CACHE_CAP);
+        uint64_t n = 1;
+        CHECK(bcmc_debug_cache_state(v, nullptr, nullptr, nullptr, &n) == BCMC_OK && n == 0);
+        CHECK(bcmc_set_cache_budget(v, 256 * 100, 256 * 1000) == BCMC_OK);
+        good_call(v, 0.5f, {1, 2, 3});
+    }
+}
+
 int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "counts") counts();
     else if (what == "cache") cache();
     else if (what == "capture") capture();
     else if (what == "batch") batch();
+    else if (what == "budget") budget();
     else return 2;
     printf("%s ok\n", what.c_str());
     return 0;
