@@ -14,7 +14,7 @@
 //   flags   per block, in units of BATCH_UNIT consecutive blocks of one volume:
 //           used by some job of its volume (new or resident) and, per job,
 //           whether it may emit (2x2x2 hull rule), as bits, with counts per
-//           unit and totals per volume and per job
+//           unit and totals per group of a volume's or a job's units
 //   lists   the new blocks, the resident used ones, and the list L of
 //           (job, block) pairs in job-major, block-ascending order (= the
 //           concatenated canonical orders): a wave per unit and list, whose
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(BATCH_UNIT) void k_batch_flags(BatchParams p) {
                 uint32_t n = 0;
                 for (int i = 0; i < UNIT_WAVES; i++) n += s_n[threadIdx.x][i];
                 p.pair_cnt[p.job_unit[j] + k] = n;
-                if (n) atomicAdd(&p.job_tot[j], (unsigned long long)n);
+                if (n) atomicAdd(&p.job_tot[p.job_group[j] + k / BATCH_GROUP], (unsigned long long)n);
             }
             __syncthreads();   // s_n is rewritten
         }
@@ -166,7 +166,9 @@ __global__ __launch_bounds__(BATCH_UNIT) void k_batch_flags(BatchParams p) {
             uint32_t n = 0;
             for (int i = 0; i < UNIT_WAVES; i++) n += s_u[i];
             p.unit_cnt[u] = n;
-            if (n) atomicAdd(&p.vol_tot[vi], (unsigned long long)(n & 0xFFFFu) << 32 | (n >> 16));
+            if (n)
+                atomicAdd(&p.vol_tot[p.vol_group[vi] + k / BATCH_GROUP],
+                          (unsigned long long)(n & 0xFFFFu) << 32 | (n >> 16));
         }
         __syncthreads();   // s_u is rewritten
     }
@@ -199,7 +201,8 @@ __global__ __launch_bounds__(BT) void k_batch_lists(BatchParams p) {
     constexpr int W = UNIT_WAVES;
     auto all = [](uint64_t x) { return x; };
     if (blockIdx.x == 0 && wave_id() == 0) {   // the run's totals; the new blocks' slots
-        const uint64_t tv = wave_range_sum(p.vol_tot, 0, p.n_vols, all), tl = wave_range_sum(p.job_tot, 0, p.n_jobs, all);
+        const uint64_t tv = wave_range_sum(p.vol_tot, 0, p.n_groups, all),
+                       tl = wave_range_sum(p.job_tot, 0, p.n_jgroups, all);
         if (lane() == 0) {
             const uint64_t n0 = p.ctr->n_slots, tn = tv >> 32;
             p.ctr->slot_base = n0;
@@ -216,10 +219,11 @@ __global__ __launch_bounds__(BT) void k_batch_lists(BatchParams p) {
             const uint32_t n = p.unit_cnt[t];
             if (!n) continue;
             const uint32_t vi = find_base(p.vol_unit, p.n_vols, t);
+            const uint64_t k = t - p.vol_unit[vi];   // the volume's k-th unit
             auto parts = [](uint32_t x) { return (uint64_t)(x & 0xFFFFu) << 32 | (x >> 16); };
-            const uint64_t o = wave_range_sum(p.vol_tot, 0, vi, all) +
-                               wave_range_sum(p.unit_cnt, p.vol_unit[vi], t, parts);
-            const uint32_t gb0 = (uint32_t)(p.vols[vi].gbase + (t - p.vol_unit[vi]) * BATCH_UNIT);
+            const uint64_t o = wave_range_sum(p.vol_tot, 0, p.vol_group[vi] + k / BATCH_GROUP, all) +
+                               wave_range_sum(p.unit_cnt, t - k % BATCH_GROUP, t, parts);
+            const uint32_t gb0 = (uint32_t)(p.vols[vi].gbase + k * BATCH_UNIT);
             if (n & 0xFFFFu)
                 list_unit(p.new_bits + t * W, o >> 32, [&](uint64_t at, uint32_t i) { p.new_list[at] = gb0 + i; });
             if (n >> 16)
@@ -228,9 +232,10 @@ __global__ __launch_bounds__(BT) void k_batch_lists(BatchParams p) {
             const uint64_t ju = t - p.n_units;
             if (!p.pair_cnt[ju]) continue;
             const uint32_t j = find_base(p.job_unit, p.n_jobs, ju);
-            const uint64_t o = wave_range_sum(p.job_tot, 0, j, all) +
-                               wave_range_sum(p.pair_cnt, p.job_unit[j], ju, all);
-            const uint32_t e0 = (uint32_t)(p.job_jbase[j] + (ju - p.job_unit[j]) * BATCH_UNIT);
+            const uint64_t k = ju - p.job_unit[j];
+            const uint64_t o = wave_range_sum(p.job_tot, 0, p.job_group[j] + k / BATCH_GROUP, all) +
+                               wave_range_sum(p.pair_cnt, ju - k % BATCH_GROUP, ju, all);
+            const uint32_t e0 = (uint32_t)(p.job_jbase[j] + k * BATCH_UNIT);
             list_unit(p.pair_bits + ju * W, o, [&](uint64_t at, uint32_t i) {
                 p.list[at] = e0 + i;
                 p.list_job[at] = j;
@@ -355,8 +360,8 @@ __global__ __launch_bounds__(BT) void k_batch_count(BatchParams p) {
     stamp(p, 5);
     // the totals have been read (lists): cleared for the next run
     if (blockIdx.x == 0) {
-        for (uint32_t i = threadIdx.x; i < p.n_vols; i += BT) p.vol_tot[i] = 0;
-        for (uint32_t i = threadIdx.x; i < p.n_jobs; i += BT) p.job_tot[i] = 0;
+        for (uint64_t i = threadIdx.x; i < p.n_groups; i += BT) p.vol_tot[i] = 0;
+        for (uint64_t i = threadIdx.x; i < p.n_jgroups; i += BT) p.job_tot[i] = 0;
     }
     if (p.ctr->err) return;   // an earlier kernel failed: nothing to do
     const uint64_t n_list = uniform64(p.ctr->n_list);

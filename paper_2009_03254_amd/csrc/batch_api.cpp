@@ -123,8 +123,8 @@ int set_schedule(bcmc_batch *b, int sb, int per_cu, int front_pc, int scan) {
 int reset_cache(bcmc_batch *b, hipStream_t s) {
     launch_fill_u32(reinterpret_cast<uint32_t *>(b->p.I_slot), 0xFFFFFFFFu, b->n_gblocks, s);
     launch_fill_u32(reinterpret_cast<uint32_t *>(b->p.ctr), 0u, sizeof(BatchCounters) / 4, s);
-    launch_fill_u32(reinterpret_cast<uint32_t *>(b->p.vol_tot), 0u, 2ull * b->n_vols, s);
-    launch_fill_u32(reinterpret_cast<uint32_t *>(b->p.job_tot), 0u, 2ull * b->n_jobs, s);
+    launch_fill_u32(reinterpret_cast<uint32_t *>(b->p.vol_tot), 0u, 2 * b->p.n_groups, s);
+    launch_fill_u32(reinterpret_cast<uint32_t *>(b->p.job_tot), 0u, 2 * b->p.n_jgroups, s);
     BCMC_HIP_TRY(hipGetLastError());
     return BCMC_OK;
 }
@@ -261,7 +261,8 @@ int bcmc_batch_create(bcmc_volume *const *vols, uint32_t n_vols, const uint32_t 
     b->n_vols = n_vols;
     b->n_jobs = n_jobs;
     std::vector<BatchVol> hv(n_vols);
-    std::vector<uint64_t> gbase(n_vols), jbase(n_jobs), vunit(n_vols), junit(n_jobs);
+    std::vector<uint64_t> gbase(n_vols), jbase(n_jobs), vunit(n_vols), junit(n_jobs), vgroup(n_vols),
+        jgroup(n_jobs);
     std::vector<uint32_t> vol_jobs;
     uint64_t gb = 0;
     for (uint32_t v = 0; v < n_vols; v++) {
@@ -273,6 +274,8 @@ int bcmc_batch_create(bcmc_volume *const *vols, uint32_t n_vols, const uint32_t 
         gb += hv[v].g.nb;
         vunit[v] = b->p.n_units;
         b->p.n_units += (hv[v].g.nb + BATCH_UNIT - 1) / BATCH_UNIT;
+        vgroup[v] = b->p.n_groups;
+        b->p.n_groups += (b->p.n_units - vunit[v] + BATCH_GROUP - 1) / BATCH_GROUP;
         hv[v].job_lo = (uint32_t)vol_jobs.size();
         for (uint32_t j = 0; j < n_jobs; j++)
             if (job_vol[j] == v) vol_jobs.push_back(j);
@@ -284,6 +287,8 @@ int bcmc_batch_create(bcmc_volume *const *vols, uint32_t n_vols, const uint32_t 
         jb += hv[job_vol[j]].g.nb;
         junit[j] = b->p.n_junits;
         b->p.n_junits += (hv[job_vol[j]].g.nb + BATCH_UNIT - 1) / BATCH_UNIT;
+        jgroup[j] = b->p.n_jgroups;
+        b->p.n_jgroups += (b->p.n_junits - junit[j] + BATCH_GROUP - 1) / BATCH_GROUP;
     }
     b->n_gblocks = gb;
     b->n_jblocks = jb;
@@ -320,7 +325,7 @@ int bcmc_batch_create(bcmc_volume *const *vols, uint32_t n_vols, const uint32_t 
     unsigned max_grid = (unsigned)(std::max(b->per_cu_max, pc4) * b->cus);
     BatchParams &p = b->p;
     BatchVol *d_vols;
-    uint64_t *d_gbase, *d_jbase, *d_vunit, *d_junit;
+    uint64_t *d_gbase, *d_jbase, *d_vunit, *d_junit, *d_vgroup, *d_jgroup;
     constexpr uint64_t W = BATCH_UNIT / 64;
     uint32_t *d_vol_jobs, *d_job_vol;
     float *d_iso;
@@ -331,8 +336,9 @@ int bcmc_batch_create(bcmc_volume *const *vols, uint32_t n_vols, const uint32_t 
         (rc = balloc(b, &d_vunit, n_vols)) || (rc = balloc(b, &d_junit, n_jobs)) ||
         (rc = balloc(b, &p.new_bits, W * p.n_units)) || (rc = balloc(b, &p.res_bits, W * p.n_units)) ||
         (rc = balloc(b, &p.pair_bits, W * p.n_junits)) || (rc = balloc(b, &p.unit_cnt, p.n_units)) ||
-        (rc = balloc(b, &p.pair_cnt, p.n_junits)) || (rc = balloc(b, &p.vol_tot, n_vols)) ||
-        (rc = balloc(b, &p.job_tot, n_jobs)) || (rc = balloc(b, &p.res_list, gb)) ||
+        (rc = balloc(b, &p.pair_cnt, p.n_junits)) || (rc = balloc(b, &p.vol_tot, p.n_groups)) ||
+        (rc = balloc(b, &p.job_tot, p.n_jgroups)) || (rc = balloc(b, &d_vgroup, n_vols)) ||
+        (rc = balloc(b, &d_jgroup, n_jobs)) || (rc = balloc(b, &p.res_list, gb)) ||
         (rc = balloc(b, &p.jmask, jb)) ||
         (rc = balloc(b, &p.new_list, gb)) || (rc = balloc(b, &p.list, jb)) ||
         (rc = balloc(b, &p.list_job, jb)) || (rc = balloc(b, &p.cnt, jb)) ||
@@ -363,6 +369,8 @@ int bcmc_batch_create(bcmc_volume *const *vols, uint32_t n_vols, const uint32_t 
         (e = hipMemcpy(d_table, mc_table_host(), 256 * 8, hipMemcpyHostToDevice)) ||
         (e = hipMemcpy(d_vunit, vunit.data(), 8 * n_vols, hipMemcpyHostToDevice)) ||
         (e = hipMemcpy(d_junit, junit.data(), 8 * n_jobs, hipMemcpyHostToDevice)) ||
+        (e = hipMemcpy(d_vgroup, vgroup.data(), 8 * n_vols, hipMemcpyHostToDevice)) ||
+        (e = hipMemcpy(d_jgroup, jgroup.data(), 8 * n_jobs, hipMemcpyHostToDevice)) ||
         (e = hipHostMalloc((void **)&b->h_ctr, sizeof(BatchCounters), hipHostMallocDefault)) ||
         (e = hipHostMalloc((void **)&b->h_job_off, 8 * (n_jobs + 1), hipHostMallocDefault)) ||
         (e = hipHostMalloc((void **)&b->h_ts, 9 * sizeof(unsigned long long), hipHostMallocDefault)) ||
@@ -376,6 +384,8 @@ int bcmc_batch_create(bcmc_volume *const *vols, uint32_t n_vols, const uint32_t 
     p.vol_gbase = d_gbase;
     p.vol_unit = d_vunit;
     p.job_unit = d_junit;
+    p.vol_group = d_vgroup;
+    p.job_group = d_jgroup;
     p.h_ctr = b->h_ctr;
     p.h_job_off = b->h_job_off;
     p.h_ts = b->h_ts;

@@ -168,13 +168,13 @@ int batch_back_per_cu(int, int *n) { return *n = 1, 0; }
 static bool batch_fails = false;
 hipError_t launch_batch(const BatchParams &p, int, int, const unsigned *, hipStream_t) {
     if (!enqueue()) return hipSuccess;
-    CHECK(all_zero(p.vol_tot, p.n_vols));   // the flags add to them
-    CHECK(all_zero(p.job_tot, p.n_jobs));
-    for (uint32_t v = 0; v < p.n_vols; v++) p.vol_tot[v] = 7ull << 32;
-    for (uint32_t j = 0; j < p.n_jobs; j++) p.job_tot[j] = 5;
+    CHECK(all_zero(p.vol_tot, p.n_groups));   // the flags add to them
+    CHECK(all_zero(p.job_tot, p.n_jgroups));
+    for (uint64_t v = 0; v < p.n_groups; v++) p.vol_tot[v] = 7ull << 32;
+    for (uint64_t j = 0; j < p.n_jgroups; j++) p.job_tot[j] = 5;
     if (batch_fails) return hipErrorLaunchFailure;
-    memset(p.vol_tot, 0, 8 * p.n_vols);
-    memset(p.job_tot, 0, 8 * p.n_jobs);
+    memset(p.vol_tot, 0, 8 * p.n_groups);
+    memset(p.job_tot, 0, 8 * p.n_jgroups);
     p.ctr->n_slots += 7;
     *p.h_ctr = *p.ctr;
     return hipSuccess;
