@@ -185,9 +185,14 @@ __global__ __launch_bounds__(256) void k_cull(Geom g, const float2 *__restrict__
         uint32_t tx, ty, tz;
         tile_of(live_tile(qq - n_stale), tx, ty, tz);
         const int z0 = first_layer(tz), z1 = min(z0 + LAYERS, (int)g.nbz);
+        // the places in the box are worked out for each tile: kept over the queue
+        // for every load they take 42 registers (135 and 3 waves per SIMD instead
+        // of 85 and 5: 59 against 56.5 us at 236 M blocks)
+        int t = (int)threadIdx.x;
+        if constexpr (QUEUE) asm volatile("" : "+v"(t));
 #pragma unroll
         for (int k = 0; k < PER; k++) {
-            const int i = (int)threadIdx.x + 256 * k;
+            const int i = t + 256 * k;
             const int li = i / SLOTS, r = i - li * SLOTS;
             const int hy = r / RX, hx = r - hy * RX;
             const int zl = z0 - 1 + li;
