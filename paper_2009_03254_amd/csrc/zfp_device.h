@@ -385,8 +385,8 @@ __host__ __device__ __forceinline__ rec_half *rec_halves(uint32_t *rec) { return
 typedef const uint64_t __attribute__((address_space(3))) *lds_words;
 typedef uint32_t __attribute__((address_space(3))) *lds_rec;
 typedef uint64_t __attribute__((address_space(3))) *lds_out;
-__host__ __device__ __forceinline__ uint16_t __attribute__((address_space(3))) *rec_halves(lds_rec rec) {
-    return (uint16_t __attribute__((address_space(3))) *)rec;
+__host__ __device__ __forceinline__ rec_half __attribute__((address_space(3))) *rec_halves(lds_rec rec) {
+    return (rec_half __attribute__((address_space(3))) *)rec;
 }
 template <bool F64, class SP, class RP>
 __host__ __device__ __forceinline__ uint64_t staged_pass1(SP st, RP rec, int rate, int &kend) {
