@@ -145,7 +145,8 @@ BCMC_API int bcmc_rebind_blocks(bcmc_volume *v, const float *d_blocks, void *hip
  * max(n_new - n_avail, ceil(n_slots/2)) slots, never beyond max_bytes/256
  * (max_bytes = 0: one slot per block).  Slot memory for the cap is reserved
  * here so growth needs no host round-trip.  Empties the cache.
- * Errors: BCMC_E_INVALID (max below initial, identity volume), BCMC_E_NOMEM. */
+ * Errors: BCMC_E_INVALID (max below initial, identity volume); BCMC_E_NOMEM
+ * (the cache has no slots until a budget fits). */
 BCMC_API int bcmc_set_cache_budget(bcmc_volume *v, uint64_t initial_bytes, uint64_t max_bytes);
 
 /* Empty the cache (every slot empty, age 2^31), keeping the budget. */
@@ -159,7 +160,9 @@ BCMC_API int bcmc_reset_cache(bcmc_volume *v, void *hip_stream);
  * when its value is < iso.  Synchronises hip_stream once to read the count.
  * Errors: BCMC_E_CAPACITY when 3*T > capacity_vertices (*n_triangles = T,
  * the first capacity_vertices records are written, the cache stays valid:
- * enlarge and call again); BCMC_E_CACHE_CAP (cache reset); BCMC_E_HIP. */
+ * enlarge and call again); BCMC_E_CACHE_CAP (cache reset); BCMC_E_HIP (also
+ * on a capturing stream, before anything is enqueued: the call waits for its
+ * count; after other failures the next call starts with an empty cache). */
 BCMC_API int bcmc_extract(bcmc_volume *v, float iso, void *d_out, uint64_t capacity_vertices,
                  uint64_t *n_triangles, void *hip_stream);
 
@@ -189,7 +192,7 @@ BCMC_API int bcmc_set_vertex_format(bcmc_volume *v, int format);
  * Errors: BCMC_E_INVALID (not an identity handle, no extract, n_verts
  * differs from the last extract, or the field changed since the extract so
  * that some block's vertex count differs: the gradient is then not valid and
- * the extract must be repeated). */
+ * the extract must be repeated), BCMC_E_HIP (also on a capturing stream). */
 BCMC_API int bcmc_backward(bcmc_volume *v, float iso, const float *d_gV, uint64_t n_verts,
                   float *d_dfield, float *d_diso, void *hip_stream);
 

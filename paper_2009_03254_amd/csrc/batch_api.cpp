@@ -37,7 +37,7 @@ struct bcmc_batch {
     int sb = 8;
     unsigned grid = 0;          // back kernel (count, scan, emission)
     unsigned front_grid = 0;    // flags and lists kernels
-    int scan = 0;               // the schedule's scan choice (reported)
+    int scan = 0;               // the schedule's scan value (reported, without effect)
     int front_pc_max = 1;       // its resident workgroups per CU
     unsigned decode_grid = 0;   // decode kernel (decode, sign masks)
     int per_cu_max = 1, cus = 256;
@@ -106,8 +106,8 @@ unsigned grid_for(bcmc_batch *b, int per_cu) {
 
 // Back kernel: `sb` blocks staged per round trip, `per_cu` workgroups per
 // CU; flags and lists kernels: `front_pc` workgroups per CU (both clamped to
-// what stays resident).  `scan` chose between two forms of the lists' offsets
-// that one form without a barrier has replaced: kept as part of the schedule.
+// what stays resident).  `scan` chooses nothing: callers and schedule files pass
+// it, and it is reported as they set it.
 int set_schedule(bcmc_batch *b, int sb, int per_cu, int front_pc, int scan) {
     int maxc = 0;
     if (batch_back_per_cu(sb, &maxc) != 0 || maxc < 1)

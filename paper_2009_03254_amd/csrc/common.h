@@ -32,7 +32,7 @@ constexpr uint32_t EVICT_REFRESH = 512;      // key span from which its base is 
 constexpr int MC_MAX_GRID = 2048;           // workgroups of the count / emission grid at most
 constexpr int MC_WAVES = 4;                  // blocks (one per wave) per MC tile
 
-enum : uint32_t { ERR_CACHE_CAP = 1u, ERR_NONFINITE = 2u, ERR_INTERNAL = 4u, ERR_TIMEOUT = 8u };
+enum : uint32_t { ERR_CACHE_CAP = 1u, ERR_NONFINITE = 2u, ERR_INTERNAL = 4u };
 
 // Device-resident scalars of one extract call.  Written only by kernels of
 // that call (zeroed by the call before), read back once by the host at its

@@ -61,9 +61,10 @@ __device__ __forceinline__ T wave_sum(T v) {
 }
 
 // ---------------------------------------------------------------------------
-// Marching cubes over the active blocks (Sec. 4.3-4.5), as the paper's three
-// steps: a count pass (per-block vertex count, Sec. 4.4), a device-wide
-// exclusive scan of the block counts, and an emission pass (Sec. 4.5).
+// Marching cubes over the active blocks (Sec. 4.3-4.5), in two passes: a count
+// (per-block vertex counts, totals per chunk of blocks, Sec. 4.4) and an
+// emission (Sec. 4.5), whose waves add up the chunks before theirs and scan a
+// chunk's counts: the paper's exclusive scan of the block counts.
 // One wave64 owns one 4^3 block: lane = dual cell.  The block and its
 // +x/+y/+z halo (5^3 samples) are staged in LDS from the cache slots of the
 // block and its 7 positive neighbours.  Only blocks flagged "can emit" by the
@@ -471,8 +472,8 @@ struct EmitSharedT {
 using EmitShared = EmitSharedT<MC_SB>;
 // The plain emission stages two blocks fewer and keeps the triangle table in
 // LDS (a per-lane lookup per block that global memory serves only after the
-// staged slots have evicted it from L1): its LDS then fits 8 workgroups per CU
-// (its registers hold it to 7, where it needs no scratch).
+// staged slots have evicted it from L1): its LDS (19.8 KB) and registers (64)
+// then fit 8 workgroups per CU, of which 7 run (EMIT_PER_CU).
 constexpr int EMIT_SB = MC_SB - 2;
 
 // The backward's LDS: the plain emission's, and per staged block the
