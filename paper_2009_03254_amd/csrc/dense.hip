@@ -18,7 +18,7 @@
 // and triangles in LDS and writes one vertex per lane.  Bound by memory: the
 // field read once for the signs and, where the surface lies, again for the
 // vertices, and the soup written.  512^3 turbulence at its median (14.5 M
-// triangles): 107 + 25 + 330 us, the signs at 5.0 TB/s (before, with each
+// triangles): 109 + 26 + 306 us, the signs at 5.0 TB/s (before, with each
 // cell's case and offset kept in memory: 985 for a classification whose lanes
 // read 64 bytes apart and 1433 for an emission whose lanes wrote 48 bytes
 // apart, 2.6 ms in all).  More waves (7 or 8 per SIMD, spilling) or two vertices
@@ -278,11 +278,11 @@ DenseGeom dense_geom(uint32_t nx, uint32_t ny, uint32_t nz) {
 
 // Words per chunk: mc_chunk_size's, but not whole rows a multiple of 4 KB
 // apart.  The waves would then start every chunk at the same x of such rows
-// and gather through the same few L2 channels: 512^3 turbulence 565 us with
-// chunks of 64 words (8 rows of 2 KB), 514 with 61 (509..514 with 60..62, 534
-// with 63, 542 with 56); 256 x 256 x 256 121 with 64, 103 with 61.  Where the
-// rows differ, 61 measured from 4 % faster (384^3, 300^3) to 4 % slower
-// (640 x 512 x 512): those keep 64.
+// and gather through the same few L2 channels: a call on 512^3 turbulence takes
+// 533..547 us with chunks of 64 words (8 rows of 2 KB) and 473..486 with 61 (three
+// fields; 60 and 62 as 61, 63 4 % and 56 5 % slower); 256 x 256 x 256 121 with 64,
+// 103 with 61.  Where the rows differ, 61 measured from 4 % faster (384^3, 300^3)
+// to 4 % slower (640 x 512 x 512): those keep 64.
 constexpr uint32_t DENSE_ODD_CHUNK = 61;
 uint32_t dense_chunk_size(const DenseGeom &g, uint32_t waves) {
     const uint32_t cs = mc_chunk_size(g.n_cwords, waves);
