@@ -228,9 +228,13 @@ int set_budget(bcmc_volume *v, uint64_t initial_bytes, uint64_t max_bytes, hipSt
         free_cache(v);
         v->init_slots = v->max_slots = 0;
         (void)reset_cache_state(v, s);
+        (void)hipStreamSynchronize(s);
         return rc;
     }
-    return reset_cache_state(v, s);
+    if ((rc = reset_cache_state(v, s))) return rc;
+    // the next call may come on any stream, also one that does not wait for this
+    BCMC_HIP_TRY(hipStreamSynchronize(s));
+    return BCMC_OK;
 }
 
 hipStream_t as_stream(void *p) { return reinterpret_cast<hipStream_t>(p); }

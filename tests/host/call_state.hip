@@ -31,6 +31,7 @@ static bool launch_fails = false;    // hipGetLastError after the launches
 static bool capturing = false;       // the stream records: kernels do not run, waits fail
 static size_t malloc_limit = ~(size_t)0;
 static int launches = 0;             // kernels enqueued
+static int unwaited = 0;             // ... since the last synchronisation
 static std::vector<uint32_t> active_now;   // the blocks the next call finds active
 
 // ---- HIP --------------------------------------------------------------------
@@ -51,7 +52,7 @@ hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *c) {
     return hipSuccess;
 }
 hipError_t hipStreamQuery(hipStream_t) { return lost || readback_fails || capturing ? hipErrorLaunchFailure : hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { return lost || readback_fails || capturing ? hipErrorLaunchFailure : hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { unwaited = 0; return lost || readback_fails || capturing ? hipErrorLaunchFailure : hipSuccess; }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
 hipError_t hipGetLastError() { return launch_fails ? hipErrorLaunchFailure : hipSuccess; }
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
@@ -74,7 +75,7 @@ static bool all_zero(const T *p, uint64_t n) {
         if (reinterpret_cast<const unsigned char *>(p)[i]) return false;
     return true;
 }
-static bool enqueue() { launches++; return !lost && !capturing; }   // does the kernel run?
+static bool enqueue() { launches++, unwaited++; return !lost && !capturing; }   // does the kernel run?
 
 uint64_t cull_tiles(const Geom &) { return 1; }
 static int last_rewrite = -1;
@@ -336,6 +337,15 @@ static void budget() {
     }
 }
 
+// A handle and a budget may be used on any stream afterwards: the budget takes
+// none that a caller could order, so neither leaves work behind.
+static void ready() {
+    bcmc_volume *v = load();
+    CHECK(unwaited == 0);
+    good_call(v, 0.5f, {1, 2, 3});
+    CHECK(bcmc_set_cache_budget(v, 256 * 100, 256 * 1000) == BCMC_OK && unwaited == 0);
+}
+
 int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "counts") counts();
@@ -343,6 +353,7 @@ int main(int argc, char **argv) {
     else if (what == "capture") capture();
     else if (what == "batch") batch();
     else if (what == "budget") budget();
+    else if (what == "ready") ready();
     else return 2;
     printf("%s ok\n", what.c_str());
     return 0;

@@ -1,7 +1,8 @@
 """What a call leaves behind when it fails, on a pretended device (the library's
 host sources compiled with tests/host/call_state.hip in place of the kernels and
 of the HIP calls): the counts, the cache and the batch's totals the next call
-starts from, what a capturing stream is given, and a budget that does not fit.  No GPU needed; skipped
+starts from, what a capturing stream is given, a budget that does not fit, and
+work left behind on a stream the caller does not name.  No GPU needed; skipped
 when hipcc is absent."""
 import os
 import subprocess
@@ -27,7 +28,7 @@ def exe(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("what", ["counts", "cache", "capture", "batch", "budget"])
+@pytest.mark.parametrize("what", ["counts", "cache", "capture", "batch", "budget", "ready"])
 def test_after_a_failed_call(exe, what):
     r = subprocess.run([exe, what], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout + r.stderr
