@@ -331,8 +331,9 @@ def batch_bench(steps, warmup):
                  "triangles_per_s": round(T / (warm_ms * 1e-3)),
                  "alg_gbs": round(alg["warm"] / (warm_ms * 1e-3) / 1e9, 2)},
         "note": "alg_gbs = the algorithmic bytes of the 192 plain calls over the batch's time; "
-                "ms are wall-clock per pass including the offsets readback; phase_ms: reset, "
-                "flags, counts scan, list scatter, decode, count, count scan, emission",
+                "ms are wall-clock per pass including the offsets readback; phase_ms: reset "
+                "(empty), flags, totals, lists, decode and masks, count, the emission's offsets, "
+                "emission",
     }
 
 
