@@ -24,6 +24,7 @@ Geom volume_geom(const bcmc_volume *v);
 uint32_t volume_rate(const bcmc_volume *v);
 int volume_is_f64(const bcmc_volume *v);
 int volume_is_identity(const bcmc_volume *v);
+int refuse_capture(hipStream_t s);
 }  // namespace bcmc
 
 struct bcmc_batch {
@@ -131,6 +132,7 @@ int reset_cache(bcmc_batch *b, hipStream_t s) {
 
 // One run on the private stream (the caller's stream waits for it).
 int run_once(bcmc_batch *b, void *d_out, uint64_t cap, hipStream_t caller) {
+    if (int rc = refuse_capture(caller)) return rc;
     b->p.out = d_out;
     b->p.cap = cap;
     BCMC_HIP_TRY(hipEventRecord(b->ev_in, caller));

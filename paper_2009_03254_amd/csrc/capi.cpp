@@ -55,6 +55,20 @@ Geom volume_geom(const bcmc_volume *v) { return v->g; }
 uint32_t volume_rate(const bcmc_volume *v) { return v->rate; }
 int volume_is_f64(const bcmc_volume *v) { return v->is_f64; }
 int volume_is_identity(const bcmc_volume *v) { return v->identity; }
+
+// For a call that waits for its counters, before anything is enqueued: a
+// capturing stream would record the kernels, the wait would fail, and a replay
+// would count into copies that no call has cleared.
+int refuse_capture(hipStream_t s) {
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &c) != hipSuccess) {
+        (void)hipGetLastError();   // the launches report it
+        return BCMC_OK;
+    }
+    if (c == hipStreamCaptureStatusNone) return BCMC_OK;
+    set_error("the call waits for its results: it cannot run on a capturing stream");
+    return BCMC_E_HIP;
+}
 }  // namespace bcmc
 
 namespace {
@@ -240,20 +254,6 @@ int set_budget(bcmc_volume *v, uint64_t initial_bytes, uint64_t max_bytes, hipSt
 hipStream_t as_stream(void *p) { return reinterpret_cast<hipStream_t>(p); }
 
 const Counters &counters(const bcmc_volume *v) { return *reinterpret_cast<const Counters *>(v->h_ctr->c); }
-
-// For a call that waits for its counters, before anything is enqueued: a
-// capturing stream would record the kernels, the wait would fail, and a replay
-// would count into copies that no call has cleared.
-int refuse_capture(hipStream_t s) {
-    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &c) != hipSuccess) {
-        (void)hipGetLastError();   // the launches report it
-        return BCMC_OK;
-    }
-    if (c == hipStreamCaptureStatusNone) return BCMC_OK;
-    set_error("the call waits for its results: it cannot run on a capturing stream");
-    return BCMC_E_HIP;
-}
 
 // Reads the counters back.  The caller waits for them anyway, so a kernel at
 // the end of the call's work writes them to pinned memory and the host polls

@@ -60,7 +60,7 @@ hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { *v = 8; re
 hipError_t hipEventCreate(hipEvent_t *) { return hipSuccess; }
 hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
-hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return capturing ? hipErrorCapturedEvent : hipSuccess; }
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 0; return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = nullptr; return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
@@ -291,7 +291,8 @@ static void capture() {
     CHECK(bcmc_backward(v, 0.5f, gV.data(), 9, field.data(), &g, nullptr) == BCMC_OK);
 }
 
-// A batch whose launches end half-way: the next run starts from zero totals.
+// A batch on a capturing stream, and one whose launches end half-way: the next
+// run starts from zero totals.
 static void batch() {
     bcmc_volume *v = load();
     const uint32_t job_vol[2] = {0, 0};
@@ -309,6 +310,11 @@ static void batch() {
         CHECK(bcmc_batch_run(b, nullptr, 0, off, nullptr) == BCMC_OK);
         CHECK(resident() == 7 * k);   // the store carries over
     }
+    capturing = true;   // refused: the store stays
+    const int before = launches;
+    CHECK(bcmc_batch_run(b, nullptr, 0, off, nullptr) == BCMC_E_HIP && launches == before);
+    capturing = false;
+    CHECK(bcmc_batch_run(b, nullptr, 0, off, nullptr) == BCMC_OK && resident() == 21);
     batch_fails = true;
     CHECK(bcmc_batch_run(b, nullptr, 0, off, nullptr) == BCMC_E_HIP);
     batch_fails = false;

@@ -21,6 +21,8 @@ def test_extract_on_a_capturing_stream():
     blocks = bc.blocks_from_field(f)
     fv, fref = bc.FieldVolume(blocks, dims), bc.FieldVolume(blocks, dims)
     dense = bc.DenseMC(dims)
+    batch = bc.Batch([ref], [(0, iso) for iso in isos])
+    soups = batch.run()[0].clone()
     out = torch.empty((1 << 20, 4), dtype=torch.int32, device="cuda")
 
     def same(a, b, iso):
@@ -41,6 +43,7 @@ def test_extract_on_a_capturing_stream():
         assert fv.extract_into(isos[1], out)[0] == bc._capi.E_HIP
         with pytest.raises(bc.BcmcError):
             dense.extract_into(f, isos[1], out)
+        assert batch.run_into(out)[0] == bc._capi.E_HIP
     for _ in range(3):   # the capture holds the caller's own work alone
         graph.replay()
     torch.cuda.synchronize()
@@ -56,5 +59,8 @@ def test_extract_on_a_capturing_stream():
         assert np.array_equal(got, want)
     rc, T = dense.extract_into(f, isos[1], out)
     assert rc == 0 and T == fref.extract(isos[1])[1]
-    for h in (vol, ref, fv, fref, dense):
+    assert torch.equal(batch.run()[0], soups)
+    info = batch.info()
+    assert info["n_new"] == 0 and info["graph"] == 1   # the store and the graph are kept
+    for h in (batch, vol, ref, fv, fref, dense):
         h.close()
